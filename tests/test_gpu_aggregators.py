@@ -146,6 +146,26 @@ def test_median_by_selection_with_ties_and_nonfinite_entries(B, m, row_align):
     assert np.array_equal(med[ok], ref[ok])
 
 
+@pytest.mark.parametrize("m,d", [(129, 1), (160, 65), (161, 63), (288, 64), (289, 129), (320, 200), (321, 33), (384, 31),
+                                 (385, 32), (575, 97), (833, 64), (960, 5), (961, 70), (1023, 257), (1024, 1)])
+def test_median_by_selection_at_the_edges_of_its_tiles(B, m, d):
+    """m > 128, sizes around the widths at which the kernel's keys per lane, lanes per column and columns per tile
+    change; columns whose search is led astray: values over hundreds of binades, a block of equal rows around
+    the middle, mostly zeros of either sign, adjacent floats, NaN in all rows but a few."""
+    G = _rand_G(m, d, 9000 + m, scale=1.0)
+    kind = torch.arange(d) % 6
+    G[:, kind == 1] = torch.sign(G[:, kind == 1]) * torch.exp(25.0 * G[:, kind == 1])
+    G[m // 4: m // 2 + 1, kind == 2] = 0.125
+    G[:, kind == 3] *= (G[:, kind == 3] > 1.0)
+    G[:, kind == 4] = 1.0 + torch.randint(0, 3, (m, d), generator=torch.Generator().manual_seed(m))[:, kind == 4] * 2.0 ** -23
+    G[3:, kind == 5] = float("nan")
+    med = B.zeno_median(G.cuda()).cpu().numpy()
+    ref = O.median(G.numpy()).astype(np.float32)
+    assert np.array_equal(np.isnan(med), np.isnan(ref))
+    ok = ~np.isnan(ref)
+    assert np.array_equal(med[ok], ref[ok])
+
+
 def test_median_with_nonfinite_entries(B):
     m, d = 6, 200
     G = _rand_G(m, d, 9)
