@@ -50,6 +50,7 @@ def _fresh(obj, src, stamp):
         deps = [os.path.join(CSRC, src), os.path.join(CSRC, "zeno_internal.h"), os.path.join(ROOT, "include", "zeno.h")]
         if src.startswith("zeno_layer") or src in ("zeno_krum.hip", "zeno_conv.hip"):
             deps.append(os.path.join(CSRC, "zeno_layer_impl.h"))
+            deps.append(os.path.join(CSRC, "zeno_split.h"))
         return all(os.path.getmtime(d) < t for d in deps)
     except OSError:
         return False

@@ -469,67 +469,42 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
   // workspace held (they meet the zeros of the masked weight tile, and 0 x NaN is NaN); the convolutions only
   // write the live entries
   // (rows beyond n_r may hold anything: a sample's row only reaches its own, discarded, results)
-  {
-    ProfScope ps(ZENO_KERNEL_AUX, 2, 0.0, stream);
-    ZENO_TRY(launch_fill_zero(ws + p.off_slice_cnt, p.sz_slice_cnt, stream));   // arrival counters start at zero
-  }
   if (p.Kp != p.Kfc) {
     ProfScope ps(ZENO_KERNEL_AUX, 0, 0.0, stream);
     ZENO_TRY(launch_fill_zero(ws + p.off_h0t, p.sz_h0t, stream));
     ZENO_TRY(launch_fill_zero(ws + p.off_dt, p.dt_stride * m, stream));
   }
-  auto conv_args = [&](int l) {
-    ConvArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.G = G;
-    a.x = x;
-    a.ldg = ldg;
-    a.n_r = n_r;
-    a.L.w_off = mdl->conv_w_off[l];
-    a.L.b_off = mdl->conv_b_off[l];
-    a.L.Hin = mdl->map_h[l];
-    a.L.Win = mdl->map_w[l];
-    a.L.Cin = mdl->map_c[l];
-    a.L.Hout = mdl->map_h[l + 1];
-    a.L.Wout = mdl->map_w[l + 1];
-    a.L.Cout = mdl->map_c[l + 1];
-    a.L.stride = mdl->cnn.conv_stride[l];
-    a.H0_in = l == 0 ? batch->features : reinterpret_cast<const float*>(ws + p.off_h0[l - 1]);
-    a.Z0 = reinterpret_cast<float*>(ws + p.off_z0[l]);
-    a.tiled_out = l + 1 == C;
-    a.Kp_fc = p.Kp;
-    a.gamma = gamma;
-    a.neg_inv_gamma = neg_inv_gamma;
-    return a;
+  auto conv_job = [&](int l, bool cand) {
+    ConvJob j;
+    std::memset(&j, 0, sizeof(j));
+    j.L.w_off = mdl->conv_w_off[l];
+    j.L.b_off = mdl->conv_b_off[l];
+    j.L.Hin = mdl->map_h[l];
+    j.L.Win = mdl->map_w[l];
+    j.L.Cin = mdl->map_c[l];
+    j.L.Hout = mdl->map_h[l + 1];
+    j.L.Wout = mdl->map_w[l + 1];
+    j.L.Cout = mdl->map_c[l + 1];
+    j.L.stride = mdl->cnn.conv_stride[l];
+    j.H0_in = l == 0 ? batch->features : reinterpret_cast<const float*>(ws + p.off_h0[l - 1]);
+    j.Z0 = reinterpret_cast<float*>(ws + p.off_z0[l]);
+    j.tiled_out = l + 1 == C;
+    j.Kp_fc = p.Kp;
+    if (!cand) {
+      j.out = l + 1 == C ? reinterpret_cast<float*>(ws + p.off_h0t) : reinterpret_cast<float*>(ws + p.off_h0[l]);
+      return j;
+    }
+    if (l > 0) {
+      j.D_in = reinterpret_cast<const float*>(ws + p.off_d[(l - 1) & 1]);
+      j.D_in_stride = (long long)p.d_stride;
+    }
+    j.out = reinterpret_cast<float*>(l + 1 == C ? ws + p.off_dt : ws + p.off_d[l & 1]);
+    j.out_stride = l + 1 == C ? (long long)(p.dt_stride / sizeof(float)) : (long long)p.d_stride;
+    return j;
   };
   auto conv_flops = [&](int l) {   // reported in place of bytes: 2 * positions * 9 c_in * c_out per source
     return 2.0 * n_r * mdl->map_h[l + 1] * mdl->map_w[l + 1] * 9.0 * mdl->map_c[l] * mdl->map_c[l + 1];
   };
-  // pass at x through the convolutions, then the candidates (layer l of the candidates needs Z0 of layer l
-  // and the input map of layer l, both written by the pass at x)
-  for (int l = 0; l < C; ++l) {
-    ConvArgs a = conv_args(l);
-    a.out = l + 1 == C ? reinterpret_cast<float*>(ws + p.off_h0t) : reinterpret_cast<float*>(ws + p.off_h0[l]);
-    ProfScope ps(ZENO_KERNEL_CONV_BASE, l, conv_flops(l), stream);
-    ZENO_TRY(launch_conv(a, stream));
-  }
-  for (int l = 0; l < C; ++l) {
-    ConvArgs a = conv_args(l);
-    a.n_cand = m;
-    if (l > 0) {
-      a.D_in = reinterpret_cast<const float*>(ws + p.off_d[(l - 1) & 1]);
-      a.D_in_stride = (long long)p.d_stride;
-    }
-    if (l + 1 == C) {
-      a.out = reinterpret_cast<float*>(ws + p.off_dt);
-      a.out_stride = (long long)(p.dt_stride / sizeof(float));
-    } else {
-      a.out = reinterpret_cast<float*>(ws + p.off_d[l & 1]);
-      a.out_stride = (long long)p.d_stride;
-    }
-    ProfScope ps(ZENO_KERNEL_CONV_CAND, l, conv_flops(l) * m * (l > 0 ? 2 : 1), stream);
-    ZENO_TRY(launch_conv(a, stream));
-  }
   // the fully connected layer on the streaming layer kernel (fp32, with the second product)
   LayerJob j;
   std::memset(&j, 0, sizeof(j));
@@ -555,13 +530,6 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
   common.slice_partials = reinterpret_cast<float*>(ws + p.off_slice_part);
   common.slice_counters = reinterpret_cast<unsigned int*>(ws + p.off_slice_cnt);
   const double fc_bytes = 4.0 * ((double)N * p.Kfc + (j.b_off >= 0 ? N : 0));
-  {
-    LayerArgs b = common;
-    b.has_base = 1;
-    b.bj = j;
-    ProfScope ps(ZENO_KERNEL_LAYER_BASE, C, fc_bytes, stream);
-    ZENO_TRY(launch_layer(b, false, false, p.MB, stream));
-  }
   LayerArgs c = common;
   c.n_cand = m;
   c.cj = j;
@@ -572,16 +540,56 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
   c.p_off = 0;
   const int fc_tiles = layer_tiles(c, false, true, p.MB);
   if (fc_tiles + kConvNormBlocks > p.P) return ZENO_ERR_WORKSPACE;
+  // The pass at x through convolution 0, then the candidates' convolution l together with the pass at x through
+  // convolution l + 1: the candidates need Z0 and the input map of their layer, both one launch old.
+  ConvArgs conv;
+  std::memset(&conv, 0, sizeof(conv));
+  conv.G = G;
+  conv.x = x;
+  conv.ldg = ldg;
+  conv.n_r = n_r;
+  conv.gamma = gamma;
+  conv.neg_inv_gamma = neg_inv_gamma;
+  {
+    ConvArgs a = conv;
+    a.has_base = 1;
+    a.bj = conv_job(0, false);
+    // ||u||^2 runs over all d coordinates: the fully connected block is summed by the layer kernel, the convolutions'
+    // kernels and biases (the first mdl->w_off[0] coordinates) here; the arrival counters start at zero
+    a.aux_m = m;
+    a.aux_pieces = kConvNormBlocks;
+    a.aux_P = p.P;
+    a.aux_p_off = fc_tiles;
+    a.aux_count = mdl->w_off[0];
+    a.aux_norm = norm_partials;
+    a.aux_zero = ws + p.off_slice_cnt;
+    a.aux_zero16 = (int)(p.sz_slice_cnt / 16);
+    ProfScope ps(ZENO_KERNEL_CONV_BASE, 0, conv_flops(0), stream);
+    ZENO_TRY(launch_conv(a, stream));
+  }
+  for (int l = 0; l < C; ++l) {
+    ConvArgs a = conv;
+    a.n_cand = m;
+    a.cj = conv_job(l, true);
+    double flops = conv_flops(l) * m * (l > 0 ? 2 : 1);
+    if (l + 1 < C) {
+      a.has_base = 1;
+      a.bj = conv_job(l + 1, false);
+      flops += conv_flops(l + 1);
+    }
+    ProfScope ps(ZENO_KERNEL_CONV_CAND, l, flops, stream);
+    ZENO_TRY(launch_conv(a, stream));
+  }
+  {
+    LayerArgs b = common;
+    b.has_base = 1;
+    b.bj = j;
+    ProfScope ps(ZENO_KERNEL_LAYER_BASE, C, fc_bytes, stream);
+    ZENO_TRY(launch_layer(b, false, false, p.MB, stream));
+  }
   {
     ProfScope ps(ZENO_KERNEL_LAYER_CAND, C, fc_bytes * m, stream);
     ZENO_TRY(launch_layer(c, false, true, p.MB, stream));
-  }
-  // ||u||^2 runs over all d coordinates: the fully connected block was summed by the layer kernel, the
-  // convolutions' kernels and biases (the first mdl->w_off[0] coordinates) are summed here; slots that no
-  // launch writes are cleared
-  {
-    ProfScope ps(ZENO_KERNEL_AUX, 1, 4.0 * (double)mdl->w_off[0] * m, stream);
-    ZENO_TRY(launch_sumsq(G, ldg, m, 0, mdl->w_off[0], kConvNormBlocks, norm_partials, p.P, fc_tiles, stream));
   }
   const int P_used = fc_tiles + kConvNormBlocks;
   {

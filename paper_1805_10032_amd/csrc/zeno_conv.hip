@@ -13,16 +13,41 @@
 // convolution).  Nothing is unfolded in memory: a patch element (position, tap, channel) is
 // gathered from the NHWC map when a lane needs it as a matrix operand.
 //
-// One wave owns 32 output positions x 32 output channels in one 32x32 fp32 accumulator block
-// (v_mfma_f32_32x32x2_f32, kernel values as the first operand so that a lane is a position and
-// its registers are channels), walks the nine taps and, per tap, the input channels eight at a
-// time (one 128-bit load per lane and operand feeds four matrix instructions; the tail of a channel
-// count that is not a multiple of eight goes two at a time).  Kernels are a few hundred KB per candidate and the maps a few MB, so everything but
-// the first touch comes from the caches; the path is bound by instruction issue and latency,
-// not by HBM.  The last convolution writes its outputs straight into the matrix-operand
+// conv_wide_kernel, conv_deep_kernel.  The products run on the bf16 matrix cores at float32 accuracy: both operands are
+// split into three bf16 pieces each and the six leading piece products accumulated (zeno_split.h).  Six
+// v_mfma_f32_32x32x16_bf16 cover 16 channels of a tap in 192 cycles where v_mfma_f32_32x32x2_f32 needs 512.  A wave
+// owns 32 output channels x 32 PB output positions (kernel values as the first operand, so that an accumulator lane is
+// a position and its registers are channels).  K is walked in units of (map of x or of the candidate) x (chunk of eight or
+// sixteen input channels), nine taps each; channels are padded to the chunk, and chunks of eight take two taps per step.
+//  * Map values, which nine taps and all channel tiles use, are split once: a workgroup stages the rows of the
+//    input map that its positions touch, with their zero border, as [piece][eight channels][pixel] in LDS, and every lane
+//    reads its position's eight channels of a tap as one 128-bit piece at a fixed offset from the position: no masks,
+//    and consecutive positions lie on consecutive 16-byte pieces (stride 1).
+//  * Launches with many tiles (wide: four waves, 128 positions x 32 or 64 channels): kernel values are split once per
+//    workgroup as well and staged next to the map; W - gamma U is formed in float32 first.  The next unit's values are
+//    requested before the present one is multiplied.
+//  * Launches with few tiles (deep: eight waves, 64 positions x 32 channels): up to four units are staged at once, the
+//    waves share out the steps, each with its own kernel values straight from memory, and add their accumulators
+//    through LDS in a fixed order; the results are finished by all of them.
+// Where both are deep, a launch carries the candidates' convolution l and the pass at x through convolution l + 1, whose
+// input map the launch before completed.  The first launch carries the pass at x through convolution 0 and two
+// small jobs that nothing in it depends on (clearing the arrival counters of the fully connected layer, the squared norms of the
+// kernels; before: two launches).
+// Bound by latency: unit by unit a workgroup requests its values, waits for them (3000-5000 cycles), splits and
+// multiplies (2000-7000); the matrix cores are busy 15-40 % of the time.  Measured (MI355X, 32 x 32 x 3 images,
+// convolutions 32-32-64-64 with strides 1-2-1-2, m = 20) against conv_layer_kernel for everything: n_r = 32, candidates'
+// convolutions 109 / 134 / 251 / 120 -> 67 / 100 / 111 / 105 us, the whole step 682 -> 468 us; n_r = 4: 19 / 26 / 36 / 32 us and
+// 47 us for the pass at x -> 24 / 36 / 34 / 25 us including it and 12 us for its first convolution, the step 209 -> 173 us.
+//
+// conv_layer_kernel serves what the staging does not cover (rows of the map too wide for LDS): one wave owns 32 positions x 32
+// channels in one fp32 accumulator block (v_mfma_f32_32x32x2_f32), and gathers every operand element from memory when it
+// needs it (one 128-bit load per lane and operand feeds four matrix instructions; the tail of a channel
+// count that is not a multiple of eight goes two at a time).
+// The last convolution writes its outputs straight into the matrix-operand
 // order of the fully connected layer (rows = samples, columns = (y, x, c)), which the
 // streaming layer kernel then consumes.
 #include "zeno_layer_impl.h"
+#include "zeno_split.h"
 
 namespace zeno {
 
@@ -33,7 +58,8 @@ namespace {
 // to occupy the matrix cores otherwise (a wave's 9 c_in / 2 dependent matrix instructions set its pace).
 template <bool CAND, int TW>
 __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
-  const ConvLayer& L = a.L;
+  const ConvJob& J = CAND ? a.cj : a.bj;
+  const ConvLayer& L = J.L;
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int tw = TW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
   const int ftiles = (L.Cout + 31) / 32;
@@ -43,8 +69,8 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
   const long long rows = (long long)a.n_r * L.Hout * L.Wout;
 
   const float* __restrict__ P = CAND ? a.G + (long long)s * a.ldg : a.x;
-  const bool second = CAND && a.D_in != nullptr;
-  const float* __restrict__ Din = second ? a.D_in + (long long)s * a.D_in_stride : nullptr;
+  const bool second = CAND && J.D_in != nullptr;
+  const float* __restrict__ Din = second ? J.D_in + (long long)s * J.D_in_stride : nullptr;
 
   // first operand: kernel row of output channel f, taps and channels contiguous
   const int f = ft * 32 + n;
@@ -68,7 +94,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
     const int iy = oy * L.stride + ky - 1, ix = ox * L.stride + kx - 1;
     const bool p_ok = r_ok && iy >= 0 && iy < L.Hin && ix >= 0 && ix < L.Win;
     const long long moff = (((long long)smp * L.Hin + (p_ok ? iy : 0)) * L.Win + (p_ok ? ix : 0)) * L.Cin;
-    const float* __restrict__ hp = a.H0_in + moff;
+    const float* __restrict__ hp = J.H0_in + moff;
     const float* __restrict__ dp = second ? Din + moff : nullptr;
     const float* __restrict__ up = Urow + tap * L.Cin;
     const float* __restrict__ wp = Wrow + tap * L.Cin;
@@ -130,7 +156,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
   }
   // accumulator element j of lane (n, h): position r (this lane's), output channel ft*32 + 8 (j/4) + 4 h + j%4
   if (!r_ok) return;
-  float* __restrict__ out = CAND ? a.out + (long long)s * a.out_stride : a.out;
+  float* __restrict__ out = CAND ? J.out + (long long)s * J.out_stride : J.out;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const int fo = ft * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
@@ -139,18 +165,18 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
     const float val = acc[j] + bias;
     float res;
     if (!CAND) {
-      a.Z0[r * L.Cout + fo] = val;
+      J.Z0[r * L.Cout + fo] = val;
       res = relu_nan(val);
     } else {
       const float dz = -a.gamma * val;
-      const float z0 = a.Z0[r * L.Cout + fo];
+      const float z0 = J.Z0[r * L.Cout + fo];
       const float hr = relu_nan(z0 + dz);
       // relu(z0 + dz) - relu(z0) without cancellation
       const float dd = (z0 > 0.f) ? ((dz < -z0) ? -z0 : dz) : hr;
       res = dd * a.neg_inv_gamma;
     }
-    if (a.tiled_out) {
-      out[tiled_index<false>(smp, pos * L.Cout + fo, a.Kp_fc)] = res;
+    if (J.tiled_out) {
+      out[tiled_index<false>(smp, pos * L.Cout + fo, J.Kp_fc)] = res;
     } else {
       out[r * L.Cout + fo] = res;
     }
@@ -162,44 +188,666 @@ __global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, l
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (long long)gridDim.x * blockDim.x) p[i] = z;
 }
 
-// Sum of squares of a slice of every candidate, piece `blk` of n_blocks, fixed order: a thread sums
-// its strided elements in fp64, lanes by xor-shuffle tree, waves in order.
-__global__ __launch_bounds__(256) void sumsq_kernel(const float* __restrict__ G, long long ldg, long long begin,
-                                                    long long count, double* __restrict__ partials, int P, int p_off) {
-  __shared__ double red[4];
-  const int s = blockIdx.y, blk = blockIdx.x, nb = gridDim.x;
-  const long long lo = count * blk / nb, hi = count * (blk + 1) / nb;
-  const float* __restrict__ row = G + (long long)s * ldg + begin;
-  double t = 0.0;
-  for (long long i = lo + threadIdx.x; i < hi; i += 256) {
-    const double v = (double)row[i];
-    t += v * v;
+// Results of one accumulator value: position r, channel fo (pre-activation of the pass at x, or its change).
+__device__ inline float conv_result(const ConvArgs& a, bool cand, float val, float z0) {
+  if (!cand) return relu_nan(val);
+  const float dz = -a.gamma * val;
+  const float hr = relu_nan(z0 + dz);
+  // relu(z0 + dz) - relu(z0) without cancellation
+  const float dd = (z0 > 0.f) ? ((dz < -z0) ? -z0 : dz) : hr;
+  return dd * a.neg_inv_gamma;
+}
+
+constexpr int kDeepSteps = 36;   // matrix steps a workgroup of conv_deep_kernel stages at once
+
+// v / d for 0 <= v, v d < 2^32, with the multiplier ceil(2^32 / d) (0: d = 1)
+__device__ inline unsigned div_magic(unsigned v, unsigned magic) { return magic == 0u ? v : __umulhi(v, magic); }
+
+// Value `off` bytes behind a wave-uniform base (32-bit offsets: one register, no address arithmetic).
+template <typename V>
+__device__ inline V at_byte(const float* __restrict__ base, unsigned off) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
+}
+// Eight consecutive floats `off` bytes behind base, of which the first nv exist (nv may be <= 0); the others are zero.  No
+// branches, so that the loads of many items are in flight together: what does not exist is read from where something does.
+// FULL: the channels are a multiple of eight, so that all eight exist or none.
+template <bool FULL>
+__device__ inline void load8(const float* __restrict__ base, unsigned off, int nv, f32x4& v0, f32x4& v1) {
+  const unsigned p = nv > 0 ? off : 0u;
+  if (FULL) {
+    v0 = at_byte<f32x4_a4>(base, p);
+    v1 = at_byte<f32x4_a4>(base, p + 16u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v0[i] = nv > 0 ? v0[i] : 0.f;
+      v1[i] = nv > 0 ? v1[i] : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v0[i] = at_byte<float>(base, p + (i < nv ? 4u * i : 0u));
+      v1[i] = at_byte<float>(base, p + (4 + i < nv ? 4u * (4 + i) : 0u));
+      v0[i] = i < nv ? v0[i] : 0.f;
+      v1[i] = 4 + i < nv ? v1[i] : 0.f;
+    }
   }
+}
+
+// Squared norm of coordinates [0, count) of candidate s, piece blk of n_blocks, in a fixed order: a thread sums its
+// strided elements in float64, lanes by xor-shuffle tree, waves in order.
+__device__ void sumsq_piece(const ConvArgs& a, int s, int blk, double* red) {
+  const int T = blockDim.x;
+  const long long lo = a.aux_count * blk / a.aux_pieces, hi = a.aux_count * (blk + 1) / a.aux_pieces;
+  const float* __restrict__ row = a.G + (long long)s * a.ldg;
+  double t = 0.0;
+  long long i = lo + threadIdx.x;
+  for (; i + 7 * T < hi; i += 8 * T) {            // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = row[i + q * T];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t += (double)v[q] * (double)v[q];
+  }
+  for (; i < hi; i += T) t += (double)row[i] * (double)row[i];
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
   __syncthreads();
-  if (threadIdx.x == 0) partials[(long long)s * P + p_off + blk] = ((red[0] + red[1]) + red[2]) + red[3];
+  if (threadIdx.x == 0) {
+    double sum = 0.0;
+    for (int w = 0; w < T / 64; ++w) sum += red[w];
+    a.aux_norm[(long long)s * a.aux_P + a.aux_p_off + blk] = sum;
+  }
+}
+
+constexpr unsigned kNoPixel = 0xffffffffu;
+
+// What a workgroup that owns NP consecutive output positions of a job needs of its input map, in rows of the map
+// with a border of one zero pixel all around: sample smp's row iy is border row smp * (Hin + 2) + iy + 1.
+template <int NP>
+struct ConvTile {
+  unsigned rows, r_first, v_first, Wv, Hv, plane;
+  int pixels;
+  __device__ inline ConvTile(const ConvArgs& a, const ConvJob& J, int pt) {
+    const ConvLayer& L = J.L;
+    rows = (unsigned)(a.n_r * L.Hout * L.Wout);
+    Wv = (unsigned)L.Win + 2u;
+    Hv = (unsigned)L.Hin + 2u;
+    r_first = (unsigned)pt * NP;
+    const unsigned r_last = (r_first + NP < rows ? r_first + NP : rows) - 1u;
+    v_first = border_row(J, r_first);
+    pixels = (int)((border_row(J, r_last) + 3u - v_first) * Wv);
+    plane = (unsigned)(pixels | 1) * 16u;         // bytes of one (piece, group of eight channels) plane
+  }
+  // topmost border row position r reads
+  __device__ inline unsigned border_row(const ConvJob& J, unsigned r) const {
+    const unsigned orow = div_magic(r, J.magic_wout), smp = div_magic(orow, J.magic_hout);
+    return smp * Hv + (orow - smp * (unsigned)J.L.Hout) * (unsigned)J.L.stride;
+  }
+  // byte offset inside a plane of the pixel that position r's first tap reads
+  __device__ inline unsigned first_pixel(const ConvJob& J, unsigned r) const {
+    const unsigned rc = r < rows ? r : rows - 1u;
+    const unsigned ox = rc - div_magic(rc, J.magic_wout) * (unsigned)J.L.Wout;
+    return ((border_row(J, rc) - v_first) * Wv + ox * (unsigned)J.L.stride) * 16u;
+  }
+  // byte offset of border pixel px inside the input map, or kNoPixel where it is border
+  __device__ inline unsigned pixel_offset(const ConvArgs& a, const ConvJob& J, unsigned px) const {
+    const ConvLayer& L = J.L;
+    const unsigned vr = div_magic(px, J.magic_wv), vx = px - vr * Wv, v = v_first + vr;
+    const unsigned smp = div_magic(v, J.magic_hv), vy = v - smp * Hv;
+    const bool inside = (vx - 1u < (unsigned)L.Win) & (vy - 1u < (unsigned)L.Hin) & (smp < (unsigned)a.n_r);
+    return inside ? ((smp * (unsigned)L.Hin + vy - 1u) * (unsigned)L.Win + (vx - 1u)) * (unsigned)L.Cin * 4u : kNoPixel;
+  }
+};
+// eight channels from c on of the pixel at byte offset off
+template <bool FULL>
+__device__ inline void load_pixel(const float* __restrict__ map, unsigned off, int c, int Cin, f32x4& v0, f32x4& v1) {
+  load8<FULL>(map, off + 4u * (unsigned)c, off != kNoPixel ? Cin - c : 0, v0, v1);
+}
+
+__device__ inline void store_split(unsigned char* o, unsigned piece_stride, const f32x4& v0, const f32x4& v1) {
+  const Split8 p = split8(v0, v1);
+  *reinterpret_cast<bf16x8*>(o) = p.h;
+  *reinterpret_cast<bf16x8*>(o + piece_stride) = p.m;
+  *reinterpret_cast<bf16x8*>(o + 2 * piece_stride) = p.l;
+}
+__device__ inline Split8 load_split(const unsigned char* o, unsigned piece_stride) {
+  Split8 p;
+  p.h = *reinterpret_cast<const bf16x8*>(o);
+  p.m = *reinterpret_cast<const bf16x8*>(o + piece_stride);
+  p.l = *reinterpret_cast<const bf16x8*>(o + 2 * piece_stride);
+  return p;
+}
+
+// What four consecutive channels fo .. fo + 3 of one position r need besides their sums, requested ahead of them.
+struct ConvOut {
+  f32x4 bias, z0;
+};
+__device__ inline ConvOut conv_out_request(const ConvArgs& a, const ConvJob& J, bool cand, const float* __restrict__ P, unsigned r,
+                                           unsigned rows, unsigned fo) {
+  const ConvLayer& L = J.L;
+  const unsigned C = (unsigned)L.Cout, row = (r < rows ? r : rows - 1u) * C;
+  ConvOut o;
+  o.bias = o.z0 = f32x4{0.f, 0.f, 0.f, 0.f};
+  if ((C & 3u) == 0u) {                           // the four channels exist together and lie 16-byte aligned
+    const unsigned fc = fo < C ? fo : 0u;
+    if (L.b_off >= 0) o.bias = at_byte<f32x4_a4>(P + L.b_off, 4u * fc);
+    if (cand) o.z0 = at_byte<f32x4>(J.Z0, 4u * (row + fc));
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned fc = fo + i < C ? fo + i : 0u;
+      if (L.b_off >= 0) o.bias[i] = at_byte<float>(P + L.b_off, 4u * fc);
+      if (cand) o.z0[i] = at_byte<float>(J.Z0, 4u * (row + fc));
+    }
+  }
+  return o;
+}
+__device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool cand, int s, const ConvOut& o, const f32x4& sum,
+                                      unsigned r, unsigned rows, unsigned fo) {
+  const unsigned C = (unsigned)J.L.Cout, row = r * C;
+  f32x4 val, res;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    val[i] = sum[i] + o.bias[i];
+    res[i] = conv_result(a, cand, val[i], o.z0[i]);
+  }
+  if (r >= rows || fo >= C) return;
+  float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
+  unsigned smp = 0, k = row + fo;
+  if (J.tiled_out) {                              // column of the fully connected layer's operand
+    smp = div_magic(div_magic(r, J.magic_wout), J.magic_hout);
+    k -= smp * (unsigned)(J.L.Hout * J.L.Wout) * C;
+  }
+  if ((C & 3u) == 0u) {
+    if (!cand) *reinterpret_cast<f32x4*>(J.Z0 + (row + fo)) = val;
+    *reinterpret_cast<f32x4*>(out + (J.tiled_out ? tiled_index<false>((int)smp, (int)k, J.Kp_fc) : (long long)k)) = res;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (fo + i < C) {
+        if (!cand) J.Z0[row + fo + i] = val[i];
+        out[J.tiled_out ? tiled_index<false>((int)smp, (int)k + i, J.Kp_fc) : (long long)(k + i)] = res[i];
+      }
+  }
+}
+
+// Many tiles: four waves, 32 PB WP positions x 32 WC channels.  One (map, channel chunk) unit at a time: its map values and
+// its kernel values are requested while the unit before is multiplied, split once and staged for all four waves.
+// CG: groups of eight channels per unit.
+template <int CG, bool FULL, int PB, int WP, int WC>
+__device__ __forceinline__ void conv_wide(const ConvArgs& a, const ConvJob& J, bool cand, int s, int tile, unsigned char* lds) {
+  static_assert(WP * WC == 4, "four waves");
+  constexpr int THREADS = 256, NP = 32 * PB * WP;
+  constexpr int STEPS = CG == 2 ? 9 : 5;                           // matrix steps of 16 k per unit (CG = 1: two taps each)
+  constexpr int NI = 3;                                            // map items a thread requests ahead
+  constexpr int KITEMS = 32 * WC * 9 * CG, NK = (KITEMS + THREADS - 1) / THREADS;   // kernel items: (channel, tap, group)
+  constexpr unsigned KROW = (32 * WC + 1) * 16, KPIECE = 2 * STEPS * KROW;          // staged kernel: [piece][step, half][channel]
+  const ConvLayer& L = J.L;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave % WC, wp = wave / WC;
+  const int cgroups = (L.Cout + 32 * WC - 1) / (32 * WC);
+  const int pt = tile / cgroups, f_base = (tile % cgroups) * 32 * WC;
+  const float* __restrict__ P = cand ? a.G + (long long)s * a.ldg : a.x;
+  const bool second = cand && J.D_in != nullptr;
+  const float* __restrict__ Din = second ? J.D_in + (long long)s * J.D_in_stride : nullptr;
+  const ConvTile<NP> T(a, J, pt);
+  const unsigned plane = T.plane;
+  unsigned char* klds = lds + 3 * CG * plane;
+  const float neg_gamma = -a.gamma;
+
+  unsigned pos_r[PB], pix[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    pos_r[pb] = T.r_first + (unsigned)((wp * PB + pb) * 32 + n);
+    pix[pb] = T.first_pixel(J, pos_r[pb]);
+  }
+  // this thread's items of a unit: map values (pixel, group) and kernel values (channel, tap, group), groups fastest
+  const int items = T.pixels * CG;
+  unsigned m_off[NI];
+#pragma unroll
+  for (int q = 0; q < NI; ++q) {
+    const int i = tid + q * THREADS;
+    m_off[q] = i < items ? T.pixel_offset(a, J, (unsigned)i / CG) : kNoPixel;
+  }
+  const int g8 = CG == 2 ? 8 * (tid & 1) : 0;                      // first channel of this thread's group
+  unsigned k_off[NK], k_at[NK];
+#pragma unroll
+  for (int q = 0; q < NK; ++q) {
+    const unsigned t = (unsigned)(tid + q * THREADS) / CG, f = t / 9u, tap = t - 9u * f;
+    k_off[q] = (((unsigned)f_base + f < (unsigned)L.Cout ? (unsigned)f_base + f : 0u) * 9u + tap) * (unsigned)L.Cin * 4u;
+    k_at[q] = (CG == 2 ? 2u * tap + (tid & 1) : tap) * KROW + f * 16u;
+  }
+  if (CG == 1) {
+    // the tenth tap of the last step: zeros
+    for (int i = tid; i < 3 * 32 * WC; i += THREADS)
+      *reinterpret_cast<f32x4*>(klds + (unsigned)(i / (32 * WC)) * KPIECE + 9 * KROW + (unsigned)(i % (32 * WC)) * 16u) = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+  f32x16 lead[PB], rest[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) lead[pb][j] = rest[pb][j] = 0.f;
+
+  const int chunks = (L.Cin + 8 * CG - 1) / (8 * CG), units = chunks * (second ? 2 : 1);
+  auto stage_item = [&](int i, const f32x4 (&v)[2]) __attribute__((always_inline)) {
+    store_split(lds + (CG == 2 ? (unsigned)(i & 1) * plane : 0u) + (unsigned)i / CG * 16u, CG * plane, v[0], v[1]);
+  };
+  const float* __restrict__ Pk = P + L.w_off;
+  const float* __restrict__ Xk = a.x + L.w_off;
+  // iteration u requests unit u, multiplies unit u - 1 meanwhile, and stages unit u
+#pragma unroll 1
+  for (int u = 0; u <= units; ++u) {
+    const bool dmap = u >= chunks;
+    const int ch = (u - (dmap ? chunks : 0)) * 8 * CG;
+    const float* __restrict__ map = dmap ? Din : J.H0_in;
+    f32x4 mv[NI][2], ku[NK][2], kv[NK][2];
+    if (u < units) {
+#pragma unroll
+      for (int q = 0; q < NI; ++q) load_pixel<FULL>(map, m_off[q], ch + g8, L.Cin, mv[q][0], mv[q][1]);
+#pragma unroll
+      for (int q = 0; q < NK; ++q) {
+        const int nv = KITEMS % THREADS == 0 || tid + q * THREADS < KITEMS ? L.Cin - ch - g8 : 0;
+        load8<FULL>(Pk, k_off[q] + 4u * (unsigned)(ch + g8), nv, ku[q][0], ku[q][1]);
+        if (dmap) load8<FULL>(Xk, k_off[q] + 4u * (unsigned)(ch + g8), nv, kv[q][0], kv[q][1]);
+      }
+    }
+    if (u > 0) {
+      const unsigned char* ka = klds + (unsigned)h * KROW + (unsigned)(wc * 32 + n) * 16u;
+      // (not unrolled: a launch is short, and straight-line code costs it more instruction fetches than it saves)
+#pragma unroll 1
+      for (int st = 0; st < STEPS; ++st, ka += 2 * KROW) {
+        const Split8 A = load_split(ka, KPIECE);
+        const int tap = CG == 2 ? st : 2 * st + h, ky = (tap * 11) >> 5;
+        const unsigned toff = (unsigned)(ky * (int)T.Wv + tap - 3 * ky) * 16u + (CG == 2 ? (unsigned)h * plane : 0u);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb) {
+          // (the tenth tap meets zero kernel values and reads pixel 0, which is border: 0 x inf would be NaN)
+          const unsigned at = CG == 1 && tap > 8 ? 0u : toff + pix[pb];
+          mfma_split(A, load_split(lds + at, CG * plane), lead[pb], rest[pb]);
+        }
+      }
+      if (u == units) break;
+      __syncthreads();                                             // everyone is done with unit u - 1
+    }
+#pragma unroll
+    for (int q = 0; q < NI; ++q)
+      if (tid + q * THREADS < items) stage_item(tid + q * THREADS, mv[q]);
+#pragma unroll
+    for (int q = 0; q < NK; ++q) {
+      if (dmap) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          ku[q][0][e] = __builtin_fmaf(neg_gamma, ku[q][0][e], kv[q][0][e]);
+          ku[q][1][e] = __builtin_fmaf(neg_gamma, ku[q][1][e], kv[q][1][e]);
+        }
+      }
+      if (tid + q * THREADS < KITEMS) store_split(klds + k_at[q], KPIECE, ku[q][0], ku[q][1]);
+    }
+#pragma unroll 1
+    for (int i = tid + NI * THREADS; i < items; i += THREADS) {    // tiles with more pixels than are requested ahead
+      f32x4 v[2];
+      load_pixel<FULL>(map, T.pixel_offset(a, J, (unsigned)i / CG), ch + g8, L.Cin, v[0], v[1]);
+      stage_item(i, v);
+    }
+    __syncthreads();                                               // unit u is complete
+  }
+  // element j of lane (n, h) is position n of the block, channel 8 (j / 4) + 4 h + j % 4 of the tile
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    ConvOut o[4];
+    const unsigned fo = (unsigned)(f_base + wc * 32 + 4 * h);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) o[q] = conv_out_request(a, J, cand, P, pos_r[pb], T.rows, fo + 8u * q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 sum;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sum[i] = join_split(lead[pb][4 * q + i], rest[pb][4 * q + i]);
+      conv_out_store(a, J, cand, s, o[q], sum, pos_r[pb], T.rows, fo + 8u * q);
+    }
+  }
+}
+
+// Few tiles: 64 positions x 32 channels, eight waves that share out the matrix steps.  Up to stage_units units are staged at
+// once; every wave requests the kernel values of all its steps of them before anything else.
+template <int CG, bool FULL>
+__device__ __forceinline__ void conv_deep(const ConvArgs& a, const ConvJob& J, bool cand, int s, int tile, unsigned char* lds) {
+  constexpr int KW = 8, THREADS = 64 * KW, PB = 2, NP = 32 * PB;
+  constexpr int STEPS = CG == 2 ? 9 : 5;
+  constexpr int NA = (kDeepSteps + KW - 1) / KW;                   // steps of a wave per stage
+  constexpr int NI = 2;
+  const ConvLayer& L = J.L;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ctiles = (L.Cout + 31) / 32;
+  const int pt = tile / ctiles, f0 = (tile % ctiles) * 32;
+  const float* __restrict__ P = cand ? a.G + (long long)s * a.ldg : a.x;
+  const bool second = cand && J.D_in != nullptr;
+  const float* __restrict__ Din = second ? J.D_in + (long long)s * J.D_in_stride : nullptr;
+  const float* __restrict__ Pk = P + L.w_off;
+  const float* __restrict__ Xk = a.x + L.w_off;
+  const ConvTile<NP> T(a, J, pt);
+  const unsigned plane = T.plane;
+  unsigned pix[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) pix[pb] = T.first_pixel(J, T.r_first + (unsigned)(32 * pb + n));
+  // the results this thread finishes at the end: wave kw takes quarter kw % 4 of block kw / 4
+  const int opb = kw >> 2, oq = kw & 3;
+  const unsigned r_out = T.r_first + (unsigned)(32 * opb + n), fo = (unsigned)(f0 + 8 * oq + 4 * h);
+  const ConvOut o = conv_out_request(a, J, cand, P, r_out, T.rows, fo);
+  const unsigned krow = (unsigned)(f0 + n < L.Cout ? f0 + n : 0) * 9u * (unsigned)L.Cin;
+  const float neg_gamma = -a.gamma;
+
+  f32x16 lead[PB], rest[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) lead[pb][j] = rest[pb][j] = 0.f;
+
+  const int chunks = (L.Cin + 8 * CG - 1) / (8 * CG), units = chunks * (second ? 2 : 1);
+  const unsigned unit_bytes = 3 * CG * plane;
+  const unsigned per_unit = (unsigned)T.pixels * CG;
+  const float inv_unit = 1.f / (float)per_unit;
+#pragma unroll 1
+  for (int u0 = 0; u0 < units; u0 += J.stage_units) {
+    const int nu = units - u0 < J.stage_units ? units - u0 : J.stage_units;
+    const int steps = nu * STEPS, items = nu * (int)per_unit;
+    // channel and map of unit u of the stage
+    auto unit_of = [&](int u, bool& dmap) {
+      dmap = u0 + u >= chunks;
+      return (u0 + u - (dmap ? chunks : 0)) * 8 * CG;
+    };
+    f32x4 ku[NA][2], kv[NA][2];
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int i = kw + q * KW < steps ? kw + q * KW : steps - 1;  // (a step too many is not used)
+      const int ul = i / STEPS, st = i - ul * STEPS;
+      bool dmap;
+      const int ch = unit_of(ul, dmap), tap = CG == 2 ? st : 2 * st + h, c = ch + (CG == 2 ? 8 * h : 0);
+      const unsigned off = 4u * (krow + (unsigned)(tap * L.Cin + c));
+      const int nv = tap < 9 ? L.Cin - c : 0;
+      load8<FULL>(Pk, off, nv, ku[q][0], ku[q][1]);
+      if (dmap) load8<FULL>(Xk, off, nv, kv[q][0], kv[q][1]);
+    }
+    if (u0 > 0) __syncthreads();                                   // everyone is done with the units before
+#pragma unroll 1
+    for (int i0 = tid; i0 < items; i0 += NI * THREADS) {
+      f32x4 v[NI][2];
+      unsigned at[NI];
+#pragma unroll
+      for (int q = 0; q < NI; ++q) {
+        const int i = i0 + q * THREADS < items ? i0 + q * THREADS : items - 1;
+        // (exact: i is below 2^21, and a quotient lies at least half an item from the next one's border)
+        const unsigned u = (unsigned)(((float)i + 0.5f) * inv_unit), e = (unsigned)i - u * per_unit;
+        bool dmap;
+        const int ch = unit_of((int)u, dmap);
+        const unsigned px = e / CG;
+        at[q] = u * unit_bytes + (CG == 2 ? (e & 1) * plane : 0u) + px * 16u;
+        const int c = ch + (CG == 2 ? 8 * (int)(e & 1) : 0);
+        const unsigned off = T.pixel_offset(a, J, px);
+        const float* map = dmap ? Din : J.H0_in;                   // (differs between lanes)
+        load_pixel<FULL>(map, off, c, L.Cin, v[q][0], v[q][1]);
+      }
+#pragma unroll
+      for (int q = 0; q < NI; ++q) store_split(lds + at[q], CG * plane, v[q][0], v[q][1]);
+    }
+    __syncthreads();                                               // the staged units are complete
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      const int i = kw + q * KW;
+      if (i < steps) {
+        const int ul = i / STEPS, st = i - ul * STEPS;
+        if (u0 + ul >= chunks) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            ku[q][0][e] = __builtin_fmaf(neg_gamma, ku[q][0][e], kv[q][0][e]);
+            ku[q][1][e] = __builtin_fmaf(neg_gamma, ku[q][1][e], kv[q][1][e]);
+          }
+        }
+        const int tap = CG == 2 ? st : 2 * st + h, ky = (tap * 11) >> 5;
+        // (a tenth tap meets zero kernel values and reads pixel 0, which is border: 0 x inf would be NaN)
+        const unsigned toff = (unsigned)(ky * (int)T.Wv + tap - 3 * ky) * 16u + (CG == 2 ? (unsigned)h * plane : 0u);
+        const Split8 A = split8(ku[q][0], ku[q][1]);
+#pragma unroll
+        for (int pb = 0; pb < PB; ++pb)
+          mfma_split(A, load_split(lds + (unsigned)ul * unit_bytes + (CG == 1 && tap > 8 ? 0u : toff + pix[pb]), CG * plane),
+                     lead[pb], rest[pb]);
+      }
+    }
+  }
+  // The waves' accumulators, added in wave order: quarter q of a block (registers 4q .. 4q + 3) is one 16-byte piece per lane.
+  __syncthreads();                                                 // the staged units are no longer needed
+  f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = join_split(lead[pb][4 * q + i], rest[pb][4 * q + i]);
+      red[((kw * PB + pb) * 4 + q) * 64 + lane] = v;
+    }
+  __syncthreads();
+  f32x4 part[KW];
+#pragma unroll
+  for (int w = 0; w < KW; ++w) part[w] = red[((w * PB + opb) * 4 + oq) * 64 + lane];
+#pragma unroll
+  for (int w = 1; w < KW; ++w) part[0] += part[w];
+  conv_out_store(a, J, cand, s, o, part[0], r_out, T.rows, fo);
+}
+
+// Blocks: [tiles of the pass at x] [tiles x candidates, candidate fastest] [squared norms: pieces x candidates] [one that
+// clears the counters].  Returns whether the block is one of the small jobs, which it then has done.
+__device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& is_base, int& s, int& tile) {
+  int b = blockIdx.x;
+  is_base = b < a.base_blocks;
+  if (!is_base) b -= a.base_blocks;
+  if (!is_base && b >= a.cand_blocks) {
+    b -= a.cand_blocks;
+    if (b < a.aux_pieces * a.aux_m) {
+      sumsq_piece(a, b / a.aux_pieces, b % a.aux_pieces, reinterpret_cast<double*>(lds));
+    } else {
+      const uint4 z = {0u, 0u, 0u, 0u};
+      for (int i = threadIdx.x; i < a.aux_zero16; i += blockDim.x) reinterpret_cast<uint4*>(a.aux_zero)[i] = z;
+    }
+    return true;
+  }
+  s = is_base ? 0 : b % a.n_cand;
+  tile = is_base ? b : b / a.n_cand;
+  return false;
+}
+
+template <int CG, bool FULL, int PB, int WP, int WC>
+__global__ __launch_bounds__(256, 2) void conv_wide_kernel(const ConvArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
+  bool is_base;
+  int s, tile;
+  if (conv_block(a, conv_lds, is_base, s, tile)) return;
+  conv_wide<CG, FULL, PB, WP, WC>(a, is_base ? a.bj : a.cj, !is_base, s, tile, conv_lds);
+}
+
+template <int CG, bool FULL>
+__global__ __launch_bounds__(512, 2) void conv_deep_kernel(const ConvArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
+  bool is_base;
+  int s, tile;
+  if (conv_block(a, conv_lds, is_base, s, tile)) return;
+  conv_deep<CG, FULL>(a, is_base ? a.bj : a.cj, !is_base, s, tile, conv_lds);
+}
+
+// ---- host side
+constexpr long long kConvLdsMost = 160 * 1024;
+constexpr long long kConvLdsTwo = 80 * 1024;      // two workgroups per compute unit
+
+unsigned magic_for(long long d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned long long)d - 1) / (unsigned long long)d); }
+
+// Most border rows that np consecutive positions touch.
+long long most_border_rows(const ConvLayer& L, int np) {
+  const long long out_rows = (np - 1 + L.Wout - 1) / L.Wout + 1;                 // output rows they can lie in
+  const long long samples = (out_rows - 2 + L.Hout) / L.Hout;                    // sample boundaries among these
+  const long long skip = (long long)L.Hin + 2 - (long long)L.Hout * L.stride;    // border rows beyond the stride at a boundary
+  return (out_rows - 1) * L.stride + 3 + samples * (skip > 0 ? skip : 0);
+}
+// LDS bytes of the map values of one unit of `groups` groups of eight channels, upper bound for every tile of np positions.
+long long map_bytes(const ConvLayer& L, int np, int groups) { return (most_border_rows(L, np) * (L.Win + 2) | 1) * 16 * 3 * groups; }
+// ... of the kernel values (wide workgroups)
+long long kernel_bytes(int wc, int groups) { return 3LL * 2 * (groups == 2 ? 9 : 5) * (32 * wc + 1) * 16; }
+
+// The quick divisions want their products below 2^32, and so do the byte offsets inside one source's maps and kernels.
+bool sizes_fit(const ConvLayer& L, int n_r, int np) {
+  const long long rows = (long long)n_r * L.Hout * L.Wout, v = (long long)n_r * (L.Hin + 2) + 2, most = 1ll << 32;
+  return rows < (1ll << 30) && rows * L.Wout < most && rows / L.Wout * L.Hout < most && v * (L.Hin + 2) < most &&
+         most_border_rows(L, np) * (L.Win + 2) * (L.Win + 2) < most && most_border_rows(L, np) * (L.Win + 2) < (1ll << 18) &&
+         4 * rows * L.Cout < most && 4ll * n_r * L.Hin * L.Win * L.Cin < most && 36ll * L.Cin * L.Cout < most;
+}
+// LDS bytes of a unit of a job with `groups` groups of eight channels.
+long long wide_bytes(const ConvLayer& L, int np, int wc, int groups) { return map_bytes(L, np, groups) + kernel_bytes(wc, groups); }
+long long deep_bytes(const ConvLayer& L, int groups) { return map_bytes(L, 64, groups); }
+bool full_groups(const ConvLayer& L) { return L.Cin % 8 == 0; }
+
+// What both kinds of launches prepare for each job; job_lds gives a job's LDS bytes and sets its groups and stage_units.
+template <typename F>
+hipError_t plan_tiles(ConvArgs& a, int np, int wc, F job_lds, long long* lds, long long* total) {
+  long long blocks[2] = {0, 0};
+  for (int q = 0; q < 2; ++q) {
+    ConvJob& j = q == 0 ? a.bj : a.cj;
+    if (q == 0 ? a.has_base == 0 : a.n_cand <= 0) continue;
+    const ConvLayer& L = j.L;
+    j.magic_wout = magic_for(L.Wout);
+    j.magic_hout = magic_for(L.Hout);
+    j.magic_wv = magic_for(L.Win + 2);
+    j.magic_hv = magic_for(L.Hin + 2);
+    const long long need = job_lds(j, q == 1 && j.D_in != nullptr ? 2 : 1);
+    if (need > *lds) *lds = need;
+    const long long rows = (long long)a.n_r * L.Hout * L.Wout;
+    blocks[q] = (rows + np - 1) / np * ((L.Cout + 32 * wc - 1) / (32 * wc)) * (q == 1 ? a.n_cand : 1);
+  }
+  *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0);
+  if (*total > (1ll << 30) || *lds > kConvLdsMost) return hipErrorInvalidValue;
+  a.base_blocks = (int)blocks[0];
+  a.cand_blocks = (int)blocks[1];
+  return hipSuccess;
+}
+
+template <int CG, bool FULL, int PB, int WP, int WC>
+hipError_t launch_wide(ConvArgs a, hipStream_t stream) {
+  constexpr int NP = 32 * PB * WP;
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wide_kernel<CG, FULL, PB, WP, WC>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsMost);
+  if (attr_err != hipSuccess) return attr_err;
+  long long lds = 64, total = 0;                                   // (the squared norms' four partial sums)
+  const hipError_t e = plan_tiles(a, NP, WC, [](ConvJob& j, int) { return wide_bytes(j.L, NP, WC, CG); }, &lds, &total);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((conv_wide_kernel<CG, FULL, PB, WP, WC>), dim3((unsigned)total), dim3(256), (size_t)lds, stream, a);
+  return hipGetLastError();
+}
+
+template <int CG, bool FULL>
+hipError_t launch_deep(ConvArgs a, hipStream_t stream) {
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_deep_kernel<CG, FULL>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsMost);
+  if (attr_err != hipSuccess) return attr_err;
+  long long lds = 8 * 8192, total = 0;                             // at least the accumulators of eight waves
+  const hipError_t e = plan_tiles(a, 64, 1, [](ConvJob& j, int maps) {
+    const int chunks = (j.L.Cin + 8 * CG - 1) / (8 * CG);
+    const long long unit = deep_bytes(j.L, CG);
+    long long n = kDeepSteps / (CG == 2 ? 9 : 5);
+    if (n > kConvLdsMost / unit) n = kConvLdsMost / unit;
+    j.stage_units = (int)(n > chunks * maps ? chunks * maps : n);
+    return j.stage_units * unit;
+  }, &lds, &total);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((conv_deep_kernel<CG, FULL>), dim3((unsigned)total), dim3(512), (size_t)lds, stream, a);
+  return hipGetLastError();
+}
+
+template <int PB, int WP, int WC>
+hipError_t launch_wide_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
+  if (groups == 1) return full ? launch_wide<1, true, PB, WP, WC>(a, stream) : launch_wide<1, false, PB, WP, WC>(a, stream);
+  return full ? launch_wide<2, true, PB, WP, WC>(a, stream) : launch_wide<2, false, PB, WP, WC>(a, stream);
+}
+hipError_t launch_deep_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
+  if (groups == 1) return full ? launch_deep<1, true>(a, stream) : launch_deep<1, false>(a, stream);
+  return full ? launch_deep<2, true>(a, stream) : launch_deep<2, false>(a, stream);
+}
+
+hipError_t launch_gather(const ConvArgs& a, hipStream_t stream) {
+  for (int q = 0; q < 2; ++q) {
+    const ConvJob& j = q == 0 ? a.bj : a.cj;
+    const int sources = q == 0 ? (a.has_base ? 1 : 0) : a.n_cand;
+    if (sources <= 0) continue;
+    const long long rows = (long long)a.n_r * j.L.Hout * j.L.Wout;
+    const long long row_blocks = (rows + 31) / 32;
+    const int ftiles = (j.L.Cout + 31) / 32;
+    const dim3 grid((unsigned)(row_blocks * ftiles), sources);
+    // one wave per tile when there are tiles enough for every SIMD of the chip twice over, else three
+    const bool wide = row_blocks * ftiles * sources >= 2048;
+    if (q == 1) {
+      if (wide) hipLaunchKernelGGL((conv_layer_kernel<true, 1>), grid, dim3(64), 0, stream, a);
+      else hipLaunchKernelGGL((conv_layer_kernel<true, 3>), grid, dim3(192), 0, stream, a);
+    } else {
+      if (wide) hipLaunchKernelGGL((conv_layer_kernel<false, 1>), grid, dim3(64), 0, stream, a);
+      else hipLaunchKernelGGL((conv_layer_kernel<false, 3>), grid, dim3(192), 0, stream, a);
+    }
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
-  const long long rows = (long long)a.n_r * a.L.Hout * a.L.Wout;
-  const long long row_blocks = (rows + 31) / 32;
-  const int ftiles = (a.L.Cout + 31) / 32;
+  // the job that dominates the launch decides its shape
+  const ConvLayer& L = a.n_cand > 0 ? a.cj.L : a.bj.L;
   const int sources = a.n_cand > 0 ? a.n_cand : 1;
-  const dim3 grid((unsigned)(row_blocks * ftiles), sources);
-  // one wave per tile when there are tiles enough for every SIMD of the chip twice over, else three
-  const bool wide = row_blocks * ftiles * sources >= 2048;
-  if (a.n_cand > 0) {
-    if (wide) hipLaunchKernelGGL((conv_layer_kernel<true, 1>), grid, dim3(64), 0, stream, a);
-    else hipLaunchKernelGGL((conv_layer_kernel<true, 3>), grid, dim3(192), 0, stream, a);
-  } else {
-    if (wide) hipLaunchKernelGGL((conv_layer_kernel<false, 1>), grid, dim3(64), 0, stream, a);
-    else hipLaunchKernelGGL((conv_layer_kernel<false, 3>), grid, dim3(192), 0, stream, a);
+  const long long rows = (long long)a.n_r * L.Hout * L.Wout;
+  const int ctiles = (L.Cout + 31) / 32;
+  const bool full = full_groups(L);
+  // groups of eight channels per unit: two, or one where the input has no more channels or where that makes room for two
+  // workgroups per compute unit (stride 2, where a position has four pixels of its own); 0: neither fits
+  auto pick_groups = [&](auto bytes, int np) {
+    long long need[3] = {0, 0, 0};
+    for (const ConvJob* j : {&a.cj, &a.bj}) {
+      if (j == &a.cj ? a.n_cand <= 0 : !a.has_base) continue;
+      if (!sizes_fit(j->L, a.n_r, np)) return 0;
+      for (int g = 1; g <= 2; ++g)
+        if (bytes(j->L, g) > need[g]) need[g] = bytes(j->L, g);
+    }
+    if (L.Cin > 8 && need[2] <= kConvLdsTwo) return 2;
+    return need[1] <= kConvLdsMost ? 1 : 0;
+  };
+  // tiles of 128 positions where they give every compute unit two workgroups or more
+  const int wc = ctiles == 1 ? 1 : 2;
+  const bool wide = (rows + 127) / 128 * ((ctiles + wc - 1) / wc) * sources >= 512;
+  if (a.n_cand > 0 && a.has_base && (wide || (full && !full_groups(a.bj.L)))) {
+    // The pass at x on its own: next to wide tiles its few workgroups, each with all of K to walk, would be the last ones to end
+    // by far (n_r = 32, convolution 3 behind the candidates' convolution 2: 148 us together, 103 + 11 us apart); and one
+    // kernel runs both jobs, so the channels of either have to be whole groups if the candidates' are.
+    ConvArgs b = a;
+    b.n_cand = 0;
+    const hipError_t e = launch_conv(b, stream);
+    if (e != hipSuccess) return e;
+    b = a;
+    b.has_base = b.aux_m = b.aux_pieces = b.aux_zero16 = 0;
+    return launch_conv(b, stream);
   }
-  return hipGetLastError();
+  if (wide) {
+    const int g = pick_groups([&](const ConvLayer& l, int gr) { return wide_bytes(l, 128, wc, gr); }, 128);
+    if (g > 0) return wc == 1 ? launch_wide_as<1, 4, 1>(g, full, a, stream) : launch_wide_as<2, 2, 2>(g, full, a, stream);
+  }
+  const int g = pick_groups([&](const ConvLayer& l, int gr) { return deep_bytes(l, gr); }, 64);
+  if (g > 0) return launch_deep_as(g, full, a, stream);
+  ConvArgs r = a;
+  r.aux_pieces = r.aux_m = r.aux_zero16 = 0;
+  const hipError_t e = launch_gather(r, stream);
+  if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0)) return e;
+  r = a;                                           // the small jobs alone
+  r.has_base = r.n_cand = 0;
+  return launch_wide<1, true, 1, 4, 1>(r, stream);
 }
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
@@ -208,12 +856,6 @@ hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {
   const long long want = (n16 + 255) / 256;
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)(want > 4096 ? 4096 : want)), dim3(256), 0, stream,
                      reinterpret_cast<uint4*>(p), n16);
-  return hipGetLastError();
-}
-
-hipError_t launch_sumsq(const float* G, long long ldg, int m, long long begin, long long count, int n_blocks,
-                        double* partials, int P, int p_off, hipStream_t stream) {
-  hipLaunchKernelGGL(sumsq_kernel, dim3(n_blocks, m), dim3(256), 0, stream, G, ldg, begin, count, partials, P, p_off);
   return hipGetLastError();
 }
 

@@ -177,28 +177,42 @@ struct ConvLayer {
   long long w_off, b_off;  // offsets inside a parameter vector; b_off = -1: no bias
   int Hin, Win, Cin, Hout, Wout, Cout, stride;
 };
-struct ConvArgs {
-  const float* G;         // [m x d]
-  const float* x;         // [d]
-  long long ldg;
-  int n_cand;             // m: the candidates' pass; 0: the pass at x
-  int n_r;
+// One convolution of one pass: of the pass at x or of the candidates.
+struct ConvJob {
   ConvLayer L;
   const float* H0_in;     // input map of the pass at x, NHWC [n_r * Hin * Win x Cin] (the images for the first convolution)
-  const float* D_in;      // candidate 0's scaled change of the input map, or nullptr (first convolution)
+  const float* D_in;      // candidate 0's scaled change of the input map, or nullptr (first convolution, pass at x)
   long long D_in_stride;  // floats between candidates
   float* Z0;              // [rows x Cout] pre-activations at x: written by the pass at x, read by the candidates
   float* out;             // pass at x: relu map; candidates: candidate 0's scaled change of the output map
   long long out_stride;   // floats between candidates (candidates' pass)
   int tiled_out;          // 1: out is the operand of the fully connected layer: rows = samples, k = (position, channel),
   int Kp_fc;              //    in matrix-operand order of padded width Kp_fc
+  // filled in by the launcher: (map, channel chunk) units staged at once, multipliers of the quick divisions
+  int stage_units;
+  unsigned magic_wout, magic_hout, magic_wv, magic_hv;
+};
+// One launch: the candidates through cj (n_cand > 0) and the pass at x through bj (has_base), which do not
+// depend on each other, and two small jobs: the squared norms of the leading aux_count coordinates of aux_m candidates in
+// aux_pieces fixed pieces (-> aux_norm[s * aux_P + aux_p_off + piece]) and clearing 16 * aux_zero16 bytes at aux_zero.
+struct ConvArgs {
+  const float* G;         // [m x d]
+  const float* x;         // [d]
+  long long ldg;
+  int n_cand;             // m, or 0
+  int has_base;
+  int n_r;
   float gamma, neg_inv_gamma;
+  ConvJob cj, bj;
+  int aux_m, aux_pieces, aux_P, aux_p_off;
+  long long aux_count;
+  double* aux_norm;
+  void* aux_zero;
+  int aux_zero16;
+  int base_blocks, cand_blocks;   // filled in by the launcher
 };
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
-// sum of squares of G[s][begin .. begin+count) for every candidate, in n_blocks fixed pieces -> partials[s*P + p_off + blk]
-hipError_t launch_sumsq(const float* G, long long ldg, int m, long long begin, long long count, int n_blocks,
-                        double* partials, int P, int p_off, hipStream_t stream);
 
 }  // namespace zeno
 #endif

@@ -29,6 +29,7 @@
 // float64 (fixed order), krum_score_kernel forms the score of one row per workgroup,
 // krum_argmin_kernel picks the winner, krum_copy_kernel copies the winning row.
 #include "zeno_layer_impl.h"
+#include "zeno_split.h"
 
 namespace zeno {
 
@@ -37,47 +38,6 @@ namespace {
 constexpr int kGramWaves = 4;
 
 typedef float f32x8 __attribute__((ext_vector_type(8)));
-
-// Three-way split of eight floats into bf16 pieces, x = h + m + l + (at most 2^-25 |x|):
-// h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), round to nearest even each time;
-// both subtractions are exact.
-__device__ inline void split3(const f32x4& v0, const f32x4& v1, bf16x8& h, bf16x8& m, bf16x8& l) {
-  // Two floats at a time: one packed conversion gives both bf16 pieces in one register, and the exact remainder of
-  // either float is one instruction, the bf16 dot product of that register with (-1, 0) or (0, -1) added to the
-  // float (v_dot2c_f32_bf16: the product with -1 is exact, the product with 0 vanishes, and the sum x - h is
-  // representable, so its single rounding changes nothing).  Seven instructions per two floats; taking the pieces'
-  // float values out of the packed register with a shift or a mask and subtracting took eleven.
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-  const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-  // The two constants go through registers: written as immediates, (-1, 0) is emitted as the inline constant -1.0,
-  // which this instruction does not read as the bf16 pair (-1, 0) (measured: the remainders then come out wrong).
-  unsigned first_bits = 0x0000bf80u, second_bits = 0xbf800000u;
-  asm("" : "+s"(first_bits), "+s"(second_bits));
-  const bf16x2 minus_first = __builtin_bit_cast(bf16x2, first_bits), minus_second = __builtin_bit_cast(bf16x2, second_bits);
-  u32x4 hu, mu, lu;
-  auto pack = [](float a, float b) {
-    const f32x2 t = {a, b};
-    return __builtin_convertvector(t, bf16x2);
-  };
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float a = x[2 * i], b = x[2 * i + 1];
-    const bf16x2 hp = pack(a, b);
-    const float ra = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_first, a, false);
-    const float rb = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_second, b, false);
-    const bf16x2 mp = pack(ra, rb);
-    const float sa = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_first, ra, false);
-    const float sb = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_second, rb, false);
-    hu[i] = __builtin_bit_cast(unsigned, hp);
-    mu[i] = __builtin_bit_cast(unsigned, mp);
-    lu[i] = __builtin_bit_cast(unsigned, pack(sa, sb));
-  }
-  h = __builtin_bit_cast(bf16x8, hu);
-  m = __builtin_bit_cast(bf16x8, mu);
-  l = __builtin_bit_cast(bf16x8, lu);
-}
 
 // CENTER: second pass; runs only if *run_flag != 0 and subtracts row *center from every row.
 // NT: streaming loads, where the rows start on 128-byte lines; the 256-byte row segments of other rows share their

@@ -1,0 +1,81 @@
+// Three-way split of float32 operands for the bf16 matrix cores, shared by the kernels that multiply at float32 accuracy.
+#ifndef ZENO_SPLIT_H_
+#define ZENO_SPLIT_H_
+
+#include "zeno_internal.h"
+
+namespace zeno {
+
+namespace {
+
+// Three-way split of eight floats into bf16 pieces, x = h + m + l + (at most 2^-25 |x|):
+// h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), round to nearest even each time;
+// both subtractions are exact.
+__device__ inline void split3(const f32x4& v0, const f32x4& v1, bf16x8& h, bf16x8& m, bf16x8& l) {
+  // Two floats at a time: one packed conversion gives both bf16 pieces in one register, and the exact remainder of
+  // either float is one instruction, the bf16 dot product of that register with (-1, 0) or (0, -1) added to the
+  // float (v_dot2c_f32_bf16: the product with -1 is exact, the product with 0 vanishes, and the sum x - h is
+  // representable, so its single rounding changes nothing).  Seven instructions per two floats; taking the pieces'
+  // float values out of the packed register with a shift or a mask and subtracting took eleven.
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const float x[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+  // The two constants go through registers: written as immediates, (-1, 0) is emitted as the inline constant -1.0,
+  // which this instruction does not read as the bf16 pair (-1, 0) (measured: the remainders then come out wrong).
+  unsigned first_bits = 0x0000bf80u, second_bits = 0xbf800000u;
+  asm("" : "+s"(first_bits), "+s"(second_bits));
+  const bf16x2 minus_first = __builtin_bit_cast(bf16x2, first_bits), minus_second = __builtin_bit_cast(bf16x2, second_bits);
+  u32x4 hu, mu, lu;
+  auto pack = [](float a, float b) {
+    const f32x2 t = {a, b};
+    return __builtin_convertvector(t, bf16x2);
+  };
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const float a = x[2 * i], b = x[2 * i + 1];
+    const bf16x2 hp = pack(a, b);
+    const float ra = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_first, a, false);
+    const float rb = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_second, b, false);
+    const bf16x2 mp = pack(ra, rb);
+    const float sa = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_first, ra, false);
+    const float sb = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_second, rb, false);
+    hu[i] = __builtin_bit_cast(unsigned, hp);
+    mu[i] = __builtin_bit_cast(unsigned, mp);
+    lu[i] = __builtin_bit_cast(unsigned, pack(sa, sb));
+  }
+  h = __builtin_bit_cast(bf16x8, hu);
+  m = __builtin_bit_cast(bf16x8, mu);
+  l = __builtin_bit_cast(bf16x8, lu);
+}
+
+// Eight consecutive k of one matrix operand as its three pieces.
+struct Split8 {
+  bf16x8 h, m, l;
+};
+__device__ inline Split8 split8(const f32x4& v0, const f32x4& v1) {
+  Split8 s;
+  split3(v0, v1, s.h, s.m, s.l);
+  return s;
+}
+
+// One k-step of 16 of a 32 x 32 block of products at float32 accuracy: the six piece products down to 2^-17 of the leading
+// one; what is dropped is about 2^-24 of |a||b| per product, one float32 rounding.  The leading products have an
+// accumulator of their own: an operand that is not finite has no useful remainder (inf - inf), and the
+// leading products alone say what the float32 product would have been (join_split).
+__device__ inline void mfma_split(const Split8& a, const Split8& b, f32x16& lead, f32x16& rest) {
+  rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, rest, 0, 0, 0);
+  rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, rest, 0, 0, 0);
+  rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, rest, 0, 0, 0);
+  rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, rest, 0, 0, 0);
+  rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, rest, 0, 0, 0);
+  lead = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, lead, 0, 0, 0);
+}
+__device__ inline float join_split(float lead, float rest) {
+  return __builtin_fabsf(lead) < __builtin_inff() ? lead + rest : lead;
+}
+
+}  // namespace
+
+}  // namespace zeno
+#endif

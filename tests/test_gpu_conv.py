@@ -105,6 +105,49 @@ def test_cnn_nonfinite_rows_and_workspace_contents(B):
     assert np.all(score_error(s[ok], s_ref, scale) <= SCORE_TOL["fp32"])
 
 
+EDGES = [
+    # (in_h, in_w, in_c, channels, strides), m, n_r
+    ((9, 7, 8, [32, 33], [1, 2]), 3, 3),         # eight channels: steps of two taps; one channel beyond a tile
+    ((8, 8, 17, [64, 12], [2, 1]), 3, 5),        # seventeen channels: a second unit of one channel; two channel tiles
+    ((4, 4, 24, [40, 40, 8], [2, 1, 1]), 4, 9),  # a second unit of one group; 2 x 2 maps, many samples per tile
+    ((1, 1, 48, [16, 16], [1, 2]), 2, 40),       # maps of one pixel
+    ((6, 5, 72, [96], [1]), 2, 2),               # more units than are staged at once
+    ((16, 16, 3, [32, 32, 64], [1, 2, 1]), 20, 30),   # wide tiles, one and two channel tiles
+    ((15, 13, 20, [20, 64], [1, 2]), 30, 21),    # wide tiles with channels that end inside a group, the last tile cut short
+    ((3, 1001, 1, [3, 2], [1, 1]), 2, 2),        # rows too wide for the staging
+]
+
+
+@pytest.mark.parametrize("case", range(len(EDGES)))
+def test_cnn_edges_of_the_staged_tiles(B, case):
+    """Every score at the fp32 tolerance at the sizes where the convolution kernels change shape: channels per unit, units
+    per stage, channel tiles, position tiles that cross rows and samples, and maps that are not staged at all."""
+    (h, w_, c, conv_c, conv_stride), m, n_r = EDGES[case]
+    desc = dict(in_h=h, in_w=w_, in_c=c, conv_c=conv_c, conv_stride=conv_stride, fc_out=7, has_bias=case != 4)
+    w = WL.make_cnn_workload(f"cnn_edge{case}", 50 + case, desc, m, 1, n_r, 0.1, 1e-3, seed=case, n_flip=1, worker_batch=4)
+    _check(B, w)
+
+
+def test_cnn_infinite_kernel_values(B):
+    """A kernel value of +-inf reaches the positions whose patch is not zero there as +-inf: a unit that it switches off at
+    every position (negative pre-activation everywhere, no zero activations in reach) leaves a finite loss difference."""
+    desc = dict(in_h=1, in_w=1, in_c=9, conv_c=[5], conv_stride=[1], fc_out=3, has_bias=True)
+    w = WL.make_cnn_workload("cnn_inf", 70, desc, 4, 1, 6, 0.1, 0.0)
+    w.features.abs_().add_(0.5)
+    taps = w.G[2][:5 * 81].view(5, 9, 9)                # [channel][tap][input channel]
+    ref = w.G[2].clone()
+    taps[1, 4, 3] = float("inf")                        # centre tap (the only one inside a 1 x 1 image): pre-activation -> -inf
+    ref[:5 * 81].view(5, 9, 9)[1, 4, 3] = 1e6           # a finite value that switches the unit off as well
+    off = WL.make_cnn_workload("cnn_inf", 70, desc, 4, 1, 6, 0.1, 0.0)
+    off.features.copy_(w.features)
+    off.G[2] = ref
+    a, b = npy(_gpu_scores(B, w)), npy(_gpu_scores(B, off))
+    # the same loss difference; the unit's own change is -z0 either way, so only rounding separates the two
+    assert np.isfinite(b[2])
+    assert np.isnan(a[2]) or a[2] == -np.inf or abs(a[2] - b[2]) <= 1e-5 * max(1.0, abs(b[2]))
+    assert np.array_equal(a[[0, 1, 3]], b[[0, 1, 3]])
+
+
 def test_cnn_error_codes(B):
     with pytest.raises(B.ZenoError):
         B.ZenoCnnModel(dict(in_h=4, in_w=4, in_c=1, conv_c=[4], conv_stride=[3], fc_out=2, has_bias=True))
