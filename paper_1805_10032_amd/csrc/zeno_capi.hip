@@ -103,7 +103,6 @@ Plan make_plan(const zeno_model* mdl, int m, int n_r) {
     if ((long long)((cover + kMaxTileRows - 1) / kMaxTileRows) * m >= 256 && tail_partial_bytes(p.MB) > p.sz_slice_part)
       p.sz_slice_part = tail_partial_bytes(p.MB);
   }
-  p.off_slice_part = take(p.sz_slice_part);
   p.off_slice_cnt = take((size_t)p.n_counters * sizeof(unsigned int));
   p.cand_stride = align_up((size_t)p.n_pad * max_np * p.esize, 256);
   if (p.L > 1) {
@@ -113,6 +112,20 @@ Plan make_plan(const zeno_model* mdl, int m, int n_r) {
   p.off_dz = take(p.sz_dz);
   p.off_norm = take((size_t)m * p.P * sizeof(double));
   p.off_diff = take((size_t)m * n_r * sizeof(double));
+  // Launches of four-wave workgroups hand over up to eight slices of every tile.  A plan that fits the static scratch array
+  // with the buffer above keeps fitting it (and takes the same slices there as on a caller's workspace).
+  size_t wide = 0;
+  for (int l = 0; l < p.L; ++l) {
+    const size_t tiles = (size_t)((pad64(D.dims[l + 1]) + 127) / 128) * m + (l + 1 < p.L ? (pad64(D.dims[l + 2]) + 127) / 128 : 0);
+    if (D.dims[l + 1] > 64 && tiles * 8 * wide_slice_bytes(p.MB) > wide) wide = tiles * 8 * wide_slice_bytes(p.MB);
+  }
+  if (wide > kWidePartialBytes) wide = kWidePartialBytes;
+  if (wide > p.sz_slice_part) {
+    if (off + p.sz_slice_part > (size_t)ZENO_STATIC_SCRATCH_BYTES) p.sz_slice_part = wide;
+    else if (off + wide > (size_t)ZENO_STATIC_SCRATCH_BYTES) p.sz_slice_part = (size_t)ZENO_STATIC_SCRATCH_BYTES - off;
+    else p.sz_slice_part = wide;
+  }
+  p.off_slice_part = take(p.sz_slice_part);
   p.total = off;
   return p;
 }
@@ -248,6 +261,11 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
   common.slice_partials = reinterpret_cast<float*>(ws + p.off_slice_part);
   common.slice_counters = reinterpret_cast<unsigned int*>(ws + p.off_slice_cnt);
 
+  // K slices of a launch of four-wave workgroups, as far as its hand-over buffer and its partial-norm slots reach
+  auto wide_slices = [&](const Launch& c, int l) {
+    const int S = layer_wide_plan(c.a, bf16, c.delta, p.MB, p.sz_slice_part);
+    return S >= 2 && (pad64(D.dims[l + 1]) + 127) / 128 * S > norm_slots_bound(D.dims[l + 1], 1, p.MB) ? 1 : S;
+  };
   std::vector<Launch> seq;
   if (L > 1) {
     Launch b;
@@ -279,6 +297,12 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
       c.a.bj = make_job(0);
       c.base_layer = 0;
       c.bytes += layer_bytes(0);
+      const int wide = query_device ? wide_slices(c, 0) : 0;
+      if (wide >= 1) c.a.wide_nw = 4;
+      if (wide >= 2) {
+        c.a.tail_cand = m;
+        c.a.tail_slices = wide;
+      }
       seq.push_back(c);
       continue;
     }
@@ -292,11 +316,25 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
     }
     // A launch whose last round of eight-wave workgroups would be partly empty runs the tiles of that round's
     // candidates, and the pass at x, in K slices at its end.
+    const int wide = query_device ? wide_slices(c, l) : 0;
+    if (wide >= 1) c.a.wide_nw = 4;
+    if (wide >= 2) {
+      c.a.tail_cand = m;
+      c.a.tail_slices = wide;
+      if (l + 1 < L) {
+        c.bytes += layer_bytes(l + 1);
+        c.wt_layer = l + 1;
+        c.base_layer = l + 1;
+      }
+      seq.push_back(c);
+      continue;
+    }
     int tail_main = m;
     const int tail_slices = query_device ? layer_tail_slices(c.a, bf16, l > 0, p.MB, &tail_main) : 0;
     if (tail_slices >= 2) {
       c.a.tail_cand = m - tail_main;
       c.a.tail_slices = tail_slices;
+      c.a.wide_nw = 8;
       if (l + 1 < L) {
         c.bytes += layer_bytes(l + 1);
         c.wt_layer = l + 1;
@@ -334,7 +372,7 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
   for (Launch& c : seq) {
     if (c.a.n_cand <= 0) continue;
     c.a.p_off = P;
-    if (c.a.tail_slices >= 2) c.a.tail_p_off = P + (pad64(D.dims[c.layer + 1]) + kMaxTileRows - 1) / kMaxTileRows;
+    if (c.a.tail_slices >= 2) c.a.tail_p_off = c.a.tail_cand == m ? P : P + (pad64(D.dims[c.layer + 1]) + kMaxTileRows - 1) / kMaxTileRows;
     P += query_device ? layer_tiles(c.a, bf16, c.delta, p.MB) : norm_slots_bound(D.dims[c.layer + 1], m, p.MB);
   }
   for (Launch& c : seq)

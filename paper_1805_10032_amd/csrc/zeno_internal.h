@@ -95,14 +95,16 @@ struct LayerArgs {
   unsigned int* slice_counters;
   int P;                // partial slots per candidate
   int p_off;            // first slot of this layer
+  int wide_nw;          // waves per workgroup a plan chose (4 or 8; 0: from the launch's size)
   // Sliced tail of a launch of eight-wave workgroups (see layer_tail_slices): the tiles of the last tail_cand
   // candidates, and of the pass at x if the launch carries it, run as tail_slices K slices each, in the blocks
-  // from main_blocks on.  Their partial accumulators go through slice_partials / slice_counters as well; their
+  // from main_blocks on.  tail_cand = n_cand: all tiles of a launch of four-wave workgroups (see layer_wide_plan).  Their partial accumulators go through slice_partials / slice_counters as well; their
   // partial norms to the slots tail_p_off + tile * tail_slices + slice.
   int tail_cand;
   int tail_slices;
   int tail_p_off;
   int main_blocks;      // filled in by the launcher
+  int src_chunk;        // sources per scheduling unit, filled in by the launcher
 };
 
 // Launchers.  Each returns the hipError_t of its launches.
@@ -119,6 +121,9 @@ constexpr int kMaxSliceGroups = 2048;
 // Sliced tails: at most this many eight-wave workgroups (tiles x slices), each handing over 8 x row blocks x 4 KB
 constexpr int kMaxTailWorkgroups = 256;
 inline size_t tail_partial_bytes(int MB) { return (size_t)kMaxTailWorkgroups * 8 * MB * 16 * 64 * sizeof(float); }
+// Launches of four-wave workgroups cut into K slices: bytes one workgroup hands over, and the most a launch may
+constexpr size_t kWidePartialBytes = size_t(32) << 20;
+inline size_t wide_slice_bytes(int MB) { return (size_t)4 * MB * 16 * 64 * sizeof(float); }
 struct KPlan {
   int k_waves;    // waves of a workgroup that share a feature tile and split K
   int k_slices;   // workgroups per feature tile
@@ -137,6 +142,8 @@ struct LaunchShape {
 hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipStream_t stream,
                         LaunchShape* shape = nullptr);
 bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB);  // run a.bj inside the candidates' launch?
+// K slices of all tiles of a launch of four-wave workgroups (1: whole tiles), 0: the launch keeps its shape
+int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget);
 // K slices for the tiles of the last (n_cand - *n_main) candidates of an eight-wave launch, or 0: no sliced tail
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main);
 int layer_tiles(const LayerArgs& a, bool bf16, bool delta, int MB);   // partial-norm slots per candidate the launch fills

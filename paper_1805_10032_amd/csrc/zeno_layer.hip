@@ -64,7 +64,7 @@ static int ks_waves(bool bf16, bool delta, int MB) {
 // are 3.1 rounds, four waves gain 2-4 % per layer; workload 5: 1024 are exactly four rounds and
 // eight waves, which copy the activations once per 256 features instead of once per 128, win).
 static int nw_for(const LayerArgs& a, bool bf16, bool delta, int MB) {
-  if (a.tail_slices >= 2) return 8;   // planned with a sliced tail, which exists for eight-wave workgroups
+  if (a.wide_nw > 0) return a.wide_nw;   // planned (layer_wide_plan, layer_tail_slices)
   const int nw = launch_nw_for(a);
   if (nw != 8 || a.n_cand <= 0) return nw;
   if (wgs_per_cu(bf16, delta, MB, 4) < 2) return 8;
@@ -159,24 +159,63 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
     e.slice_counters = (int)groups;
     if (a.n_cand > 0) e.norm_slots *= kp.k_slices;
   }
-  if (a.tail_slices >= 2 && NW == 8) {
-    const long long tiles = (a.has_base ? job_tiles(a.bj, 256) : 0) + (long long)job_tiles(a.cj, 256) * a.tail_cand;
-    e.slice_bytes = tiles * a.tail_slices * 8 * MB * 16 * 64 * (long long)sizeof(float);
+  if (a.tail_slices >= 2 && NW == a.wide_nw) {
+    const long long tiles = (a.has_base ? job_tiles(a.bj, 32 * NW) : 0) + (long long)job_tiles(a.cj, 32 * NW) * a.tail_cand;
+    e.slice_bytes = tiles * a.tail_slices * NW * MB * 16 * 64 * (long long)sizeof(float);
     e.slice_counters = (int)tiles;
-    e.norm_slots = a.tail_p_off - a.p_off + job_tiles(a.cj, 256) * a.tail_slices;   // both ranges, counted from p_off
+    e.norm_slots = a.tail_p_off - a.p_off + job_tiles(a.cj, 32 * NW) * a.tail_slices;   // both ranges, counted from p_off
   }
   return e;
 }
 
-// Does the eight-wave workgroup of this kind double-buffer its activation chunks (the sliced tail needs it)?
-static bool wide_double_buffered(bool bf16, bool delta, int MB) {
-  auto pick = [&](auto mb) {
-    constexpr int M = decltype(mb)::value;
-    return bf16 ? (delta ? Lds<true, true, M, 8>::DBUF : Lds<true, false, M, 8>::DBUF)
-                : (delta ? Lds<false, true, M, 8>::DBUF : Lds<false, false, M, 8>::DBUF);
+// Does the workgroup of NW waves (8 or 4) of this kind double-buffer its activation chunks (slices need it)?
+static bool wide_double_buffered(bool bf16, bool delta, int MB, int NW) {
+  auto pick = [&](auto mb, auto nw) {
+    constexpr int M = decltype(mb)::value, W = decltype(nw)::value;
+    return bf16 ? (delta ? Lds<true, true, M, W>::DBUF : Lds<true, false, M, W>::DBUF)
+                : (delta ? Lds<false, true, M, W>::DBUF : Lds<false, false, M, W>::DBUF);
   };
-  return MB == 1 ? pick(std::integral_constant<int, 1>{}) : MB == 2 ? pick(std::integral_constant<int, 2>{})
-                                                                     : pick(std::integral_constant<int, 4>{});
+  auto pick_nw = [&](auto mb) {
+    return NW == 8 ? pick(mb, std::integral_constant<int, 8>{}) : pick(mb, std::integral_constant<int, 4>{});
+  };
+  return MB == 1 ? pick_nw(std::integral_constant<int, 1>{}) : MB == 2 ? pick_nw(std::integral_constant<int, 2>{})
+                                                                        : pick_nw(std::integral_constant<int, 4>{});
+}
+
+// Candidate launches with too few 256-feature tiles for eight-wave workgroups: four-wave workgroups, all tiles (and those of
+// the pass at x, if it rides along) cut into as many K slices as cost least by the count
+//     rounds x (chunks of a slice + 4 if sliced),   rounds = workgroups per compute unit, rounded up,
+// in chunk times; the 4 is the hand-over of the partial accumulators.  One wave per tile with K split over the waves of a
+// workgroup, which these launches took below 256 workgroups, copies the activations once per 32 features and holds so much
+// LDS for it that a compute unit runs two to four waves.  Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32,
+// m = 20: 3072 -> 2048 (336 tiles) 141 / 147 / 125 / 134, 141; 2048 -> 2048 with the second product 162 / 172 / 143 / 152, 162;
+// 3072 -> 512 (81 tiles) 77 / 50 / 40 / 48, 48.  bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88;
+// 777 -> 333 with the second product (100 tiles) 41 / 37 / 49 / 49, 57.
+// Layers of at most 64 features keep the one-wave tiles (half a workgroup or more would be idle), and so do launches that
+// make no half round of workgroups this way (896 -> 100, 7 candidates: 7 tiles; fp32 with the second product and four row
+// blocks, which is single-buffered and has no slices: 24 -> 100 us).  Returns the slices (1: none) or 0 where the launch
+// keeps its shape; budget: bytes for the partial accumulators.
+int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
+  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  const long long tiles = (a.has_base ? job_tiles(a.bj, 128) : 0) + (long long)job_tiles(a.cj, 128) * a.n_cand;
+  const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
+  const int min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
+  int most = 1;
+  if (a.slice_partials != nullptr && a.slice_counters != nullptr && tiles <= kMaxSliceGroups) {
+    most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
+    const long long by_bytes = (long long)(budget / ((size_t)4 * MB * 16 * 64 * sizeof(float))) / tiles;
+    if (most > by_bytes) most = by_bytes < 1 ? 1 : (int)by_bytes;
+  }
+  int best = 1;
+  double best_cost = 0.0;
+  for (int S = 1; S <= most; ++S) {
+    const double cost = (double)((tiles * S + n_cu - 1) / n_cu) * ((double)chunks / S + (S > 1 ? 4.0 : 0.0));
+    if (S == 1 || cost < best_cost) {
+      best = S;
+      best_cost = cost;
+    }
+  }
+  return 2 * tiles * best < n_cu ? 0 : best;
 }
 
 // Sliced tail of a candidate launch of eight-wave workgroups.  When the workgroups of the launch do not fill their
@@ -188,7 +227,7 @@ static bool wide_double_buffered(bool bf16, bool delta, int MB) {
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main_out) {
   *n_main_out = a.n_cand;
   if (a.n_cand <= 0 || launch_nw_for(a) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
-  if (!wide_double_buffered(bf16, delta, MB)) return 0;
+  if (!wide_double_buffered(bf16, delta, MB, 8)) return 0;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
   const int tiles8 = job_tiles(a.cj, 256);
   const long long full = (long long)tiles8 * a.n_cand / slots * slots;
@@ -211,7 +250,8 @@ int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_
 
 int layer_tiles(const LayerArgs& a, bool bf16, bool delta, int MB) {
   const int NW = nw_for(a, bf16, delta, MB);
-  const int tail = a.tail_slices >= 2 ? job_tiles(a.cj, 256) * a.tail_slices : 0;
+  const int tail = a.tail_slices >= 2 ? job_tiles(a.cj, 32 * NW) * a.tail_slices : 0;
+  if (tail > 0 && a.tail_cand == a.n_cand) return tail;
   return job_tiles(a.cj, 32 * NW) * layer_k_plan(a, bf16, delta, MB, NW, true).k_slices + tail;
 }
 

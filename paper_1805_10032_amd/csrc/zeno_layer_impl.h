@@ -46,7 +46,7 @@ namespace {
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-constexpr int kSrcChunk = 16;  // sources per scheduling unit (one feature tile each)
+constexpr int kSrcChunk = 16;  // most sources per scheduling unit (one feature tile each)
 
 template <bool BF16>
 struct Tr;
@@ -404,17 +404,18 @@ struct Lds {
 // products, which read their 64 columns at the unshifted positions.  Nothing else knows of the shift.  The
 // first tile's columns before the row and the last (extra) tile's columns behind it are masked.
 //
-// TAIL (eight-wave workgroups): the launch ends with the tiles of its last a.tail_cand candidates (may be none) and
+// TAIL (eight- and four-wave workgroups): the launch ends with the tiles of its last a.tail_cand candidates (may be none) and
 // of the pass at x, if it rides along, cut into a.tail_slices K slices each.  A launch whose workgroups do not fill their last
 // round of resident slots would run that round at a fraction of the chip; cut into slices the same tiles are
-// several times as many workgroups, each a fraction as long.  The slices of a tile hand their partial accumulators
+// several times as many workgroups, each a fraction as long.  With all candidates in the tail (four-wave workgroups, chosen by
+// layer_wide_plan) the whole launch is sliced, and its blocks follow the same schedule as whole tiles do.  The slices of a tile hand their partial accumulators
 // over through memory as the K slices of one-wave tiles do (last workgroup to arrive adds them in slice order).
 template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS, int RING = 0, bool TAIL = false>
 __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) {
   static_assert(KS == 1 || NW == 1, "K is only split in one-tile workgroups");
   using T = Tr<BF16>;
   using LD = Lds<BF16, DELTA, MB, NW, RING>;
-  static_assert(!TAIL || (NW == 8 && KS == 1 && LD::DBUF), "sliced tails exist for double-buffered eight-wave workgroups");
+  static_assert(!TAIL || (NW >= 4 && KS == 1 && LD::DBUF), "sliced tiles exist for double-buffered wide workgroups");
   static_assert(!RING || (BF16 && KS == 1 && NW > 1 && LD::DBUF), "the shifted grid exists for wide bf16 workgroups with double buffers");
   static_assert(KS == 1 || LD::DBUF, "the single-buffer loop has workgroup barriers, which waves with different K ranges cannot share");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   // feature tile each), the rest the candidates.
   // Candidates: workgroups are dealt round-robin to the 8 XCDs (blockIdx % 8), each
   // with its own L2.  The work is cut into units of one feature tile x a chunk of up
-  // to kSrcChunk candidates; units go round-robin to the XCDs and the workgroups of
+  // to kSrcChunk candidates (source_chunk); units go round-robin to the XCDs and the workgroups of
   // a unit occupy consecutive slots of their XCD.  The workgroups that run together
   // on an XCD therefore stream the SAME rows of W (second product) at about the
   // same time and share them through that L2, while everything that is private to
@@ -471,6 +472,19 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     ks = ((int)blockIdx.x - a.main_blocks) % n_slices;
     if (is_base) {
       nt = tail_tile;
+    } else if (n_main == 0) {
+      // every tile is sliced: (tile, slice) pairs take the place of the tiles in the schedule below
+      const int bid = (int)blockIdx.x - a.main_blocks - tail_base_tiles * n_slices;
+      const int cc = a.src_chunk;
+      const int n_cchunks = (a.n_cand + cc - 1) / cc;
+      const int xcd = bid & 7, slot = bid >> 3;
+      const int unit = (slot / cc) * 8 + xcd;
+      if (unit >= n_tiles * n_slices * n_cchunks) return;
+      nt = unit / n_cchunks / n_slices;
+      ks = unit / n_cchunks % n_slices;
+      s = (unit % n_cchunks) * cc + slot % cc;
+      if (s >= a.n_cand) return;
+      tail_tile = tail_base_tiles + s * n_tiles + nt;   // its number among the tiles that hand over
     } else {
       const int g = tail_tile - tail_base_tiles;
       nt = g % n_tiles;
@@ -485,7 +499,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     int bid = blockIdx.x - a.base_blocks;
     ks = bid % n_slices;
     bid /= n_slices;
-    const int cc = n_main < kSrcChunk ? n_main : kSrcChunk;
+    const int cc = a.src_chunk;
     const int n_cchunks = (n_main + cc - 1) / cc;
     const int xcd = bid & 7, slot = bid >> 3;
     const int unit = (slot / cc) * 8 + xcd;
@@ -585,8 +599,8 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   // first tile of the next slice, which that slice counts).
   auto take_tile = [&](auto full_c, auto odd_c, f32x4 (&u)[8], bool count) __attribute__((always_inline)) {
     constexpr int MODE = decltype(full_c)::value;
-    if (MODE == 2) {
-      // rows beyond the matrix were read from row N-1: discard them
+    if (MODE != 1) {
+      // rows beyond the matrix were read from row N-1: discard them (MODE 0: the steady loop loads its tiles the MODE 2 way)
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 8; ++i) u[i] = (row0 + 4 * i + (lane >> 4) < N) ? u[i] : zero;
@@ -738,7 +752,6 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
 
   auto run = [&](auto full_c, auto base_c) __attribute__((always_inline)) {
     constexpr int MODE = decltype(full_c)::value;
-    constexpr bool FULL = MODE != 0;
     constexpr bool SECOND = DELTA && !decltype(base_c)::value;
     // The wave's 32 bias values are requested first of all (lane i < 32 keeps feature row0 + i's),
     // so that the epilogue does not start with a round trip to memory.
@@ -772,17 +785,23 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
         if (c + 1 < c_end) chunk(full_c, base_c, std::false_type{}, std::true_type{}, u0, w1, c + 1);
       }
     } else {
-    if (FULL && DBUF && c_end - c_begin >= 4) {
+    // A width that is not a multiple of the chunk (MODE 0) is ragged in its last chunk only: the chunks before it run the
+    // steady loop of MODE 2, whose loads cross chunks, in wide workgroups (the waves of one-wave tiles split K and have few
+    // chunks each, where the longer code only costs: 784 -> 10, 20 candidates: 16 -> 17 us) (33 candidates, 1001 -> 777, bf16, n_r = 128: 51 -> 43 us;
+    // 3000 -> 1000, fp32, n_r = 32: 149 -> 121 us; 1500 -> 700, bf16, n_r = 32: 54 -> 42 us).
+    using SteadyMode = std::integral_constant<int, MODE == 0 ? 2 : MODE>;
+    const int c_full = MODE == 0 ? (c_end < (K >> 6) ? c_end : K >> 6) : c_end;
+    if ((MODE != 0 || NW > 1) && DBUF && c_full - c_begin >= 4) {
       // steady state: pairs of chunks whose loads (two chunks ahead) all exist
-      load_tile<MODE, NT>(u0, Ufirst, lane_off, row0, c_begin << 6, N, K, lane);
-      load_tile<MODE, NT>(u1, Ufirst + 64, lane_off, row0, (c_begin + 1) << 6, N, K, lane);
+      load_tile<SteadyMode::value, NT>(u0, Ufirst, lane_off, row0, c_begin << 6, N, K, lane);
+      load_tile<SteadyMode::value, NT>(u1, Ufirst + 64, lane_off, row0, (c_begin + 1) << 6, N, K, lane);
       if (SECOND) {
         load_W(w0, c_begin);
         load_W(w1, c_begin + 1);
       }
-      for (; c + 3 < c_end; c += 2) {
-        chunk(full_c, base_c, std::true_type{}, std::false_type{}, u0, w0, c);
-        chunk(full_c, base_c, std::true_type{}, std::true_type{}, u1, w1, c + 1);
+      for (; c + 3 < c_full; c += 2) {
+        chunk(SteadyMode{}, base_c, std::true_type{}, std::false_type{}, u0, w0, c);
+        chunk(SteadyMode{}, base_c, std::true_type{}, std::true_type{}, u1, w1, c + 1);
       }
     } else {
       if (c_begin < c_end) load_tile<MODE, NT>(u0, Ufirst, lane_off, row0, c_begin << 6, N, K, lane);
@@ -1118,6 +1137,23 @@ __global__ void pack_features_kernel(const float* __restrict__ features, int n_r
   }
 }
 
+// Sources per scheduling unit: at most kSrcChunk, in units of equal size (20 candidates: two units of 10, not of 16 and 4, which
+// the round-robin would deal to alternate XCDs: 3072 -> 2048 in fp32, n_r = 32, 190 -> 141 us), and so many units that the
+// XCD with the most workgroups has as few as possible.
+inline int source_chunk(int tiles, int n_src) {
+  int best = 0;
+  long long best_load = 0;
+  for (int nc = (n_src + kSrcChunk - 1) / kSrcChunk; nc <= n_src && nc <= 4 * ((n_src + kSrcChunk - 1) / kSrcChunk) + 8; ++nc) {
+    const int cc = (n_src + nc - 1) / nc;
+    const long long load = ((long long)tiles * ((n_src + cc - 1) / cc) + 7) / 8 * cc;
+    if (best == 0 || load < best_load) {
+      best = cc;
+      best_load = load;
+    }
+  }
+  return best;
+}
+
 int job_tiles(const LayerJob& j, int BN) { return (cover_rows(j.N, j.last) + BN - 1) / BN; }
 
 template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS = 1, int RING = 0, bool TAIL = false>
@@ -1141,7 +1177,7 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   if (NW != 1 || a.k_slices < 1) a.k_slices = 1;
   if (a.k_slices > 1 && (a.slice_partials == nullptr || a.slice_counters == nullptr)) return hipErrorInvalidValue;
   if (!TAIL) a.tail_cand = a.tail_slices = 0;
-  if (TAIL && (a.tail_cand < 0 || a.tail_cand >= a.n_cand || (a.tail_cand == 0 && !a.has_base) || a.tail_slices < 2 ||
+  if (TAIL && (a.tail_cand < 0 || a.tail_cand > a.n_cand || (a.tail_cand == 0 && !a.has_base) || a.tail_slices < 2 ||
                a.slice_partials == nullptr || a.slice_counters == nullptr))
     return hipErrorInvalidValue;
   // TAIL: the pass at x has no leading blocks, its tiles are sliced like the tail candidates'
@@ -1149,7 +1185,7 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   const int n_main = a.n_cand - a.tail_cand;
   int cand_blocks = 0;
   if (n_main > 0) {
-    const int cc = n_main < kSrcChunk ? n_main : kSrcChunk;
+    const int cc = a.src_chunk = source_chunk(job_tiles(a.cj, BN), n_main);
     const int units = job_tiles(a.cj, BN) * ((n_main + cc - 1) / cc);
     cand_blocks = ((units + 7) / 8) * 8 * cc * a.k_slices;
   }
@@ -1158,10 +1194,16 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   if (TAIL) {
     const long long tiles = (a.has_base ? job_tiles(a.bj, BN) : 0) + (long long)job_tiles(a.cj, BN) * a.tail_cand;
     // every slice keeps at least two chunks of every job; the hand-over buffers hold all sliced tiles
-    if ((a.cj.Kp >> 6) < 2 * a.tail_slices || (a.has_base && (a.bj.Kp >> 6) < 2 * a.tail_slices) ||
-        tiles * a.tail_slices > kMaxTailWorkgroups || tiles > kMaxSliceGroups)
+    if ((a.cj.Kp >> 6) < 2 * a.tail_slices || (a.has_base && (a.bj.Kp >> 6) < 2 * a.tail_slices) || tiles > kMaxSliceGroups ||
+        (n_main > 0 && tiles * a.tail_slices > kMaxTailWorkgroups))
       return hipErrorInvalidValue;
-    tail_blocks = (int)tiles * a.tail_slices;
+    if (n_main > 0) {
+      tail_blocks = (int)tiles * a.tail_slices;
+    } else {
+      const int cc = a.src_chunk = source_chunk(job_tiles(a.cj, BN) * a.tail_slices, a.n_cand);
+      const int units = job_tiles(a.cj, BN) * a.tail_slices * ((a.n_cand + cc - 1) / cc);
+      tail_blocks = (a.has_base ? job_tiles(a.bj, BN) * a.tail_slices : 0) + (units + 7) / 8 * 8 * cc;
+    }
   }
   hipLaunchKernelGGL((layer_kernel<BF16, DELTA, MB, NW, NT, KS, RING, TAIL>), dim3(a.main_blocks + tail_blocks),
                      dim3(64 * NW * KS), lds_bytes, stream, a);
@@ -1260,6 +1302,12 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
     const bool base_ok = !a.has_base || (a.bj.Kp >> 6) >= 2 * a.k_slices;
     const bool cand_ok = a.n_cand == 0 || (a.cj.Kp >> 6) >= 2 * a.k_slices;
     if (!(base_ok && cand_ok)) return hipErrorInvalidValue;
+  }
+  if constexpr (NW == 4 && Lds<BF16, DELTA, MB, NW>::DBUF) {
+    if (a.tail_slices >= 2) {
+      if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true>(a, stream, shape);
+      return launch_inst<BF16, DELTA, MB, NW, false, 1, 0, true>(a, stream, shape);
+    }
   }
   if constexpr (NW == 8 && Lds<BF16, DELTA, MB, NW>::DBUF) {
     if (a.tail_slices >= 2) {

@@ -1,0 +1,61 @@
+"""Launches of four-wave workgroups whose tiles are all cut into K slices (too few wide tiles to fill the chip otherwise), and
+uneven candidate counts in the scheduling units: every score against the oracle, the launch shapes read back."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_10032_amd import workloads as WL
+from tests._util import SCORE_TOL, npy, oracle_terms, rows_to_gpu, score_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1805_10032_amd import binding
+    binding.load_library()
+    return binding
+
+
+CASES = [
+    # dims, m, n_r, fwd, row_align, bias
+    ([3072, 512, 10], 20, 32, "fp32", 1, True),        # the pass at x rides along, sliced as well
+    ([1030, 600, 300, 10], 33, 100, "bf16", 1, True),  # four row blocks, ragged K, a width that ends inside a tile
+    ([960, 520, 130], 17, 40, "bf16", 32, False),      # two row blocks; 17 candidates: units of 9 and 8
+    ([2048, 700], 20, 20, "fp32", 32, True),           # one layer: the pass at x is the same layer
+    ([1024, 1024, 1024, 65], 12, 64, "fp32", 4, True), # second product in fp32, two row blocks; 65 outputs
+    ([2048, 900, 10], 12, 150, "bf16", 32, True),      # two passes over G
+    ([640, 449, 1], 100, 3, "bf16", 1, True),          # squared loss, few samples, 100 candidates
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_sliced_layers_all_rows(B, case):
+    dims, m, n_r, fwd, row_align, bias = CASES[case]
+    loss = "squared" if dims[-1] == 1 else "softmax_ce"
+    w = WL.make_mlp_workload(f"sliced{case}", 80 + case, dims, m, m // 3, n_r, 0.05, 1e-3, fwd, seed=case, has_bias=bias,
+                             loss=loss, n_flip=m // 6, n_noise=m // 6, noise_std=2.0, worker_batch=16)
+    dev = torch.device("cuda", 0)
+    mdl = B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd)
+    G = rows_to_gpu(B, w.G, row_align, dev)
+    args = (mdl, w.x.to(dev), G, w.features.to(dev), w.gamma, w.rho)
+    batch = dict(labels=None if w.labels is None else w.labels.to(dev), targets=None if w.targets is None else w.targets.to(dev))
+    ws = B.alloc_workspace(mdl, m, n_r, dev)
+    ws.view(torch.float32)[: ws.numel() // 4].fill_(float("nan"))   # every slot is written before it is read
+    B.profile_enable(True)
+    try:
+        s = B.zeno_score(*args, workspace=ws, **batch)
+        torch.cuda.synchronize()
+        recs = B.profile_collect(detail=True)
+    finally:
+        B.profile_enable(False)
+    wide = [r for r in recs if r["kernel"] == "layer_cand" and r["waves"] == 4]
+    assert any(r["k_slices"] >= 2 and r["tail_candidates"] == m for r in wide), recs
+    s_ref, scale = oracle_terms(w)
+    err = score_error(npy(s), s_ref, scale)
+    assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
+    # the slices are added in slice order whoever arrives last, and the static scratch array takes the same slices
+    assert torch.equal(s, B.zeno_score(*args, workspace=ws, **batch))
+    if mdl.workspace_bytes(m, n_r) <= B.STATIC_SCRATCH_BYTES:
+        assert torch.equal(s, B.zeno_score_static(*args, **batch))
+

@@ -115,3 +115,18 @@ def test_library_sources_never_allocate_device_memory():
         text = open(os.path.join(csrc, name)).read()
         text = re.sub(r"//[^\n]*|/\*.*?\*/", "", text, flags=re.S)
         assert not pat.search(text), name
+
+
+def test_the_hand_over_buffer_does_not_cost_a_call_the_static_scratch():
+    """The buffer through which sliced launches hand over grows with the model, but only up to the 32 MiB static array for the
+    plans that fit it with the smallest buffer (8 MiB; here 11.5 to 23 MiB in all)."""
+    from paper_1805_10032_amd import binding as B
+    sizes = []
+    for width in range(64, 2049, 64):
+        mdl = B.ZenoModel([1024, width, 512, 10], True, "softmax_ce", "fp32")
+        assert mdl.plan_check(20, 32) == 0
+        sizes.append(mdl.workspace_bytes(20, 32))
+    assert sizes == sorted(sizes) and sizes[-1] == B.STATIC_SCRATCH_BYTES
+    # beyond it the buffer has its full size
+    wide = B.ZenoModel([1024, 2048, 2048, 10], True, "softmax_ce", "fp32").workspace_bytes(20, 32)
+    assert wide > B.STATIC_SCRATCH_BYTES + (8 << 20)
