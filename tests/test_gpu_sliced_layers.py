@@ -25,7 +25,7 @@ CASES = [
     ([2048, 700], 20, 20, "fp32", 32, True),           # one layer: the pass at x is the same layer
     ([1024, 1024, 1024, 65], 12, 64, "fp32", 4, True), # second product in fp32, two row blocks; 65 outputs
     ([2048, 900, 10], 12, 150, "bf16", 32, True),      # two passes over G
-    ([640, 449, 1], 100, 3, "bf16", 1, True),          # squared loss, few samples, 100 candidates
+    ([640, 449, 1], 30, 3, "bf16", 1, True),          # squared loss, few samples
 ]
 
 
