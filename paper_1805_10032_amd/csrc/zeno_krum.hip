@@ -26,8 +26,8 @@
 // order, and accumulates the RB(RB+1)/2 block products S_ab += T_a T_b^T, a <= b.  The
 // four waves of a workgroup add their accumulators through LDS in a fixed tree and
 // write one partial Gram per workgroup; krum_reduce_kernel sums the partials in
-// float64 (fixed order), krum_score_kernel forms the score of one row per workgroup,
-// krum_argmin_kernel picks the winner, krum_copy_kernel copies the winning row.
+// float64 (fixed order), krum_score_kernel forms the score of one row per workgroup and its last workgroup picks the
+// winner (up to 32 rows the reduction's last workgroup does both), krum_copy_kernel copies the winning row.
 #include "zeno_layer_impl.h"
 #include "zeno_split.h"
 
@@ -39,7 +39,28 @@ constexpr int kGramWaves = 4;
 
 typedef float f32x8 __attribute__((ext_vector_type(8)));
 
-// CENTER: second pass; runs only if *run_flag != 0 and subtracts row *center from every row.
+// What the kernels of one call leave each other in the workspace, cleared by its first one.
+struct KrumState {
+  int32_t again;                 // a distance that enters a score cancels: run the second pass
+  uint32_t reduced[2];           // workgroups of the reduction / rows of the scores that have arrived, per pass
+  uint32_t scored[2];
+};
+
+// Values that other workgroups of the same launch read: stored and loaded past the caches (the L2 of an XCD is not seen by
+// the others), with the arrival counted after the stores have completed.
+__device__ inline void publish(double* p, double v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+__device__ inline double published(const double* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+// Counts the workgroup's arrival once all its threads have published; true in the workgroup that is the last of `total`.
+__device__ inline bool last_to_arrive(uint32_t* counter, uint32_t total) {
+  __shared__ uint32_t arrived;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0) arrived = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  return arrived + 1u == total;
+}
+
+// CENTER: second pass; runs only if the first one asked for it and subtracts row *center from every row.
 // NT: streaming loads, where the rows start on 128-byte lines; the 256-byte row segments of other rows share their
 // outer lines with the wave's next chunk, which streaming loads would fetch from memory again (dense rows of
 // workload 5, m = 64: 3.0 -> 2.8 ms with plain loads; the same switch made the averaging kernel slower, 1.68 -> 1.85 ms,
@@ -48,9 +69,10 @@ template <int RB, bool CENTER, bool NT>
 __global__ __launch_bounds__(64 * kGramWaves, RB == 1 ? 3 : 2) void krum_gram_kernel(const float* __restrict__ G, long long ldg,
                                                                     int m, long long d, float* __restrict__ partial,
                                                                     const int32_t* __restrict__ center,
-                                                                    const int32_t* __restrict__ run_flag) {
+                                                                    KrumState* __restrict__ state) {
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  if (CENTER && *run_flag == 0) return;   // uniform over the launch
+  if (CENTER && state->again == 0) return;   // uniform over the launch
+  if (!CENTER && blockIdx.x == 0 && threadIdx.x == 0) *state = KrumState{};
   const float* __restrict__ crow = CENTER ? G + (long long)(*center) * ldg : G;
   constexpr int PAIRS = RB * (RB + 1) / 2;
   constexpr int TILE_BYTES = 32 * 64 * 4;
@@ -230,11 +252,12 @@ template <int RB, int NBL, bool CENTER>
 __global__ __launch_bounds__(64 * kSharedWaves) void krum_gram_shared_kernel(const float* __restrict__ G, long long ldg, int m,
                                                                              long long d, float* __restrict__ partial,
                                                                              const int32_t* __restrict__ center,
-                                                                             const int32_t* __restrict__ run_flag) {
+                                                                             KrumState* __restrict__ state) {
   using SG = SharedGram<RB>;
   static_assert(NBL == 2 * RB || NBL == 2 * RB - 1, "live 16-row blocks of RB 32-row tiles");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
-  if (CENTER && *run_flag == 0) return;   // uniform over the launch
+  if (CENTER && state->again == 0) return;   // uniform over the launch
+  if (!CENTER && blockIdx.x == 0 && threadIdx.x == 0) *state = KrumState{};
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // The 64-column chunks are dealt round-robin to the workgroups: workgroups run at about the same pace, so at any
@@ -528,38 +551,107 @@ __global__ __launch_bounds__(64 * kSharedWaves) void krum_gram_shared_kernel(con
   }
 }
 
-// Sum of the per-workgroup partial Grams in float64, in workgroup order: one thread per entry.
-// pass 0 clears the flag that asks for the second pass; pass 1 runs only if it is set.
-__global__ __launch_bounds__(256) void krum_reduce_kernel(const float* __restrict__ partial, int n_partials,
-                                                          int entries, double* __restrict__ gram, int pass,
-                                                          int32_t* __restrict__ flag) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (pass == 1 && *flag == 0) return;
-  if (pass == 0 && e == 0) *flag = 0;   // (set, if at all, by the score kernel that follows)
-  if (e >= entries) return;
-  double t = 0.0;
-  int w = 0;
-  for (; w + 8 <= n_partials; w += 8) {   // eight loads in flight, added in workgroup order
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = partial[(long long)(w + q) * entries + e];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t += (double)v[q];
+// Squared distance of two rows from their Gram entries.  It is rounding noise when it is far below the squares it is
+// formed from, unless the rows are bit-identical (all three entries equal, the distance exactly 0).
+__device__ inline double row_distance(double sii, double sjj, double sij, bool& cancels) {
+  double dd = sii + sjj - 2.0 * sij;
+  cancels = (dd < 1e-3 * (sii + sjj)) && !(sii == sjj && sii == sij);
+  dd = dd < 0.0 ? 0.0 : dd;
+  return (dd == dd) ? dd : __builtin_inf();      // a NaN/Inf row is infinitely far from every row: ranks stay a permutation
+}
+// Smallest score, ties to the lower index (one thread).
+template <typename F>
+__device__ inline int32_t best_row(int m, F score) {
+  int best = 0;
+  double least = score(0);
+  for (int i = 1; i < m; ++i) {
+    const double v = score(i);
+    if (v < least) {
+      best = i;
+      least = v;
+    }
   }
-  for (; w < n_partials; ++w) t += (double)partial[(long long)w * entries + e];
-  gram[e] = t;
+  return best;
 }
 
-// Krum score of row i = blockIdx.x: squared distances to the other rows from the summed Gram
-// blocks, ranked by counting (ties to the lower index), the m-b-2 smallest summed in
-// ascending order.
+// Sum of the per-workgroup partial Grams in float64: a workgroup takes 32 entries, eight threads per entry an eighth of
+// the partials each, added in order (one thread per entry, four workgroups of them for m <= 32, was a chain of 768 loads:
+// 36 us of the 83 us of a call with m = 20, d = 1.58 M; 6 us this way).
+// m <= 32: the last workgroup to finish also forms all scores and picks the winner; the distances of a row are ranked by
+// counting (ties to the lower index) and the m-b-2 smallest summed in ascending order, as in krum_score_kernel.
+constexpr int kReduceEntries = 32, kReduceParts = 8;
+__global__ __launch_bounds__(kReduceEntries * kReduceParts) void krum_reduce_kernel(
+    const float* __restrict__ partial, int n_partials, int entries, double* __restrict__ gram, int m, int b,
+    float* __restrict__ scores_out, int32_t* __restrict__ chosen, int pass, KrumState* __restrict__ state) {
+  __shared__ double part[kReduceParts][kReduceEntries];
+  if (pass == 1 && state->again == 0) return;
+  const int tid = threadIdx.x, el = tid % kReduceEntries, q = tid / kReduceEntries;
+  const int e = blockIdx.x * kReduceEntries + el;
+  const int w1 = (int)((long long)n_partials * (q + 1) / kReduceParts);
+  int w = (int)((long long)n_partials * q / kReduceParts);
+  double t = 0.0;
+  for (; w + 16 <= w1; w += 16) {        // sixteen loads in flight, added in workgroup order
+    float v[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v[i] = partial[(long long)(w + i) * entries + e];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) t += (double)v[i];
+  }
+  for (; w < w1; ++w) t += (double)partial[(long long)w * entries + e];
+  part[q][el] = t;
+  __syncthreads();
+  if (q == 0) {
+    for (int i = 1; i < kReduceParts; ++i) t += part[i][el];
+    if (m <= 32) publish(gram + e, t);
+    else gram[e] = t;
+  }
+  if (m > 32 || !last_to_arrive(&state->reduced[pass], gridDim.x)) return;
+  __shared__ double S[32][33], sorted[32][33];
+  for (int i = tid; i < 1024; i += kReduceEntries * kReduceParts) S[i >> 5][i & 31] = published(gram + i);
+  __syncthreads();
+  double dist[4];
+  bool cancels[4];
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {          // pair (i, j); the row itself is never a neighbour
+    const int i = 8 * p + q, j = el;
+    cancels[p] = false;
+    dist[p] = __builtin_inf();
+    if (i < m && j < m && i != j) dist[p] = row_distance(S[i][i], S[j][j], S[i < j ? i : j][i < j ? j : i], cancels[p]);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 4; ++p) S[8 * p + q][el] = dist[p];      // (the Gram entries are no longer needed)
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int i = 8 * p + q, j = el;
+    if (i < m && j < m) {
+      int rank = 0;
+      for (int k = 0; k < m; ++k) rank += (S[i][k] < dist[p]) || (S[i][k] == dist[p] && k < j);
+      sorted[i][rank] = dist[p];
+      // a cancelling distance among the m-b-2 that enter the score: ask for the second pass
+      if (pass == 0 && rank < m - b - 2 && cancels[p]) state->again = 1;
+    }
+  }
+  __syncthreads();
+  if (tid < m) {
+    double total = 0.0;
+    for (int r = 0; r < m - b - 2; ++r) total += sorted[tid][r];
+    S[tid][32] = total;
+    if (scores_out != nullptr) scores_out[tid] = (float)total;
+  }
+  __syncthreads();
+  if (tid == 0) *chosen = best_row(m, [&](int i) { return S[i][32]; });
+}
+
+// m > 32: Krum score of row i = blockIdx.x from the summed Gram blocks, as above; the last row to finish picks the winner.
 __global__ __launch_bounds__(128) void krum_score_kernel(const double* __restrict__ gram, int rb, int m, int b,
                                                          double* __restrict__ score64, float* __restrict__ scores_out,
-                                                         int pass, int32_t* __restrict__ flag) {
+                                                         int32_t* __restrict__ chosen, int pass, KrumState* __restrict__ state) {
   __shared__ double dist[128];
   __shared__ double sorted[128];
   __shared__ int cancels[128];
-  if (pass == 1 && *flag == 0) return;
+  if (pass == 1 && state->again == 0) return;
   const int i = blockIdx.x, j = threadIdx.x;
   auto S = [&](int r, int c) {   // Gram entry (r, c), stored for block pairs a <= b only
     if (r > c) { const int t = r; r = c; c = t; }
@@ -568,13 +660,9 @@ __global__ __launch_bounds__(128) void krum_score_kernel(const double* __restric
     return gram[p * 1024 + (r & 31) * 32 + (c & 31)];
   };
   if (j < m) {
-    const double sii = S(i, i), sjj = S(j, j), sij = S(i, j);
-    double dd = sii + sjj - 2.0 * sij;
-    // the difference is rounding noise when it is far below the squares it is formed from, unless
-    // the rows are bit-identical (all three entries equal, the distance exactly 0)
-    cancels[j] = (j != i) && (dd < 1e-3 * (sii + sjj)) && !(sii == sjj && sii == sij);
-    dd = dd < 0.0 ? 0.0 : dd;
-    dd = (dd == dd) ? dd : __builtin_inf();      // a NaN/Inf row is infinitely far from every row: ranks stay a permutation
+    bool cancel;
+    const double dd = row_distance(S(i, i), S(j, j), S(i, j), cancel);
+    cancels[j] = j != i && cancel;
     dist[j] = (j == i) ? __builtin_inf() : dd;   // the row itself is never a neighbour
   }
   __syncthreads();
@@ -587,27 +675,19 @@ __global__ __launch_bounds__(128) void krum_score_kernel(const double* __restric
     }
     sorted[rank] = dj;
     // a cancelling distance among the m-b-2 that enter the score: ask for the second pass
-    if (pass == 0 && rank < m - b - 2 && cancels[j]) *flag = 1;
+    if (pass == 0 && rank < m - b - 2 && cancels[j]) state->again = 1;
   }
   __syncthreads();
   if (j == 0) {
     double total = 0.0;
     for (int r = 0; r < m - b - 2; ++r) total += sorted[r];
-    score64[i] = total;
+    publish(score64 + i, total);
     if (scores_out != nullptr) scores_out[i] = (float)total;
   }
-}
-
-// Winner: smallest score, ties to the lower index.
-__global__ void krum_argmin_kernel(const double* __restrict__ score64, int m, int32_t* __restrict__ chosen, int pass,
-                                   const int32_t* __restrict__ flag) {
-  if (pass == 1 && *flag == 0) return;
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    int best = 0;
-    for (int i = 1; i < m; ++i)
-      if (score64[i] < score64[best]) best = i;
-    *chosen = best;
-  }
+  if (!last_to_arrive(&state->scored[pass], gridDim.x)) return;
+  if (j < m) sorted[j] = published(score64 + j);
+  __syncthreads();
+  if (j == 0) *chosen = best_row(m, [&](int r) { return sorted[r]; });
 }
 
 __global__ __launch_bounds__(256) void krum_copy_kernel(const float* __restrict__ G, long long ldg, long long d,
@@ -653,19 +733,19 @@ inline bool rows_on_lines(const float* G, long long ldg) { return reinterpret_ca
 
 template <int RB, int NBL, bool CENTER>
 hipError_t launch_gram_shared(const float* G, long long ldg, int m, long long d, float* partial, int grid, const int32_t* center,
-                              const int32_t* run_flag, hipStream_t stream) {
+                              KrumState* state, hipStream_t stream) {
   constexpr int lds = SharedGram<RB>::LDS_BYTES;
   static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&krum_gram_shared_kernel<RB, NBL, CENTER>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (attr_err != hipSuccess) return attr_err;
   hipLaunchKernelGGL((krum_gram_shared_kernel<RB, NBL, CENTER>), dim3(grid), dim3(64 * kSharedWaves), lds, stream, G, ldg, m, d,
-                     partial, center, run_flag);
+                     partial, center, state);
   return hipGetLastError();
 }
 
 template <int RB, bool CENTER, bool NT>
 hipError_t launch_gram_nt(const float* G, long long ldg, int m, long long d, float* partial, int grid, const int32_t* center,
-                          const int32_t* run_flag, hipStream_t stream) {
+                          KrumState* state, hipStream_t stream) {
   constexpr int lds = kGramWaves * RB * 32 * 64 * 4;
   static const hipError_t attr_err =
       lds > 48 * 1024 ? hipFuncSetAttribute(reinterpret_cast<const void*>(&krum_gram_kernel<RB, CENTER, NT>),
@@ -673,26 +753,26 @@ hipError_t launch_gram_nt(const float* G, long long ldg, int m, long long d, flo
                       : hipSuccess;
   if (attr_err != hipSuccess) return attr_err;
   hipLaunchKernelGGL((krum_gram_kernel<RB, CENTER, NT>), dim3(grid), dim3(64 * kGramWaves), lds, stream, G, ldg, m, d, partial,
-                     center, run_flag);
+                     center, state);
   return hipGetLastError();
 }
 template <int RB, bool CENTER>
 hipError_t launch_gram(const float* G, long long ldg, int m, long long d, float* partial, int grid, const int32_t* center,
-                       const int32_t* run_flag, hipStream_t stream) {
-  if (rows_on_lines(G, ldg)) return launch_gram_nt<RB, CENTER, true>(G, ldg, m, d, partial, grid, center, run_flag, stream);
-  return launch_gram_nt<RB, CENTER, false>(G, ldg, m, d, partial, grid, center, run_flag, stream);
+                       KrumState* state, hipStream_t stream) {
+  if (rows_on_lines(G, ldg)) return launch_gram_nt<RB, CENTER, true>(G, ldg, m, d, partial, grid, center, state, stream);
+  return launch_gram_nt<RB, CENTER, false>(G, ldg, m, d, partial, grid, center, state, stream);
 }
 
 template <bool CENTER>
 hipError_t launch_gram_rb(int rb, const float* G, long long ldg, int m, long long d, float* partial, int grid,
-                          const int32_t* center, const int32_t* run_flag, hipStream_t stream) {
-  if (rb == 1) return launch_gram<1, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
-  if (rb == 2) return launch_gram<2, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
+                          const int32_t* center, KrumState* state, hipStream_t stream) {
+  if (rb == 1) return launch_gram<1, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
+  if (rb == 2) return launch_gram<2, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
   const int nbl = (m + 15) / 16;   // live 16-row blocks
-  if (nbl == 5) return launch_gram_shared<3, 5, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
-  if (nbl == 6) return launch_gram_shared<3, 6, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
-  if (nbl == 7) return launch_gram_shared<4, 7, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
-  return launch_gram_shared<4, 8, CENTER>(G, ldg, m, d, partial, grid, center, run_flag, stream);
+  if (nbl == 5) return launch_gram_shared<3, 5, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
+  if (nbl == 6) return launch_gram_shared<3, 6, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
+  if (nbl == 7) return launch_gram_shared<4, 7, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
+  return launch_gram_shared<4, 8, CENTER>(G, ldg, m, d, partial, grid, center, state, stream);
 }
 
 }  // namespace
@@ -707,27 +787,28 @@ size_t krum_workspace_bytes(int m) {
 hipError_t launch_krum(const float* G, long long ldg, int m, long long d, int b, float* out, int32_t* chosen,
                        float* scores_out, void* workspace, hipStream_t stream) {
   const int rb = (m + 31) / 32;
-  const int grid = gram_grid(rb);
   float* partial = reinterpret_cast<float*>(workspace);
   const int entries = (rb * (rb + 1) / 2) * 1024;
   double* gram = reinterpret_cast<double*>(reinterpret_cast<unsigned char*>(workspace) +
-                                           align_up((size_t)grid * entries * sizeof(float), 256));
+                                           align_up((size_t)gram_grid(rb) * entries * sizeof(float), 256));
   double* score64 = gram + align_up((size_t)entries * sizeof(double), 256) / sizeof(double);
-  int32_t* flag = reinterpret_cast<int32_t*>(score64 + align_up(128 * sizeof(double), 256) / sizeof(double));
+  KrumState* state = reinterpret_cast<KrumState*>(score64 + align_up(128 * sizeof(double), 256) / sizeof(double));
+  // no more workgroups than there are 64-column chunks for their waves (shared chunks: for themselves); every one writes a
+  // partial Gram that the reduction reads
+  const long long chunks = (d + 63) / 64, useful = rb <= 2 ? (chunks + kGramWaves - 1) / kGramWaves : chunks;
+  const int grid = (int)(useful < gram_grid(rb) ? useful : gram_grid(rb));
   // pass 0 on the rows as they are; pass 1, only if pass 0 found a cancelling distance (decided on the
   // device: its kernels return at once otherwise), on the rows minus the row pass 0 chose
   for (int pass = 0; pass < 2; ++pass) {
-    hipError_t e = pass == 0 ? launch_gram_rb<false>(rb, G, ldg, m, d, partial, grid, nullptr, nullptr, stream)
-                             : launch_gram_rb<true>(rb, G, ldg, m, d, partial, grid, chosen, flag, stream);
+    hipError_t e = pass == 0 ? launch_gram_rb<false>(rb, G, ldg, m, d, partial, grid, nullptr, state, stream)
+                             : launch_gram_rb<true>(rb, G, ldg, m, d, partial, grid, chosen, state, stream);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(krum_reduce_kernel, dim3((entries + 255) / 256), dim3(256), 0, stream, partial, grid, entries, gram,
-                       pass, flag);
+    hipLaunchKernelGGL(krum_reduce_kernel, dim3(entries / kReduceEntries), dim3(kReduceEntries * kReduceParts), 0, stream, partial,
+                       grid, entries, gram, m, b, scores_out, chosen, pass, state);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(krum_score_kernel, dim3(m), dim3(128), 0, stream, gram, rb, m, b, score64, scores_out, pass, flag);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(krum_argmin_kernel, dim3(1), dim3(64), 0, stream, score64, m, chosen, pass, flag);
+    if (m <= 32) continue;   // scored by the reduction's last workgroup
+    hipLaunchKernelGGL(krum_score_kernel, dim3(m), dim3(128), 0, stream, gram, rb, m, b, score64, scores_out, chosen, pass, state);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -166,3 +166,24 @@ def test_krum_tight_honest_cluster(B, m, d, b, spread):
     idx = int(chosen.item())
     assert idx in set(honest.tolist()) and ref[idx] <= ref.min() * (1.0 + 2e-3)
     assert np.array_equal(npy(out), npy(G[idx]))
+
+
+@pytest.mark.parametrize("m,d", [(32, 1), (32, 65), (33, 1), (33, 257), (7, 256), (128, 64)])
+def test_krum_few_columns_and_calls_in_a_row(B, m, d):
+    """Fewer 64-column chunks than workgroups, on both sides of the row count that moves the scores into the reduction; the
+    counters of a call that took the second pass are left behind for the next call, which has to give the same bits."""
+    g = torch.Generator().manual_seed(5 * m + d)
+    b = min(m // 4, m - 3)
+    spread = torch.randn(1, d, generator=g) + 0.5 * torch.randn(m, d, generator=g)
+    tight = torch.randn(1, d, generator=g) + 1e-4 * torch.randn(m, d, generator=g)
+    if d > 1:
+        _check(B, spread, b)
+    rows, close = rows_to_gpu(B, spread, 1), rows_to_gpu(B, tight, 1)
+    first = None
+    for _ in range(3):
+        _, c1, k1 = B.zeno_krum(rows, b)
+        _, c2, k2 = B.zeno_krum(close, b)
+        torch.cuda.synchronize()
+        now = (int(c1.item()), npy(k1).tobytes(), int(c2.item()), npy(k2).tobytes())
+        assert first is None or now == first
+        first = now
