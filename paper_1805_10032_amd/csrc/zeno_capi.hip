@@ -405,6 +405,32 @@ zeno_status_t score_enqueue(const zeno_model* model, const Plan& p, const float*
   const zeno_model_desc_t& D = model->desc;
   const bool bf16 = D.fwd == ZENO_FWD_BF16;
   const int L = p.L, n_r = batch->n_r, C = D.dims[L];
+  if (small_model_fits(D.dims, L, m, n_r)) {
+    // one launch instead of 2 L + 3, no scratch
+    SmallArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.G = G;
+    a.x = x;
+    a.ldg = ldg;
+    a.L = L;
+    for (int l = 0; l <= L; ++l) a.dims[l] = D.dims[l];
+    for (int l = 0; l < L; ++l) {
+      a.w_off[l] = model->w_off[l];
+      a.b_off[l] = model->b_off[l];
+    }
+    a.loss = D.loss;
+    a.n_r = n_r;
+    a.features = batch->features;
+    a.labels = batch->labels;
+    a.targets = batch->targets;
+    a.gamma = gamma;
+    a.neg_inv_gamma = gamma > 0.f ? -1.0f / gamma : 0.f;
+    a.rho = rho;
+    a.scores = scores;
+    ProfScope ps(ZENO_KERNEL_LAYER_CAND, 0, 4.0 * (double)model->d * (m + 1), stream);
+    ZENO_TRY(launch_score_small(a, bf16, m, stream));
+    return ZENO_OK;
+  }
   double* norm_partials = reinterpret_cast<double*>(ws + p.off_norm);
   double* sample_diff = reinterpret_cast<double*>(ws + p.off_diff);
   float* dZ = reinterpret_cast<float*>(ws + p.off_dz);

@@ -168,6 +168,23 @@ hipError_t launch_score_combine(const double* sample_diff, const double* norm_pa
 // the same with the candidates' partial norms P_stride slots apart, the first P of them in use
 hipError_t launch_score_combine_strided(const double* sample_diff, const double* norm_partials, int P_stride, int P,
                                         int m, int n_r_total, float rho, float* scores, hipStream_t stream);
+// ---- small models in one launch (zeno_small.hip)
+struct SmallArgs {
+  const float* G;
+  const float* x;
+  long long ldg;
+  int L, dims[ZENO_MAX_LAYERS + 1];
+  long long w_off[ZENO_MAX_LAYERS], b_off[ZENO_MAX_LAYERS];
+  int loss, n_r;
+  const float* features;
+  const int32_t* labels;
+  const float* targets;
+  float gamma, neg_inv_gamma, rho;
+  float* scores;
+  int pitch;   // filled in by the launcher
+};
+bool small_model_fits(const int* dims, int L, int m, int n_r);
+hipError_t launch_score_small(SmallArgs a, bool bf16, int m, hipStream_t stream);
 // x_next != nullptr: also write x_next = x - gamma * average (out may then be nullptr)
 hipError_t launch_masked_average(const float* G, long long ldg, const float* scores, int m, long long d, int b,
                                  float* out, int32_t* selected, hipStream_t stream, float gamma = 0.f,
