@@ -39,10 +39,13 @@
 // convolutions 109 / 134 / 251 / 120 -> 67 / 100 / 111 / 105 us, the whole step 682 -> 468 us; n_r = 4: 19 / 26 / 36 / 32 us and
 // 47 us for the pass at x -> 24 / 36 / 34 / 25 us including it and 12 us for its first convolution, the step 209 -> 173 us.
 //
-// conv_layer_kernel serves what the staging does not cover (rows of the map too wide for LDS): one wave owns 32 positions x 32
+// conv_layer_kernel serves what the staging does not cover (rows of the map too wide for LDS) or covers badly (channels that
+// are no multiple of eight, see launch_conv): one wave owns 32 positions x 32
 // channels in one fp32 accumulator block (v_mfma_f32_32x32x2_f32), and gathers every operand element from memory when it
 // needs it (one 128-bit load per lane and operand feeds four matrix instructions; the tail of a channel
-// count that is not a multiple of eight goes two at a time).
+// count that is not a multiple of eight goes two at a time).  It carries the pass at x through the next layer as well, in its
+// first row of workgroups (a launch of its own is 10-13 us; convolutions 33-33-8 with strides 2 on 32x32, m = 39, n_r = 4: the
+// step 125 us with separate launches for everything, 114 us now).
 // The last convolution writes its outputs straight into the matrix-operand
 // order of the fully connected layer (rows = samples, columns = (y, x, c)), which the
 // streaming layer kernel then consumes.
@@ -56,20 +59,23 @@ namespace {
 // TW = 3: three waves share one tile and take one kernel row (ky) each; their accumulators are added through
 // LDS in the fixed order (0 + 1) + 2 and wave 0 finishes the tile.  Used when the launch has too few tiles
 // to occupy the matrix cores otherwise (a wave's 9 c_in / 2 dependent matrix instructions set its pace).
-template <bool CAND, int TW>
+// The first row of the grid is the pass at x, if the launch carries it.
+template <int TW>
 __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
-  const ConvJob& J = CAND ? a.cj : a.bj;
+  const bool cand = !a.has_base || blockIdx.y > 0;
+  const ConvJob& J = cand ? a.cj : a.bj;
   const ConvLayer& L = J.L;
   const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
   const int tw = TW > 1 ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
   const int ftiles = (L.Cout + 31) / 32;
   const int ft = blockIdx.x % ftiles, rb = blockIdx.x / ftiles;
-  const int s = blockIdx.y;
+  const int s = (int)blockIdx.y - (a.has_base ? 1 : 0);
   const int K = 9 * L.Cin;
   const long long rows = (long long)a.n_r * L.Hout * L.Wout;
+  if ((long long)rb * 32 >= rows) return;          // (the grid is as wide as the larger of two jobs)
 
-  const float* __restrict__ P = CAND ? a.G + (long long)s * a.ldg : a.x;
-  const bool second = CAND && J.D_in != nullptr;
+  const float* __restrict__ P = cand ? a.G + (long long)s * a.ldg : a.x;
+  const bool second = cand && J.D_in != nullptr;
   const float* __restrict__ Din = second ? J.D_in + (long long)s * J.D_in_stride : nullptr;
 
   // first operand: kernel row of output channel f, taps and channels contiguous
@@ -156,7 +162,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
   }
   // accumulator element j of lane (n, h): position r (this lane's), output channel ft*32 + 8 (j/4) + 4 h + j%4
   if (!r_ok) return;
-  float* __restrict__ out = CAND ? J.out + (long long)s * J.out_stride : J.out;
+  float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const int fo = ft * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
@@ -164,7 +170,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
     const float bias = L.b_off >= 0 ? P[L.b_off + fo] : 0.f;
     const float val = acc[j] + bias;
     float res;
-    if (!CAND) {
+    if (!cand) {
       J.Z0[r * L.Cout + fo] = val;
       res = relu_nan(val);
     } else {
@@ -764,38 +770,39 @@ hipError_t launch_deep(ConvArgs a, hipStream_t stream) {
   return hipGetLastError();
 }
 
+// (channels that are no multiple of eight are staged up to one group of them only)
 template <int PB, int WP, int WC>
 hipError_t launch_wide_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
-  if (groups == 1) return full ? launch_wide<1, true, PB, WP, WC>(a, stream) : launch_wide<1, false, PB, WP, WC>(a, stream);
-  return full ? launch_wide<2, true, PB, WP, WC>(a, stream) : launch_wide<2, false, PB, WP, WC>(a, stream);
+  if (groups == 2) return launch_wide<2, true, PB, WP, WC>(a, stream);
+  return full ? launch_wide<1, true, PB, WP, WC>(a, stream) : launch_wide<1, false, PB, WP, WC>(a, stream);
 }
 hipError_t launch_deep_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
-  if (groups == 1) return full ? launch_deep<1, true>(a, stream) : launch_deep<1, false>(a, stream);
-  return full ? launch_deep<2, true>(a, stream) : launch_deep<2, false>(a, stream);
+  if (groups == 2) return launch_deep<2, true>(a, stream);
+  return full ? launch_deep<1, true>(a, stream) : launch_deep<1, false>(a, stream);
 }
 
+// More than eight channels that are no multiple of eight: the gathering kernel.  The staged tiles would read every channel by
+// itself and test it (us per candidates' launch with the pass at x through the next layer, gathered / staged: 33 -> 33 on 16x16,
+// stride 2, m = 39, n_r = 4: 30 / 56; on 14x14, m = 20, n_r = 32: 73 / 129; 20 -> 20 on 28x28, stride 1, m = 30, n_r = 48:
+// 476 / 514; only the same with stride 2 is the other way round: 193 / 162).
+bool gathered(const ConvLayer& L) { return !full_groups(L) && L.Cin > 8; }
+
 hipError_t launch_gather(const ConvArgs& a, hipStream_t stream) {
-  for (int q = 0; q < 2; ++q) {
-    const ConvJob& j = q == 0 ? a.bj : a.cj;
-    const int sources = q == 0 ? (a.has_base ? 1 : 0) : a.n_cand;
+  long long blocks = 0, tiles = 0;                 // of the wider job, of all sources
+  for (const ConvJob* j : {&a.bj, &a.cj}) {
+    const int sources = j == &a.bj ? (a.has_base ? 1 : 0) : a.n_cand;
     if (sources <= 0) continue;
-    const long long rows = (long long)a.n_r * j.L.Hout * j.L.Wout;
-    const long long row_blocks = (rows + 31) / 32;
-    const int ftiles = (j.L.Cout + 31) / 32;
-    const dim3 grid((unsigned)(row_blocks * ftiles), sources);
-    // one wave per tile when there are tiles enough for every SIMD of the chip twice over, else three
-    const bool wide = row_blocks * ftiles * sources >= 2048;
-    if (q == 1) {
-      if (wide) hipLaunchKernelGGL((conv_layer_kernel<true, 1>), grid, dim3(64), 0, stream, a);
-      else hipLaunchKernelGGL((conv_layer_kernel<true, 3>), grid, dim3(192), 0, stream, a);
-    } else {
-      if (wide) hipLaunchKernelGGL((conv_layer_kernel<false, 1>), grid, dim3(64), 0, stream, a);
-      else hipLaunchKernelGGL((conv_layer_kernel<false, 3>), grid, dim3(192), 0, stream, a);
-    }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    const long long rows = (long long)a.n_r * j->L.Hout * j->L.Wout;
+    const long long n = (rows + 31) / 32 * ((j->L.Cout + 31) / 32);
+    if (n > blocks) blocks = n;
+    tiles += n * sources;
   }
-  return hipSuccess;
+  if (tiles == 0) return hipSuccess;
+  const dim3 grid((unsigned)blocks, (a.has_base ? 1 : 0) + a.n_cand);
+  // one wave per tile when there are tiles enough for every SIMD of the chip twice over, else three
+  if (tiles >= 2048) hipLaunchKernelGGL(conv_layer_kernel<1>, grid, dim3(64), 0, stream, a);
+  else hipLaunchKernelGGL(conv_layer_kernel<3>, grid, dim3(192), 0, stream, a);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -823,24 +830,27 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   // tiles of 128 positions where they give every compute unit two workgroups or more
   const int wc = ctiles == 1 ? 1 : 2;
   const bool wide = (rows + 127) / 128 * ((ctiles + wc - 1) / wc) * sources >= 512;
-  if (a.n_cand > 0 && a.has_base && (wide || (full && !full_groups(a.bj.L)))) {
+  // Channels that are no multiple of eight: the gathering kernel, but for wide tiles of one group of them (before those give every
+  // compute unit two workgroups, gathered / staged with the pass at x through the next layer: 1 -> 33 on 32x32, stride 2, m = 39,
+  // n_r = 4: 26 / 43 us; 3 -> 64 on 8x8, stride 2, m = 10, n_r = 2: 16 / 24; from there on 3 -> 32 on 32x32, m = 20: n_r = 4 25 / 23,
+  // n_r = 32 136 / 68).  The pass at x alone is staged: the small jobs of its launch need as long.
+  const bool gather = gathered(L) || (!full && !wide && a.n_cand > 0);
+  if (a.n_cand > 0 && a.has_base && !gather && (wide || gathered(a.bj.L) || (full && !full_groups(a.bj.L)))) {
     // The pass at x on its own: next to wide tiles its few workgroups, each with all of K to walk, would be the last ones to end
     // by far (n_r = 32, convolution 3 behind the candidates' convolution 2: 148 us together, 103 + 11 us apart); and one
-    // kernel runs both jobs, so the channels of either have to be whole groups if the candidates' are.
-    ConvArgs b = a;
+    // staging kernel runs both jobs, so the channels of either have to be whole groups if the candidates' are.
+    ConvArgs b = a, c = a;
     b.n_cand = 0;
+    c.has_base = c.aux_m = c.aux_pieces = c.aux_zero16 = 0;
     const hipError_t e = launch_conv(b, stream);
-    if (e != hipSuccess) return e;
-    b = a;
-    b.has_base = b.aux_m = b.aux_pieces = b.aux_zero16 = 0;
-    return launch_conv(b, stream);
+    return e != hipSuccess ? e : launch_conv(c, stream);
   }
-  if (wide) {
+  if (wide && !gather) {
     const int g = pick_groups([&](const ConvLayer& l, int gr) { return wide_bytes(l, 128, wc, gr); }, 128);
     if (g > 0) return wc == 1 ? launch_wide_as<1, 4, 1>(g, full, a, stream) : launch_wide_as<2, 2, 2>(g, full, a, stream);
   }
   const int g = pick_groups([&](const ConvLayer& l, int gr) { return deep_bytes(l, gr); }, 64);
-  if (g > 0) return launch_deep_as(g, full, a, stream);
+  if (g > 0 && !gather) return launch_deep_as(g, full, a, stream);
   ConvArgs r = a;
   r.aux_pieces = r.aux_m = r.aux_zero16 = 0;
   const hipError_t e = launch_gather(r, stream);

@@ -128,6 +128,19 @@ def test_cnn_edges_of_the_staged_tiles(B, case):
     _check(B, w)
 
 
+@pytest.mark.parametrize("h,w_,c,conv_c,conv_stride,m,n_r", [
+    (9, 7, 1, [33, 100, 5], [2, 1, 2], 5, 3),     # pass at x with more tiles than a candidate, then fewer; then none
+    (8, 8, 3, [12, 64, 9], [1, 2, 1], 6, 5),      # 64 channels for the pass at x, 12 for the candidates
+    (16, 16, 20, [7, 8, 31], [1, 1, 2], 9, 12),   # a first layer that is gathered: the small jobs in a launch of their own
+    (32, 32, 3, [33, 16], [1, 1], 24, 6),         # staged wide tiles beside a gathered pass at x, one wave per tile after them
+    (5, 5, 16, [20, 20], [1, 2], 40, 2),          # whole groups for the candidates, not for the pass at x
+])
+def test_cnn_channels_that_are_no_multiple_of_eight(B, h, w_, c, conv_c, conv_stride, m, n_r):
+    """Every score where staged and gathered layers follow each other and share a launch with the pass at x."""
+    desc = dict(in_h=h, in_w=w_, in_c=c, conv_c=conv_c, conv_stride=conv_stride, fc_out=7, has_bias=True)
+    _check(B, WL.make_cnn_workload("cnn_gather", 80, desc, m, 1, n_r, 0.1, 1e-3, seed=m, n_flip=1, worker_batch=4))
+
+
 def test_cnn_infinite_kernel_values(B):
     """A kernel value of +-inf reaches the positions whose patch is not zero there as +-inf: a unit that it switches off at
     every position (negative pre-activation everywhere, no zero activations in reach) leaves a finite loss difference."""
