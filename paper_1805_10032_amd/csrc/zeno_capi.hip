@@ -454,9 +454,13 @@ zeno_status_t score_enqueue(const zeno_model* model, const Plan& p, const float*
       ZENO_TRY(launch_layer(l.a, bf16, l.delta, p.MB, stream, &shape));
       ps.set_shape(shape, l.a.n_cand > 0 && l.a.has_base, l.a.n_cand > 0 && l.delta, l.a.n_cand, l.a.tail_cand);
     }
+    const float* z0 = reinterpret_cast<const float*>(ws + p.off_z0[L - 1]);
     ProfScope ps(ZENO_KERNEL_LOSS, 0, 4.0 * (m + 1) * rows * C, stream);
-    ZENO_TRY(launch_loss(reinterpret_cast<const float*>(ws + p.off_z0[L - 1]), dZ, batch->labels, batch->targets,
-                         D.loss, m, n_r, begin, rows, C, sample_diff, stream));
+    if (rows == n_r && loss_score_fits(n_r, C)) {   // the only pass
+      ZENO_TRY(launch_loss_score(z0, dZ, batch->labels, batch->targets, D.loss, m, n_r, C, norm_partials, P, P, rho, scores, stream));
+      return ZENO_OK;
+    }
+    ZENO_TRY(launch_loss(z0, dZ, batch->labels, batch->targets, D.loss, m, n_r, begin, rows, C, sample_diff, stream));
   }
   ProfScope ps(ZENO_KERNEL_COMBINE, 0, 8.0 * m * (n_r + P), stream);
   ZENO_TRY(launch_score_combine(sample_diff, norm_partials, P, m, n_r, rho, scores, stream));
@@ -658,6 +662,11 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
   const int P_used = fc_tiles + kConvNormBlocks;
   {
     ProfScope ps(ZENO_KERNEL_LOSS, 0, 4.0 * (m + 1) * n_r * N, stream);
+    if (loss_score_fits(n_r, N)) {
+      ZENO_TRY(launch_loss_score(j.Z0, dZ, batch->labels, batch->targets, mdl->cnn.loss, m, n_r, N, norm_partials, p.P, P_used, rho,
+                                 scores, stream));
+      return ZENO_OK;
+    }
     ZENO_TRY(launch_loss(j.Z0, dZ, batch->labels, batch->targets, mdl->cnn.loss, m, n_r, 0, n_r, N, sample_diff, stream));
   }
   ProfScope ps(ZENO_KERNEL_COMBINE, 0, 8.0 * m * (n_r + P_used), stream);

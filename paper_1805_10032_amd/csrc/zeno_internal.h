@@ -168,6 +168,10 @@ hipError_t launch_score_combine(const double* sample_diff, const double* norm_pa
 // the same with the candidates' partial norms P_stride slots apart, the first P of them in use
 hipError_t launch_score_combine_strided(const double* sample_diff, const double* norm_partials, int P_stride, int P,
                                         int m, int n_r_total, float rho, float* scores, hipStream_t stream);
+// both in one launch, for samples that are all there at once and where loss_score_fits
+bool loss_score_fits(int n_r, int C);
+hipError_t launch_loss_score(const float* Z0, const float* dZ, const int32_t* labels, const float* targets, int loss, int m, int n_r,
+                             int C, const double* norm_partials, int P_stride, int P, float rho, float* scores, hipStream_t stream);
 // ---- small models in one launch (zeno_small.hip)
 struct SmallArgs {
   const float* G;
