@@ -599,8 +599,9 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   // first tile of the next slice, which that slice counts).
   auto take_tile = [&](auto full_c, auto odd_c, f32x4 (&u)[8], bool count) __attribute__((always_inline)) {
     constexpr int MODE = decltype(full_c)::value;
-    if (MODE != 1) {
-      // rows beyond the matrix were read from row N-1: discard them (MODE 0: the steady loop loads its tiles the MODE 2 way)
+    if (MODE == 2 || (MODE == 0 && NW > 1)) {
+      // rows beyond the matrix were read from row N-1: discard them (MODE 0: the steady loop of wide workgroups loads its tiles
+      // the MODE 2 way; one-wave workgroups would only zero zeros: 2724 -> 222, bf16, 9 candidates: 38 -> 39.5 us)
       const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int i = 0; i < 8; ++i) u[i] = (row0 + 4 * i + (lane >> 4) < N) ? u[i] : zero;
