@@ -182,24 +182,63 @@ static bool wide_double_buffered(bool bf16, bool delta, int MB, int NW) {
                                                                         : pick_nw(std::integral_constant<int, 4>{});
 }
 
+// One-wave workgroups (k_waves of them sharing a tile) that fit on a compute unit by their LDS.
+static int one_wave_residents(bool bf16, bool delta, int MB, int k_waves) {
+  auto pick = [&](auto mb) {
+    constexpr int M = decltype(mb)::value;
+    return bf16 ? (delta ? Lds<true, true, M, 1>::TOTAL : Lds<true, false, M, 1>::TOTAL)
+                : (delta ? Lds<false, true, M, 1>::TOTAL : Lds<false, false, M, 1>::TOTAL);
+  };
+  const int lds = MB == 1 ? pick(std::integral_constant<int, 1>{}) : MB == 2 ? pick(std::integral_constant<int, 2>{})
+                                                                              : pick(std::integral_constant<int, 4>{});
+  const int n = 160 * 1024 / (lds * k_waves);
+  return n < 1 ? 1 : n;
+}
+
+// Would a candidate launch that is too small for wide workgroups be slower as one-wave tiles than as four-wave workgroups?
+// One wave per tile with K split over the waves of a workgroup copies the activations once per 32 features and holds so much
+// LDS for it that a compute unit runs one to four such workgroups; but it hands nothing over through memory, and as long as
+// its workgroups are resident all at once it is the faster of the two.  Measured on 3692 random launches (K 64 to 4096, 66 to
+// 2048 features, 3 to 100 candidates; time as one-wave tiles / as four-wave workgroups, geometric mean, and how many of the latter
+// are more than 3 % slower):
+//  * K split over waves, all resident at once: 0.93, 999 of 1473; more than one round of them: 1.44, 33 of 642.
+//  * No split (a K of the launch is short): a quarter of a round or less, or at most 20 MB of activations copied in all: 1.03, 393
+//    of 1314; beyond both: 1.22, 13 of 263.
+//  * Not where the pass at x has more than twice the candidates' chunks (it sets the pace, and four waves of one-wave
+//    tiles walk its K in parallel: 512 -> 1630, 8 candidates, fp32: 30 -> 54 us), and for layers without the second product in bf16,
+//    which wait for memory either way, only for four row blocks, or two beyond 1.25 rounds (the others: 1.10, 8 of 49).
+static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int MB) {
+  const KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
+  const long long tiles = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)job_tiles(a.cj, 32) * a.n_cand;
+  const int chunks = a.cj.Kp >> 6;
+  if (a.has_base && (a.bj.Kp >> 6) > 2 * chunks) return false;
+  const long long workgroups = tiles * one.k_slices, round = (long long)compute_units() * one_wave_residents(bf16, delta, MB, one.k_waves);
+  if (bf16 && !delta && MB < 4) return MB == 2 && one.k_waves > 1 && 4 * workgroups > 5 * round;
+  if (one.k_waves > 1) return workgroups > round;
+  const long long copied = tiles * chunks * (MB * 32LL * 64 * (bf16 ? 2 : 4) * (delta ? 2 : 1));
+  return 4 * workgroups > round && copied > 20000000;
+}
+
 // Candidate launches with too few 256-feature tiles for eight-wave workgroups: four-wave workgroups, all tiles (and those of
 // the pass at x, if it rides along) cut into as many K slices as cost least by the count
-//     rounds x (chunks of a slice + 4 if sliced),   rounds = workgroups per compute unit, rounded up,
-// in chunk times; the 4 is the hand-over of the partial accumulators.  One wave per tile with K split over the waves of a
-// workgroup, which these launches took below 256 workgroups, copies the activations once per 32 features and holds so much
-// LDS for it that a compute unit runs two to four waves.  Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32,
+//     rounds x (chunks of a slice + hand-over if sliced),   rounds = workgroups per compute unit, rounded up,
+// in chunk times, the hand-over of the partial accumulators being 4 of them, 6 in bf16 without the second product, whose chunks
+// are the shortest (113 launches with four row blocks: 1.35 and 1.37 times as fast as one-wave tiles with 4 and 6).
+// Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32,
 // m = 20: 3072 -> 2048 (336 tiles) 141 / 147 / 125 / 134, 141; 2048 -> 2048 with the second product 162 / 172 / 143 / 152, 162;
 // 3072 -> 512 (81 tiles) 77 / 50 / 40 / 48, 48.  bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88;
 // 777 -> 333 with the second product (100 tiles) 41 / 37 / 49 / 49, 57.
 // Layers of at most 64 features keep the one-wave tiles (half a workgroup or more would be idle), and so do launches that
-// make no half round of workgroups this way (896 -> 100, 7 candidates: 7 tiles; fp32 with the second product and four row
-// blocks, which is single-buffered and has no slices: 24 -> 100 us).  Returns the slices (1: none) or 0 where the launch
-// keeps its shape; budget: bytes for the partial accumulators.
+// are faster on them (one_wave_tiles_slower) or make no half round of workgroups this way (896 -> 100, 7 candidates: 7
+// tiles; fp32 with the second product and four row blocks, which is single-buffered and has no slices: 24 -> 100 us).
+// Returns the slices (1: none) or 0 where the launch keeps its shape; budget: bytes for the partial accumulators.
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
   if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  if (launch_nw_for(a) == 1 && !one_wave_tiles_slower(a, bf16, delta, MB)) return 0;
   const long long tiles = (a.has_base ? job_tiles(a.bj, 128) : 0) + (long long)job_tiles(a.cj, 128) * a.n_cand;
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
   const int min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
+  const double hand_over = bf16 && !delta ? 6.0 : 4.0;
   int most = 1;
   if (a.slice_partials != nullptr && a.slice_counters != nullptr && tiles <= kMaxSliceGroups) {
     most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
@@ -209,7 +248,7 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
   int best = 1;
   double best_cost = 0.0;
   for (int S = 1; S <= most; ++S) {
-    const double cost = (double)((tiles * S + n_cu - 1) / n_cu) * ((double)chunks / S + (S > 1 ? 4.0 : 0.0));
+    const double cost = (double)((tiles * S + n_cu - 1) / n_cu) * ((double)chunks / S + (S > 1 ? hand_over : 0.0));
     if (S == 1 || cost < best_cost) {
       best = S;
       best_cost = cost;

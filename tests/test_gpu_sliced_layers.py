@@ -21,11 +21,11 @@ CASES = [
     # dims, m, n_r, fwd, row_align, bias
     ([3072, 512, 10], 20, 32, "fp32", 1, True),        # the pass at x rides along, sliced as well
     ([1030, 600, 300, 10], 33, 100, "bf16", 1, True),  # four row blocks, ragged K, a width that ends inside a tile
-    ([960, 520, 130], 17, 40, "bf16", 32, False),      # two row blocks; 17 candidates: units of 9 and 8
+    ([960, 520, 130], 17, 40, "fp32", 32, False),      # two row blocks; 17 candidates: units of 9 and 8
     ([2048, 700], 20, 20, "fp32", 32, True),           # one layer: the pass at x is the same layer
     ([1024, 1024, 1024, 65], 12, 64, "fp32", 4, True), # second product in fp32, two row blocks; 65 outputs
     ([2048, 900, 10], 12, 150, "bf16", 32, True),      # two passes over G
-    ([640, 449, 1], 30, 3, "bf16", 1, True),          # squared loss, few samples
+    ([640, 449, 1], 30, 3, "fp32", 1, True),          # squared loss, few samples
 ]
 
 
@@ -59,3 +59,37 @@ def test_sliced_layers_all_rows(B, case):
     if mdl.workspace_bytes(m, n_r) <= B.STATIC_SCRATCH_BYTES:
         assert torch.equal(s, B.zeno_score_static(*args, **batch))
 
+
+
+@pytest.mark.parametrize("dims,m,n_r,fwd,row_align,waves", [
+    ([512, 128], 63, 5, "fp32", 1, [1]),                 # 256 one-wave workgroups, resident all at once
+    ([512, 128], 64, 5, "fp32", 1, [4]),                 # 260
+    ([1000, 100], 40, 40, "bf16", 1, [1]),               # narrow output layers in bf16, packed rows
+    ([900, 70], 30, 100, "bf16", 1, [1]),
+    ([1500, 300], 12, 100, "bf16", 1, [1]),
+    ([960, 520, 130], 17, 40, "bf16", 32, [1, 1]),       # with the pass at x, without and with the second product
+    ([640, 449, 1], 30, 3, "bf16", 1, [1, 1]),
+    ([320, 1600, 66], 8, 70, "fp32", 4, [1, 1]),         # the pass at x has five times the candidates' chunks
+    ([256, 1024], 20, 70, "bf16", 1, [4]),               # short K: activations copied once per 32 features, 44 MB
+    ([128, 1024], 15, 70, "bf16", 1, [1]),               # 17 MB
+])
+def test_one_wave_tiles_where_they_are_resident_at_once(dims, m, n_r, fwd, row_align, waves):
+    """Launches on both sides of the line between one-wave tiles and four-wave workgroups: shape and every score."""
+    from paper_1805_10032_amd import binding as B
+    B.load_library()
+    w = WL.make_mlp_workload(f"onewave{m}", 170 + m, dims, m, m // 3, n_r, 0.05, 1e-3, fwd, seed=m, loss="squared" if dims[-1] == 1 else
+                             "softmax_ce", n_flip=m // 6, n_noise=m // 6, noise_std=2.0, worker_batch=16)
+    dev = torch.device("cuda", 0)
+    batch = dict(labels=None if w.labels is None else w.labels.to(dev), targets=None if w.targets is None else w.targets.to(dev))
+    B.profile_enable(True)
+    try:
+        s = B.zeno_score(B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd), w.x.to(dev), rows_to_gpu(B, w.G, row_align, dev), w.features.to(dev),
+                         w.gamma, w.rho, **batch)
+        torch.cuda.synchronize()
+        recs = B.profile_collect(detail=True)
+    finally:
+        B.profile_enable(False)
+    assert [r["waves"] for r in recs if r["kernel"] == "layer_cand"] == waves, recs
+    s_ref, scale = oracle_terms(w)
+    err = score_error(npy(s), s_ref, scale)
+    assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
