@@ -219,22 +219,40 @@ static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int
   return 4 * workgroups > round && copied > 20000000;
 }
 
-// Candidate launches with too few 256-feature tiles for eight-wave workgroups: four-wave workgroups, all tiles (and those of
+// Does a launch of four-wave workgroups stream its rows on the shifted column grid, which its slices do not have?
+static bool on_shifted_grid(const LayerArgs& a, bool bf16, bool delta, int MB) {
+  auto has_grid = [&](auto mb) {
+    constexpr int M = decltype(mb)::value;
+    return delta ? Lds<true, true, M, 4, 1>::DBUF : Lds<true, false, M, 4, 1>::DBUF;
+  };
+  if (!bf16 || launch_lines_aligned(a) || launch_ring_kind(a) == 0) return false;
+  return MB == 1 ? has_grid(std::integral_constant<int, 1>{}) : MB == 2 ? has_grid(std::integral_constant<int, 2>{})
+                                                                         : has_grid(std::integral_constant<int, 4>{});
+}
+
+// Candidate launches with too few 256-feature tiles for eight-wave workgroups.
+// Fewer 128-feature tiles than compute units (one-wave tiles otherwise): four-wave workgroups, all tiles (and those of
 // the pass at x, if it rides along) cut into as many K slices as cost least by the count
 //     rounds x (chunks of a slice + hand-over if sliced),   rounds = workgroups per compute unit, rounded up,
 // in chunk times, the hand-over of the partial accumulators being 4 of them, 6 in bf16 without the second product, whose chunks
 // are the shortest (113 launches with four row blocks: 1.35 and 1.37 times as fast as one-wave tiles with 4 and 6).
-// Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32,
-// m = 20: 3072 -> 2048 (336 tiles) 141 / 147 / 125 / 134, 141; 2048 -> 2048 with the second product 162 / 172 / 143 / 152, 162;
-// 3072 -> 512 (81 tiles) 77 / 50 / 40 / 48, 48.  bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88;
-// 777 -> 333 with the second product (100 tiles) 41 / 37 / 49 / 49, 57.
+// Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32, m = 20: 3072 -> 512 (81 tiles) 77 / 50 / 40 / 48, 48.
+// bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88; 777 -> 333 with the second product (100 tiles)
+// 41 / 37 / 49 / 49, 57.
+// More of them (whole four-wave tiles otherwise): three slices where the candidates fill more than one round of compute units and
+// all tiles at most 4/3, which the slices make four full rounds of a third, for K from 28 chunks on.  Random launches, whole /
+// sliced: 1.14 (5 of 128 more than 3 % slower); from 12 chunks on 1.08 (42 of 242); up to 3/2 rounds in two
+// slices 0.95 (28 of 43); in bf16 without the second product, which waits for memory either way, 1.02 (20 of 64); on the
+// shifted grid, which slices do not have, 0.93 (5 of 10).  fp32, n_r = 32, m = 20: 3072 -> 2048 (336 tiles) 141 whole, 125 in
+// three slices; 2048 -> 2048 with the second product 162, 143.
 // Layers of at most 64 features keep the one-wave tiles (half a workgroup or more would be idle), and so do launches that
 // are faster on them (one_wave_tiles_slower) or make no half round of workgroups this way (896 -> 100, 7 candidates: 7
 // tiles; fp32 with the second product and four row blocks, which is single-buffered and has no slices: 24 -> 100 us).
 // Returns the slices (1: none) or 0 where the launch keeps its shape; budget: bytes for the partial accumulators.
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
   if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
-  if (launch_nw_for(a) == 1 && !one_wave_tiles_slower(a, bf16, delta, MB)) return 0;
+  const bool whole_tiles = launch_nw_for(a) == 4;
+  if (!whole_tiles && !one_wave_tiles_slower(a, bf16, delta, MB)) return 0;
   const long long tiles = (a.has_base ? job_tiles(a.bj, 128) : 0) + (long long)job_tiles(a.cj, 128) * a.n_cand;
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
   const int min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
@@ -244,6 +262,10 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
     most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
     const long long by_bytes = (long long)(budget / ((size_t)4 * MB * 16 * 64 * sizeof(float))) / tiles;
     if (most > by_bytes) most = by_bytes < 1 ? 1 : (int)by_bytes;
+  }
+  if (whole_tiles) {
+    const bool last_round_empty = (long long)job_tiles(a.cj, 128) * a.n_cand > n_cu && 3 * tiles <= 4 * n_cu;
+    return last_round_empty && chunks >= 28 && most >= 3 && (delta || !bf16) && !on_shifted_grid(a, bf16, delta, MB) ? 3 : 0;
   }
   int best = 1;
   double best_cost = 0.0;

@@ -61,6 +61,28 @@ def test_sliced_layers_all_rows(B, case):
 
 
 
+def _shapes_and_scores(name, dims, m, n_r, fwd, row_align):
+    """Launch records of the candidates' layers; every score against the oracle."""
+    from paper_1805_10032_amd import binding as B
+    B.load_library()
+    w = WL.make_mlp_workload(name, 170 + m, dims, m, m // 3, n_r, 0.05, 1e-3, fwd, seed=m, loss="squared" if dims[-1] == 1 else
+                             "softmax_ce", n_flip=m // 6, n_noise=m // 6, noise_std=2.0, worker_batch=16)
+    dev = torch.device("cuda", 0)
+    batch = dict(labels=None if w.labels is None else w.labels.to(dev), targets=None if w.targets is None else w.targets.to(dev))
+    B.profile_enable(True)
+    try:
+        s = B.zeno_score(B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd), w.x.to(dev), rows_to_gpu(B, w.G, row_align, dev), w.features.to(dev),
+                         w.gamma, w.rho, **batch)
+        torch.cuda.synchronize()
+        recs = B.profile_collect(detail=True)
+    finally:
+        B.profile_enable(False)
+    s_ref, scale = oracle_terms(w)
+    err = score_error(npy(s), s_ref, scale)
+    assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
+    return [r for r in recs if r["kernel"] == "layer_cand"]
+
+
 @pytest.mark.parametrize("dims,m,n_r,fwd,row_align,waves", [
     ([512, 128], 63, 5, "fp32", 1, [1]),                 # 256 one-wave workgroups, resident all at once
     ([512, 128], 64, 5, "fp32", 1, [4]),                 # 260
@@ -75,21 +97,21 @@ def test_sliced_layers_all_rows(B, case):
 ])
 def test_one_wave_tiles_where_they_are_resident_at_once(dims, m, n_r, fwd, row_align, waves):
     """Launches on both sides of the line between one-wave tiles and four-wave workgroups: shape and every score."""
-    from paper_1805_10032_amd import binding as B
-    B.load_library()
-    w = WL.make_mlp_workload(f"onewave{m}", 170 + m, dims, m, m // 3, n_r, 0.05, 1e-3, fwd, seed=m, loss="squared" if dims[-1] == 1 else
-                             "softmax_ce", n_flip=m // 6, n_noise=m // 6, noise_std=2.0, worker_batch=16)
-    dev = torch.device("cuda", 0)
-    batch = dict(labels=None if w.labels is None else w.labels.to(dev), targets=None if w.targets is None else w.targets.to(dev))
-    B.profile_enable(True)
-    try:
-        s = B.zeno_score(B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd), w.x.to(dev), rows_to_gpu(B, w.G, row_align, dev), w.features.to(dev),
-                         w.gamma, w.rho, **batch)
-        torch.cuda.synchronize()
-        recs = B.profile_collect(detail=True)
-    finally:
-        B.profile_enable(False)
-    assert [r["waves"] for r in recs if r["kernel"] == "layer_cand"] == waves, recs
-    s_ref, scale = oracle_terms(w)
-    err = score_error(npy(s), s_ref, scale)
-    assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
+    recs = _shapes_and_scores("onewave", dims, m, n_r, fwd, row_align)
+    assert [r["waves"] for r in recs] == waves, recs
+
+
+@pytest.mark.parametrize("dims,m,n_r,fwd,row_align,slices,streaming", [
+    ([2048, 700], 43, 33, "bf16", 1, 1, 2),              # 264 tiles, packed 16-byte aligned rows: the shifted grid
+    ([2048, 702], 43, 33, "bf16", 1, 1, 3),              # 8-byte aligned
+    ([2048, 700], 43, 33, "bf16", 32, 1, 1),             # line-aligned, one product in bf16
+    ([1792, 700], 43, 9, "fp32", 1, 3, 0),               # 28 chunks: sliced
+    ([1728, 700], 43, 9, "fp32", 1, 1, 0),               # 27
+    ([1792, 512], 64, 9, "fp32", 32, 1, 1),              # the candidates fill one round exactly
+    ([1792, 700], 57, 9, "fp32", 1, 1, 0),               # 348 tiles: more than 4/3 rounds
+])
+def test_whole_four_wave_tiles_and_their_slices(dims, m, n_r, fwd, row_align, slices, streaming):
+    """Launches with 128-feature tiles for every compute unit: sliced only where their last round would be nearly empty, and not
+    on the shifted column grid."""
+    (r,) = _shapes_and_scores("whole", dims, m, n_r, fwd, row_align)
+    assert (r["waves"], r["k_slices"], r["streaming"], r["tail_candidates"]) == (4, slices, streaming, m if slices > 1 else 0), r
