@@ -405,7 +405,7 @@ zeno_status_t score_enqueue(const zeno_model* model, const Plan& p, const float*
   const zeno_model_desc_t& D = model->desc;
   const bool bf16 = D.fwd == ZENO_FWD_BF16;
   const int L = p.L, n_r = batch->n_r, C = D.dims[L];
-  if (small_model_fits(D.dims, L, m, n_r)) {
+  if (small_model_fits(D.dims, L, m, n_r, bf16)) {
     // one launch instead of 2 L + 3, no scratch
     SmallArgs a;
     std::memset(&a, 0, sizeof(a));

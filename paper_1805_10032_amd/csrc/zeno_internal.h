@@ -187,7 +187,7 @@ struct SmallArgs {
   float* scores;
   int pitch;   // filled in by the launcher
 };
-bool small_model_fits(const int* dims, int L, int m, int n_r);
+bool small_model_fits(const int* dims, int L, int m, int n_r, bool bf16);
 hipError_t launch_score_small(SmallArgs a, bool bf16, int m, hipStream_t stream);
 // x_next != nullptr: also write x_next = x - gamma * average (out may then be nullptr)
 hipError_t launch_masked_average(const float* G, long long ldg, const float* scores, int m, long long d, int b,

@@ -278,17 +278,20 @@ int small_pitch(const int* dims, int L) {
 // n_r = 32, then m = 100, n_r = 4): one layer, 196 steps (784 -> 10): 25.3 / 30.5, 48.7 / 52.9; 300 steps (1200 -> 10): 30.6
 // (before the loads ran a group ahead: 34.0) / 30.6; two layers, 416 steps (784 -> 64 -> 10): 43.1 / 72.0, 72.3 / 96.3; four
 // layers, 496 steps (256 -> 128 -> 128 -> 128 -> 10 has 632): 51.0 / 59.6, 75.2 / 85.2; 936 steps: 97.6 / 86.4, 118.0 / 115.6.
+// With bf16 operands, whose general path multiplies eight times as fast, half as many (random models up to 250 steps a layer and
+// 256 candidates, this path's gain: float32 1.37, none of 157 more than 2 % slower; bf16 up to 125 steps a layer 1.28, 2 of 79;
+// bf16 beyond that 1.04, 24 of 71, by up to 9 %).
 // More classes would put several rounds of exponentials behind each other (784 -> 32: 37.8 / 32.4, 59.2 / 46.8).  Beyond 256
-// candidates the workgroups of a CU follow each other.  Rows shorter than four floats cannot be read four at a time.
-bool small_model_fits(const int* dims, int L, int m, int n_r) {
-  if (n_r > kRows || dims[L] > kMaxClasses) return false;
+// candidates the workgroups of a CU follow each other (random models, 257 to 1024 candidates: 1.06, 49 of 216 slower, by up to
+// 18 %).  Rows shorter than four floats cannot be read four at a time.
+bool small_model_fits(const int* dims, int L, int m, int n_r, bool bf16) {
+  if (n_r > kRows || dims[L] > kMaxClasses || m > 256) return false;
   long long steps = 0;
   for (int l = 0; l < L; ++l) {
     if (dims[l] < 4 || dims[l + 1] > kMaxWidth) return false;
     steps += (long long)((dims[l + 1] + 31) / 32) * ((dims[l] + 7) / 8) * (l > 0 ? 3 : 2);
   }
-  steps *= (m + 255) / 256;
-  return steps <= 250LL * L && steps <= 600;
+  return steps <= (bf16 ? 125LL : 250LL) * L && steps <= 600;
 }
 
 hipError_t launch_score_small(SmallArgs a, bool bf16, int m, hipStream_t stream) {
@@ -302,7 +305,7 @@ hipError_t launch_score_small(SmallArgs a, bool bf16, int m, hipStream_t stream)
     return e;
   }();
   if (attr_err != hipSuccess) return attr_err;
-  if (lds > most || !small_model_fits(a.dims, a.L, m, a.n_r)) return hipErrorInvalidValue;
+  if (lds > most || !small_model_fits(a.dims, a.L, m, a.n_r, bf16)) return hipErrorInvalidValue;
   if (bf16) hipLaunchKernelGGL(score_small_kernel<true>, dim3(m), dim3(kThreads), lds, stream, a);
   else hipLaunchKernelGGL(score_small_kernel<false>, dim3(m), dim3(kThreads), lds, stream, a);
   return hipGetLastError();

@@ -23,9 +23,12 @@ CASES = [
     ([7, 16], 5, 32, "bf16", 1, False, True),              # most classes, all samples, end of a row inside a step
     ([784, 17], 4, 8, "fp32", 32, True, False),            # one class more
     ([785, 10], 9, 33, "fp32", 1, True, False),            # one sample more
-    ([1000, 10], 20, 31, "bf16", 1, True, True),           # 250 steps; 1001 would be 252
+    ([1000, 10], 20, 31, "fp32", 1, True, True),           # 250 steps; 1001 would be 252
     ([1001, 10], 20, 31, "fp32", 1, True, False),
-    ([64, 33, 10], 257, 5, "fp32", 1, True, True),         # two tiles, more workgroups than CUs
+    ([496, 10], 20, 31, "bf16", 1, True, True),            # 124 steps, and 126: the line for bf16 operands
+    ([497, 10], 20, 31, "bf16", 1, True, False),
+    ([64, 33, 10], 256, 5, "fp32", 1, True, True),         # two tiles, a workgroup for every CU
+    ([64, 33, 10], 257, 5, "fp32", 1, True, False),        # one candidate more
     ([30, 32, 65, 96, 97, 1], 6, 17, "fp32", 1, True, True),   # one to four tiles, squared loss
     ([21, 128, 4, 2], 8, 32, "bf16", 4, True, True),       # widest layer, shortest hidden row
     ([50, 129, 3], 4, 3, "fp32", 1, True, False),          # one feature too wide
