@@ -833,8 +833,13 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   // Channels that are no multiple of eight: the gathering kernel, but for wide tiles of one group of them (before those give every
   // compute unit two workgroups, gathered / staged with the pass at x through the next layer: 1 -> 33 on 32x32, stride 2, m = 39,
   // n_r = 4: 26 / 43 us; 3 -> 64 on 8x8, stride 2, m = 10, n_r = 2: 16 / 24; from there on 3 -> 32 on 32x32, m = 20: n_r = 4 25 / 23,
-  // n_r = 32 136 / 68).  The pass at x alone is staged: the small jobs of its launch need as long.
-  const bool gather = gathered(L) || (!full && !wide && a.n_cand > 0);
+  // n_r = 32 136 / 68).
+  // Neither where input and output channels are so few that a wide tile's products are mostly padding (time as wide tiles / gathered,
+  // whole steps: up to 2 -> 16 or 4 -> 8 channels 1.04 on 21 random models, 19 of them slower as wide tiles, by up to 20 %; the
+  // others 0.89 on 135).  The pass at x alone is staged up to 512 tiles of 64 positions x 32 channels, the small jobs of its launch
+  // need as long (staged / gathered: 0.97 below 256 tiles, 1.01 on 38 up to 512, 1.02 on 32 beyond, 22 of them slower).
+  const bool few = (L.Cin <= 2 && L.Cout <= 16) || (L.Cin <= 4 && L.Cout <= 8);
+  const bool gather = gathered(L) || (!full && (a.n_cand > 0 ? !wide || few : (rows + 63) / 64 * ctiles >= 512));
   if (a.n_cand > 0 && a.has_base && !gather && (wide || gathered(a.bj.L) || (full && !full_groups(a.bj.L)))) {
     // The pass at x on its own: next to wide tiles its few workgroups, each with all of K to walk, would be the last ones to end
     // by far (n_r = 32, convolution 3 behind the candidates' convolution 2: 148 us together, 103 + 11 us apart); and one

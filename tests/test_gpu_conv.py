@@ -169,3 +169,11 @@ def test_cnn_error_codes(B):
     mdl = B.ZenoCnnModel(dict(in_h=4, in_w=4, in_c=1, conv_c=[4], conv_stride=[1], fc_out=2, has_bias=True))
     assert mdl.workspace_bytes(4, 129) == 0 and mdl.workspace_bytes(4, 128) > 0
     assert mdl.plan_check(4, 4) == 2
+
+
+@pytest.mark.parametrize("c,first,m,n_r", [(2, 16, 9, 30), (2, 17, 9, 30), (3, 16, 9, 30), (4, 8, 9, 30), (5, 8, 9, 30), (1, 1, 10, 33)])
+def test_cnn_few_channels_in_many_tiles(B, c, first, m, n_r):
+    """Both sides of the line between wide staged tiles and gathered ones for a first convolution with few channels (at least 512
+    tiles of 128 positions)."""
+    desc = dict(in_h=16, in_w=16, in_c=c, conv_c=[first, 8], conv_stride=[1, 2], fc_out=7, has_bias=True)
+    _check(B, WL.make_cnn_workload("cnn_few", 90, desc, m, 1, n_r, 0.1, 1e-3, seed=c, n_flip=1, worker_batch=4))
