@@ -11,6 +11,12 @@ namespace {
 // Three-way split of eight floats into bf16 pieces, x = h + m + l + (at most 2^-25 |x|):
 // h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), round to nearest even each time;
 // both subtractions are exact.
+// The leading piece of a finite |x| from 0x1.ffp127 (3.396e38) on would be rounded to infinity: FINITE gives it the largest bf16
+// value instead, and the other two pieces take up the rest (four maxima of three and a branch that is never taken on ordinary
+// data: the steps of two convolutional models 157.2 -> 158.9 and 449 -> 454 us; one test for all values of a thread, with the
+// staging code twice or with the result in a flag, took 160.3 and 458).  Below about 1e-33 the last pieces underflow, and
+// products keep fewer than 24 bits.
+template <bool FINITE = false>
 __device__ inline void split3(const f32x4& v0, const f32x4& v1, bf16x8& h, bf16x8& m, bf16x8& l) {
   // Two floats at a time: one packed conversion gives both bf16 pieces in one register, and the exact remainder of
   // either float is one instruction, the bf16 dot product of that register with (-1, 0) or (0, -1) added to the
@@ -31,16 +37,30 @@ __device__ inline void split3(const f32x4& v0, const f32x4& v1, bf16x8& h, bf16x
     const f32x2 t = {a, b};
     return __builtin_convertvector(t, bf16x2);
   };
+  unsigned lead[4];   // (an array: __builtin_bit_cast of a vector's element reads element 0, whatever its index)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) lead[i] = __builtin_bit_cast(unsigned, pack(x[2 * i], x[2 * i + 1]));
+  if (FINITE) {
+    float top = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) top = __builtin_fmaxf(top, __builtin_fabsf(x[i]));
+    if (__any(top >= 0x1.ffp127f)) {
+      // (infinity has the next bit pattern after the largest finite value, in either half and with either sign)
+      auto rounded_up = [](float v) { return (__builtin_bit_cast(unsigned, v) & 0x7fffffffu) - 0x7f7f8000u < 0x8000u; };
+#pragma unroll
+      for (int i = 0; i < 4; ++i) lead[i] -= (rounded_up(x[2 * i]) ? 1u : 0u) + (rounded_up(x[2 * i + 1]) ? 0x10000u : 0u);
+    }
+  }
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float a = x[2 * i], b = x[2 * i + 1];
-    const bf16x2 hp = pack(a, b);
+    const bf16x2 hp = __builtin_bit_cast(bf16x2, lead[i]);
     const float ra = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_first, a, false);
     const float rb = __builtin_amdgcn_fdot2_f32_bf16(hp, minus_second, b, false);
     const bf16x2 mp = pack(ra, rb);
     const float sa = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_first, ra, false);
     const float sb = __builtin_amdgcn_fdot2_f32_bf16(mp, minus_second, rb, false);
-    hu[i] = __builtin_bit_cast(unsigned, hp);
+    hu[i] = lead[i];
     mu[i] = __builtin_bit_cast(unsigned, mp);
     lu[i] = __builtin_bit_cast(unsigned, pack(sa, sb));
   }
@@ -55,14 +75,15 @@ struct Split8 {
 };
 __device__ inline Split8 split8(const f32x4& v0, const f32x4& v1) {
   Split8 s;
-  split3(v0, v1, s.h, s.m, s.l);
+  split3<true>(v0, v1, s.h, s.m, s.l);
   return s;
 }
 
 // One k-step of 16 of a 32 x 32 block of products at float32 accuracy: the six piece products down to 2^-17 of the leading
 // one; what is dropped is about 2^-24 of |a||b| per product, one float32 rounding.  The leading products have an
 // accumulator of their own: an operand that is not finite has no useful remainder (inf - inf), and the
-// leading products alone say what the float32 product would have been (join_split).
+// leading products alone say what the float32 product would have been (join_split).  A sum of leading products may overflow
+// where the float32 sum ends within 1 % of its largest value.
 __device__ inline void mfma_split(const Split8& a, const Split8& b, f32x16& lead, f32x16& rest) {
   rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, rest, 0, 0, 0);
   rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, rest, 0, 0, 0);

@@ -141,24 +141,51 @@ def test_cnn_channels_that_are_no_multiple_of_eight(B, h, w_, c, conv_c, conv_st
     _check(B, WL.make_cnn_workload("cnn_gather", 80, desc, m, 1, n_r, 0.1, 1e-3, seed=m, n_flip=1, worker_batch=4))
 
 
-def test_cnn_infinite_kernel_values(B):
-    """A kernel value of +-inf reaches the positions whose patch is not zero there as +-inf: a unit that it switches off at
-    every position (negative pre-activation everywhere, no zero activations in reach) leaves a finite loss difference."""
-    desc = dict(in_h=1, in_w=1, in_c=9, conv_c=[5], conv_stride=[1], fc_out=3, has_bias=True)
-    w = WL.make_cnn_workload("cnn_inf", 70, desc, 4, 1, 6, 0.1, 0.0)
+RANGE = [
+    # (in_h, in_w, in_c, channels, strides), m, n_r
+    ((5, 6, 8, [16, 12], [1, 2]), 7, 5),           # staged, few tiles, steps of two taps
+    ((16, 16, 16, [32, 8], [1, 1]), 8, 40),        # staged, many tiles
+    ((5, 6, 9, [11, 12], [1, 2]), 7, 5),           # gathered
+]
+
+
+def _range_workload(case):
+    (h, w_, c, conv_c, conv_stride), m, n_r = RANGE[case]
+    desc = dict(in_h=h, in_w=w_, in_c=c, conv_c=conv_c, conv_stride=conv_stride, fc_out=3, has_bias=True)
+    w = WL.make_cnn_workload("cnn_range", 70 + case, desc, m, 1, n_r, 0.1, 0.0)
     w.features.abs_().add_(0.5)
-    taps = w.G[2][:5 * 81].view(5, 9, 9)                # [channel][tap][input channel]
-    ref = w.G[2].clone()
-    taps[1, 4, 3] = float("inf")                        # centre tap (the only one inside a 1 x 1 image): pre-activation -> -inf
-    ref[:5 * 81].view(5, 9, 9)[1, 4, 3] = 1e6           # a finite value that switches the unit off as well
-    off = WL.make_cnn_workload("cnn_inf", 70, desc, 4, 1, 6, 0.1, 0.0)
-    off.features.copy_(w.features)
-    off.G[2] = ref
-    a, b = npy(_gpu_scores(B, w)), npy(_gpu_scores(B, off))
-    # the same loss difference; the unit's own change is -z0 either way, so only rounding separates the two
-    assert np.isfinite(b[2])
-    assert np.isnan(a[2]) or a[2] == -np.inf or abs(a[2] - b[2]) <= 1e-5 * max(1.0, abs(b[2]))
-    assert np.array_equal(a[[0, 1, 3]], b[[0, 1, 3]])
+    return w, c
+
+
+@pytest.mark.parametrize("case", range(len(RANGE)))
+def test_cnn_infinite_kernel_values(B, case):
+    """A kernel value of -inf at x (centre tap: it only meets values above zero) switches its unit off everywhere, for the pass at x
+    and for every candidate; the other units' scores are finite and those of the oracle.  Where operands are split into
+    pieces, the remainders of an infinite value are NaN and must not reach the sum."""
+    w, c = _range_workload(case)
+    w.x[:9 * c].view(9, c)[4, 3] = -float("inf")
+    with np.errstate(invalid="ignore"):
+        err = _check(B, w)
+    assert np.all(np.isfinite(err)) and np.all(np.isfinite(npy(_gpu_scores(B, w))))
+
+
+@pytest.mark.parametrize("case", range(len(RANGE)))
+def test_cnn_finite_values_at_the_end_of_the_range(B, case):
+    """Finite kernel values up to the largest float32, which bf16 rounds to infinity, meet zeros only (a channel of the images that
+    is zero, a unit that is off): the scores are finite and those of the oracle."""
+    w, c = _range_workload(case)
+    (_, _, _, conv_c, _), m, n_r = RANGE[case]
+    w.features.view(n_r, -1, c)[:, :, 2] = 0.0
+    first = 9 * c * conv_c[0]
+    w.x[first + 5] = -1e3                                       # bias: unit 5 of the first convolution is off
+    big = float(np.finfo(np.float32).max)
+    for i, v in ((1, big), (2, -big), (3, 3.3962e38), (4, -3.39e38)):
+        w.G[i, :first].view(conv_c[0], 9, c)[0, 4, 2] = v       # meets the channel of zeros
+    second = first + conv_c[0]
+    for i, v in ((4, big), (5, -big), (6, 3.3962e38)):
+        w.G[i, second:second + 9 * conv_c[0] * conv_c[1]].view(conv_c[1], 9, conv_c[0])[1, 4, 5] = v   # meets the unit that is off
+    err = _check(B, w)
+    assert np.all(np.isfinite(err))
 
 
 def test_cnn_error_codes(B):
