@@ -235,10 +235,11 @@ const char* zeno_status_string(int32_t status);
 
 /* Host-only self-check of the scratch layout of zeno_score (Definition 2's m+1 forward passes keep
  * their activations there): walks the launch sequence for (model, m, n_r) without touching a
- * device and verifies, for every workgroup width a launch may take, that everything the launch
- * writes lies inside its slot of the workspace.  OK, INVALID_ARG for bad arguments, WORKSPACE if a
+ * device and verifies, for every workgroup width a launch may take and every number of K slices that
+ * launches of four-wave workgroups may be cut into, that everything the launch writes (activations, norms, partial
+ * accumulators and their counters) lies inside its slot of the workspace.  OK, INVALID_ARG for bad arguments, WORKSPACE if a
  * launch would leave its slot (a bug in the library: zeno_score makes the same check for the
- * widths it really uses and then enqueues nothing).  UNSUPPORTED for convolutional models. */
+ * widths and slices it really uses and then enqueues nothing).  UNSUPPORTED for convolutional models. */
 zeno_status_t zeno_score_plan_check(const zeno_model_t* model, int32_t m, int32_t n_r);
 
 /* Per-launch timing, a measurement aid (Section 5.3 prices the step by its

@@ -222,10 +222,12 @@ struct Launch {
 // input the previous launch completed) either inside that launch or as a launch of its
 // own in front of it.  A single-layer model needs one launch.  *P_out receives the
 // partial-norm slots per candidate.  query_device = false plans without asking the
-// device for occupancies (every merge is then planned as merged, the wider case).
+// device for occupancies (every merge is then planned as merged, the wider case), and
+// every launch that may run as four-wave workgroups in K slices as `slices` of them, as
+// far as it may be cut (0: none does).
 std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const float* x, const float* G, int64_t ldg,
                                    int m, float gamma, unsigned char* ws, int rows, bool first_pass, int* P_out,
-                                   bool query_device = true) {
+                                   bool query_device = true, int slices = 0) {
   const zeno_model_desc_t& D = model->desc;
   const bool bf16 = D.fwd == ZENO_FWD_BF16;
   const int L = p.L;
@@ -263,7 +265,13 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
 
   // K slices of a launch of four-wave workgroups, as far as its hand-over buffer and its partial-norm slots reach
   auto wide_slices = [&](const Launch& c, int l) {
-    const int S = layer_wide_plan(c.a, bf16, c.delta, p.MB, p.sz_slice_part);
+    int S = 0;
+    if (query_device) {
+      S = layer_wide_plan(c.a, bf16, c.delta, p.MB, p.sz_slice_part);
+    } else if (slices > 0) {
+      S = layer_wide_most(c.a, bf16, c.delta, p.MB, p.sz_slice_part);
+      if (S > slices) S = slices;
+    }
     return S >= 2 && (pad64(D.dims[l + 1]) + 127) / 128 * S > norm_slots_bound(D.dims[l + 1], 1, p.MB) ? 1 : S;
   };
   std::vector<Launch> seq;
@@ -297,7 +305,7 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
       c.a.bj = make_job(0);
       c.base_layer = 0;
       c.bytes += layer_bytes(0);
-      const int wide = query_device ? wide_slices(c, 0) : 0;
+      const int wide = wide_slices(c, 0);
       if (wide >= 1) c.a.wide_nw = 4;
       if (wide >= 2) {
         c.a.tail_cand = m;
@@ -316,7 +324,7 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
     }
     // A launch whose last round of eight-wave workgroups would be partly empty runs the tiles of that round's
     // candidates, and the pass at x, in K slices at its end.
-    const int wide = query_device ? wide_slices(c, l) : 0;
+    const int wide = wide_slices(c, l);
     if (wide >= 1) c.a.wide_nw = 4;
     if (wide >= 2) {
       c.a.tail_cand = m;
@@ -373,7 +381,7 @@ std::vector<Launch> layer_sequence(const zeno_model* model, const Plan& p, const
     if (c.a.n_cand <= 0) continue;
     c.a.p_off = P;
     if (c.a.tail_slices >= 2) c.a.tail_p_off = c.a.tail_cand == m ? P : P + (pad64(D.dims[c.layer + 1]) + kMaxTileRows - 1) / kMaxTileRows;
-    P += query_device ? layer_tiles(c.a, bf16, c.delta, p.MB) : norm_slots_bound(D.dims[c.layer + 1], m, p.MB);
+    P += query_device || c.a.wide_nw > 0 ? layer_tiles(c.a, bf16, c.delta, p.MB) : norm_slots_bound(D.dims[c.layer + 1], m, p.MB);
   }
   for (Launch& c : seq)
     if (c.a.n_cand > 0) c.a.P = P;
@@ -869,12 +877,14 @@ zeno_status_t zeno_score_plan_check(const zeno_model_t* model, int32_t m, int32_
   static const int widths[3] = {1, 4, 8};
   for (int begin = 0; begin < n_r; begin += p.pass_rows) {
     const int rows = (n_r - begin) < p.pass_rows ? (n_r - begin) : p.pass_rows;
-    int P = 0;
-    const std::vector<Launch> seq = layer_sequence(model, p, fake, fake, model->d, m, 0.1f, ws, rows, begin == 0, &P,
-                                                   /*query_device=*/false);
-    for (const Launch& L : seq)
-      for (int NW : widths)
-        if (!launch_fits(p, L, NW, false)) return ZENO_ERR_WORKSPACE;
+    for (int slices = 0; slices <= 8; ++slices) {
+      int P = 0;
+      const std::vector<Launch> seq = layer_sequence(model, p, fake, fake, model->d, m, 0.1f, ws, rows, begin == 0, &P,
+                                                     /*query_device=*/false, slices);
+      for (const Launch& L : seq)
+        for (int NW : widths)
+          if ((L.a.wide_nw == 0 || L.a.wide_nw == NW) && !launch_fits(p, L, NW, false)) return ZENO_ERR_WORKSPACE;
+    }
   }
   return ZENO_OK;
 }

@@ -144,6 +144,8 @@ hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipSt
 bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB);  // run a.bj inside the candidates' launch?
 // K slices of all tiles of a launch of four-wave workgroups (1: whole tiles), 0: the launch keeps its shape
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget);
+// ... and the most it may be whatever the device (0: never such a launch)
+int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget);
 // K slices for the tiles of the last (n_cand - *n_main) candidates of an eight-wave launch, or 0: no sliced tail
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main);
 int layer_tiles(const LayerArgs& a, bool bf16, bool delta, int MB);   // partial-norm slots per candidate the launch fills

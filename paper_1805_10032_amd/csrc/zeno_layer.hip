@@ -195,6 +195,23 @@ static int one_wave_residents(bool bf16, bool delta, int MB, int k_waves) {
   return n < 1 ? 1 : n;
 }
 
+// 128-feature tiles of a launch.
+static long long wide_tiles(const LayerArgs& a) {
+  return (a.has_base ? job_tiles(a.bj, 128) : 0) + (long long)job_tiles(a.cj, 128) * a.n_cand;
+}
+
+// Most K slices a launch of four-wave workgroups may be cut into: every slice keeps two chunks of every job, and the hand-over
+// buffers hold all tiles.  0: the launch never takes such workgroups by layer_wide_plan.  No device is asked.
+int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
+  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  const long long tiles = wide_tiles(a);
+  if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles > kMaxSliceGroups) return 1;
+  const int chunks = a.cj.Kp >> 6, min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
+  const long long by_bytes = (long long)(budget / wide_slice_bytes(MB)) / tiles;
+  const long long most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
+  return most > by_bytes ? (by_bytes < 1 ? 1 : (int)by_bytes) : most < 1 ? 1 : (int)most;
+}
+
 // Would a candidate launch that is too small for wide workgroups be slower as one-wave tiles than as four-wave workgroups?
 // One wave per tile with K split over the waves of a workgroup copies the activations once per 32 features and holds so much
 // LDS for it that a compute unit runs one to four such workgroups; but it hands nothing over through memory, and as long as
@@ -250,19 +267,13 @@ static bool on_shifted_grid(const LayerArgs& a, bool bf16, bool delta, int MB) {
 // tiles; fp32 with the second product and four row blocks, which is single-buffered and has no slices: 24 -> 100 us).
 // Returns the slices (1: none) or 0 where the launch keeps its shape; budget: bytes for the partial accumulators.
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
-  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  const int most = layer_wide_most(a, bf16, delta, MB, budget);
+  if (most == 0) return 0;
   const bool whole_tiles = launch_nw_for(a) == 4;
   if (!whole_tiles && !one_wave_tiles_slower(a, bf16, delta, MB)) return 0;
-  const long long tiles = (a.has_base ? job_tiles(a.bj, 128) : 0) + (long long)job_tiles(a.cj, 128) * a.n_cand;
+  const long long tiles = wide_tiles(a);
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
-  const int min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
   const double hand_over = bf16 && !delta ? 6.0 : 4.0;
-  int most = 1;
-  if (a.slice_partials != nullptr && a.slice_counters != nullptr && tiles <= kMaxSliceGroups) {
-    most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
-    const long long by_bytes = (long long)(budget / ((size_t)4 * MB * 16 * 64 * sizeof(float))) / tiles;
-    if (most > by_bytes) most = by_bytes < 1 ? 1 : (int)by_bytes;
-  }
   if (whole_tiles) {
     const bool last_round_empty = (long long)job_tiles(a.cj, 128) * a.n_cand > n_cu && 3 * tiles <= 4 * n_cu;
     return last_round_empty && chunks >= 28 && most >= 3 && (delta || !bf16) && !on_shifted_grid(a, bf16, delta, MB) ? 3 : 0;

@@ -130,3 +130,22 @@ def test_the_hand_over_buffer_does_not_cost_a_call_the_static_scratch():
     # beyond it the buffer has its full size
     wide = B.ZenoModel([1024, 2048, 2048, 10], True, "softmax_ce", "fp32").workspace_bytes(20, 32)
     assert wide > B.STATIC_SCRATCH_BYTES + (8 << 20)
+
+
+@pytest.mark.parametrize("fwd", ["fp32", "bf16"])
+@pytest.mark.parametrize("n_r", [9, 40, 100, 200])
+def test_sliced_launches_stay_inside_their_slots(B, fwd, n_r):
+    """Launches cut into K slices hand over through a buffer whose size follows the model, the candidates and the static
+    array; the walk covers every number of slices, for one, two and four row blocks, one and two passes, on both sides of the
+    width where the plan stops fitting the array, and where the norms have a slot per slice."""
+    sizes = set()
+    for dims in ([1024, w, 512, 10] for w in range(128, 2561, 192)):
+        mdl = B.ZenoModel(dims, True, "softmax_ce", fwd)
+        for m in (5, 20, 43, 150):
+            assert mdl.plan_check(m, n_r) == 0, (dims, m)
+            sizes.add(mdl.workspace_bytes(m, n_r))
+    assert min(sizes) < B.STATIC_SCRATCH_BYTES < max(sizes)
+    for dims in ([3072, 128], [4096, 129, 65], [700, 1300, 100, 90, 10], [5000, 65]):
+        mdl = B.ZenoModel(dims, False, "softmax_ce", fwd)
+        for m in (1, 3, 63, 64, 255, 1024):
+            assert mdl.plan_check(m, n_r) == 0, (dims, m)
