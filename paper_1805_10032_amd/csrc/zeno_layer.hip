@@ -212,28 +212,37 @@ int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
   return most > by_bytes ? (by_bytes < 1 ? 1 : (int)by_bytes) : most < 1 ? 1 : (int)most;
 }
 
-// Would a candidate launch that is too small for wide workgroups be slower as one-wave tiles than as four-wave workgroups?
+// Would a candidate launch that is too small for wide workgroups be slower as one-wave tiles than as four-wave workgroups in
+// `slices` K slices, which take `cost` chunk times (see layer_wide_plan)?
 // One wave per tile with K split over the waves of a workgroup copies the activations once per 32 features and holds so much
 // LDS for it that a compute unit runs one to four such workgroups; but it hands nothing over through memory, and as long as
 // its workgroups are resident all at once it is the faster of the two.  Measured on 3692 random launches (K 64 to 4096, 66 to
 // 2048 features, 3 to 100 candidates; time as one-wave tiles / as four-wave workgroups, geometric mean, and how many of the latter
-// are more than 3 % slower):
+// are more than 3 % slower; by the rule as a whole 1.43, 27 of 832):
 //  * K split over waves, all resident at once: 0.93, 999 of 1473; more than one round of them: 1.44, 33 of 642.
+//    Two waves are few for a compute unit: where no more fit and the tile is not cut into K slices either, more than half a round is
+//    enough from 16 chunks on (1.41, 5 of 70).
 //  * No split (a K of the launch is short): a quarter of a round or less, or at most 20 MB of activations copied in all: 1.03, 393
-//    of 1314; beyond both: 1.22, 13 of 263.
-//  * Not where the pass at x has more than twice the candidates' chunks (it sets the pace, and four waves of one-wave
-//    tiles walk its K in parallel: 512 -> 1630, 8 candidates, fp32: 30 -> 54 us), and for layers without the second product in bf16,
-//    which wait for memory either way, only for four row blocks, or two beyond 1.25 rounds (the others: 1.10, 8 of 49).
-static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int MB) {
+//    of 1313; beyond both: 1.22, 13 of 264.  And, where only the pass at x has a short K, if the slices take less than 0.8 of the
+//    chunks that a one-wave tile walks: 1.52, none of 21.
+//  * Not where K is split over waves and the pass at x has more than twice the candidates' chunks: it sets the pace, and four waves
+//    of one-wave tiles walk its K in parallel (27 launches: 1.03, 10 of them slower, by up to 44 %: 512 -> 1630, 8 candidates,
+//    fp32: 30 -> 54 us; 37 without the split: 1.20, 3 slower).
+//  * Layers without the second product in bf16, which wait for memory either way, only for four row blocks, or two beyond 1.25
+//    rounds (the others: 1.10, 8 of 49).
+static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int MB, int slices, double cost) {
   const KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
-  const long long tiles = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)job_tiles(a.cj, 32) * a.n_cand;
-  const int chunks = a.cj.Kp >> 6;
-  if (a.has_base && (a.bj.Kp >> 6) > 2 * chunks) return false;
-  const long long workgroups = tiles * one.k_slices, round = (long long)compute_units() * one_wave_residents(bf16, delta, MB, one.k_waves);
+  const int chunks = a.cj.Kp >> 6, base_chunks = a.has_base ? a.bj.Kp >> 6 : 0;
+  if (one.k_waves > 1 && base_chunks > 2 * chunks) return false;
+  const long long base_tiles = a.has_base ? job_tiles(a.bj, 32) : 0, cand_tiles = (long long)job_tiles(a.cj, 32) * a.n_cand;
+  const long long workgroups = (base_tiles + cand_tiles) * one.k_slices;
+  const long long round = (long long)compute_units() * one_wave_residents(bf16, delta, MB, one.k_waves);
   if (bf16 && !delta && MB < 4) return MB == 2 && one.k_waves > 1 && 4 * workgroups > 5 * round;
+  if (one.k_waves == 2 && one.k_slices == 1 && chunks >= 16) return true;
   if (one.k_waves > 1) return workgroups > round;
-  const long long copied = tiles * chunks * (MB * 32LL * 64 * (bf16 ? 2 : 4) * (delta ? 2 : 1));
-  return 4 * workgroups > round && copied > 20000000;
+  if (slices >= 2 && cost < 0.8 * chunks / one.k_slices) return true;
+  const long long chunk_bytes = MB * 32LL * 64 * (bf16 ? 2 : 4) * (delta ? 2 : 1);
+  return 4 * workgroups > round && (cand_tiles * chunks + base_tiles * base_chunks) * chunk_bytes > 20000000;
 }
 
 // Does a launch of four-wave workgroups stream its rows on the shifted column grid, which its slices do not have?
@@ -270,7 +279,6 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
   const int most = layer_wide_most(a, bf16, delta, MB, budget);
   if (most == 0) return 0;
   const bool whole_tiles = launch_nw_for(a) == 4;
-  if (!whole_tiles && !one_wave_tiles_slower(a, bf16, delta, MB)) return 0;
   const long long tiles = wide_tiles(a);
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
   const double hand_over = bf16 && !delta ? 6.0 : 4.0;
@@ -287,7 +295,7 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
       best_cost = cost;
     }
   }
-  return 2 * tiles * best < n_cu ? 0 : best;
+  return 2 * tiles * best < n_cu || !one_wave_tiles_slower(a, bf16, delta, MB, best, best_cost) ? 0 : best;
 }
 
 // Sliced tail of a candidate launch of eight-wave workgroups.  When the workgroups of the launch do not fill their
