@@ -92,7 +92,7 @@ def _shapes_and_scores(name, dims, m, n_r, fwd, row_align):
     ([960, 520, 130], 17, 40, "bf16", 32, [1, 1]),       # with the pass at x, without and with the second product
     ([640, 449, 1], 30, 3, "bf16", 1, [1, 1]),
     ([320, 1600, 66], 8, 70, "fp32", 4, [1, 1]),         # the pass at x has five times the candidates' chunks, K split over waves
-    ([64, 2432, 1000], 5, 100, "bf16", 1, [4, 4]),       # 38 times, without the split: 26 MB of activations copied
+    ([64, 2432, 1000], 7, 100, "bf16", 1, [4, 4]),       # 38 times, without the split: 29 MB of activations copied
     ([64, 2432, 66], 7, 100, "bf16", 1, [1, 1]),         # 9 MB
     ([30, 897, 363, 244, 1], 17, 7, "bf16", 1, [1, 4, 1, 1]),   # no split for the pass at x, whose K is short: three slices
     ([1024, 600], 8, 100, "fp32", 1, [4]),               # two waves a tile, 171 tiles
