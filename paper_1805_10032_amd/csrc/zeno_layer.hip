@@ -88,8 +88,10 @@ int layer_nw(const LayerArgs& a, bool bf16, bool delta, int MB) { return nw_for(
 //    hand-over, cheap on an idle chip, take several microseconds each once the memory system is loaded).
 //  * One exception: a launch with somewhat more tiles than compute units whose wide workgroups fit only one
 //    per compute unit (four LDS layouts) would run a full round and a nearly empty one.  One-wave
-//    workgroups, two per tile, several per compute unit, run it in one round (3072 -> 512, 20 candidates:
-//    54 -> 48 us; three or four per tile: 53, 64 us).
+//    workgroups, two per tile, several per compute unit, run it in one round.  Most launches of more than 64
+//    features take four-wave workgroups instead (layer_wide_plan).  Score and update, without / with it: fp32, n_r = 32,
+//    2048 -> 64, m = 140 and 185: 81.1 / 77.1, 92.3 / 88.2 us; 3072 -> 50, m = 150: 102.5 / 99.3; 4096 -> 64, m = 130:
+//    102.0 / 98.4; with n_r = 64 103.3 / 98.0, 115.2 / 131.6 (the one shape that loses), 133.3 / 129.3, 140.4 / 136.1.
 KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device) {
   KPlan plan = {1, 1};
   if (NW != 1 || (!a.has_base && a.n_cand <= 0)) return plan;

@@ -120,3 +120,11 @@ def test_whole_four_wave_tiles_and_their_slices(dims, m, n_r, fwd, row_align, sl
     on the shifted column grid."""
     (r,) = _shapes_and_scores("whole", dims, m, n_r, fwd, row_align)
     assert (r["waves"], r["k_slices"], r["streaming"], r["tail_candidates"]) == (4, slices, streaming, m if slices > 1 else 0), r
+
+
+@pytest.mark.parametrize("m,k_slices", [(127, 1), (128, 2), (191, 2), (192, 1)])   # 256, 258, 384, 386 tiles of 32 features
+def test_two_one_wave_workgroups_per_tile(m, k_slices):
+    """At most 64 features and more tiles than compute units, up to one and a half times as many: two one-wave workgroups share
+    a tile, on both sides a workgroup of several waves has a tile to itself."""
+    (r,) = _shapes_and_scores("two", [2048, 64], m, 5, "fp32", 1)
+    assert (r["waves"], r["k_slices"]) == (1, k_slices), r
