@@ -114,7 +114,10 @@ void zeno_model_destroy(zeno_model_t* model);
  * W[c_out][ky][kx][c_in] row-major followed, if has_bias, by bias[c_out]; then the fully connected
  * W[fc_out][h * w * c], whose input is the last map flattened in (y, x, c) order, and its bias.
  * The batch's features are the images, [n_r x in_h * in_w * in_c].
- * Forward passes run in fp32 on the fp32 matrix cores; batches of more than 128 samples are
+ * Forward passes run at float32 accuracy: the fully connected layer and some convolutions on the fp32 matrix cores, the
+ * other convolutions on the bf16 ones, every operand split into three bf16 pieces (six piece products).  Infinities and NaN
+ * come out as in float32 arithmetic and finite operands stay finite; a sum that ends within 1 % of the largest float32 may
+ * overflow, and products of operands below about 1e-33 keep fewer than 24 bits.  Batches of more than 128 samples are
  * UNSUPPORTED by zeno_score for these models.  HOST struct, copied by zeno_cnn_model_create. */
 #define ZENO_MAX_CONV 8
 typedef struct {
@@ -255,17 +258,20 @@ zeno_status_t zeno_score_plan_check(const zeno_model_t* model, int32_t m, int32_
 typedef enum {
   ZENO_KERNEL_PACK = 0,       /* batch features into matrix-operand order */
   ZENO_KERNEL_LAYER_BASE = 1, /* one layer of the pass at x */
-  ZENO_KERNEL_LAYER_CAND = 2, /* one layer of the m candidate passes (streams G) */
-  ZENO_KERNEL_LOSS = 3,       /* per-sample loss differences */
+  ZENO_KERNEL_LAYER_CAND = 2, /* one layer of the m candidate passes (streams G); the whole score of a small model, which is
+                                 one launch (its record has layer 0 and no launch shape: waves = 0) */
+  ZENO_KERNEL_LOSS = 3,       /* per-sample loss differences; up to 16 classes and 64 samples also what COMBINE does */
   ZENO_KERNEL_COMBINE = 4,    /* mean, norm and the three-term score */
   ZENO_KERNEL_AVERAGE = 5,    /* selection + average of the chosen rows */
   ZENO_KERNEL_MEAN = 6,
   ZENO_KERNEL_MEDIAN = 7,
   ZENO_KERNEL_AVERAGE_UPDATE = 8, /* selection + average + x_next = x - gamma * average */
   ZENO_KERNEL_KRUM = 9,           /* Gram matrix + selection + copy of the chosen row */
-  ZENO_KERNEL_CONV_BASE = 10,     /* one convolution of the pass at x */
-  ZENO_KERNEL_CONV_CAND = 11,     /* one convolution of the m candidate passes */
-  ZENO_KERNEL_AUX = 12            /* fills, squared norms of the convolution kernels */
+  ZENO_KERNEL_CONV_BASE = 10,     /* first convolution of the pass at x, with the squared norms of the candidates' convolution
+                                     kernels and the clearing of the arrival counters; one or two launches */
+  ZENO_KERNEL_CONV_CAND = 11,     /* one convolution of the m candidate passes and the pass at x through the next one; one or
+                                     two launches */
+  ZENO_KERNEL_AUX = 12            /* fills of padded operands */
 } zeno_kernel_t;
 
 typedef struct {
@@ -284,10 +290,12 @@ typedef struct {
   int32_t merged;     /* 1: the launch carries the candidates' layer AND the pass at x through another layer */
   int32_t second;     /* 1: candidates with the second matrix product (layers after the first) */
   int32_t k_slices;   /* workgroups that share one feature tile and split the input width: 1..8 (launches of one-wave
-                         tiles: every tile; eight-wave launches: the tiles of the sliced tail, see tail_candidates) */
+                         tiles and four-wave launches: every tile; eight-wave launches: the tiles of the sliced tail, see
+                         tail_candidates) */
   int32_t candidates;      /* candidate launches: the rows of G the launch streams */
-  int32_t tail_candidates; /* eight-wave launches: the last so many candidates' tiles (and the pass at x, if merged)
-                              ran as k_slices K slices each at the end of the launch; 0: none */
+  int32_t tail_candidates; /* the last so many candidates' tiles (and the pass at x, if merged) ran as k_slices K slices each:
+                              in eight-wave launches at the end of the launch, behind whole tiles; in four-wave launches all
+                              of them (= candidates).  0: none */
 } zeno_profile_record_t;
 
 zeno_status_t zeno_profile_enable(int32_t enable);

@@ -33,11 +33,12 @@
 // input map the launch before completed.  The first launch carries the pass at x through convolution 0 and two
 // small jobs that nothing in it depends on (clearing the arrival counters of the fully connected layer, the squared norms of the
 // kernels; before: two launches).
-// Bound by latency: unit by unit a workgroup requests its values, waits for them (3000-5000 cycles), splits and
-// multiplies (2000-7000); the matrix cores are busy 15-40 % of the time.  Measured (MI355X, 32 x 32 x 3 images,
+// Bound by latency: unit by unit a workgroup requests its values, waits for them, splits and multiplies; the matrix cores are
+// busy for 5-26 % of the candidates' launches, the vector ALU for 17-54 % (counted).  Measured (MI355X, 32 x 32 x 3 images,
 // convolutions 32-32-64-64 with strides 1-2-1-2, m = 20) against conv_layer_kernel for everything: n_r = 32, candidates'
-// convolutions 109 / 134 / 251 / 120 -> 67 / 100 / 111 / 105 us, the whole step 682 -> 449 us; n_r = 4: 19 / 26 / 36 / 32 us and
-// 47 us for the pass at x -> 24 / 36 / 34 / 25 us including it and 12 us for its first convolution, the step 209 -> 157 us (both with the loss and the score in one launch).
+// convolutions 109 / 134 / 251 / 120 -> 65 / 99 / 110 / 115 us, the whole step 682 -> 454 us; n_r = 4: 19 / 26 / 36 / 32 us and
+// 47 us for the pass at x -> 22 (two launches) / 35 / 32 / 23 us including it and 9 us for its first convolution, the step 209 ->
+// 159 us (both with the loss and the score in one launch).
 //
 // conv_layer_kernel serves what the staging does not cover (rows of the map too wide for LDS) or covers badly (channels that
 // are no multiple of eight, see launch_conv): one wave owns 32 positions x 32

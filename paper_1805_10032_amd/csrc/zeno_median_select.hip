@@ -30,10 +30,12 @@
 // then serves the memory lines that unaligned rows make them share.
 //
 // Bound by vector instructions: 39 per key for m = 300 (4 to fetch and map it, 8 for the first four pivots, about 4 to 5
-// passes of 3 plus some 70 per pass and lane for the pivots), 81 % of the issue slots.  Measured (MI355X), normally
-// distributed columns, against the 32 counting passes over LDS that this kernel replaces: m = 129, d = 3.0 M 2970 -> 595 us;
-// m = 300, d = 1.58 M 2420 -> 577 us (3.3 TB/s); m = 512, d = 0.8 M 1820 -> 517 us; m = 1024, d = 0.4 M 2170 -> 569 us;
-// 40 % zeros: the same or less; values spread over sixty binades, where interpolation helps little: 1.8-2.5 x faster.
+// passes of 3 plus some 70 per pass and lane for the pivots; counted: 2.87e8 wave instructions for 4.7e8 keys), which take
+// 78 % of the issue slots of a call of 601 us.  Measured (MI355X; a worker's gradients around a common one, a third of the rows
+// faulty, calls in a series on buffers in turn): m = 300, d = 1.58 M 601 us (3.2 TB/s), where the 32 counting passes over LDS
+// that this kernel replaces took 2420; on repeated, normally distributed columns m = 129, d = 3.0 M 2970 -> 595 us; m = 512,
+// d = 0.8 M 1820 -> 517 us; m = 1024, d = 0.4 M 2170 -> 569 us; 40 % zeros: the same or less; values spread over sixty
+// binades, where interpolation helps little: 1.8-2.5 x faster.
 #include <limits.h>
 #include <stdint.h>
 

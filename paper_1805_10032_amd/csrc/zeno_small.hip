@@ -14,8 +14,8 @@
 // its feature (weights) or its sample (activations) per step of 8 k and feeds four instructions, the i-th of which contracts
 // k = i and 4 + i of the step; four steps are requested together, one group ahead.
 // Bound by latency: a dependent chain of round trips per layer.  Measured (MI355X, wall time of score and update in a series
-// of calls, m = 20, n_r = 32): 784 -> 10: 30.5 -> 25.3 us, 784 -> 64 -> 10: 72.0 -> 43.1, 64 -> 48 -> 40 -> 30 -> 20 -> 10:
-// 70.8 -> 40.1, 64 -> 1: 28.7 -> 20.6.
+// of calls, m = 20, n_r = 32, float32): 784 -> 10: 30.1 -> 24.2 us, 784 -> 64 -> 10: 72.0 -> 43.1, 64 -> 48 -> 40 -> 30 -> 20 -> 10:
+// 70.8 -> 40.1; m = 8, n_r = 16: 64 -> 1: 28.8 -> 18.9.
 #include <type_traits>
 
 #include "zeno_layer_impl.h"
