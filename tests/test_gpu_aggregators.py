@@ -166,6 +166,21 @@ def test_median_by_selection_at_the_edges_of_its_tiles(B, m, d):
     assert np.array_equal(med[ok], ref[ok])
 
 
+@pytest.mark.parametrize("m,d", [(130, 524_388), (320, 262_500), (1024, 66_000)])
+def test_median_by_selection_over_many_tiles(B, m, d):
+    """m > 128, more tiles than one generation of workgroups takes: every column near a multiple of 32 Ki columns and a random
+    choice of the others; clustered rows with a colluding block, so that waves mix columns found by their lists with others."""
+    g = torch.Generator(device="cuda").manual_seed(m)
+    G = torch.randn((m, d), generator=g, device="cuda") * 0.02 + torch.randn(d, generator=g, device="cuda") * 0.01
+    G[m // 8: m // 4] = -4.0 * G[m // 4:].mean(0)
+    G[m // 2, ::4099] = float("nan")
+    med = B.zeno_median(G)
+    edges = torch.arange(0, d, 32768)[:, None] + torch.arange(-40, 40)
+    cols = torch.cat([edges.flatten(), torch.randint(0, d, (5000,), generator=torch.Generator().manual_seed(m))]).clamp(0, d - 1)
+    ref = O.median(G[:, cols.cuda()].cpu().numpy()).astype(np.float32)
+    assert np.array_equal(med.cpu().numpy()[cols.numpy()], ref, equal_nan=True)
+
+
 def test_median_with_nonfinite_entries(B):
     m, d = 6, 200
     G = _rand_G(m, d, 9)
