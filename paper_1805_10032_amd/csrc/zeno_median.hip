@@ -1,9 +1,18 @@
 // Marginal median (Definition 4): for every coordinate j the one-dimensional
 // median of the m values G[0][j] .. G[m-1][j].  Each lane owns one column (four
 // adjacent ones up to m = 32, read with one 128-bit load per row) and keeps its
-// values in registers as order-preserving integer keys.
+// values in registers, as floats: v_min_f32 and v_max_f32 order them like integer
+// keys would, but for NaNs, which a wave that meets any (half an instruction per
+// value to see) replaces by infinities and counts.  Mapping every value to a key
+// took five instructions, of 23 per value in all for m = 100, and the selections of
+// the padding for every slot instead of the last few went through spilled scalar
+// registers.  Bound by memory up to m = 64 and by the vector instructions next to it
+// above (MI355X, before -> now: m = 100, d = 14.7 M 1294 -> 1118 us, 5.3 TB/s;
+// d = 4 M: m = 128 579 -> 428, m = 96 361 -> 288, m = 72 245 -> 213, m = 32 unchanged;
+// a fifth of the rows NaN: m = 100 1270 -> 1174, m = 20 unchanged).  Sorting as if there were
+// no NaNs and doing such columns again: the same without NaNs, 1.5 times as long with them.
 //
-// Only the middle of the order is needed, so no full sort is done: the m keys
+// Only the middle of the order is needed, so no full sort is done: the m values
 // are padded to a power of two P with equally many -inf and +inf keys (one more
 // +inf when P-m is odd), which pins the median to positions P/2-1 (m odd) or
 // P/2-1 and P/2 (m even) of the sorted order.  The two halves are sorted by
@@ -16,9 +25,8 @@
 // instantiated for Q real slots (m rounded up to a multiple of 4, of 8 above
 // 64), the lowest (P-Q)/2 positions of the first half hold the constant -inf key and the
 // highest (P-Q)/2 of the second half the constant +inf key.  An ascending
-// compare-exchange never moves those, so after unrolling the compiler deletes
-// every compare-exchange that touches one: the network that runs is the one for
-// Q keys, not for P.  The Q-m slots left over are padded at run time.
+// compare-exchange never moves those and is left out where it would touch one: the
+// network that runs is the one for Q keys, not for P.  The Q-m slots left over are padded at run time.
 #include <limits.h>
 #include <stdint.h>
 
@@ -30,20 +38,28 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// Monotone map float -> int32: integer order equals the total order
-// -inf < ... < -0 < +0 < ... < +inf < NaN (every NaN becomes the top key).
-__device__ inline int float_key(float f) {
-  int k = __float_as_int(f);
-  k ^= (k >> 31) & 0x7fffffff;
-  return (f != f) ? INT_MAX : k;
+// Minimum and maximum of two floats, neither of them a NaN: one instruction (the compiler would quiet its operands first).
+__device__ inline float min_of(float a, float b) {
+  float r;
+  asm("v_min_f32_e32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
 }
-__device__ inline float key_float(int k) {
-  return __int_as_float(k ^ ((k >> 31) & 0x7fffffff));
+__device__ inline float max_of(float a, float b) {
+  float r;
+  asm("v_max_f32_e32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+// Lanes in which a or b is a NaN.
+__device__ inline unsigned long long nan_lanes(float a, float b) {
+  unsigned long long r;
+  asm("v_cmp_u_f32_e64 %0, %1, %2" : "=s"(r) : "v"(a), "v"(b));
+  return r;
 }
 
-// Ascending odd-even merge sort of v[0..H), fully unrolled (H is a power of two).
-template <int H>
-__device__ inline void sort_regs(int (&v)[H]) {
+// Ascending odd-even merge sort of v[0..H), fully unrolled (H is a power of two).  The lowest LOW values are -inf and the
+// highest HIGH ones +inf: a compare-exchange that touches one of them would change nothing and is left out.
+template <int H, int LOW, int HIGH>
+__device__ inline void sort_regs(float (&v)[H]) {
 #pragma unroll
   for (int p = 1; p < H; p <<= 1) {
 #pragma unroll
@@ -53,10 +69,10 @@ __device__ inline void sort_regs(int (&v)[H]) {
 #pragma unroll
         for (int i = 0; i < k; ++i) {
           const int lo = i + j, hi = i + j + k;
-          if (hi < H && lo / (2 * p) == hi / (2 * p)) {
-            const int a = v[lo], c = v[hi];
-            v[lo] = a < c ? a : c;
-            v[hi] = a < c ? c : a;
+          if (hi < H - HIGH && lo >= LOW && lo / (2 * p) == hi / (2 * p)) {
+            const float a = v[lo], c = v[hi];
+            v[lo] = min_of(a, c);
+            v[hi] = max_of(a, c);
           }
         }
       }
@@ -70,6 +86,7 @@ __global__ __launch_bounds__(kThreads) void median_kernel(const float* __restric
   typedef float vf __attribute__((ext_vector_type(VEC)));
   constexpr int H = P / 2;
   constexpr int C = (P - Q) / 2;  // constant keys per half
+  constexpr int REAL = P >= 16 ? Q - (P > 64 ? 8 : 4) : P == 2 ? 0 : P / 2;   // m is larger than this (launch_q, launch_median)
   static_assert(P == Q || (Q % 4 == 0 && Q < P && Q > P / 2), "Q real slots, more than half of P");
   const long long stride = (long long)gridDim.x * kThreads;
   const long long n_vec = d / VEC;  // the launcher sends the d % VEC columns left over to the VEC = 1 kernel
@@ -78,9 +95,10 @@ __global__ __launch_bounds__(kThreads) void median_kernel(const float* __restric
     // Each lane owns VEC adjacent columns and reads them with one load per row.
     // All Q loads are issued back to back without branches: slot i reads row
     // min(i, m-1); the slots beyond m re-read the last row (cached) and are
-    // overwritten by padding keys.  The address is kept as a per-lane pointer that
+    // overwritten by padding values.  The address is kept as a per-lane pointer that
     // is stepped row by row (the empty asm keeps it in vector registers; a table
     // of wave-uniform row addresses would not fit the scalar register file).
+    vf res;
     const float* p = G + j * VEC;
     vf val[Q];
 #pragma unroll
@@ -90,38 +108,50 @@ __global__ __launch_bounds__(kThreads) void median_kernel(const float* __restric
       } else {
         val[i] = *reinterpret_cast<const vf*>(p);
       }
-      p += (i + 1 < m) ? ldg : 0;
+      p += (i < REAL || i + 1 < m) ? ldg : 0;
       asm volatile("" : "+v"(p));
     }
-    vf res;
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
-      int a[H], b[H];
-      auto slot_key = [&](int i) {
-        // run-time padding: the first f padding slots sort below everything, the rest above
-        return (i < m) ? float_key(val[i][v]) : (i - m < f ? INT_MIN : INT_MAX);
+      // The sorting instructions would drop NaNs: a wave that meets any puts infinities in their place; they are the last
+      // ranks of their column.
+      unsigned long long any_nan = 0;
+#pragma unroll
+      for (int i = 0; i < Q; i += 2) any_nan |= nan_lanes(val[i][v], val[i + 1][v]);
+      int nans = 0;
+      if (any_nan != 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) {
+          const bool nan = (__float_as_uint(val[i][v]) & 0x7fffffffu) > 0x7f800000u;
+          nans += nan && (i < REAL || i < m) ? 1 : 0;
+          val[i][v] = nan ? __builtin_inff() : val[i][v];
+        }
+      }
+      float a[H], b[H];
+      auto slot = [&](int i) {
+        // the first REAL slots always hold rows; run-time padding: the first f padding slots are lowest, the rest highest
+        return i < REAL || i < m ? val[i][v] : (i - m < f ? -__builtin_inff() : __builtin_inff());
       };
 #pragma unroll
-      for (int i = 0; i < C; ++i) a[i] = INT_MIN;
+      for (int i = 0; i < C; ++i) a[i] = -__builtin_inff();
 #pragma unroll
-      for (int i = 0; i < H - C; ++i) a[C + i] = slot_key(i);
+      for (int i = 0; i < H - C; ++i) a[C + i] = slot(i);
 #pragma unroll
-      for (int i = 0; i < C; ++i) b[H - 1 - i] = INT_MAX;
+      for (int i = 0; i < C; ++i) b[H - 1 - i] = __builtin_inff();
 #pragma unroll
-      for (int i = H - C; i < Q; ++i) b[i - (H - C)] = slot_key(i);
-      sort_regs<H>(a);
-      sort_regs<H>(b);
-      int lo = INT_MIN, hi = INT_MAX;
+      for (int i = H - C; i < Q; ++i) b[i - (H - C)] = slot(i);
+      sort_regs<H, C, 0>(a);
+      sort_regs<H, 0, C>(b);
+      float lo = min_of(a[C], b[H - 1 - C]), hi = max_of(a[C], b[H - 1 - C]);
 #pragma unroll
-      for (int i = 0; i < H; ++i) {
-        const int x = a[i], y = b[H - 1 - i];
-        const int mn = x < y ? x : y, mx = x < y ? y : x;
-        lo = lo > mn ? lo : mn;
-        hi = hi < mx ? hi : mx;
+      for (int i = C + 1; i < H; ++i) {
+        const float x = a[i], y = b[H - 1 - i];
+        lo = max_of(lo, min_of(x, y));
+        hi = min_of(hi, max_of(x, y));
       }
-      const float fa = key_float(lo), fb = key_float(hi);
-      const float r = (m & 1) ? fa : (float)(0.5 * ((double)fa + (double)fb));
-      res[v] = r;
+      const float none = __builtin_nanf("");
+      const float fa = (m - 1) / 2 + nans >= m ? none : lo, fb = m / 2 + nans >= m ? none : hi;
+      res[v] = (m & 1) ? fa : (float)(0.5 * ((double)fa + (double)fb));
     }
     *reinterpret_cast<vf*>(out + j * VEC) = res;
   }
