@@ -485,7 +485,27 @@ struct CnnPlan {
   size_t off_h0t, off_dt, dt_stride, sz_h0t;                                  // operands of the fully connected layer
   size_t off_wt, off_z0fc, off_dz, off_norm, off_diff, total;
   size_t off_slice_part, off_slice_cnt, sz_slice_cnt;   // K slices of the fully connected layer's launches
+  size_t least;                                         // bytes without the kernel fragments, which come last
+  size_t off_pack, pack_stride;                         // kernel fragments of the m candidates and of x
+  ConvPack pack[ZENO_MAX_CONV];
+  int pack_jobs;
+  bool fragments;                                       // the model takes kernel fragments and split maps where the workspace holds them
+  size_t off_hs[ZENO_MAX_CONV], off_ds[2], ds_stride;   // split maps: of the pass at x (input of l), of the candidates (bytes)
 };
+
+ConvLayer conv_layer(const zeno_model* mdl, int l) {
+  ConvLayer L;
+  L.w_off = mdl->conv_w_off[l];
+  L.b_off = mdl->conv_b_off[l];
+  L.Hin = mdl->map_h[l];
+  L.Win = mdl->map_w[l];
+  L.Cin = mdl->map_c[l];
+  L.Hout = mdl->map_h[l + 1];
+  L.Wout = mdl->map_w[l + 1];
+  L.Cout = mdl->map_c[l + 1];
+  L.stride = mdl->cnn.conv_stride[l];
+  return L;
+}
 
 CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
   CnnPlan p;
@@ -528,13 +548,41 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
   p.sz_slice_cnt = align_up((size_t)kMaxSliceGroups * sizeof(unsigned int), 256);
   p.off_slice_cnt = take(p.sz_slice_cnt);
   p.off_diff = take((size_t)m * n_r * sizeof(double));
+  p.least = off;
+  p.total = off;
+  p.fragments = true;
+  for (int l = 0; l < C; ++l) p.fragments = p.fragments && conv_takes_fragments(conv_layer(mdl, l), n_r, l);
+  if (!p.fragments) return p;
+  size_t max_split = 0;
+  for (int l = 0; l < C; ++l) {
+    const ConvLayer L = conv_layer(mdl, l);
+    ConvPack& k = p.pack[l];
+    k.w_off = L.w_off;
+    k.off = (long long)p.pack_stride;
+    k.Cin = L.Cin;
+    k.Cout = L.Cout;
+    k.groups = l > 0 ? 2 : 1;
+    k.steps = conv_steps(k.Cin);
+    k.sets = l > 0 ? 2 : 1;
+    k.first = p.pack_jobs;
+    p.pack_jobs += (k.Cout + 31) / 32 * k.steps;
+    p.pack_stride += (size_t)((k.Cout + 31) / 32) * k.steps * k.sets * kConvFragBytes;
+    if (l == 0) continue;
+    const size_t bytes = split_map_bytes(n_r * L.Hin * L.Win, L.Cin);
+    p.off_hs[l] = take(bytes);
+    if (bytes > max_split) max_split = bytes;
+  }
+  p.ds_stride = align_up(max_split, 256);
+  if (C > 1)
+    for (int i = 0; i < 2; ++i) p.off_ds[i] = take(p.ds_stride * m);
+  p.off_pack = take(p.pack_stride * (m + 1));
   p.total = off;
   return p;
 }
 
 zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const float* x, const float* G, int64_t ldg,
                                 int m, const zeno_batch_t* batch, float gamma, float rho, float* scores,
-                                unsigned char* ws, hipStream_t stream) {
+                                unsigned char* ws, size_t ws_bytes, hipStream_t stream) {
   const int C = p.n_conv, n_r = batch->n_r, N = mdl->cnn.fc_out;
   const float neg_inv_gamma = gamma > 0.f ? -1.0f / gamma : 0.f;
   double* norm_partials = reinterpret_cast<double*>(ws + p.off_norm);
@@ -550,29 +598,39 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     ZENO_TRY(launch_fill_zero(ws + p.off_h0t, p.sz_h0t, stream));
     ZENO_TRY(launch_fill_zero(ws + p.off_dt, p.dt_stride * m, stream));
   }
+  const bool fragments = p.fragments && ws_bytes >= p.total;
   auto conv_job = [&](int l, bool cand) {
     ConvJob j;
     std::memset(&j, 0, sizeof(j));
-    j.L.w_off = mdl->conv_w_off[l];
-    j.L.b_off = mdl->conv_b_off[l];
-    j.L.Hin = mdl->map_h[l];
-    j.L.Win = mdl->map_w[l];
-    j.L.Cin = mdl->map_c[l];
-    j.L.Hout = mdl->map_h[l + 1];
-    j.L.Wout = mdl->map_w[l + 1];
-    j.L.Cout = mdl->map_c[l + 1];
-    j.L.stride = mdl->cnn.conv_stride[l];
+    j.L = conv_layer(mdl, l);
     j.H0_in = l == 0 ? batch->features : reinterpret_cast<const float*>(ws + p.off_h0[l - 1]);
     j.Z0 = reinterpret_cast<float*>(ws + p.off_z0[l]);
+    j.pack_off = p.pack[l].off;
+    j.pack_sets = p.pack[l].sets;
     j.tiled_out = l + 1 == C;
     j.Kp_fc = p.Kp;
+    if (fragments && l > 0) j.H0_in = reinterpret_cast<const float*>(ws + p.off_hs[l]);
+    j.split_out = fragments && l + 1 < C;
     if (!cand) {
+      if (j.split_out) {
+        j.out = reinterpret_cast<float*>(ws + p.off_hs[l + 1]);
+        return j;
+      }
       j.out = l + 1 == C ? reinterpret_cast<float*>(ws + p.off_h0t) : reinterpret_cast<float*>(ws + p.off_h0[l]);
       return j;
     }
     if (l > 0) {
       j.D_in = reinterpret_cast<const float*>(ws + p.off_d[(l - 1) & 1]);
       j.D_in_stride = (long long)p.d_stride;
+      if (fragments) {
+        j.D_in = reinterpret_cast<const float*>(ws + p.off_ds[(l - 1) & 1]);
+        j.D_in_stride = (long long)(p.ds_stride / sizeof(float));
+      }
+    }
+    if (j.split_out) {
+      j.out = reinterpret_cast<float*>(ws + p.off_ds[l & 1]);
+      j.out_stride = (long long)(p.ds_stride / sizeof(float));
+      return j;
     }
     j.out = reinterpret_cast<float*>(l + 1 == C ? ws + p.off_dt : ws + p.off_d[l & 1]);
     j.out_stride = l + 1 == C ? (long long)(p.dt_stride / sizeof(float)) : (long long)p.d_stride;
@@ -626,6 +684,11 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
   conv.n_r = n_r;
   conv.gamma = gamma;
   conv.neg_inv_gamma = neg_inv_gamma;
+  if (fragments) {
+    conv.pack = ws + p.off_pack;
+    conv.pack_stride = (long long)p.pack_stride;
+    conv.pack_x = m;
+  }
   {
     ConvArgs a = conv;
     a.has_base = 1;
@@ -640,6 +703,11 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     a.aux_norm = norm_partials;
     a.aux_zero = ws + p.off_slice_cnt;
     a.aux_zero16 = (int)(p.sz_slice_cnt / 16);
+    if (conv.pack != nullptr) {
+      a.pack_jobs = p.pack_jobs;
+      a.pack_layers = C;
+      std::memcpy(a.pack_layer, p.pack, sizeof(p.pack));
+    }
     ProfScope ps(ZENO_KERNEL_CONV_BASE, 0, conv_flops(0), stream);
     ZENO_TRY(launch_conv(a, stream));
   }
@@ -832,9 +900,9 @@ zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float*
   if (model->kind == 1) {
     if (batch->n_r > kMaxPassRows) return ZENO_ERR_UNSUPPORTED;
     const CnnPlan cp = make_cnn_plan(model, m, batch->n_r);
-    if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < cp.total) return ZENO_ERR_WORKSPACE;
+    if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < cp.least) return ZENO_ERR_WORKSPACE;
     return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, reinterpret_cast<unsigned char*>(workspace),
-                             reinterpret_cast<hipStream_t>(stream_));
+                             workspace_bytes, reinterpret_cast<hipStream_t>(stream_));
   }
   const Plan p = make_plan(model, m, batch->n_r);
   if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < p.total) return ZENO_ERR_WORKSPACE;
@@ -849,10 +917,11 @@ zeno_status_t zeno_score_static(const zeno_model_t* model, const float* x, const
   if (model->kind == 1) {
     if (batch->n_r > kMaxPassRows) return ZENO_ERR_UNSUPPORTED;
     const CnnPlan cp = make_cnn_plan(model, m, batch->n_r);
-    if (cp.total > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;
+    if (cp.least > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;
     unsigned char* cws = nullptr;
     if (static_scratch(&cws) != hipSuccess) return ZENO_ERR_DEVICE;
-    return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, cws, reinterpret_cast<hipStream_t>(stream_));
+    return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, cws, (size_t)ZENO_STATIC_SCRATCH_BYTES,
+                             reinterpret_cast<hipStream_t>(stream_));
   }
   const Plan p = make_plan(model, m, batch->n_r);
   if (p.total > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;

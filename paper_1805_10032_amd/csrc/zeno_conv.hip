@@ -13,9 +13,32 @@
 // convolution).  Nothing is unfolded in memory: a patch element (position, tap, channel) is
 // gathered from the NHWC map when a lane needs it as a matrix operand.
 //
-// conv_wide_kernel, conv_deep_kernel.  The products run on the bf16 matrix cores at float32 accuracy: both operands are
-// split into three bf16 pieces each and the six leading piece products accumulated (zeno_split.h).  Six
-// v_mfma_f32_32x32x16_bf16 cover 16 channels of a tap in 192 cycles where v_mfma_f32_32x32x2_f32 needs 512.  A wave
+// conv_packed_kernel (models whose first convolution has up to eight input channels and all others a multiple of eight above).  The
+// products run on the bf16 matrix cores at float32 accuracy: both operands are split into three bf16 pieces each and the six
+// leading piece products accumulated (zeno_split.h).  Six v_mfma_f32_32x32x16_bf16 cover 16 channels of a tap in 192 cycles
+// where v_mfma_f32_32x32x2_f32 needs 512.  K is walked in units of (map of x or of the candidate) x (sixteen input channels), nine
+// steps (taps) each.
+//  * Every value is split once.  The first launch writes the kernels, U and W - gamma U, as fragments in the lanes' order (ConvPack),
+//    and every launch writes its results as a split map for the next (split_map_bytes), from which a workgroup copies the
+//    pixels that its positions touch, border included, straight to LDS: a copy is 64 lanes x 16 bytes without registers, the pixels'
+//    offsets are computed once per workgroup.  With stride 2 even and odd pixels of a row are kept apart in LDS, so that
+//    consecutive positions read consecutive 16-byte pieces.
+//  * A workgroup is eight waves with 64 positions x 32 channels, which share out the steps, three fragments requested ahead, and
+//    add their accumulators through LDS in a fixed order; two workgroups per compute unit.  The candidates' first convolution
+//    (conv_flat) gives each wave 32 positions of its own instead.
+//  * The launch of the candidates' convolution l carries the pass at x through convolution l + 1.
+// Bound by latency: of the 12 us of a workgroup of 32 -> 32 channels with stride 2 (m = 20, n_r = 32) 2.6 pass before its first
+// copies are requested, 1.9 and 2.4 waiting for the copies of its two stages, 1.2 in the products of each, 2 in the sums and results.
+// Measured (MI355X, 32 x 32 x 3 images, convolutions 32-32-64-64 with strides 1-2-1-2, m = 20) against the kernels below:
+// n_r = 32, candidates' convolutions 66 + 10 / 99 + 10 / 109 + 13 / 115 us with the pass at x on its own -> 64 / 79 / 109 / 65, fragments 6 us,
+// the step 455 -> 343 us; n_r = 4: 35 / 33 / 23 us for the last three -> 18 / 20 / 17, the step 159 -> 118 us.  Over 40 random models of
+// this kind 1.08 times as fast, single convolutions on 8 x 8 images as fast as before.  Models with other convolutions among them
+// would alternate between both kinds of maps, in two launches for every one: 0.81-0.95 on 14 of 18, so they keep to the
+// kernels below.  Splitting the maps in the workgroup that stages them (four times as many vector instructions): 106 us where the copies
+// take 79; persistent workgroups that request the next candidate's copies ahead of their sums: 95.
+//
+// conv_wide_kernel, conv_deep_kernel (other models, the pass at x through the first convolution, and calls whose workspace holds no
+// fragments).  The same products; a wave
 // owns 32 output channels x 32 PB output positions (kernel values as the first operand, so that an accumulator lane is
 // a position and its registers are channels).  K is walked in units of (map of x or of the candidate) x (chunk of eight or
 // sixteen input channels), nine taps each; channels are padded to the chunk, and chunks of eight take two taps per step.
@@ -56,6 +79,270 @@
 namespace zeno {
 
 namespace {
+
+__global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, long long n16) {
+  const uint4 z = {0u, 0u, 0u, 0u};
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (long long)gridDim.x * blockDim.x) p[i] = z;
+}
+
+// Results of one accumulator value: position r, channel fo (pre-activation of the pass at x, or its change).
+__device__ inline float conv_result(const ConvArgs& a, bool cand, float val, float z0) {
+  if (!cand) return relu_nan(val);
+  const float dz = -a.gamma * val;
+  const float hr = relu_nan(z0 + dz);
+  // relu(z0 + dz) - relu(z0) without cancellation
+  const float dd = (z0 > 0.f) ? ((dz < -z0) ? -z0 : dz) : hr;
+  return dd * a.neg_inv_gamma;
+}
+
+constexpr int kDeepSteps = 36;   // matrix steps a workgroup of conv_deep_kernel stages at once
+
+// v / d for 0 <= v, v d < 2^32, with the multiplier ceil(2^32 / d) (0: d = 1)
+__device__ inline unsigned div_magic(unsigned v, unsigned magic) { return magic == 0u ? v : __umulhi(v, magic); }
+
+// Value `off` bytes behind a wave-uniform base (32-bit offsets: one register, no address arithmetic).
+template <typename V>
+__device__ inline V at_byte(const float* __restrict__ base, unsigned off) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
+}
+// Eight consecutive floats `off` bytes behind base, of which the first nv exist (nv may be <= 0); the others are zero.  No
+// branches, so that the loads of many items are in flight together: what does not exist is read from where something does.
+// FULL: the channels are a multiple of eight, so that all eight exist or none.
+template <bool FULL>
+__device__ inline void load8(const float* __restrict__ base, unsigned off, int nv, f32x4& v0, f32x4& v1) {
+  const unsigned p = nv > 0 ? off : 0u;
+  if (FULL) {
+    v0 = at_byte<f32x4_a4>(base, p);
+    v1 = at_byte<f32x4_a4>(base, p + 16u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v0[i] = nv > 0 ? v0[i] : 0.f;
+      v1[i] = nv > 0 ? v1[i] : 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v0[i] = at_byte<float>(base, p + (i < nv ? 4u * i : 0u));
+      v1[i] = at_byte<float>(base, p + (4 + i < nv ? 4u * (4 + i) : 0u));
+      v0[i] = i < nv ? v0[i] : 0.f;
+      v1[i] = 4 + i < nv ? v1[i] : 0.f;
+    }
+  }
+}
+
+// Squared norm of coordinates [0, count) of candidate s, piece blk of n_blocks, in a fixed order: a thread sums its
+// strided elements in float64, lanes by xor-shuffle tree, waves in order.
+__device__ void sumsq_piece(const ConvArgs& a, int s, int blk, double* red) {
+  const int T = blockDim.x;
+  const long long lo = a.aux_count * blk / a.aux_pieces, hi = a.aux_count * (blk + 1) / a.aux_pieces;
+  const float* __restrict__ row = a.G + (long long)s * a.ldg;
+  double t = 0.0;
+  long long i = lo + threadIdx.x;
+  for (; i + 7 * T < hi; i += 8 * T) {            // eight loads in flight
+    float v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = row[i + q * T];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t += (double)v[q] * (double)v[q];
+  }
+  for (; i < hi; i += T) t += (double)row[i] * (double)row[i];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double sum = 0.0;
+    for (int w = 0; w < T / 64; ++w) sum += red[w];
+    a.aux_norm[(long long)s * a.aux_P + a.aux_p_off + blk] = sum;
+  }
+}
+
+__device__ inline void store_split(unsigned char* o, unsigned piece_stride, const f32x4& v0, const f32x4& v1) {
+  const Split8 p = split8(v0, v1);
+  *reinterpret_cast<bf16x8*>(o) = p.h;
+  *reinterpret_cast<bf16x8*>(o + piece_stride) = p.m;
+  *reinterpret_cast<bf16x8*>(o + 2 * piece_stride) = p.l;
+}
+// Fragments of job `job` (channel tile, step of some layer) of source s, one wave: U and, for candidates of a layer with a
+// second product, W - gamma U.
+__device__ void pack_fragment(const ConvArgs& a, int s, int job) {
+  int l = 0;
+  while (l + 1 < a.pack_layers && job >= a.pack_layer[l + 1].first) ++l;
+  const ConvPack& L = a.pack_layer[l];
+  const int lane = threadIdx.x & 63, n = lane & 31, h = lane >> 5;
+  const int ct = (job - L.first) / L.steps, i = (job - L.first) % L.steps;
+  const int per_unit = L.groups == 2 ? 9 : 5, unit = i / per_unit, st = i - unit * per_unit;
+  const int tap = L.groups == 2 ? st : 2 * st + h, c = unit * 8 * L.groups + (L.groups == 2 ? 8 * h : 0);
+  const int f = ct * 32 + n;
+  const int nv = tap < 9 && f < L.Cout ? L.Cin - c : 0;
+  const float* __restrict__ P = (s == a.pack_x ? a.x : a.G + (long long)s * a.ldg) + L.w_off;
+  const bool second = L.sets == 2 && s != a.pack_x;
+  const unsigned off = 4u * (unsigned)((f * 9 + tap) * L.Cin + c);
+  f32x4 u0, u1, w0, w1;
+  if (L.Cin % 8 == 0) {
+    load8<true>(P, off, nv, u0, u1);
+    if (second) load8<true>(a.x + L.w_off, off, nv, w0, w1);
+  } else {
+    load8<false>(P, off, nv, u0, u1);
+    if (second) load8<false>(a.x + L.w_off, off, nv, w0, w1);
+  }
+  unsigned char* o = a.pack + (long long)s * a.pack_stride + L.off + (long long)(ct * L.sets * L.steps + i) * kConvFragBytes + lane * 16;
+  store_split(o, 1024, u0, u1);
+  if (second) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      u0[e] = __builtin_fmaf(-a.gamma, u0[e], w0[e]);
+      u1[e] = __builtin_fmaf(-a.gamma, u1[e], w1[e]);
+    }
+    store_split(o + (long long)L.steps * kConvFragBytes, 1024, u0, u1);
+  }
+}
+
+constexpr unsigned kNoPixel = 0xffffffffu;
+
+// What a workgroup that owns NP consecutive output positions of a job needs of its input map, in rows of the map
+// with a border of one zero pixel all around: sample smp's row iy is border row smp * (Hin + 2) + iy + 1.
+template <int NP>
+struct ConvTile {
+  unsigned rows, r_first, v_first, Wv, Hv, plane;
+  int pixels;
+  __device__ inline ConvTile(const ConvArgs& a, const ConvJob& J, int pt) {
+    const ConvLayer& L = J.L;
+    rows = (unsigned)(a.n_r * L.Hout * L.Wout);
+    Wv = (unsigned)L.Win + 2u;
+    Hv = (unsigned)L.Hin + 2u;
+    r_first = (unsigned)pt * NP;
+    const unsigned r_last = (r_first + NP < rows ? r_first + NP : rows) - 1u;
+    v_first = border_row(J, r_first);
+    pixels = (int)((border_row(J, r_last) + 3u - v_first) * Wv);
+    plane = (unsigned)(pixels | 1) * 16u;         // bytes of one (piece, group of eight channels) plane
+  }
+  // topmost border row position r reads
+  __device__ inline unsigned border_row(const ConvJob& J, unsigned r) const {
+    const unsigned orow = div_magic(r, J.magic_wout), smp = div_magic(orow, J.magic_hout);
+    return smp * Hv + (orow - smp * (unsigned)J.L.Hout) * (unsigned)J.L.stride;
+  }
+  // byte offset inside a plane of the pixel that position r's first tap reads
+  __device__ inline unsigned first_pixel(const ConvJob& J, unsigned r) const {
+    const unsigned rc = r < rows ? r : rows - 1u;
+    const unsigned ox = rc - div_magic(rc, J.magic_wout) * (unsigned)J.L.Wout;
+    return ((border_row(J, rc) - v_first) * Wv + ox * (unsigned)J.L.stride) * 16u;
+  }
+  // position of the input map that border row `row` of the tile holds at column vx; behind the last one where it is border
+  __device__ inline unsigned pixel_position(const ConvArgs& a, const ConvJob& J, unsigned row, unsigned vx) const {
+    const ConvLayer& L = J.L;
+    const unsigned v = v_first + row, smp = __umulhi(v, J.magic_hv), vy = v - smp * Hv;
+    const bool inside = (vx - 1u < (unsigned)L.Win) & (vy - 1u < (unsigned)L.Hin) & (smp < (unsigned)a.n_r);
+    const unsigned at = (smp * (unsigned)L.Hin + vy - 1u) * (unsigned)L.Win + (vx - 1u);
+    return inside ? at : (unsigned)(a.n_r * L.Hin * L.Win);
+  }
+  // byte offset of border pixel px inside the input map, or kNoPixel where it is border
+  __device__ inline unsigned pixel_offset(const ConvArgs& a, const ConvJob& J, unsigned px) const {
+    const ConvLayer& L = J.L;
+    const unsigned vr = div_magic(px, J.magic_wv), vx = px - vr * Wv, v = v_first + vr;
+    const unsigned smp = div_magic(v, J.magic_hv), vy = v - smp * Hv;
+    const bool inside = (vx - 1u < (unsigned)L.Win) & (vy - 1u < (unsigned)L.Hin) & (smp < (unsigned)a.n_r);
+    return inside ? ((smp * (unsigned)L.Hin + vy - 1u) * (unsigned)L.Win + (vx - 1u)) * (unsigned)L.Cin * 4u : kNoPixel;
+  }
+};
+// eight channels from c on of the pixel at byte offset off
+template <bool FULL>
+__device__ inline void load_pixel(const float* __restrict__ map, unsigned off, int c, int Cin, f32x4& v0, f32x4& v1) {
+  load8<FULL>(map, off + 4u * (unsigned)c, off != kNoPixel ? Cin - c : 0, v0, v1);
+}
+
+// 64 lanes x 16 bytes, each lane's from its own address, to consecutive bytes of LDS from `to` (wave-uniform) on; no registers.
+__device__ inline void copy_to_lds(const unsigned char* from, unsigned char* to) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
+                                   (__attribute__((address_space(3))) void*)to, 16, 0, 0);
+}
+__device__ inline Split8 load_split(const unsigned char* o, unsigned piece_stride) {
+  Split8 p;
+  p.h = *reinterpret_cast<const bf16x8*>(o);
+  p.m = *reinterpret_cast<const bf16x8*>(o + piece_stride);
+  p.l = *reinterpret_cast<const bf16x8*>(o + 2 * piece_stride);
+  return p;
+}
+
+// Four consecutive channels fo .. fo + 3 (a multiple of four) of position r of a split map with C (a multiple of eight) channels.
+__device__ inline void store_split_out(float* out, unsigned C, f32x4 v, unsigned r, unsigned rows, unsigned fo) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const unsigned groups = (C + 15u) / 16u * 2u, map_plane = (rows + 1u) * 16u;
+  if (r >= rows || fo >= 8u * groups) return;
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  if (fo >= C) v = zero;
+  const Split8 p = split8(v, zero);
+  unsigned char* o = reinterpret_cast<unsigned char*>(out) + (unsigned long long)((fo >> 4) * 6u + ((fo >> 3) & 1u)) * map_plane +
+                     r * 16u + (fo & 4u) * 2u;
+  const unsigned long long piece = 2ull * map_plane;
+  auto low = [](const bf16x8& x) { return __builtin_bit_cast(u32x2, __builtin_shufflevector(x, x, 0, 1, 2, 3)); };
+  *reinterpret_cast<u32x2*>(o) = low(p.h);
+  *reinterpret_cast<u32x2*>(o + piece) = low(p.m);
+  *reinterpret_cast<u32x2*>(o + 2 * piece) = low(p.l);
+  if (r + 1u == rows) {                           // the position of zeros behind the last one
+    const u32x2 z = {0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 3; ++i) *reinterpret_cast<u32x2*>(o + 16 + i * piece) = z;
+  }
+}
+
+// What four consecutive channels fo .. fo + 3 of one position r need besides their sums, requested ahead of them.
+struct ConvOut {
+  f32x4 bias, z0;
+};
+__device__ inline ConvOut conv_out_request(const ConvArgs& a, const ConvJob& J, bool cand, const float* __restrict__ P, unsigned r,
+                                           unsigned rows, unsigned fo) {
+  const ConvLayer& L = J.L;
+  const unsigned C = (unsigned)L.Cout, row = (r < rows ? r : rows - 1u) * C;
+  ConvOut o;
+  o.bias = o.z0 = f32x4{0.f, 0.f, 0.f, 0.f};
+  if ((C & 3u) == 0u) {                           // the four channels exist together and lie 16-byte aligned
+    const unsigned fc = fo < C ? fo : 0u;
+    if (L.b_off >= 0) o.bias = at_byte<f32x4_a4>(P + L.b_off, 4u * fc);
+    if (cand) o.z0 = at_byte<f32x4>(J.Z0, 4u * (row + fc));
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const unsigned fc = fo + i < C ? fo + i : 0u;
+      if (L.b_off >= 0) o.bias[i] = at_byte<float>(P + L.b_off, 4u * fc);
+      if (cand) o.z0[i] = at_byte<float>(J.Z0, 4u * (row + fc));
+    }
+  }
+  return o;
+}
+__device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool cand, int s, const ConvOut& o, const f32x4& sum,
+                                      unsigned r, unsigned rows, unsigned fo) {
+  const unsigned C = (unsigned)J.L.Cout, row = r * C;
+  f32x4 val, res;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    val[i] = sum[i] + o.bias[i];
+    res[i] = conv_result(a, cand, val[i], o.z0[i]);
+  }
+  float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
+  if (J.split_out) {
+    if (r < rows && fo < C && !cand) *reinterpret_cast<f32x4*>(J.Z0 + (row + fo)) = val;
+    store_split_out(out, C, res, r, rows, fo);
+    return;
+  }
+  if (r >= rows || fo >= C) return;
+  unsigned smp = 0, k = row + fo;
+  if (J.tiled_out) {                              // column of the fully connected layer's operand
+    smp = div_magic(div_magic(r, J.magic_wout), J.magic_hout);
+    k -= smp * (unsigned)(J.L.Hout * J.L.Wout) * C;
+  }
+  if ((C & 3u) == 0u) {
+    if (!cand) *reinterpret_cast<f32x4*>(J.Z0 + (row + fo)) = val;
+    *reinterpret_cast<f32x4*>(out + (J.tiled_out ? tiled_index<false>((int)smp, (int)k, J.Kp_fc) : (long long)k)) = res;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (fo + i < C) {
+        if (!cand) J.Z0[row + fo + i] = val[i];
+        out[J.tiled_out ? tiled_index<false>((int)smp, (int)k + i, J.Kp_fc) : (long long)(k + i)] = res[i];
+      }
+  }
+}
 
 // TW = 3: three waves share one tile and take one kernel row (ky) each; their accumulators are added through
 // LDS in the fixed order (0 + 1) + 2 and wave 0 finishes the tile.  Used when the launch has too few tiles
@@ -164,6 +451,15 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
   // accumulator element j of lane (n, h): position r (this lane's), output channel ft*32 + 8 (j/4) + 4 h + j%4
   if (!r_ok) return;
   float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
+  if (J.split_out) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const unsigned fo = (unsigned)(ft * 32 + 8 * q + 4 * h);
+      const f32x4 sum = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+      conv_out_store(a, J, cand, s, conv_out_request(a, J, cand, P, (unsigned)r, (unsigned)rows, fo), sum, (unsigned)r, (unsigned)rows, fo);
+    }
+    return;
+  }
 #pragma unroll
   for (int j = 0; j < 16; ++j) {
     const int fo = ft * 32 + 8 * (j >> 2) + 4 * h + (j & 3);
@@ -187,195 +483,6 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
     } else {
       out[r * L.Cout + fo] = res;
     }
-  }
-}
-
-__global__ __launch_bounds__(256) void fill_zero_kernel(uint4* __restrict__ p, long long n16) {
-  const uint4 z = {0u, 0u, 0u, 0u};
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n16; i += (long long)gridDim.x * blockDim.x) p[i] = z;
-}
-
-// Results of one accumulator value: position r, channel fo (pre-activation of the pass at x, or its change).
-__device__ inline float conv_result(const ConvArgs& a, bool cand, float val, float z0) {
-  if (!cand) return relu_nan(val);
-  const float dz = -a.gamma * val;
-  const float hr = relu_nan(z0 + dz);
-  // relu(z0 + dz) - relu(z0) without cancellation
-  const float dd = (z0 > 0.f) ? ((dz < -z0) ? -z0 : dz) : hr;
-  return dd * a.neg_inv_gamma;
-}
-
-constexpr int kDeepSteps = 36;   // matrix steps a workgroup of conv_deep_kernel stages at once
-
-// v / d for 0 <= v, v d < 2^32, with the multiplier ceil(2^32 / d) (0: d = 1)
-__device__ inline unsigned div_magic(unsigned v, unsigned magic) { return magic == 0u ? v : __umulhi(v, magic); }
-
-// Value `off` bytes behind a wave-uniform base (32-bit offsets: one register, no address arithmetic).
-template <typename V>
-__device__ inline V at_byte(const float* __restrict__ base, unsigned off) {
-  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + off);
-}
-// Eight consecutive floats `off` bytes behind base, of which the first nv exist (nv may be <= 0); the others are zero.  No
-// branches, so that the loads of many items are in flight together: what does not exist is read from where something does.
-// FULL: the channels are a multiple of eight, so that all eight exist or none.
-template <bool FULL>
-__device__ inline void load8(const float* __restrict__ base, unsigned off, int nv, f32x4& v0, f32x4& v1) {
-  const unsigned p = nv > 0 ? off : 0u;
-  if (FULL) {
-    v0 = at_byte<f32x4_a4>(base, p);
-    v1 = at_byte<f32x4_a4>(base, p + 16u);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v0[i] = nv > 0 ? v0[i] : 0.f;
-      v1[i] = nv > 0 ? v1[i] : 0.f;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      v0[i] = at_byte<float>(base, p + (i < nv ? 4u * i : 0u));
-      v1[i] = at_byte<float>(base, p + (4 + i < nv ? 4u * (4 + i) : 0u));
-      v0[i] = i < nv ? v0[i] : 0.f;
-      v1[i] = 4 + i < nv ? v1[i] : 0.f;
-    }
-  }
-}
-
-// Squared norm of coordinates [0, count) of candidate s, piece blk of n_blocks, in a fixed order: a thread sums its
-// strided elements in float64, lanes by xor-shuffle tree, waves in order.
-__device__ void sumsq_piece(const ConvArgs& a, int s, int blk, double* red) {
-  const int T = blockDim.x;
-  const long long lo = a.aux_count * blk / a.aux_pieces, hi = a.aux_count * (blk + 1) / a.aux_pieces;
-  const float* __restrict__ row = a.G + (long long)s * a.ldg;
-  double t = 0.0;
-  long long i = lo + threadIdx.x;
-  for (; i + 7 * T < hi; i += 8 * T) {            // eight loads in flight
-    float v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) v[q] = row[i + q * T];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t += (double)v[q] * (double)v[q];
-  }
-  for (; i < hi; i += T) t += (double)row[i] * (double)row[i];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = t;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double sum = 0.0;
-    for (int w = 0; w < T / 64; ++w) sum += red[w];
-    a.aux_norm[(long long)s * a.aux_P + a.aux_p_off + blk] = sum;
-  }
-}
-
-constexpr unsigned kNoPixel = 0xffffffffu;
-
-// What a workgroup that owns NP consecutive output positions of a job needs of its input map, in rows of the map
-// with a border of one zero pixel all around: sample smp's row iy is border row smp * (Hin + 2) + iy + 1.
-template <int NP>
-struct ConvTile {
-  unsigned rows, r_first, v_first, Wv, Hv, plane;
-  int pixels;
-  __device__ inline ConvTile(const ConvArgs& a, const ConvJob& J, int pt) {
-    const ConvLayer& L = J.L;
-    rows = (unsigned)(a.n_r * L.Hout * L.Wout);
-    Wv = (unsigned)L.Win + 2u;
-    Hv = (unsigned)L.Hin + 2u;
-    r_first = (unsigned)pt * NP;
-    const unsigned r_last = (r_first + NP < rows ? r_first + NP : rows) - 1u;
-    v_first = border_row(J, r_first);
-    pixels = (int)((border_row(J, r_last) + 3u - v_first) * Wv);
-    plane = (unsigned)(pixels | 1) * 16u;         // bytes of one (piece, group of eight channels) plane
-  }
-  // topmost border row position r reads
-  __device__ inline unsigned border_row(const ConvJob& J, unsigned r) const {
-    const unsigned orow = div_magic(r, J.magic_wout), smp = div_magic(orow, J.magic_hout);
-    return smp * Hv + (orow - smp * (unsigned)J.L.Hout) * (unsigned)J.L.stride;
-  }
-  // byte offset inside a plane of the pixel that position r's first tap reads
-  __device__ inline unsigned first_pixel(const ConvJob& J, unsigned r) const {
-    const unsigned rc = r < rows ? r : rows - 1u;
-    const unsigned ox = rc - div_magic(rc, J.magic_wout) * (unsigned)J.L.Wout;
-    return ((border_row(J, rc) - v_first) * Wv + ox * (unsigned)J.L.stride) * 16u;
-  }
-  // byte offset of border pixel px inside the input map, or kNoPixel where it is border
-  __device__ inline unsigned pixel_offset(const ConvArgs& a, const ConvJob& J, unsigned px) const {
-    const ConvLayer& L = J.L;
-    const unsigned vr = div_magic(px, J.magic_wv), vx = px - vr * Wv, v = v_first + vr;
-    const unsigned smp = div_magic(v, J.magic_hv), vy = v - smp * Hv;
-    const bool inside = (vx - 1u < (unsigned)L.Win) & (vy - 1u < (unsigned)L.Hin) & (smp < (unsigned)a.n_r);
-    return inside ? ((smp * (unsigned)L.Hin + vy - 1u) * (unsigned)L.Win + (vx - 1u)) * (unsigned)L.Cin * 4u : kNoPixel;
-  }
-};
-// eight channels from c on of the pixel at byte offset off
-template <bool FULL>
-__device__ inline void load_pixel(const float* __restrict__ map, unsigned off, int c, int Cin, f32x4& v0, f32x4& v1) {
-  load8<FULL>(map, off + 4u * (unsigned)c, off != kNoPixel ? Cin - c : 0, v0, v1);
-}
-
-__device__ inline void store_split(unsigned char* o, unsigned piece_stride, const f32x4& v0, const f32x4& v1) {
-  const Split8 p = split8(v0, v1);
-  *reinterpret_cast<bf16x8*>(o) = p.h;
-  *reinterpret_cast<bf16x8*>(o + piece_stride) = p.m;
-  *reinterpret_cast<bf16x8*>(o + 2 * piece_stride) = p.l;
-}
-__device__ inline Split8 load_split(const unsigned char* o, unsigned piece_stride) {
-  Split8 p;
-  p.h = *reinterpret_cast<const bf16x8*>(o);
-  p.m = *reinterpret_cast<const bf16x8*>(o + piece_stride);
-  p.l = *reinterpret_cast<const bf16x8*>(o + 2 * piece_stride);
-  return p;
-}
-
-// What four consecutive channels fo .. fo + 3 of one position r need besides their sums, requested ahead of them.
-struct ConvOut {
-  f32x4 bias, z0;
-};
-__device__ inline ConvOut conv_out_request(const ConvArgs& a, const ConvJob& J, bool cand, const float* __restrict__ P, unsigned r,
-                                           unsigned rows, unsigned fo) {
-  const ConvLayer& L = J.L;
-  const unsigned C = (unsigned)L.Cout, row = (r < rows ? r : rows - 1u) * C;
-  ConvOut o;
-  o.bias = o.z0 = f32x4{0.f, 0.f, 0.f, 0.f};
-  if ((C & 3u) == 0u) {                           // the four channels exist together and lie 16-byte aligned
-    const unsigned fc = fo < C ? fo : 0u;
-    if (L.b_off >= 0) o.bias = at_byte<f32x4_a4>(P + L.b_off, 4u * fc);
-    if (cand) o.z0 = at_byte<f32x4>(J.Z0, 4u * (row + fc));
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const unsigned fc = fo + i < C ? fo + i : 0u;
-      if (L.b_off >= 0) o.bias[i] = at_byte<float>(P + L.b_off, 4u * fc);
-      if (cand) o.z0[i] = at_byte<float>(J.Z0, 4u * (row + fc));
-    }
-  }
-  return o;
-}
-__device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool cand, int s, const ConvOut& o, const f32x4& sum,
-                                      unsigned r, unsigned rows, unsigned fo) {
-  const unsigned C = (unsigned)J.L.Cout, row = r * C;
-  f32x4 val, res;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    val[i] = sum[i] + o.bias[i];
-    res[i] = conv_result(a, cand, val[i], o.z0[i]);
-  }
-  if (r >= rows || fo >= C) return;
-  float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
-  unsigned smp = 0, k = row + fo;
-  if (J.tiled_out) {                              // column of the fully connected layer's operand
-    smp = div_magic(div_magic(r, J.magic_wout), J.magic_hout);
-    k -= smp * (unsigned)(J.L.Hout * J.L.Wout) * C;
-  }
-  if ((C & 3u) == 0u) {
-    if (!cand) *reinterpret_cast<f32x4*>(J.Z0 + (row + fo)) = val;
-    *reinterpret_cast<f32x4*>(out + (J.tiled_out ? tiled_index<false>((int)smp, (int)k, J.Kp_fc) : (long long)k)) = res;
-  } else {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (fo + i < C) {
-        if (!cand) J.Z0[row + fo + i] = val[i];
-        out[J.tiled_out ? tiled_index<false>((int)smp, (int)k + i, J.Kp_fc) : (long long)(k + i)] = res[i];
-      }
   }
 }
 
@@ -646,8 +753,177 @@ __device__ __forceinline__ void conv_deep(const ConvArgs& a, const ConvJob& J, b
   conv_out_store(a, J, cand, s, o, part[0], r_out, T.rows, fo);
 }
 
+// The waves' accumulators of 64 positions x 32 channels, added in wave order; wave kw then finishes quarter kw % 4 of block kw / 4.
+template <int KW, int PB>
+__device__ __forceinline__ f32x4 sum_waves(const f32x16 (&lead)[PB], const f32x16 (&rest)[PB], unsigned char* lds, int kw, int lane) {
+  // quarter q of a block (registers 4q .. 4q + 3) is one 16-byte piece per lane
+  f32x4* red = reinterpret_cast<f32x4*>(lds);
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      f32x4 v;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = join_split(lead[pb][4 * q + i], rest[pb][4 * q + i]);
+      red[((kw * PB + pb) * 4 + q) * 64 + lane] = v;
+    }
+  __syncthreads();
+  f32x4 part[KW];
+#pragma unroll
+  for (int w = 0; w < KW; ++w) part[w] = red[((w * PB + (kw >> 2)) * 4 + (kw & 3)) * 64 + lane];
+#pragma unroll
+  for (int w = 1; w < KW; ++w) part[0] += part[w];
+  return part[0];
+}
+
+// Kernel fragments and split maps from memory: 64 positions x 32 channels, eight waves that share out the matrix steps.
+__device__ __forceinline__ void conv_packed(const ConvArgs& a, const ConvJob& J, bool cand, int s, int tile, unsigned char* lds) {
+  constexpr int KW = 8, PB = 2, NP = 32 * PB, STEPS = 9, NA = 3;
+  const ConvLayer& L = J.L;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ctiles = (L.Cout + 31) / 32;
+  const int pt = (int)div_magic((unsigned)tile, J.magic_ctiles), ct = tile - pt * ctiles;
+  const float* __restrict__ P = cand ? a.G + (long long)s * a.ldg : a.x;
+  const bool second = cand && J.D_in != nullptr;
+  const unsigned char* H0 = reinterpret_cast<const unsigned char*>(J.H0_in);
+  const unsigned char* D = reinterpret_cast<const unsigned char*>(J.D_in) + (second ? (long long)s * J.D_in_stride * 4 : 0);
+  const ConvTile<NP> T(a, J, pt);
+  // With stride 2 a row of the staged map holds its even pixels first, then the odd ones, so that consecutive positions read
+  // consecutive pieces.
+  const unsigned Wv = T.Wv, even = L.stride == 2 ? (Wv + 1u) / 2u : Wv;
+  const unsigned px_runs = ((unsigned)T.pixels + 63u) / 64u, plane = px_runs * 1024u, unit_bytes = 6u * plane;
+  unsigned pix[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb) {
+    const unsigned at = T.first_pixel(J, T.r_first + (unsigned)(32 * pb + n)) / 16u, row = div_magic(at, J.magic_wv);
+    pix[pb] = (row * Wv + (at - row * Wv) / (unsigned)L.stride) * 16u;
+  }
+  const int chunks = (L.Cin + 15) / 16, units = chunks * (second ? 2 : 1);
+  const unsigned positions = (unsigned)(a.n_r * L.Hin * L.Win), map_plane = (positions + 1u) * 16u;
+  const unsigned char* __restrict__ frags = a.pack + (long long)(cand ? s : a.pack_x) * a.pack_stride + J.pack_off +
+                                            (long long)ct * J.pack_sets * chunks * STEPS * kConvFragBytes + lane * 16;
+
+  // offsets of the tile's pixels inside a plane of the map, once for all planes
+  unsigned* offs = reinterpret_cast<unsigned*>(lds + J.offs_at);
+  for (unsigned at = (unsigned)tid; at < px_runs * 64u; at += 64u * KW) {
+    const unsigned row = __umulhi(at, J.magic_wv), k = at - row * Wv, odd = k >= even ? 1u : 0u;
+    offs[at] = T.pixel_position(a, J, row, ((k - (odd ? even : 0u)) << (L.stride - 1)) + odd) * 16u;
+  }
+  f32x16 lead[PB], rest[PB];
+#pragma unroll
+  for (int pb = 0; pb < PB; ++pb)
+#pragma unroll
+    for (int j = 0; j < 16; ++j) lead[pb][j] = rest[pb][j] = 0.f;
+
+#pragma unroll 1
+  for (int u0 = 0; u0 < units; u0 += J.stage_units) {
+    const int nu = units - u0 < J.stage_units ? units - u0 : J.stage_units;
+    const int steps = nu * STEPS;
+    const unsigned char* fr = frags + (long long)(u0 * STEPS + kw) * kConvFragBytes;
+    __syncthreads();                                               // the offsets are there; everyone is done with the units before
+    // copies of 64 pixels of one (unit, piece, group) plane each, the planes of a run of pixels one after the other
+    const int planes = 6 * nu, copies = planes * (int)px_runs, of_x = 6 * (chunks - u0);   // planes from of_x on are the candidate's
+    const unsigned char* from_x = H0 + (long long)(6 * u0) * map_plane;
+    const unsigned char* from_cand = D + (long long)(6 * (u0 - chunks)) * map_plane;
+    int run = 0, q = copies * kw / KW, left = copies * (kw + 1) / KW - q;
+    while (q >= planes) {
+      q -= planes;
+      ++run;
+    }
+#pragma unroll 1
+    while (left > 0) {
+      const unsigned off = offs[run * 64 + lane];
+      const int end = q + left < planes ? q + left : planes;
+      left -= end - q;
+#pragma unroll 2
+      for (; q < end; ++q)
+        copy_to_lds((q < of_x ? from_x : from_cand) + (unsigned long long)(unsigned)q * map_plane + off,
+                    lds + (unsigned)q * plane + (unsigned)run * 1024u);
+      q = 0;
+      ++run;
+    }
+    // a wave's fragments three steps at a time, the first ones together with the copies
+    Split8 A[NA];
+    auto request = [&](int i0) __attribute__((always_inline)) {
+#pragma unroll
+      for (int j = 0; j < NA; ++j) A[j] = load_split(i0 + j * KW < steps ? fr + j * (KW * kConvFragBytes) : frags, 1024);
+      fr += NA * KW * kConvFragBytes;
+    };
+    request(kw);
+    __builtin_amdgcn_s_waitcnt(0x0f70);                            // vmcnt(0)
+    __syncthreads();                                               // the staged units are complete
+#pragma unroll 1
+    for (int i0 = kw; i0 < steps; i0 += NA * KW) {
+      if (i0 > kw) request(i0);
+#pragma unroll
+      for (int j = 0; j < NA; ++j) {
+        const int i = i0 + j * KW;
+        if (i < steps) {
+          const int ul = i / STEPS, tap = i - ul * STEPS, ky = (tap * 11) >> 5, kx = tap - 3 * ky;
+          const unsigned toff = (unsigned)(ky * (int)Wv) + (L.stride == 2 ? (kx == 1 ? even : (unsigned)kx >> 1) : (unsigned)kx);
+          const unsigned char* m = lds + (unsigned)ul * unit_bytes + (unsigned)h * plane + toff * 16u;
+#pragma unroll
+          for (int pb = 0; pb < PB; ++pb) mfma_split(A[j], load_split(m + pix[pb], 2 * plane), lead[pb], rest[pb]);
+        }
+      }
+    }
+  }
+  const unsigned r_out = T.r_first + (unsigned)(32 * (kw >> 2) + n), fo = (unsigned)(ct * 32 + 8 * (kw & 3) + 4 * h);
+  const ConvOut o = conv_out_request(a, J, cand, P, r_out, T.rows, fo);
+  __syncthreads();                                                 // the staged units are no longer needed
+  const f32x4 sum = sum_waves<KW, PB>(lead, rest, lds, kw, lane);
+  conv_out_store(a, J, cand, s, o, sum, r_out, T.rows, fo);
+}
+
+// The candidates' first convolution, at most eight input channels, kernel fragments from memory: eight waves with 32 positions x
+// 32 channels each, which all take every step.
+__device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, int s, int tile, unsigned char* lds) {
+  constexpr int THREADS = 512, NP = 256, STEPS = 5;
+  const ConvLayer& L = J.L;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ctiles = (L.Cout + 31) / 32;
+  const int pt = (int)div_magic((unsigned)tile, J.magic_ctiles), ct = tile - pt * ctiles;
+  const ConvTile<NP> T(a, J, pt);
+  const unsigned plane = T.plane, r = T.r_first + (unsigned)(32 * wave + n), pix = T.first_pixel(J, r);
+  const unsigned char* __restrict__ frags = a.pack + (long long)s * a.pack_stride + J.pack_off + (long long)ct * STEPS * kConvFragBytes + lane * 16;
+#pragma unroll 1
+  for (int i = tid; i < T.pixels; i += THREADS) {
+    f32x4 v[2];
+    load_pixel<false>(J.H0_in, T.pixel_offset(a, J, (unsigned)i), 0, L.Cin, v[0], v[1]);
+    store_split(lds + (unsigned)i * 16u, plane, v[0], v[1]);
+  }
+  f32x16 lead, rest;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) lead[j] = rest[j] = 0.f;
+  Split8 A = load_split(frags, 1024);
+  __syncthreads();
+#pragma unroll 1
+  for (int i = 0; i < STEPS; ++i) {
+    const Split8 next = load_split(frags + (i + 1 < STEPS ? i + 1 : 0) * kConvFragBytes, 1024);
+    const int tap = 2 * i + h, ky = (tap * 11) >> 5;
+    const unsigned toff = (unsigned)(ky * (int)T.Wv + tap - 3 * ky) * 16u;
+    // (the tenth tap meets zero kernel values and reads pixel 0, which is border: 0 x inf would be NaN)
+    mfma_split(A, load_split(lds + (tap > 8 ? 0u : toff + pix), plane), lead, rest);
+    A = next;
+  }
+  const float* __restrict__ P = a.G + (long long)s * a.ldg;
+  const unsigned fo = (unsigned)(ct * 32 + 4 * h);
+  ConvOut o[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) o[q] = conv_out_request(a, J, true, P, r, T.rows, fo + 8u * q);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    f32x4 sum;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) sum[i] = join_split(lead[4 * q + i], rest[4 * q + i]);
+    conv_out_store(a, J, true, s, o[q], sum, r, T.rows, fo + 8u * q);
+  }
+}
+
 // Blocks: [tiles of the pass at x] [tiles x candidates, candidate fastest] [squared norms: pieces x candidates] [one that
-// clears the counters].  Returns whether the block is one of the small jobs, which it then has done.
+// clears the counters] [kernel fragments].  Returns whether the block is one of the small jobs, which it then has done.
 __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& is_base, int& s, int& tile) {
   int b = blockIdx.x;
   is_base = b < a.base_blocks;
@@ -656,14 +932,17 @@ __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& i
     b -= a.cand_blocks;
     if (b < a.aux_pieces * a.aux_m) {
       sumsq_piece(a, b / a.aux_pieces, b % a.aux_pieces, reinterpret_cast<double*>(lds));
-    } else {
+    } else if (b == a.aux_pieces * a.aux_m) {
       const uint4 z = {0u, 0u, 0u, 0u};
       for (int i = threadIdx.x; i < a.aux_zero16; i += blockDim.x) reinterpret_cast<uint4*>(a.aux_zero)[i] = z;
+    } else {
+      const int waves = blockDim.x >> 6, job = (b - a.aux_pieces * a.aux_m - 1) * waves + (threadIdx.x >> 6);
+      if (job < a.pack_jobs * (a.pack_x + 1)) pack_fragment(a, job / a.pack_jobs, job % a.pack_jobs);
     }
     return true;
   }
-  s = is_base ? 0 : b % a.n_cand;
-  tile = is_base ? b : b / a.n_cand;
+  tile = is_base ? b : (int)div_magic((unsigned)b, a.magic_cand);
+  s = is_base ? 0 : b - tile * a.n_cand;
   return false;
 }
 
@@ -685,6 +964,16 @@ __global__ __launch_bounds__(512, 2) void conv_deep_kernel(const ConvArgs a) {
   conv_deep<CG, FULL>(a, is_base ? a.bj : a.cj, !is_base, s, tile, conv_lds);
 }
 
+__global__ __launch_bounds__(512, 4) void conv_packed_kernel(const ConvArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
+  bool is_base;
+  int s, tile;
+  if (conv_block(a, conv_lds, is_base, s, tile)) return;
+  const ConvJob J = is_base ? a.bj : a.cj;
+  if (J.flat) conv_flat(a, J, s, tile, conv_lds);
+  else conv_packed(a, J, !is_base, s, tile, conv_lds);
+}
+
 // ---- host side
 constexpr long long kConvLdsMost = 160 * 1024;
 constexpr long long kConvLdsTwo = 80 * 1024;      // two workgroups per compute unit
@@ -693,6 +982,12 @@ unsigned magic_for(long long d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) 
 
 // Most border rows that np consecutive positions touch.
 long long most_border_rows(const ConvLayer& L, int np) {
+  if (np % L.Wout == 0) {
+    // tiles start at the beginning of a row: whole rows, and whole samples or parts of one where these numbers divide each other
+    const long long n = np / L.Wout;
+    if (L.Hout % n == 0) return (n - 1) * L.stride + 3;
+    if (n % L.Hout == 0) return (n / L.Hout - 1) * (L.Hin + 2) + (long long)(L.Hout - 1) * L.stride + 3;
+  }
   const long long out_rows = (np - 1 + L.Wout - 1) / L.Wout + 1;                 // output rows they can lie in
   const long long samples = (out_rows - 2 + L.Hout) / L.Hout;                    // sample boundaries among these
   const long long skip = (long long)L.Hin + 2 - (long long)L.Hout * L.stride;    // border rows beyond the stride at a boundary
@@ -713,11 +1008,13 @@ bool sizes_fit(const ConvLayer& L, int n_r, int np) {
 // LDS bytes of a unit of a job with `groups` groups of eight channels.
 long long wide_bytes(const ConvLayer& L, int np, int wc, int groups) { return map_bytes(L, np, groups) + kernel_bytes(wc, groups); }
 long long deep_bytes(const ConvLayer& L, int groups) { return map_bytes(L, 64, groups); }
+// LDS bytes of a unit of a split map (whole runs of 64 pixels)
+long long split_unit_bytes(const ConvLayer& L) { return (most_border_rows(L, 64) * (L.Win + 2) + 63) / 64 * 1024 * 6; }
 bool full_groups(const ConvLayer& L) { return L.Cin % 8 == 0; }
 
 // What both kinds of launches prepare for each job; job_lds gives a job's LDS bytes and sets its groups and stage_units.
 template <typename F>
-hipError_t plan_tiles(ConvArgs& a, int np, int wc, F job_lds, long long* lds, long long* total) {
+hipError_t plan_tiles(ConvArgs& a, int np_most, int wc, F job_lds, long long* lds, long long* total) {
   long long blocks[2] = {0, 0};
   for (int q = 0; q < 2; ++q) {
     ConvJob& j = q == 0 ? a.bj : a.cj;
@@ -727,15 +1024,21 @@ hipError_t plan_tiles(ConvArgs& a, int np, int wc, F job_lds, long long* lds, lo
     j.magic_hout = magic_for(L.Hout);
     j.magic_wv = magic_for(L.Win + 2);
     j.magic_hv = magic_for(L.Hin + 2);
+    j.magic_ctiles = magic_for((L.Cout + 31) / 32);
     const long long need = job_lds(j, q == 1 && j.D_in != nullptr ? 2 : 1);
     if (need > *lds) *lds = need;
+    const int np = np_most > 0 ? np_most : j.flat ? 256 : 64;
     const long long rows = (long long)a.n_r * L.Hout * L.Wout;
     blocks[q] = (rows + np - 1) / np * ((L.Cout + 32 * wc - 1) / (32 * wc)) * (q == 1 ? a.n_cand : 1);
   }
-  *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0);
+  const int waves = wc > 0 && np_most == 128 ? 4 : 8;
+  *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0) +
+           ((long long)a.pack_jobs * (a.pack_x + 1) + waves - 1) / waves;
   if (*total > (1ll << 30) || *lds > kConvLdsMost) return hipErrorInvalidValue;
   a.base_blocks = (int)blocks[0];
   a.cand_blocks = (int)blocks[1];
+  a.magic_cand = magic_for(a.n_cand);
+
   return hipSuccess;
 }
 
@@ -786,7 +1089,29 @@ hipError_t launch_deep_as(int groups, bool full, const ConvArgs& a, hipStream_t 
 // itself and test it (us per candidates' launch with the pass at x through the next layer, gathered / staged: 33 -> 33 on 16x16,
 // stride 2, m = 39, n_r = 4: 30 / 56; on 14x14, m = 20, n_r = 32: 73 / 129; 20 -> 20 on 28x28, stride 1, m = 30, n_r = 48:
 // 476 / 514; only the same with stride 2 is the other way round: 193 / 162).
+bool few_channels(const ConvLayer& L) { return (L.Cin <= 2 && L.Cout <= 16) || (L.Cin <= 4 && L.Cout <= 8); }
 bool gathered(const ConvLayer& L) { return !full_groups(L) && L.Cin > 8; }
+
+hipError_t launch_packed(ConvArgs a, hipStream_t stream) {
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_packed_kernel),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsTwo);
+  if (attr_err != hipSuccess) return attr_err;
+  long long lds = 8 * 8192, total = 0;                             // at least the accumulators of eight waves
+  const hipError_t e = plan_tiles(a, 0, 1, [](ConvJob& j, int maps) {
+    j.flat = j.L.Cin <= 8;
+    if (j.flat) return map_bytes(j.L, 256, 1);
+    const int chunks = (j.L.Cin + 15) / 16;
+    const long long unit = split_unit_bytes(j.L);
+    long long n = (kConvLdsTwo - unit / 24) / unit;
+    j.stage_units = (int)(n > chunks * maps ? chunks * maps : n);
+    const long long staged = j.stage_units * unit;
+    j.offs_at = (int)(staged > 8 * 8192 ? staged : 8 * 8192);
+    return j.offs_at + unit / 24;
+  }, &lds, &total);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(conv_packed_kernel, dim3((unsigned)total), dim3(512), (size_t)lds, stream, a);
+  return hipGetLastError();
+}
 
 hipError_t launch_gather(const ConvArgs& a, hipStream_t stream) {
   long long blocks = 0, tiles = 0;                 // of the wider job, of all sources
@@ -809,6 +1134,7 @@ hipError_t launch_gather(const ConvArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
+  if (a.pack != nullptr && a.pack_jobs == 0) return launch_packed(a, stream);
   // the job that dominates the launch decides its shape
   const ConvLayer& L = a.n_cand > 0 ? a.cj.L : a.bj.L;
   const int sources = a.n_cand > 0 ? a.n_cand : 1;
@@ -839,15 +1165,14 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   // whole steps: up to 2 -> 16 or 4 -> 8 channels 1.04 on 21 random models, 19 of them slower as wide tiles, by up to 20 %; the
   // others 0.89 on 135).  The pass at x alone is staged up to 512 tiles of 64 positions x 32 channels, the small jobs of its launch
   // need as long (staged / gathered: 0.97 below 256 tiles, 1.01 on 38 up to 512, 1.02 on 32 beyond, 22 of them slower).
-  const bool few = (L.Cin <= 2 && L.Cout <= 16) || (L.Cin <= 4 && L.Cout <= 8);
-  const bool gather = gathered(L) || (!full && (a.n_cand > 0 ? !wide || few : (rows + 63) / 64 * ctiles >= 512));
+  const bool gather = gathered(L) || (!full && (a.n_cand > 0 ? !wide || few_channels(L) : (rows + 63) / 64 * ctiles >= 512));
   if (a.n_cand > 0 && a.has_base && !gather && (wide || gathered(a.bj.L) || (full && !full_groups(a.bj.L)))) {
     // The pass at x on its own: next to wide tiles its few workgroups, each with all of K to walk, would be the last ones to end
     // by far (n_r = 32, convolution 3 behind the candidates' convolution 2: 148 us together, 103 + 11 us apart); and one
     // staging kernel runs both jobs, so the channels of either have to be whole groups if the candidates' are.
     ConvArgs b = a, c = a;
     b.n_cand = 0;
-    c.has_base = c.aux_m = c.aux_pieces = c.aux_zero16 = 0;
+    c.has_base = c.aux_m = c.aux_pieces = c.aux_zero16 = c.pack_jobs = 0;
     const hipError_t e = launch_conv(b, stream);
     return e != hipSuccess ? e : launch_conv(c, stream);
   }
@@ -858,12 +1183,17 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   const int g = pick_groups([&](const ConvLayer& l, int gr) { return deep_bytes(l, gr); }, 64);
   if (g > 0 && !gather) return launch_deep_as(g, full, a, stream);
   ConvArgs r = a;
-  r.aux_pieces = r.aux_m = r.aux_zero16 = 0;
+  r.aux_pieces = r.aux_m = r.aux_zero16 = r.pack_jobs = 0;
   const hipError_t e = launch_gather(r, stream);
-  if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0)) return e;
+  if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0 && a.pack_jobs <= 0)) return e;
   r = a;                                           // the small jobs alone
   r.has_base = r.n_cand = 0;
   return launch_wide<1, true, 1, 4, 1>(r, stream);
+}
+
+bool conv_takes_fragments(const ConvLayer& L, int n_r, int index) {
+  if (index == 0) return L.Cin <= 8 && !few_channels(L) && sizes_fit(L, n_r, 256) && map_bytes(L, 256, 1) <= kConvLdsTwo;
+  return L.Cin > 8 && full_groups(L) && sizes_fit(L, n_r, 64) && split_unit_bytes(L) / 24 * 25 <= kConvLdsTwo;
 }
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {

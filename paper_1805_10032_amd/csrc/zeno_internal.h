@@ -216,12 +216,26 @@ struct ConvJob {
   float* Z0;              // [rows x Cout] pre-activations at x: written by the pass at x, read by the candidates
   float* out;             // pass at x: relu map; candidates: candidate 0's scaled change of the output map
   long long out_stride;   // floats between candidates (candidates' pass)
+  int split_out;          // 1: out is a split map (below)
   int tiled_out;          // 1: out is the operand of the fully connected layer: rows = samples, k = (position, channel),
   int Kp_fc;              //    in matrix-operand order of padded width Kp_fc
-  // filled in by the launcher: (map, channel chunk) units staged at once, multipliers of the quick divisions
-  int stage_units;
-  unsigned magic_wout, magic_hout, magic_wv, magic_hv;
+  long long pack_off;     // byte offset of the layer's kernel fragments inside a source's
+  int pack_sets;          // 2, or 1 for the first convolution
+  // filled in by the launcher: (map, channel chunk) units staged at once, groups of eight channels a unit has, multipliers
+  // of the quick divisions
+  int stage_units, flat, offs_at;
+  unsigned magic_wout, magic_hout, magic_wv, magic_hv, magic_ctiles;
 };
+// Kernels of one convolution as the matrix instructions take them: fragments of 32 output channels x 16 k (a step), split into
+// three bf16 pieces of 64 lanes x 16 bytes.  A source's fragments of a layer: [channel tile][U, then W - gamma U][step][piece][lane].
+struct ConvPack {
+  long long w_off, off;   // of the kernels inside a parameter vector; byte offset inside a source's fragments
+  int Cin, Cout, groups;  // groups of eight channels per unit: 2 (a step is a tap of 16 channels) or 1 (two taps of eight)
+  int steps, sets;        // steps of one set; 2 sets, or 1 for the first convolution (and W alone for the pass at x)
+  int first;              // jobs (channel tile, step) of the layers before
+};
+constexpr int kConvFragBytes = 3 * 64 * 16;
+inline int conv_steps(int Cin) { return Cin > 8 ? (Cin + 15) / 16 * 9 : 5; }
 // One launch: the candidates through cj (n_cand > 0) and the pass at x through bj (has_base), which do not
 // depend on each other, and two small jobs: the squared norms of the leading aux_count coordinates of aux_m candidates in
 // aux_pieces fixed pieces (-> aux_norm[s * aux_P + aux_p_off + piece]) and clearing 16 * aux_zero16 bytes at aux_zero.
@@ -239,9 +253,21 @@ struct ConvArgs {
   double* aux_norm;
   void* aux_zero;
   int aux_zero16;
-  int base_blocks, cand_blocks;   // filled in by the launcher
+  // kernel fragments of candidates 0 .. n_sources - 2 and of x, written by the launch that has pack_jobs, read by the later ones; or nullptr
+  unsigned char* pack;
+  long long pack_stride;  // bytes between sources
+  int pack_jobs, pack_layers, pack_x;   // jobs per source; number of layers; the source that is x
+  ConvPack pack_layer[ZENO_MAX_CONV];
+  // filled in by the launcher
+  int base_blocks, cand_blocks;
+  unsigned magic_cand;
 };
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
+// Whether convolution `index` of a model may take its kernels as fragments (a model does if all of its convolutions do).  The
+// input maps of all but the first are then split maps: three bf16 pieces per value, [sixteen channels][piece][eight
+// channels][position][8], one more position of zeros behind the last, channels up to a multiple of 16 (zeros).
+bool conv_takes_fragments(const ConvLayer& L, int n_r, int index);
+inline size_t split_map_bytes(int positions, int C) { return (size_t)3 * ((C + 15) / 16 * 2) * (positions + 1) * 16; }
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 
 }  // namespace zeno

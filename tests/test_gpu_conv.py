@@ -105,6 +105,37 @@ def test_cnn_nonfinite_rows_and_workspace_contents(B):
     assert np.all(score_error(s[ok], s_ref, scale) <= SCORE_TOL["fp32"])
 
 
+FRAGMENTS = [
+    # (in_h, in_w, in_c, channels, strides), m, n_r
+    ((32, 32, 3, [32, 32, 64, 64], [1, 2, 1, 2]), 7, 3),   # whole rows per tile; two channel tiles
+    ((9, 7, 1, [24, 40, 33], [1, 2, 1]), 5, 4),            # units of one group of eight channels; tiles across samples; a tile of one channel
+    ((5, 5, 8, [16, 16], [2, 2]), 3, 1),                   # eight channels of features; fewer positions than a tile
+    ((12, 10, 2, [48, 16, 96, 16], [1, 1, 2, 1]), 4, 9),   # three units, three channel tiles
+    ((33, 31, 3, [64], [2]), 3, 2),                        # one convolution: straight into the fully connected layer
+]
+
+
+@pytest.mark.parametrize("case", range(len(FRAGMENTS)))
+def test_cnn_fragments_and_split_maps(B, case):
+    """Models that take reordered kernels and maps: against the oracle, with whatever the workspace held before, and with a
+    workspace that lacks room for them (float32 sums in another order: 4 eps per addition of some 600 on 4 layers at most)."""
+    (h, w_, c, conv_c, conv_stride), m, n_r = FRAGMENTS[case]
+    desc = dict(in_h=h, in_w=w_, in_c=c, conv_c=conv_c, conv_stride=conv_stride, fc_out=10, has_bias=case % 2 == 0)
+    w = WL.make_cnn_workload(f"cnn_fr{case}", 80 + case, desc, m, 1, n_r, 0.1, 1e-3, n_flip=1)
+    _check(B, w)
+    dev = torch.device("cuda", 0)
+    mdl = B.ZenoCnnModel(w.desc, w.loss)
+    args = (mdl, w.x.to(dev), w.G.contiguous().to(dev), w.features.to(dev), w.gamma, w.rho)
+    out = []
+    for short in (0, 0, 256):
+        ws = B.alloc_workspace(mdl, m, n_r, dev)
+        ws[: ws.numel() // 4 * 4].view(torch.float32).fill_(float("nan") if out else 0.0)
+        out.append(npy(B.zeno_score(*args, labels=w.labels.to(dev), workspace=ws[: ws.numel() - short])))
+    assert np.array_equal(out[0], out[1])
+    s_ref, scale = O.cnn_scores(npy(w.x), npy(w.G), w.gamma, w.rho, w.desc, w.loss, npy(w.features), npy(w.labels))
+    assert np.all(score_error(out[2], s_ref, scale) <= SCORE_TOL["fp32"])
+
+
 EDGES = [
     # (in_h, in_w, in_c, channels, strides), m, n_r
     ((9, 7, 8, [32, 33], [1, 2]), 3, 3),         # eight channels: steps of two taps; one channel beyond a tile
