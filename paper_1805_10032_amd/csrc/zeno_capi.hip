@@ -720,11 +720,21 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
       a.has_base = 1;
       a.bj = conv_job(l + 1, false);
       flops += conv_flops(l + 1);
+    } else if (N <= kConvFcMost) {
+      // the operand of the fully connected layer's pass at x has been complete for a launch
+      a.fc_N = N;
+      a.fc_K = p.Kfc;
+      a.fc_Kp = p.Kp;
+      a.fc_w_off = j.w_off;
+      a.fc_b_off = j.b_off;
+      a.fc_h0 = reinterpret_cast<const float*>(ws + p.off_h0t);
+      a.fc_wt = reinterpret_cast<float*>(ws + p.off_wt);
+      a.fc_z0 = j.Z0;
     }
     ProfScope ps(ZENO_KERNEL_CONV_CAND, l, flops, stream);
     ZENO_TRY(launch_conv(a, stream));
   }
-  {
+  if (N > kConvFcMost) {
     LayerArgs b = common;
     b.has_base = 1;
     b.bj = j;

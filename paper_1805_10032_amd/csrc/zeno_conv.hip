@@ -31,7 +31,7 @@
 // copies are requested, 1.9 and 2.4 waiting for the copies of its two stages, 1.2 in the products of each, 2 in the sums and results.
 // Measured (MI355X, 32 x 32 x 3 images, convolutions 32-32-64-64 with strides 1-2-1-2, m = 20) against the kernels below:
 // n_r = 32, candidates' convolutions 66 + 10 / 99 + 10 / 109 + 13 / 115 us with the pass at x on its own -> 64 / 79 / 109 / 65, fragments 6 us,
-// the step 455 -> 343 us; n_r = 4: 35 / 33 / 23 us for the last three -> 18 / 20 / 17, the step 159 -> 118 us.  Over 40 random models of
+// the step 455 -> 343 us (334 with fc_sample); n_r = 4: 35 / 33 / 23 us for the last three -> 18 / 20 / 17, the step 159 -> 118 us (106).  Over 40 random models of
 // this kind 1.08 times as fast, single convolutions on 8 x 8 images as fast as before.  Models with other convolutions among them
 // would alternate between both kinds of maps, in two launches for every one: 0.81-0.95 on 14 of 18, so they keep to the
 // kernels below.  Splitting the maps in the workgroup that stages them (four times as many vector instructions): 106 us where the copies
@@ -195,6 +195,65 @@ __device__ void pack_fragment(const ConvArgs& a, int s, int job) {
       u1[e] = __builtin_fmaf(-a.gamma, u1[e], w1[e]);
     }
     store_split(o + (long long)L.steps * kConvFragBytes, 1024, u0, u1);
+  }
+}
+
+// The pass at x through a narrow fully connected layer, next to the candidates' last convolution, which it does not depend on
+// (a launch of the layer kernel behind it took 13 us, most of it latency; here the step is 11 us shorter).  One sample per
+// workgroup: a thread sums its quads of columns in float32, lanes by xor-shuffle tree and waves in order in float64.
+__device__ void fc_sample(const ConvArgs& a, int r, float* red) {
+  const float* __restrict__ W = a.x + a.fc_w_off;
+  const float* __restrict__ h = a.fc_h0 + tiled_index<false>(r, 0, a.fc_Kp);
+  const int T = blockDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int quads = a.fc_K >> 2;
+  for (int n0 = 0; n0 < a.fc_N; n0 += 8) {
+    f32x4 sum[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 2
+    for (int q = threadIdx.x; q < quads; q += T) {
+      const f32x4 hv = *reinterpret_cast<const f32x4*>(h + (q >> 1) * 256 + (q & 1) * 128);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const f32x4 w = *reinterpret_cast<const f32x4_a4*>(W + (long long)(n0 + i < a.fc_N ? n0 + i : n0) * a.fc_K + 4 * q);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(hv[e], w[e], sum[i][e]);
+      }
+    }
+    const int k = 4 * quads + (int)threadIdx.x;      // up to three columns behind the quads
+    const bool rest = k < a.fc_K;
+    const float hr = rest ? h[(k >> 3) * 256 + ((k >> 2) & 1) * 128 + (k & 3)] : 0.f;
+    double* sums = reinterpret_cast<double*>(red);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int n = n0 + i < a.fc_N ? n0 + i : n0;
+      double t = ((double)sum[i][0] + sum[i][1]) + ((double)sum[i][2] + sum[i][3]);
+      if (rest) t += (double)hr * (double)W[(long long)n * a.fc_K + k];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+      if (lane == 0) sums[wave * 8 + i] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < 8 && n0 + (int)threadIdx.x < a.fc_N) {
+      const int n = n0 + (int)threadIdx.x;
+      double t = a.fc_b_off >= 0 ? (double)a.x[a.fc_b_off + n] : 0.0;
+      for (int w = 0; w < T / 64; ++w) t += sums[w * 8 + threadIdx.x];
+      a.fc_z0[(long long)r * a.fc_N + n] = (float)t;
+    }
+  }
+}
+// The layer's weights in matrix-operand order, columns beyond K zeros (rows beyond N only reach results that are discarded).
+constexpr int kFcPieces = 4;   // 16-byte pieces a thread copies
+__device__ void fc_weights(const ConvArgs& a, int block) {
+  const long long pieces = (long long)a.fc_N * (a.fc_Kp >> 2);
+#pragma unroll
+  for (int i = 0; i < kFcPieces; ++i) {
+    const long long at = ((long long)block * kFcPieces + i) * blockDim.x + threadIdx.x;
+    if (at >= pieces) return;
+    const int n = (int)(at / (a.fc_Kp >> 2)), k = 4 * (int)(at % (a.fc_Kp >> 2));
+    const f32x4 v = load4_masked(a.x + a.fc_w_off + (long long)n * a.fc_K, k, a.fc_K, k < a.fc_K);
+    *reinterpret_cast<f32x4*>(a.fc_wt + tiled_index<false>(n, k, a.fc_Kp)) = v;
   }
 }
 
@@ -923,14 +982,17 @@ __device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, i
 }
 
 // Blocks: [tiles of the pass at x] [tiles x candidates, candidate fastest] [squared norms: pieces x candidates] [one that
-// clears the counters] [kernel fragments].  Returns whether the block is one of the small jobs, which it then has done.
+// clears the counters] [kernel fragments], or [samples of the fully connected layer] [its weights].  Returns whether the block is one of the small jobs, which it then has done.
 __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& is_base, int& s, int& tile) {
   int b = blockIdx.x;
   is_base = b < a.base_blocks;
   if (!is_base) b -= a.base_blocks;
   if (!is_base && b >= a.cand_blocks) {
     b -= a.cand_blocks;
-    if (b < a.aux_pieces * a.aux_m) {
+    if (a.fc_N > 0) {                              // (a launch has these or the following)
+      if (b < a.n_r) fc_sample(a, b, reinterpret_cast<float*>(lds));
+      else fc_weights(a, b - a.n_r);
+    } else if (b < a.aux_pieces * a.aux_m) {
       sumsq_piece(a, b / a.aux_pieces, b % a.aux_pieces, reinterpret_cast<double*>(lds));
     } else if (b == a.aux_pieces * a.aux_m) {
       const uint4 z = {0u, 0u, 0u, 0u};
@@ -1034,6 +1096,7 @@ hipError_t plan_tiles(ConvArgs& a, int np_most, int wc, F job_lds, long long* ld
   const int waves = wc > 0 && np_most == 128 ? 4 : 8;
   *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0) +
            ((long long)a.pack_jobs * (a.pack_x + 1) + waves - 1) / waves;
+  if (a.fc_N > 0) *total += a.n_r + ((long long)a.fc_N * (a.fc_Kp / 4) + 64 * waves * kFcPieces - 1) / (64 * waves * kFcPieces);
   if (*total > (1ll << 30) || *lds > kConvLdsMost) return hipErrorInvalidValue;
   a.base_blocks = (int)blocks[0];
   a.cand_blocks = (int)blocks[1];
@@ -1048,7 +1111,7 @@ hipError_t launch_wide(ConvArgs a, hipStream_t stream) {
   static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wide_kernel<CG, FULL, PB, WP, WC>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsMost);
   if (attr_err != hipSuccess) return attr_err;
-  long long lds = 64, total = 0;                                   // (the squared norms' four partial sums)
+  long long lds = 512, total = 0;                                  // (the small jobs' partial sums)
   const hipError_t e = plan_tiles(a, NP, WC, [](ConvJob& j, int) { return wide_bytes(j.L, NP, WC, CG); }, &lds, &total);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL((conv_wide_kernel<CG, FULL, PB, WP, WC>), dim3((unsigned)total), dim3(256), (size_t)lds, stream, a);
@@ -1183,9 +1246,9 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   const int g = pick_groups([&](const ConvLayer& l, int gr) { return deep_bytes(l, gr); }, 64);
   if (g > 0 && !gather) return launch_deep_as(g, full, a, stream);
   ConvArgs r = a;
-  r.aux_pieces = r.aux_m = r.aux_zero16 = r.pack_jobs = 0;
+  r.aux_pieces = r.aux_m = r.aux_zero16 = r.pack_jobs = r.fc_N = 0;
   const hipError_t e = launch_gather(r, stream);
-  if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0 && a.pack_jobs <= 0)) return e;
+  if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0 && a.pack_jobs <= 0 && a.fc_N <= 0)) return e;
   r = a;                                           // the small jobs alone
   r.has_base = r.n_cand = 0;
   return launch_wide<1, true, 1, 4, 1>(r, stream);

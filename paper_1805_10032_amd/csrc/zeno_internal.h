@@ -253,6 +253,11 @@ struct ConvArgs {
   double* aux_norm;
   void* aux_zero;
   int aux_zero16;
+  // the pass at x through a narrow fully connected layer (fc_N > 0): Z0 = H0 W^T + b, [n_r x fc_N], and W in matrix-operand order
+  int fc_N, fc_K, fc_Kp;
+  long long fc_w_off, fc_b_off;
+  const float* fc_h0;     // in matrix-operand order of width fc_Kp
+  float *fc_wt, *fc_z0;
   // kernel fragments of candidates 0 .. n_sources - 2 and of x, written by the launch that has pack_jobs, read by the later ones; or nullptr
   unsigned char* pack;
   long long pack_stride;  // bytes between sources
@@ -263,6 +268,7 @@ struct ConvArgs {
   unsigned magic_cand;
 };
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
+constexpr int kConvFcMost = 32;   // widest layer that launch_conv takes as a small job
 // Whether convolution `index` of a model may take its kernels as fragments (a model does if all of its convolutions do).  The
 // input maps of all but the first are then split maps: three bf16 pieces per value, [sixteen channels][piece][eight
 // channels][position][8], one more position of zeros behind the last, channels up to a multiple of 16 (zeros).

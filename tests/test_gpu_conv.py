@@ -136,6 +136,15 @@ def test_cnn_fragments_and_split_maps(B, case):
     assert np.all(score_error(out[2], s_ref, scale) <= SCORE_TOL["fp32"])
 
 
+@pytest.mark.parametrize("out", [8, 9, 32, 33])
+@pytest.mark.parametrize("hw,conv_c", [(5, [7]), (8, [16, 24])])
+def test_cnn_widths_of_the_fully_connected_layer(B, hw, conv_c, out):
+    """Up to 32 outputs its pass at x rides with the candidates' last convolution (eight outputs at a time); 175 and 1536
+    columns, the former no multiple of four; gathered and staged convolutions."""
+    desc = dict(in_h=hw, in_w=hw, in_c=3, conv_c=conv_c, conv_stride=[1] * len(conv_c), fc_out=out, has_bias=out != 9)
+    _check(B, WL.make_cnn_workload(f"cnn_fc{out}", 120 + out, desc, 4, 1, 6, 0.1, 1e-3, n_flip=1))
+
+
 EDGES = [
     # (in_h, in_w, in_c, channels, strides), m, n_r
     ((9, 7, 8, [32, 33], [1, 2]), 3, 3),         # eight channels: steps of two taps; one channel beyond a tile
