@@ -12,10 +12,10 @@
 // A layer has at most four 32-feature tiles (widths after the input up to 128); each is shared by KP = 8 / 4 / 2 waves
 // (1 / 2 / 3-4 tiles) that split K and add their accumulators through LDS in wave order.  A lane holds four consecutive k of
 // its feature (weights) or its sample (activations) per step of 8 k and feeds four instructions, the i-th of which contracts
-// k = i and 4 + i of the step; four steps are requested together, one group ahead.
-// Bound by latency: a dependent chain of round trips per layer.  Measured (MI355X, wall time of score and update in a series
-// of calls, m = 20, n_r = 32, float32): 784 -> 10: 30.1 -> 24.2 us, 784 -> 64 -> 10: 72.0 -> 43.1, 64 -> 48 -> 40 -> 30 -> 20 -> 10:
-// 70.8 -> 40.1; m = 8, n_r = 16: 64 -> 1: 28.8 -> 18.9.
+// k = i and 4 + i of the step; a step is requested one ahead of its products.
+// Bound by latency: a dependent chain of round trips per layer, and instructions fetched as they are first run.  Measured (MI355X, wall time of score and update in a series
+// of calls, m = 20, n_r = 32, float32; general path -> this one, four steps at a time -> one): 784 -> 10: 30.1 -> 25.9 -> 23.5 us,
+// 784 -> 64 -> 10: 72.0 -> 43.1 -> 35.0; m = 40, n_r = 16: 256 -> 100 -> 50 -> 10: 47.8 -> 39.6; m = 8, n_r = 16: 64 -> 1: 28.8 -> 19.9.
 #include <type_traits>
 
 #include "zeno_layer_impl.h"
@@ -28,7 +28,6 @@ constexpr int kWaves = 8, kThreads = 64 * kWaves;
 constexpr int kMaxWidth = 128;   // widest layer output (four tiles)
 constexpr int kRows = 32;        // samples
 constexpr int kMaxClasses = 16;  // widest output layer: the threads of a workgroup take a class of a sample each
-constexpr int kAhead = 4;        // steps of a wave requested together, one group ahead of its use
 static_assert(kThreads == kRows * kMaxClasses, "one thread per sample and class");
 
 template <bool BF16>
@@ -80,9 +79,12 @@ __global__ __launch_bounds__(kThreads) void score_small_kernel(const SmallArgs a
   __shared__ double totals[2][kWaves];
   __shared__ int label[kRows];
   __shared__ float target[kRows];
+  // requested now, stored behind the first layer's products (a wave would wait for them here)
+  int label_mine = 0;
+  float target_mine = 0.f;
   if (tid < a.n_r) {
-    if (a.loss == ZENO_LOSS_SQUARED) target[tid] = a.targets[tid];
-    else label[tid] = a.labels[tid];
+    if (a.loss == ZENO_LOSS_SQUARED) target_mine = a.targets[tid];
+    else label_mine = a.labels[tid];
   }
   const float neg_gamma = -a.gamma;
   double nrm = 0.0;
@@ -112,59 +114,60 @@ __global__ __launch_bounds__(kThreads) void score_small_kernel(const SmallArgs a
       const int steps = (K + 7) / 8, s_begin = steps * kp / kp_count, s_end = steps * (kp + 1) / kp_count;
       auto contract = [&](auto second_tag) {
         constexpr bool SECOND = decltype(second_tag)::value;
-        struct Group {
-          f32x4 w[kAhead], u[kAhead], b[kAhead], dv[kAhead];
+        // One step ahead of its products and hardly anything unrolled: the launch is short, its instructions come from memory as
+        // they are first run, and straight-line code costs more than the round trips it hides (1, 2, 3, 4 steps a group, one
+        // group ahead: 784 -> 10 23.7 / 24.8 / 25.7 / 26.3 us per score and update, 784 -> 64 -> 10 36.6 / 38.8 / 41.1 / 43.1).
+        struct Step {
+          f32x4 w, u, b, dv;
         };
-        auto request = [&](Group& g, int s0) {
-#pragma unroll
-          for (int q = 0; q < kAhead; ++q) {
-            const int s = s0 + q < s_end ? s0 + q : s_end - 1;       // (a step too many is not used)
-            const int k = 8 * s + 4 * h;
-            g.w[q] = load_row4(wrow, k, K);
-            g.u[q] = load_row4(urow, k, K);
-            if constexpr (SECOND) {
-              g.b[q] = *reinterpret_cast<const f32x4*>(h_in + n * pitch + k);
-              g.dv[q] = *reinterpret_cast<const f32x4*>(d_in + n * pitch + k);
-            } else {
-              g.b[q] = load_row4(frow, k, K);
-            }
+        auto request = [&](Step& g, int s) {
+          s = s < s_end ? s : s_end - 1;                             // (a step too many is not used)
+          const int k = 8 * s + 4 * h;
+          g.w = load_row4(wrow, k, K);
+          g.u = load_row4(urow, k, K);
+          if constexpr (SECOND) {
+            g.b = *reinterpret_cast<const f32x4*>(h_in + n * pitch + k);
+            g.dv = *reinterpret_cast<const f32x4*>(d_in + n * pitch + k);
+          } else {
+            g.b = load_row4(frow, k, K);
           }
         };
-        auto multiply = [&](Group& g, int s0) {
+        auto multiply = [&](Step& g, int s) {
+          if (s >= s_end) return;
+          const int k = 8 * s + 4 * h;
+          if (8 * s + 8 > K) {
+            g.w = end_of_row4(g.w, k, K);
+            g.u = end_of_row4(g.u, k, K);
+            if constexpr (!SECOND) g.b = end_of_row4(g.b, k, K);
+          }
+          const f32x4 u = g.u;
+          if (f_ok) nrm += (double)((u[0] * u[0] + u[1] * u[1]) + (u[2] * u[2] + u[3] * u[3]));
+          const f32x4 wr = operand<BF16>(g.w), ur = operand<BF16>(u), b = SECOND ? g.b : operand<BF16>(g.b);
 #pragma unroll
-          for (int q = 0; q < kAhead; ++q) {
-            if (s0 + q >= s_end) break;
-            const int k = 8 * (s0 + q) + 4 * h;
-            if (8 * (s0 + q) + 8 > K) {
-              g.w[q] = end_of_row4(g.w[q], k, K);
-              g.u[q] = end_of_row4(g.u[q], k, K);
-              if constexpr (!SECOND) g.b[q] = end_of_row4(g.b[q], k, K);
-            }
-            const f32x4 u = g.u[q];
-            if (f_ok) nrm += (double)((u[0] * u[0] + u[1] * u[1]) + (u[2] * u[2] + u[3] * u[3]));
-            const f32x4 wr = operand<BF16>(g.w[q]), ur = operand<BF16>(u), b = SECOND ? g.b[q] : operand<BF16>(g.b[q]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              z = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[i], b[i], z, 0, 0, 0);
-              c = __builtin_amdgcn_mfma_f32_32x32x2f32(ur[i], b[i], c, 0, 0, 0);
-              if constexpr (SECOND)
-                c = __builtin_amdgcn_mfma_f32_32x32x2f32(operand<BF16>(__builtin_fmaf(neg_gamma, ur[i], wr[i])), g.dv[q][i], c, 0, 0, 0);
-            }
+          for (int i = 0; i < 4; ++i) {
+            z = __builtin_amdgcn_mfma_f32_32x32x2f32(wr[i], b[i], z, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x2f32(ur[i], b[i], c, 0, 0, 0);
+            if constexpr (SECOND)
+              c = __builtin_amdgcn_mfma_f32_32x32x2f32(operand<BF16>(__builtin_fmaf(neg_gamma, ur[i], wr[i])), g.dv[i], c, 0, 0, 0);
           }
         };
         if (s_begin >= s_end) return;
-        Group even, odd;
+        Step even, odd;
         request(even, s_begin);
 #pragma unroll 1
-        for (int s0 = s_begin; s0 < s_end; s0 += 2 * kAhead) {
-          request(odd, s0 + kAhead);
-          multiply(even, s0);
-          request(even, s0 + 2 * kAhead);
-          multiply(odd, s0 + kAhead);
+        for (int s = s_begin; s < s_end; s += 2) {
+          request(odd, s + 1);
+          multiply(even, s);
+          request(even, s + 2);
+          multiply(odd, s + 1);
         }
       };
       if (second) contract(std::true_type{});
       else contract(std::false_type{});
+    }
+    if (l == 0 && tid < kRows) {
+      label[tid] = label_mine;
+      target[tid] = target_mine;
     }
     // The accumulators of the waves that share a tile, added in wave order; the waves finish a quarter of the tile's
     // features each (two of two waves).  Quarter q: registers 4 q .. 4 q + 3, i.e. sample n, features 8 q + 4 h .. + 3.
@@ -186,19 +189,12 @@ __global__ __launch_bounds__(kThreads) void score_small_kernel(const SmallArgs a
 #pragma unroll 1
       for (int qq = 0; qq < quarters; ++qq) {
         const int q = kp * quarters + qq, f0 = tile * 32 + 8 * q + 4 * h;
-        f32x4 tz[8], tc[8];
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-          const int from = tile * kp_count + (w < kp_count ? w : 0);
-          tz[w] = red[(from * 8 + q) * 64 + lane];
-          tc[w] = red[(from * 8 + 4 + q) * 64 + lane];
-        }
-        f32x4 zs = tz[0], cs = tc[0];
-#pragma unroll
-        for (int w = 1; w < 8; ++w) {
-          if (w >= kp_count) break;
-          zs += tz[w];
-          cs += tc[w];
+        const f32x4* part = red + (tile * kp_count * 8 + q) * 64 + lane;
+        f32x4 zs = part[0], cs = part[4 * 64];
+#pragma unroll 1
+        for (int w = 1; w < kp_count; ++w) {
+          zs += part[w * 8 * 64];
+          cs += part[(w * 8 + 4) * 64];
         }
         f32x4 hv, dd;
 #pragma unroll
@@ -274,13 +270,11 @@ int small_pitch(const int* dims, int L) {
 }  // namespace
 
 // One workgroup per candidate pays while a workgroup's matrix steps (8 k of a tile; the second product counts) stay below what
-// the general path spends on its 2 L + 3 launches.  Measured (us per score and update, this path / the general one; m = 20,
-// n_r = 32, then m = 100, n_r = 4): one layer, 196 steps (784 -> 10): 25.3 / 30.5, 48.7 / 52.9; 300 steps (1200 -> 10): 30.6
-// (before the loads ran a group ahead: 34.0) / 30.6; two layers, 416 steps (784 -> 64 -> 10): 43.1 / 72.0, 72.3 / 96.3; four
-// layers, 496 steps (256 -> 128 -> 128 -> 128 -> 10 has 632): 51.0 / 59.6, 75.2 / 85.2; 936 steps: 97.6 / 86.4, 118.0 / 115.6.
-// With bf16 operands, whose general path multiplies eight times as fast, half as many (random models up to 250 steps a layer and
-// 256 candidates, this path's gain: float32 1.37, none of 157 more than 2 % slower; bf16 up to 125 steps a layer 1.28, 2 of 79;
-// bf16 beyond that 1.04, 24 of 71, by up to 9 %).
+// the general path spends on its 2 L + 3 launches.  Measured on 962 random models with up to 400 steps a layer, time of score and
+// update on the general path / this one: float32 up to 300 steps a layer 1.60, none of 471 more than 2 % slower; 300 to 350 1.50, 1 of 32;
+// beyond that 9 of 27, by up to 8 %; 600 to 800 steps in all 1.82, 800 to 1300 1.50, 1 of 29.  bf16 operands, whose general path
+// multiplies eight times as fast: up to 200 steps a layer 1.40, none of 366, but for four layers of that length.  Single layers, with
+// the fewest launches to save, are among the slower ones from 350 (222) steps on and change sides at 250 (125).
 // More classes would put several rounds of exponentials behind each other (784 -> 32: 37.8 / 32.4, 59.2 / 46.8).  Beyond 256
 // candidates the workgroups of a CU follow each other (random models, 257 to 1024 candidates: 1.06, 49 of 216 slower, by up to
 // 18 %).  Rows shorter than four floats cannot be read four at a time.
@@ -291,7 +285,8 @@ bool small_model_fits(const int* dims, int L, int m, int n_r, bool bf16) {
     if (dims[l] < 4 || dims[l + 1] > kMaxWidth) return false;
     steps += (long long)((dims[l + 1] + 31) / 32) * ((dims[l] + 7) / 8) * (l > 0 ? 3 : 2);
   }
-  return steps <= (bf16 ? 125LL : 250LL) * L && steps <= 600;
+  if (L == 1) return steps <= (bf16 ? 125 : 250);
+  return steps <= (bf16 ? 180LL : 300LL) * L && steps <= (bf16 ? 600 : 1000);
 }
 
 hipError_t launch_score_small(SmallArgs a, bool bf16, int m, hipStream_t stream) {

@@ -32,6 +32,11 @@ CASES = [
     ([30, 32, 65, 96, 97, 1], 6, 17, "fp32", 1, True, True),   # one to four tiles, squared loss
     ([21, 128, 4, 2], 8, 32, "bf16", 4, True, True),       # widest layer, shortest hidden row
     ([50, 129, 3], 4, 3, "fp32", 1, True, False),          # one feature too wide
+    ([2208, 32, 10], 5, 9, "fp32", 1, True, True),         # two layers: 564 steps, and 606 (600 is the line)
+    ([2376, 32, 10], 5, 9, "fp32", 1, True, False),
+    ([800, 80, 40, 32, 10], 6, 31, "fp32", 1, True, True), # four layers: 687 steps
+    ([1248, 16, 10], 7, 5, "bf16", 1, True, True),         # 318 steps, and 366: the line for two layers of bf16 operands is 360
+    ([1440, 16, 10], 7, 5, "bf16", 1, True, False),
 ]
 
 
