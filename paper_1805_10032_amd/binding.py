@@ -122,8 +122,15 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     return lib
 
 
+# torch.cuda.current_stream() builds a Stream object, 2.8 us of the 10 us that the host spends on a call, and the smallest calls
+# are bound by the host (64 -> 1, eight candidates, score and update: 19.9 -> 14.7 us); the raw handle takes 0.2.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    return int(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return int(_raw_stream(torch.cuda.current_device()))
 
 
 def _dev(t: torch.Tensor, dtype, name: str) -> int:
