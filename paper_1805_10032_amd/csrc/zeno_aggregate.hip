@@ -55,6 +55,7 @@ constexpr int kBlockVec = kThreads * kVec;   // float4 columns per block (16 KB 
 // rows whose loads are in flight together (x kVec loads each); the variant that
 // looks its rows up in the selected list keeps more in flight to cover the lookup
 constexpr int kRowsAll = 2, kRowsSel = 4;
+constexpr int kRowsFew = 4;                   // the same for one column a thread
 constexpr int kMaxBlocks = 9;                // blocks per burst: 9 x 16 KB of LDS
 
 __device__ inline void store_burst(float* p, const f32x4& v) {
@@ -76,13 +77,15 @@ __device__ inline float sgd_step(float x, double gamma, double avg) {
 
 // UPDATE: also (or only, out == nullptr) write x_next = x - gamma * average; x_next may
 // be x itself (every column is read and written by one thread).
-template <bool ALL, bool UPDATE>
+// V: float4 columns of a thread (kVec, or one where the columns are few).
+template <bool ALL, bool UPDATE, int V>
 __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* __restrict__ G,
                                                                   const float* __restrict__ scores, int m,
                                                                   long long d, long long ldg, int b, int n_blocks,
                                                                   float* __restrict__ out,
                                                                   int32_t* __restrict__ selected, float gamma,
                                                                   const float* x, float* x_next) {
+  constexpr int BLOCK = kThreads * V;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   // [selected row list][burst buffer]; the selection's scratch (keys, flags) lies
   // in the burst buffer, which is not used before the selection is over
@@ -97,34 +100,34 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
 
   const double n = (double)n_sel;
   // second burst buffer (new parameters) behind the first (average) when both are written
-  const int xoff = (UPDATE && out != nullptr) ? n_blocks * kBlockVec : 0;
+  const int xoff = (UPDATE && out != nullptr) ? n_blocks * BLOCK : 0;
   const long long n_vec = d / 4;
   // balanced contiguous share of the column blocks, worked through in bursts of n_blocks
-  const long long blocks_total = (n_vec + kBlockVec - 1) / kBlockVec;
+  const long long blocks_total = (n_vec + BLOCK - 1) / BLOCK;
   const long long blk_begin = blocks_total * blockIdx.x / gridDim.x;
   const long long blk_end = blocks_total * (blockIdx.x + 1) / gridDim.x;
   for (long long g = blk_begin; g < blk_end; g += n_blocks) {
     const int nb = (int)(blk_end - g < n_blocks ? blk_end - g : n_blocks);
     for (int i = 0; i < nb; ++i) {
-      const long long c0 = (g + i) * kBlockVec + threadIdx.x;
-      double acc[kVec][4];
+      const long long c0 = (g + i) * BLOCK + threadIdx.x;
+      double acc[V][4];
 #pragma unroll
-      for (int v = 0; v < kVec; ++v)
+      for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[v][e] = 0.0;
       // columns beyond the end re-read the last full column (in bounds) and are not written
-      long long col[kVec];
+      long long col[V];
 #pragma unroll
-      for (int v = 0; v < kVec; ++v) {
+      for (int v = 0; v < V; ++v) {
         const long long c = c0 + v * kThreads;
         col[v] = (c < n_vec ? c : n_vec - 1) * 4;
       }
-      f32x4 xv[kVec];
+      f32x4 xv[V];
       if (UPDATE) {
 #pragma unroll
-        for (int v = 0; v < kVec; ++v) xv[v] = *reinterpret_cast<const f32x4_a4*>(x + col[v]);
+        for (int v = 0; v < V; ++v) xv[v] = *reinterpret_cast<const f32x4_a4*>(x + col[v]);
       }
-      constexpr int RB = ALL ? kRowsAll : kRowsSel;
+      constexpr int RB = V == 1 ? kRowsFew : ALL ? kRowsAll : kRowsSel;
       int s = 0;
       // the list entries of the NEXT batch are fetched while this batch's loads are
       // in flight (entries past the end repeat the last one and are never used)
@@ -132,12 +135,12 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
 #pragma unroll
       for (int t = 0; t < RB; ++t) rows[t] = ALL ? t : sel_list[t < n_sel ? t : n_sel - 1];
       for (; s + RB <= n_sel; s += RB) {
-        f32x4 x[RB][kVec];
+        f32x4 x[RB][V];
 #pragma unroll
         for (int t = 0; t < RB; ++t) {
           const float* rp = G + (long long)rows[t] * ldg;
 #pragma unroll
-          for (int v = 0; v < kVec; ++v) x[t][v] = load_stream4(rp + col[v]);
+          for (int v = 0; v < V; ++v) x[t][v] = load_stream4(rp + col[v]);
         }
         // keep the whole batch of loads in flight: without the fences the scheduler
         // interleaves loads and additions to save registers and waits after every few loads
@@ -151,22 +154,22 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
 #pragma unroll
         for (int t = 0; t < RB; ++t)
 #pragma unroll
-          for (int v = 0; v < kVec; ++v)
+          for (int v = 0; v < V; ++v)
 #pragma unroll
             for (int e = 0; e < 4; ++e) acc[v][e] += (double)x[t][v][e];
       }
       for (; s < n_sel; ++s) {
         const long long row = ALL ? s : sel_list[s];
-        f32x4 x[kVec];
+        f32x4 x[V];
 #pragma unroll
-        for (int v = 0; v < kVec; ++v) x[v] = load_stream4(G + row * ldg + col[v]);
+        for (int v = 0; v < V; ++v) x[v] = load_stream4(G + row * ldg + col[v]);
 #pragma unroll
-        for (int v = 0; v < kVec; ++v)
+        for (int v = 0; v < V; ++v)
 #pragma unroll
           for (int e = 0; e < 4; ++e) acc[v][e] += (double)x[v][e];
       }
 #pragma unroll
-      for (int v = 0; v < kVec; ++v) {
+      for (int v = 0; v < V; ++v) {
         f32x4 r, xn;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -174,15 +177,15 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
           r[e] = (float)avg;
           if (UPDATE) xn[e] = sgd_step(xv[v][e], (double)gamma, avg);
         }
-        const int slot = i * kBlockVec + v * kThreads + threadIdx.x;
+        const int slot = i * BLOCK + v * kThreads + threadIdx.x;
         if (!UPDATE || out != nullptr) burst[slot] = r;
         if (UPDATE) burst[xoff + slot] = xn;
       }
     }
     __syncthreads();
-    const long long g0 = g * kBlockVec;
+    const long long g0 = g * BLOCK;
     const long long left = n_vec - g0;
-    const int n_out = (int)(left < (long long)nb * kBlockVec ? left : (long long)nb * kBlockVec);
+    const int n_out = (int)(left < (long long)nb * BLOCK ? left : (long long)nb * BLOCK);
     if (!UPDATE || out != nullptr)
       for (int j = threadIdx.x; j < n_out; j += kThreads) store_burst(out + (g0 + j) * 4, burst[j]);
     if (UPDATE)
@@ -213,10 +216,17 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   const int n_bufs = (update && out != nullptr) ? 2 : 1;   // burst buffers: the average, the new parameters
   const int max_blocks = kMaxBlocks / n_bufs;
   const long long n_vec = d / 4;
+  // Few columns: a quarter of them per workgroup, which is then four times as many.  Measured (us per update / Mean, four
+  // columns a thread -> one): m = 100, d = 7850 32.3 -> 21.1 / 47.2 -> 27.0, d = 300000 29.7 -> 21.5 / 40.4 -> 22.8; m = 20, d = 106122
+  // 9.9 -> 7.5 / 11.6 -> 7.1, d = 500000 10.9 -> 8.8 / 11.1 -> 8.1, d = 1000001 13.9 -> 13.7 / 15.1 -> 15.6; beyond that slower (m = 20,
+  // d = 4000000 41.9 -> 46.4 / 53.1 -> 57.0).  Eight and sixteen rows in flight gain at d = 7850 only (18.0 and 17.8) and lose above.
+  const bool few = n_vec < 163840;
+  const int block_vec = few ? kThreads : kBlockVec;
   // burst length: as long as LDS allows while at least ~512 workgroups' worth of groups remain
-  long long nb = n_vec / ((long long)kBlockVec * 512);
+  long long nb = few ? 1 : n_vec / ((long long)kBlockVec * 512);
   const int n_blocks = (int)(nb < 1 ? 1 : (nb > max_blocks ? max_blocks : nb));
-  const size_t lds = ZENO_MAX_CANDIDATES * sizeof(int) + (size_t)n_bufs * n_blocks * kBlockVec * 16;
+  const size_t bursts = (size_t)n_bufs * n_blocks * block_vec * 16, scratch = ZENO_MAX_CANDIDATES * (sizeof(float) + sizeof(int));
+  const size_t lds = ZENO_MAX_CANDIDATES * sizeof(int) + (bursts > scratch ? bursts : scratch);
   // as many workgroups as the chip holds at once (LDS-limited), each with a balanced share of the blocks
   static const int n_cu = [] {
     int dev = 0, v = 0;
@@ -226,16 +236,16 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   }();
   int per_cu = (int)((160 * 1024) / (lds + 512));
   per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
-  const long long blocks_total = (n_vec + kBlockVec - 1) / kBlockVec;
+  const long long blocks_total = (n_vec + block_vec - 1) / block_vec;
   const long long resident = (long long)n_cu * per_cu;
   const int grid = (int)(blocks_total < 1 ? 1 : (blocks_total > resident ? resident : blocks_total));
   // once per process (initialisation of a local static is thread-safe)
   static const hipError_t attr_err = [] {
     const int lds_max = (int)(ZENO_MAX_CANDIDATES * sizeof(int) + (size_t)kMaxBlocks * kBlockVec * 16);
-    const void* kernels[4] = {reinterpret_cast<const void*>(&masked_average_kernel<true, false>),
-                              reinterpret_cast<const void*>(&masked_average_kernel<false, false>),
-                              reinterpret_cast<const void*>(&masked_average_kernel<true, true>),
-                              reinterpret_cast<const void*>(&masked_average_kernel<false, true>)};
+    const void* kernels[4] = {reinterpret_cast<const void*>(&masked_average_kernel<true, false, kVec>),
+                              reinterpret_cast<const void*>(&masked_average_kernel<false, false, kVec>),
+                              reinterpret_cast<const void*>(&masked_average_kernel<true, true, kVec>),
+                              reinterpret_cast<const void*>(&masked_average_kernel<false, true, kVec>)};
     for (const void* k : kernels) {
       hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
       if (e != hipSuccess) return e;
@@ -246,12 +256,16 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   const bool all = scores == nullptr;
   const int bb = all ? 0 : b;
 #define ZENO_LAUNCH_AVG(ALLV, UPD)                                                                                  \
-  hipLaunchKernelGGL((masked_average_kernel<ALLV, UPD>), dim3(grid), dim3(kThreads), lds, stream, G, scores, m, d, \
-                     ldg, bb, n_blocks, out, selected, gamma, x, x_next)
-  if (all && !update) ZENO_LAUNCH_AVG(true, false);
-  else if (all) ZENO_LAUNCH_AVG(true, true);
-  else if (!update) ZENO_LAUNCH_AVG(false, false);
-  else ZENO_LAUNCH_AVG(false, true);
+  if (few)                                                                                                          \
+    hipLaunchKernelGGL((masked_average_kernel<ALLV, UPD, 1>), dim3(grid), dim3(kThreads), lds, stream, G, scores,    \
+                       m, d, ldg, bb, n_blocks, out, selected, gamma, x, x_next);                                   \
+  else                                                                                                              \
+    hipLaunchKernelGGL((masked_average_kernel<ALLV, UPD, kVec>), dim3(grid), dim3(kThreads), lds, stream, G, scores, \
+                       m, d, ldg, bb, n_blocks, out, selected, gamma, x, x_next)
+  if (all && !update) { ZENO_LAUNCH_AVG(true, false); }
+  else if (all) { ZENO_LAUNCH_AVG(true, true); }
+  else if (!update) { ZENO_LAUNCH_AVG(false, false); }
+  else { ZENO_LAUNCH_AVG(false, true); }
 #undef ZENO_LAUNCH_AVG
   return hipGetLastError();
 }

@@ -181,6 +181,21 @@ def test_median_by_selection_over_many_tiles(B, m, d):
     assert np.array_equal(med.cpu().numpy()[cols.numpy()], ref, equal_nan=True)
 
 
+@pytest.mark.parametrize("d", [1023, 1025, 4 * 163840 - 1, 4 * 163840 + 5])
+def test_average_on_both_sides_of_the_columns_per_thread(B, d):
+    """One column of four floats a thread below 163840 of them, four from there on: bit for bit, with a b that leaves a batch of
+    rows incomplete; the update as well."""
+    m, b, gamma = 13, 4, float(np.float32(0.1))            # (the call takes a float32)
+    G = _rand_G(m, d, 77 + d, scale=2.0)
+    scores, x = torch.randn(m, generator=torch.Generator().manual_seed(d)), _rand_G(1, d, 78 + d)[0]
+    out, sel = B.zeno_aggregate(G.cuda(), scores.cuda(), b)
+    ref, ref_sel = O.zeno_aggregate(G.numpy(), scores.numpy(), b)
+    assert np.array_equal(out.cpu().numpy(), ref.astype(np.float32)) and np.array_equal(sel.cpu().numpy(), ref_sel)
+    assert np.array_equal(B.zeno_mean(G.cuda()).cpu().numpy(), O.mean(G.numpy()).astype(np.float32))
+    x_next, _, _ = B.zeno_aggregate_update(G.cuda(), scores.cuda(), b, gamma, x.cuda())
+    assert np.array_equal(x_next.cpu().numpy(), O.zeno_update(x.numpy(), G.numpy(), scores.numpy(), b, gamma)[0].astype(np.float32))
+
+
 def test_median_with_nonfinite_entries(B):
     m, d = 6, 200
     G = _rand_G(m, d, 9)
