@@ -141,7 +141,7 @@ int64_t zeno_model_num_params(const zeno_model_t* model);
 /* Bytes of DEVICE scratch that zeno_score needs for m candidates and a batch of
  * n_r samples (activations of the m+1 forward passes, partial norms).  Returns
  * 0 for invalid arguments.  A convolutional model whose convolutions have at most eight (the first) and
- * multiples of eight above that (all others) input channels also runs, more slowly, without the last part of it, the
+ * multiples of eight above that (all others) input channels also runs, more slowly, with less: without room for
  * reordered kernels and maps; its scores then agree up to the order of float32 sums. */
 size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t n_r);
 
@@ -170,8 +170,8 @@ zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float*
  * arguments, kernels and results as zeno_score, bit for bit, but the scratch is a static device
  * array inside the library (ZENO_STATIC_SCRATCH_BYTES per GPU, held until the process ends), so
  * the call allocates nothing, frees nothing and takes no workspace.
- *   UNSUPPORTED if zeno_score_workspace_bytes(model, m, n_r), without the part of it that a convolutional
- *     model can do without, exceeds ZENO_STATIC_SCRATCH_BYTES
+ *   UNSUPPORTED if zeno_score_workspace_bytes(model, m, n_r), or the less that a convolutional model can do
+ *     with, exceeds ZENO_STATIC_SCRATCH_BYTES
  *     (32 MiB covers e.g. a 3072->512->10 model with m = 20, or the paper's m = 20, n_r = 4 on
  *     far larger models; it does not cover hundreds of candidates on 2048-wide layers);
  *   DEVICE if the array's address cannot be obtained on the current device.

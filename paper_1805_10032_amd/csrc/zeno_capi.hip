@@ -485,11 +485,10 @@ struct CnnPlan {
   size_t off_h0t, off_dt, dt_stride, sz_h0t;                                  // operands of the fully connected layer
   size_t off_wt, off_z0fc, off_dz, off_norm, off_diff, total;
   size_t off_slice_part, off_slice_cnt, sz_slice_cnt;   // K slices of the fully connected layer's launches
-  size_t least;                                         // bytes without the kernel fragments, which come last
   size_t off_pack, pack_stride;                         // kernel fragments of the m candidates and of x
   ConvPack pack[ZENO_MAX_CONV];
   int pack_jobs;
-  bool fragments;                                       // the model takes kernel fragments and split maps where the workspace holds them
+  bool fragments;                                       // kernel fragments and split maps take the place of the maps above
   size_t off_hs[ZENO_MAX_CONV], off_ds[2], ds_stride;   // split maps: of the pass at x (input of l), of the candidates (bytes)
 };
 
@@ -507,7 +506,8 @@ ConvLayer conv_layer(const zeno_model* mdl, int l) {
   return L;
 }
 
-CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
+// fragments: as the model runs with kernel fragments and split maps (nothing is laid out, total 0, if it cannot).
+CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r, bool fragments) {
   CnnPlan p;
   std::memset(&p, 0, sizeof(p));
   const int C = mdl->cnn.n_conv;
@@ -522,17 +522,20 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
     off = align_up(off + bytes, 256);
     return at;
   };
+  for (int l = 0; l < C && fragments; ++l)
+    if (!conv_takes_fragments(conv_layer(mdl, l), n_r, l)) return p;
+  p.fragments = fragments;
   size_t max_map = 0;
   for (int l = 0; l < C; ++l) {
     const size_t map = (size_t)n_r * mdl->map_h[l + 1] * mdl->map_w[l + 1] * mdl->map_c[l + 1];
     p.off_z0[l] = take(map * sizeof(float));
-    if (l + 1 < C) {
+    if (l + 1 < C && !fragments) {
       p.off_h0[l] = take(map * sizeof(float));
       if (map > max_map) max_map = map;
     }
   }
   p.d_stride = align_up(max_map * sizeof(float), 256) / sizeof(float);
-  if (C > 1)
+  if (C > 1 && !fragments)
     for (int i = 0; i < 2; ++i) p.off_d[i] = take(p.d_stride * sizeof(float) * m);
   p.sz_h0t = (size_t)p.n_pad * p.Kp * sizeof(float);
   p.off_h0t = take(p.sz_h0t);
@@ -548,11 +551,8 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
   p.sz_slice_cnt = align_up((size_t)kMaxSliceGroups * sizeof(unsigned int), 256);
   p.off_slice_cnt = take(p.sz_slice_cnt);
   p.off_diff = take((size_t)m * n_r * sizeof(double));
-  p.least = off;
   p.total = off;
-  p.fragments = true;
-  for (int l = 0; l < C; ++l) p.fragments = p.fragments && conv_takes_fragments(conv_layer(mdl, l), n_r, l);
-  if (!p.fragments) return p;
+  if (!fragments) return p;
   size_t max_split = 0;
   for (int l = 0; l < C; ++l) {
     const ConvLayer L = conv_layer(mdl, l);
@@ -580,9 +580,21 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r) {
   return p;
 }
 
+// The plan for a workspace of `bytes`: with fragments where these fit and need at most kFragmentBytes more than the plan without
+// (split maps are half as large again; several GiB more could be memory that a caller's candidates need).
+constexpr size_t kFragmentBytes = size_t(4) << 30;
+CnnPlan pick_cnn_plan(const zeno_model* mdl, int m, int n_r, size_t bytes) {
+  const CnnPlan plain = make_cnn_plan(mdl, m, n_r, false), f = make_cnn_plan(mdl, m, n_r, true);
+  return f.total != 0 && f.total <= bytes && f.total <= plain.total + kFragmentBytes ? f : plain;
+}
+size_t cnn_workspace_bytes(const zeno_model* mdl, int m, int n_r) {
+  const size_t plain = make_cnn_plan(mdl, m, n_r, false).total, picked = pick_cnn_plan(mdl, m, n_r, SIZE_MAX).total;
+  return picked > plain ? picked : plain;
+}
+
 zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const float* x, const float* G, int64_t ldg,
                                 int m, const zeno_batch_t* batch, float gamma, float rho, float* scores,
-                                unsigned char* ws, size_t ws_bytes, hipStream_t stream) {
+                                unsigned char* ws, hipStream_t stream) {
   const int C = p.n_conv, n_r = batch->n_r, N = mdl->cnn.fc_out;
   const float neg_inv_gamma = gamma > 0.f ? -1.0f / gamma : 0.f;
   double* norm_partials = reinterpret_cast<double*>(ws + p.off_norm);
@@ -598,7 +610,7 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     ZENO_TRY(launch_fill_zero(ws + p.off_h0t, p.sz_h0t, stream));
     ZENO_TRY(launch_fill_zero(ws + p.off_dt, p.dt_stride * m, stream));
   }
-  const bool fragments = p.fragments && ws_bytes >= p.total;
+  const bool fragments = p.fragments;
   auto conv_job = [&](int l, bool cand) {
     ConvJob j;
     std::memset(&j, 0, sizeof(j));
@@ -898,7 +910,7 @@ int64_t zeno_model_num_params(const zeno_model_t* model) { return model == nullp
 
 size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t n_r) {
   if (model == nullptr || m < 1 || m > ZENO_MAX_CANDIDATES || n_r < 1) return 0;
-  if (model->kind == 1) return n_r > kMaxPassRows ? 0 : make_cnn_plan(model, m, n_r).total;
+  if (model->kind == 1) return n_r > kMaxPassRows ? 0 : cnn_workspace_bytes(model, m, n_r);
   return make_plan(model, m, n_r).total;
 }
 
@@ -909,10 +921,10 @@ zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float*
   if (st != ZENO_OK) return st;
   if (model->kind == 1) {
     if (batch->n_r > kMaxPassRows) return ZENO_ERR_UNSUPPORTED;
-    const CnnPlan cp = make_cnn_plan(model, m, batch->n_r);
-    if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < cp.least) return ZENO_ERR_WORKSPACE;
+    const CnnPlan cp = pick_cnn_plan(model, m, batch->n_r, workspace_bytes);
+    if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < cp.total) return ZENO_ERR_WORKSPACE;
     return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, reinterpret_cast<unsigned char*>(workspace),
-                             workspace_bytes, reinterpret_cast<hipStream_t>(stream_));
+                             reinterpret_cast<hipStream_t>(stream_));
   }
   const Plan p = make_plan(model, m, batch->n_r);
   if (workspace == nullptr || !aligned(workspace, 256) || workspace_bytes < p.total) return ZENO_ERR_WORKSPACE;
@@ -926,12 +938,11 @@ zeno_status_t zeno_score_static(const zeno_model_t* model, const float* x, const
   if (st != ZENO_OK) return st;
   if (model->kind == 1) {
     if (batch->n_r > kMaxPassRows) return ZENO_ERR_UNSUPPORTED;
-    const CnnPlan cp = make_cnn_plan(model, m, batch->n_r);
-    if (cp.least > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;
+    const CnnPlan cp = pick_cnn_plan(model, m, batch->n_r, (size_t)ZENO_STATIC_SCRATCH_BYTES);
+    if (cp.total > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;
     unsigned char* cws = nullptr;
     if (static_scratch(&cws) != hipSuccess) return ZENO_ERR_DEVICE;
-    return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, cws, (size_t)ZENO_STATIC_SCRATCH_BYTES,
-                             reinterpret_cast<hipStream_t>(stream_));
+    return cnn_score_enqueue(model, cp, x, G, ldg, m, batch, gamma, rho, scores, cws, reinterpret_cast<hipStream_t>(stream_));
   }
   const Plan p = make_plan(model, m, batch->n_r);
   if (p.total > (size_t)ZENO_STATIC_SCRATCH_BYTES) return ZENO_ERR_UNSUPPORTED;
