@@ -51,6 +51,8 @@ def _fresh(obj, src, stamp):
         if src.startswith("zeno_layer") or src in ("zeno_krum.hip", "zeno_conv.hip", "zeno_small.hip"):
             deps.append(os.path.join(CSRC, "zeno_layer_impl.h"))
             deps.append(os.path.join(CSRC, "zeno_split.h"))
+        if src == "zeno_conv.hip":
+            deps.append(os.path.join(CSRC, "zeno_index.h"))
         return all(os.path.getmtime(d) < t for d in deps)
     except OSError:
         return False

@@ -73,6 +73,7 @@
 // The last convolution writes its outputs straight into the matrix-operand
 // order of the fully connected layer (rows = samples, columns = (y, x, c)), which the
 // streaming layer kernel then consumes.
+#include "zeno_index.h"
 #include "zeno_layer_impl.h"
 #include "zeno_split.h"
 
@@ -96,9 +97,6 @@ __device__ inline float conv_result(const ConvArgs& a, bool cand, float val, flo
 }
 
 constexpr int kDeepSteps = 36;   // matrix steps a workgroup of conv_deep_kernel stages at once
-
-// v / d for 0 <= v, v d < 2^32, with the multiplier ceil(2^32 / d) (0: d = 1)
-__device__ inline unsigned div_magic(unsigned v, unsigned magic) { return magic == 0u ? v : __umulhi(v, magic); }
 
 // Value `off` bytes behind a wave-uniform base (32-bit offsets: one register, no address arithmetic).
 template <typename V>
@@ -842,7 +840,7 @@ __device__ __forceinline__ void conv_packed(const ConvArgs& a, const ConvJob& J,
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
   const int kw = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ctiles = (L.Cout + 31) / 32;
-  const int pt = (int)div_magic((unsigned)tile, J.magic_ctiles), ct = tile - pt * ctiles;
+  const int pt = (int)div_any((unsigned)tile, (unsigned)ctiles, J.magic_ctiles), ct = tile - pt * ctiles;
   const float* __restrict__ P = cand ? a.G + (long long)s * a.ldg : a.x;
   const bool second = cand && J.D_in != nullptr;
   const unsigned char* H0 = reinterpret_cast<const unsigned char*>(J.H0_in);
@@ -943,7 +941,7 @@ __device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, i
   const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, h = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ctiles = (L.Cout + 31) / 32;
-  const int pt = (int)div_magic((unsigned)tile, J.magic_ctiles), ct = tile - pt * ctiles;
+  const int pt = (int)div_any((unsigned)tile, (unsigned)ctiles, J.magic_ctiles), ct = tile - pt * ctiles;
   const ConvTile<NP> T(a, J, pt);
   const unsigned plane = T.plane, r = T.r_first + (unsigned)(32 * wave + n), pix = T.first_pixel(J, r);
   const unsigned char* __restrict__ frags = a.pack + (long long)s * a.pack_stride + J.pack_off + (long long)ct * STEPS * kConvFragBytes + lane * 16;
@@ -1003,7 +1001,8 @@ __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& i
     }
     return true;
   }
-  tile = is_base ? b : (int)div_magic((unsigned)b, a.magic_cand);
+  // (blocks times candidates may exceed 2^32, and so may tiles times channel tiles)
+  tile = is_base ? b : (int)div_any((unsigned)b, (unsigned)a.n_cand, a.magic_cand);
   s = is_base ? 0 : b - tile * a.n_cand;
   return false;
 }
@@ -1039,8 +1038,6 @@ __global__ __launch_bounds__(512, 4) void conv_packed_kernel(const ConvArgs a) {
 // ---- host side
 constexpr long long kConvLdsMost = 160 * 1024;
 constexpr long long kConvLdsTwo = 80 * 1024;      // two workgroups per compute unit
-
-unsigned magic_for(long long d) { return d <= 1 ? 0u : (unsigned)(((1ull << 32) + (unsigned long long)d - 1) / (unsigned long long)d); }
 
 // Most border rows that np consecutive positions touch.
 long long most_border_rows(const ConvLayer& L, int np) {
@@ -1097,7 +1094,7 @@ hipError_t plan_tiles(ConvArgs& a, int np_most, int wc, F job_lds, long long* ld
   *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0) +
            ((long long)a.pack_jobs * (a.pack_x + 1) + waves - 1) / waves;
   if (a.fc_N > 0) *total += a.n_r + ((long long)a.fc_N * (a.fc_Kp / 4) + 64 * waves * kFcPieces - 1) / (64 * waves * kFcPieces);
-  if (*total > (1ll << 30) || *lds > kConvLdsMost) return hipErrorInvalidValue;
+  if (*total > kConvMostBlocks || *lds > kConvLdsMost) return hipErrorInvalidValue;
   a.base_blocks = (int)blocks[0];
   a.cand_blocks = (int)blocks[1];
   a.magic_cand = magic_for(a.n_cand);

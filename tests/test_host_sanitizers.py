@@ -38,3 +38,14 @@ def test_argument_layer_under_address_and_ub_sanitizers(tmp_path):
     assert res.returncode == 0, res.stdout + res.stderr
     assert "host checks passed" in res.stdout
     assert "runtime error" not in res.stderr and "AddressSanitizer" not in res.stderr, res.stderr
+
+
+def test_index_arithmetic_of_the_convolution_kernels(tmp_path):
+    """The quick divisions against plain ones over everything a launch may meet (1 .. 1024 candidates and any number of channel
+    tiles, up to the largest grid): a quotient one too large would read the row before the candidates' matrix."""
+    exe = str(tmp_path / "index_checks")
+    subprocess.run(["g++", "-std=c++17", "-O2", "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1805_10032_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "sanitize", "index_checks.cpp"), "-o", exe], check=True, capture_output=True, text=True)
+    res = subprocess.run([exe], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0 and "index checks passed" in res.stdout, res.stdout + res.stderr
