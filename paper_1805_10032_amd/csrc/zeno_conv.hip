@@ -210,7 +210,7 @@ __device__ void fc_sample(const ConvArgs& a, int r, float* red) {
     for (int i = 0; i < 8; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
     for (int q = threadIdx.x; q < quads; q += T) {
-      const f32x4 hv = *reinterpret_cast<const f32x4*>(h + (q >> 1) * 256 + (q & 1) * 128);
+      const f32x4 hv = *reinterpret_cast<const f32x4*>(h + operand_column(4 * q));
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const f32x4 w = *reinterpret_cast<const f32x4_a4*>(W + (long long)(n0 + i < a.fc_N ? n0 + i : n0) * a.fc_K + 4 * q);
@@ -220,7 +220,7 @@ __device__ void fc_sample(const ConvArgs& a, int r, float* red) {
     }
     const int k = 4 * quads + (int)threadIdx.x;      // up to three columns behind the quads
     const bool rest = k < a.fc_K;
-    const float hr = rest ? h[(k >> 3) * 256 + ((k >> 2) & 1) * 128 + (k & 3)] : 0.f;
+    const float hr = rest ? h[operand_column(k)] : 0.f;
     double* sums = reinterpret_cast<double*>(red);
     __syncthreads();
 #pragma unroll

@@ -20,5 +20,8 @@ constexpr unsigned div_any(unsigned v, unsigned d, unsigned magic) {
   return q * d > v ? q - 1u : q;
 }
 
+// Floats between column 0 and column k of a row in float32 matrix-operand order (32 rows x 8 columns, half by half of the columns).
+constexpr long long operand_column(int k) { return (long long)(k >> 3) * 256 + ((k >> 2) & 1) * 128 + (k & 3); }
+
 }  // namespace zeno
 #endif

@@ -42,6 +42,12 @@ int main() {
     for (unsigned v = most < 3000 ? 0 : most - 3000; v < most; ++v) CHECK(div_magic(v, magic) == v / d);
   }
   CHECK(div_magic(4120u * 1023u + 1022u, magic_for(1023)) == 4121u && div_any(4120u * 1023u + 1022u, 1023u, magic_for(1023)) == 4120u);
+  // columns of a wide operand row: the offsets pass 2^31 floats from column 2^26 on
+  const int columns[] = {0, 3, 4, 7, 8, 175, (1 << 26) - 1, 1 << 26, (1 << 26) + 5, 0x7fffffff};
+  for (int k : columns) {
+    const long long group = k / 8, half = k % 8 / 4;
+    CHECK(operand_column(k) == group * 8 * 32 + half * 4 * 32 + k % 4);
+  }
   std::puts("index checks passed");
   return 0;
 }

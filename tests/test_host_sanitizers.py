@@ -42,7 +42,8 @@ def test_argument_layer_under_address_and_ub_sanitizers(tmp_path):
 
 def test_index_arithmetic_of_the_convolution_kernels(tmp_path):
     """The quick divisions against plain ones over everything a launch may meet (1 .. 1024 candidates and any number of channel
-    tiles, up to the largest grid): a quotient one too large would read the row before the candidates' matrix."""
+    tiles, up to the largest grid): a quotient one too large would read the row before the candidates' matrix.  The columns of an
+    operand row, up to the widest."""
     exe = str(tmp_path / "index_checks")
     subprocess.run(["g++", "-std=c++17", "-O2", "-fsanitize=undefined", "-fno-sanitize-recover=undefined",
                     "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_1805_10032_amd", "csrc"),
