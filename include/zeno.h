@@ -170,8 +170,7 @@ zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float*
  * arguments, kernels and results as zeno_score, bit for bit, but the scratch is a static device
  * array inside the library (ZENO_STATIC_SCRATCH_BYTES per GPU, held until the process ends), so
  * the call allocates nothing, frees nothing and takes no workspace.
- *   UNSUPPORTED if zeno_score_workspace_bytes(model, m, n_r), or the less that a convolutional model can do
- *     with, exceeds ZENO_STATIC_SCRATCH_BYTES
+ *   UNSUPPORTED if zeno_score_workspace_bytes(model, m, n_r) exceeds ZENO_STATIC_SCRATCH_BYTES
  *     (32 MiB covers e.g. a 3072->512->10 model with m = 20, or the paper's m = 20, n_r = 4 on
  *     far larger models; it does not cover hundreds of candidates on 2048-wide layers);
  *   DEVICE if the array's address cannot be obtained on the current device.

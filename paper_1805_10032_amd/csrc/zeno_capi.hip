@@ -1,6 +1,7 @@
 // C ABI of the Zeno library: argument checks, workspace layout and launch
 // sequencing.  Every step of the path runs in the HIP kernels of this library;
 // the host only validates and enqueues.
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -489,7 +490,7 @@ struct CnnPlan {
   ConvPack pack[ZENO_MAX_CONV];
   int pack_jobs;
   bool fragments;                                       // kernel fragments and split maps take the place of the maps above
-  size_t off_hs[ZENO_MAX_CONV], off_ds[2], ds_stride;   // split maps: of the pass at x (input of l), of the candidates (bytes)
+  size_t off_hs[ZENO_MAX_CONV], off_ds[2], ds_stride[2];   // split maps: of the pass at x (input of l), of the candidates (bytes; even layers' results, odd ones')
 };
 
 ConvLayer conv_layer(const zeno_model* mdl, int l) {
@@ -553,7 +554,6 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r, bool fragments) {
   p.off_diff = take((size_t)m * n_r * sizeof(double));
   p.total = off;
   if (!fragments) return p;
-  size_t max_split = 0;
   for (int l = 0; l < C; ++l) {
     const ConvLayer L = conv_layer(mdl, l);
     ConvPack& k = p.pack[l];
@@ -570,26 +570,28 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r, bool fragments) {
     if (l == 0) continue;
     const size_t bytes = split_map_bytes(n_r * L.Hin * L.Win, L.Cin);
     p.off_hs[l] = take(bytes);
-    if (bytes > max_split) max_split = bytes;
+    size_t& stride = p.ds_stride[(l - 1) & 1];
+    stride = std::max(stride, align_up(bytes, 256));
   }
-  p.ds_stride = align_up(max_split, 256);
-  if (C > 1)
-    for (int i = 0; i < 2; ++i) p.off_ds[i] = take(p.ds_stride * m);
+  for (int i = 0; i < 2; ++i) p.off_ds[i] = take(p.ds_stride[i] * m);
   p.off_pack = take(p.pack_stride * (m + 1));
   p.total = off;
   return p;
 }
 
 // The plan for a workspace of `bytes`: with fragments where these fit and need at most kFragmentBytes more than the plan without
-// (split maps are half as large again; several GiB more could be memory that a caller's candidates need).
+// (split maps are half as large again; several GiB more could be memory that a caller's candidates need).  A model that fits the
+// static scratch array without them only does without them in every workspace, so that both entry points sum in the same order.
+// A workspace that is too small for the plan without is too small for either.
 constexpr size_t kFragmentBytes = size_t(4) << 30;
 CnnPlan pick_cnn_plan(const zeno_model* mdl, int m, int n_r, size_t bytes) {
-  const CnnPlan plain = make_cnn_plan(mdl, m, n_r, false), f = make_cnn_plan(mdl, m, n_r, true);
-  return f.total != 0 && f.total <= bytes && f.total <= plain.total + kFragmentBytes ? f : plain;
-}
-size_t cnn_workspace_bytes(const zeno_model* mdl, int m, int n_r) {
-  const size_t plain = make_cnn_plan(mdl, m, n_r, false).total, picked = pick_cnn_plan(mdl, m, n_r, SIZE_MAX).total;
-  return picked > plain ? picked : plain;
+  const CnnPlan plain = make_cnn_plan(mdl, m, n_r, false);
+  CnnPlan f = make_cnn_plan(mdl, m, n_r, true);
+  if (f.total == 0) return plain;
+  f.total = std::max(f.total, plain.total);
+  const size_t fixed = ZENO_STATIC_SCRATCH_BYTES;
+  const bool take = f.total <= plain.total + kFragmentBytes && (f.total <= fixed || plain.total > fixed);
+  return take && f.total <= bytes ? f : plain;
 }
 
 zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const float* x, const float* G, int64_t ldg,
@@ -636,12 +638,12 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
       j.D_in_stride = (long long)p.d_stride;
       if (fragments) {
         j.D_in = reinterpret_cast<const float*>(ws + p.off_ds[(l - 1) & 1]);
-        j.D_in_stride = (long long)(p.ds_stride / sizeof(float));
+        j.D_in_stride = (long long)(p.ds_stride[(l - 1) & 1] / sizeof(float));
       }
     }
     if (j.split_out) {
       j.out = reinterpret_cast<float*>(ws + p.off_ds[l & 1]);
-      j.out_stride = (long long)(p.ds_stride / sizeof(float));
+      j.out_stride = (long long)(p.ds_stride[l & 1] / sizeof(float));
       return j;
     }
     j.out = reinterpret_cast<float*>(l + 1 == C ? ws + p.off_dt : ws + p.off_d[l & 1]);
@@ -910,7 +912,7 @@ int64_t zeno_model_num_params(const zeno_model_t* model) { return model == nullp
 
 size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t n_r) {
   if (model == nullptr || m < 1 || m > ZENO_MAX_CANDIDATES || n_r < 1) return 0;
-  if (model->kind == 1) return n_r > kMaxPassRows ? 0 : cnn_workspace_bytes(model, m, n_r);
+  if (model->kind == 1) return n_r > kMaxPassRows ? 0 : pick_cnn_plan(model, m, n_r, SIZE_MAX).total;
   return make_plan(model, m, n_r).total;
 }
 

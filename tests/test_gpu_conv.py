@@ -83,6 +83,28 @@ def test_cnn_on_the_static_scratch_array(B):
     assert torch.equal(_gpu_scores(B, w, static=True), _gpu_scores(B, w))
 
 
+@pytest.mark.parametrize("hw,conv_c,m,n_r", [
+    (14, [32, 32, 64, 64], 20, 4),    # kernel fragments and split maps fit the array
+    (16, [32, 32, 64, 64], 20, 4),    # they do not, the plain maps do
+    (32, [32, 32, 64, 64], 10, 4),
+    (8, [64, 48], 23, 2),
+])
+def test_cnn_static_scratch_and_workspace_sum_in_the_same_order(B, hw, conv_c, m, n_r):
+    """Bit for bit the same scores from both entry points for every model that the static array holds."""
+    desc = dict(in_h=hw, in_w=hw, in_c=3, conv_c=conv_c, conv_stride=[1, 2, 1, 2][:len(conv_c)], fc_out=10, has_bias=True)
+    w = WL.make_cnn_workload("cnn_static", 40, desc, m, 3, n_r, 0.1, 1e-3, n_flip=2, worker_batch=4)
+    _check(B, w)
+    assert torch.equal(_gpu_scores(B, w, static=True), _gpu_scores(B, w))
+
+
+def test_cnn_beyond_the_static_scratch_array(B):
+    desc = dict(in_h=32, in_w=32, in_c=3, conv_c=[32, 32, 64, 64], conv_stride=[1, 2, 1, 2], fc_out=10, has_bias=True)
+    w = WL.make_cnn_workload("cnn_static", 41, desc, 20, 3, 4, 0.1, 1e-3, worker_batch=2)
+    with pytest.raises(B.ZenoError) as e:
+        _gpu_scores(B, w, static=True)
+    assert e.value.status == 2
+
+
 def test_cnn_nonfinite_rows_and_workspace_contents(B):
     desc = dict(in_h=6, in_w=6, in_c=2, conv_c=[6, 6], conv_stride=[1, 2], fc_out=3, has_bias=True)
     w = WL.make_cnn_workload("cnn_nf", 38, desc, 7, 2, 5, 0.1, 1e-3)
