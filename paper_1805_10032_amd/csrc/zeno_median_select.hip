@@ -53,6 +53,7 @@ namespace {
 
 constexpr unsigned kNegInfKey = 0x807fffffu;            // signed-order key of -inf: subtracted, so that NaNs of either sign wrap to the top
 constexpr unsigned kPosInf = 0x7f800000u - kNegInfKey;  // keys above this one are NaNs
+constexpr unsigned kZero = 0u - kNegInfKey;             // key of +0; that of -0 is the one below
 
 __device__ inline unsigned sel_key(float f) {
   const int k = __float_as_int(f);
@@ -432,7 +433,7 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
           const bool in_y = (want_y < 0) ? behind : (want_y < 4 * P) & (ky <= last);
           const bool low = !behind & ((!have_x & (want_x < 0)) | (!have_y & (want_y < 0)));
           const bool got_x = !have_x & in_x, got_y = !have_y & in_y;
-          x = got_x ? (want_x < 0 ? after : sel_key(kx + 0.f)) : x;   // (-0 + 0 is +0: one zero only)
+          x = got_x ? (want_x < 0 ? after : sel_key(kx + 0.f)) : x;   // (-0 + 0 is +0: one zero only, for now)
           y = got_y ? (want_y < 0 ? after : sel_key(ky + 0.f)) : y;
           const bool unreached = !low & !((have_x | got_x) & (have_y | got_y));
           have_x |= got_x;
@@ -445,7 +446,21 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
           q = from + (float)((int)k - kAim - (int)(unreached ? c : c_hi)) * slope;
         }
       }
-      // (keys tell the two zeros apart, comparisons of floats do not)
+      // Comparisons of floats take the two zeros for one: a zero of some rank is the negative one where more values have their
+      // sign set.
+      const bool zero_x = have_x & (x == kZero), zero_y = have_y & (y == kZero);
+      if (__ballot(zero_x | zero_y) != 0) {
+        unsigned c = 0u, signs = 0u;
+#pragma unroll
+        for (int i = 0; i < NK; ++i) {                   // the signs of 32 values in a register
+          signs = __builtin_amdgcn_alignbit(signs, u[i], 31);
+          if (i % 32 == 31 || i == NK - 1) c += __builtin_popcount(signs), signs = 0u;
+        }
+        c = lanes_sum<P>(c);
+        x = zero_x & (k < c) ? kZero - 1u : x;
+        y = zero_y & (k + 1u < c) ? kZero - 1u : y;
+      }
+      // (keys tell the two zeros apart)
       lo = flo > -__builtin_inff() ? sel_key(flo == 0.f ? -0.f : flo) : 0u;
       hi = fhi < __builtin_inff() ? sel_key(fhi == 0.f ? -0.f : fhi) : UINT_MAX;
     }

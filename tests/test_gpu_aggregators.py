@@ -146,6 +146,34 @@ def test_median_by_selection_with_ties_and_nonfinite_entries(B, m, row_align):
     assert np.array_equal(med[ok], ref[ok])
 
 
+@pytest.mark.parametrize("m", [1, 2, 7, 20, 33, 100, 128, 129, 300, 513, 1024])
+def test_median_keeps_the_sign_of_zero(B, m):
+    """-0 sorts below +0 whatever the other columns hold: columns of zeros of either sign with the middle on either side of the
+    line between them, alone and around other values, beside columns that the search for m > 128 finds in other ways."""
+    d = 192
+    g = torch.Generator().manual_seed(8000 + m)
+    U = torch.rand((m, d), generator=g)
+    X = torch.randn((m, d), generator=g)
+    zero = torch.where(torch.rand((m, d), generator=g) < torch.linspace(0.3, 0.7, d), -0.0, 0.0)
+    G = X.clone()
+    for kind, part in ((0, 1.1), (1, 0.6), (2, 0.2), (3, 0.05)):            # share of zeros in the column
+        cols = torch.arange(d) % 6 == kind
+        G[:, cols] = torch.where(U < part, zero, X)[:, cols]
+    G[:, 4::12] = torch.round(X * 2)[:, 4::12]                               # few values, zeros of either sign among them
+    G[m // 2:, 0::24] = float("nan")
+    G[m // 2, 1::30] = float("inf")
+    v = np.sort(G.numpy(), axis=0)                                           # NaN last; the zeros of a column in any order
+    n = (G.numpy() < 0).sum(0) + ((G.numpy() == 0) & np.signbit(G.numpy())).sum(0)
+    k = (m - 1) // 2
+    def at(r):
+        return np.where(v[r] == 0, np.where(r < n, np.float32(-0.0), np.float32(0.0)), v[r]).astype(np.float64)
+    ref = (at(k) if m & 1 else 0.5 * (at(k) + at(k + 1))).astype(np.float32)
+    med = B.zeno_median(G.cuda()).cpu().numpy()
+    ok = ~np.isnan(ref)
+    assert np.array_equal(np.isnan(med), ~ok)
+    assert np.array_equal(med[ok].view(np.int32), ref[ok].view(np.int32))
+
+
 @pytest.mark.parametrize("m,d", [(129, 1), (160, 65), (161, 63), (288, 64), (289, 129), (320, 200), (321, 33), (384, 31),
                                  (385, 32), (575, 97), (833, 64), (960, 5), (961, 70), (1023, 257), (1024, 1)])
 def test_median_by_selection_at_the_edges_of_its_tiles(B, m, d):
