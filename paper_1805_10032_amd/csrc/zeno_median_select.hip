@@ -16,8 +16,10 @@
 //    smallest of the fourth values, some thirteen values for P = 8: x and y are in there, or the next pivot is the successor of
 //    that value, or lies lower.
 //  * Lanes that agree on a median may have met a value that fills the middle of the column (the zero of an inactive unit, colluding
-//    rows): that value and its successor are counted first.
-//  * Columns that three such passes do not finish, and waves whose lanes agree too often or whose second pivot is far off, go on
+//    rows): that value and its successor are counted first.  Where lanes agree in most columns of a wave, these hold few values
+//    (signs, quantised gradients): the lanes' other medians are tried in the same way, or, with some ten copies of a value only, the
+//    bracket follows at once.
+//  * Columns that three passes with lists do not finish, and waves whose second pivot is far off, go on
 //    with a bracket lo <= x < hi of keys whose order is that of the values: the pivot is interpolated between the bounds (as
 //    floats) at the rank wanted, one pass gives the number of keys below it and the keys next to it on either side (three
 //    instructions per key), and the bounds move to these, so that a block of equal keys closes the bracket as well.  It ends when
@@ -39,9 +41,12 @@
 // Bound by vector instructions: 26 per value for m = 300 (counted: 2.05e8 wave instructions on normally distributed columns, 39
 // per value and 2.87e8 before, when four pivots were counted first and all further passes moved by one key).  Measured (MI355X, before ->
 // now; calls in a series on buffers in turn): m = 300, d = 1.58 M, a worker's gradients around a common one, a third of the rows
-// faulty 602 -> 500 us (3.8 TB/s), m = 129, d = 3.0 M 560 -> 495, m = 512, d = 0.8 M 548 -> 427, m = 1024, d = 0.4 M 629 -> 525; normally
-// distributed columns 15-27 % shorter; a fifth of the rows NaN 644 -> 570 for m = 300; 40 % zeros 588 -> 410; columns of some
-// dozen different values are the exception, 536 -> 575 for m = 300 and 450 -> 625 for m = 129.
+// faulty 602 -> 510 us (3.7 TB/s), m = 129, d = 3.0 M 560 -> 468, m = 512, d = 0.8 M 548 -> 434, m = 1024, d = 0.4 M 629 -> 525; normally
+// distributed columns 18-28 % shorter; a fifth of the rows NaN 576 -> 465 for m = 300; 40 % zeros 588 -> 372.  Columns of few values,
+// normally distributed and rounded to a half, a quarter, an eighth, a sixteenth of their deviation (before -> lists alone -> now): m = 300
+// 535 -> 568 -> 396, 538 -> 770 -> 517, 540 -> 707 -> 535, 547 -> 560 -> 543; m = 129 448 -> 621 -> 364, 450 -> 667 -> 467, 457 ->
+// 506 -> 475, 463 -> 431 -> 454; m = 1024 486 -> 500 -> 375, 529 -> 829 -> 458, 529 -> 863 -> 607, 533 -> 788 -> 594: with one
+// workgroup per compute unit its slowest wave decides.
 #include <limits.h>
 #include <stdint.h>
 
@@ -75,6 +80,12 @@ __device__ inline unsigned dpp(unsigned v) {
 }
 constexpr int kRun = 8;                                 // tiles a workgroup takes one after the other
 constexpr int kAim = 5;                                 // ranks by which the collecting pivot aims below the one wanted
+// Columns of few values, by the copies of the value that lanes agree on, squared, per row.  Up to 1 / kSome the lists find x sooner
+// than the bracket (us, lists / bracket from the lanes' medians: m = 512, 3 copies 439 / 477; m = 700, 9 copies 577 / 543; m = 1024,
+// 6 copies 556 / 582, 13 copies 670 / 606); from kMany on the lanes' medians, kTries of them after the first (bracket / tries:
+// m = 300, 15 copies 535 / 590, 30 copies 523 / 496; m = 1024, 50 copies 600 / 642, 100 copies 593 / 459; one try less costs 2-6 %).
+constexpr int kTries = 3;
+constexpr unsigned kMany = 3, kSome = 10;
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kMirror8 = 0x141, kMirror16 = 0x140;  // lane permutations inside 4, 4, 8, 16 lanes
 // Reductions over the P lanes of a column; every lane receives the result.
 template <int P>
@@ -374,29 +385,57 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
       float p = lanes_add<P>(w[0]) * (1.f / P);
       const float slope = lanes_add<P>(__builtin_fabsf(w[0] - p)) * rank_scale;
       // lanes that agree on a value: it may fill the middle of the column (the zero of an inactive unit, colluding rows)
-      const bool twin = (wb == dpp<kXor1>(wb)) | (wb == dpp<kXor2>(wb)) | (wb == dpp<kMirror8>(wb));
-      const float apart = twin ? __builtin_fabsf(w[0] - p) : __builtin_inff(), least = lanes_fmin<P>(apart);
-      const unsigned twin_key = ~lanes_min<P>((twin & (apart == least)) ? ~sel_key(w[0] + 0.f) : UINT_MAX);
-      const unsigned long long twins = __ballot(twin);
+      const bool twin = (wb == dpp<kXor1>(wb)) | (wb == dpp<kXor2>(wb)) | (wb == dpp<kMirror8>(wb)) | (P == 16 && wb == dpp<kMirror16>(wb));
       unsigned after = 0u;                               // the key whose successor the pivot is, where no wanted key is below it
       bool behind = false;                               // whether the pivot is such a one
-      if (twins != 0) {
-        const float tv = twin_key != 0u ? sel_float(twin_key) : p, tn = twin_key != 0u ? sel_float(twin_key + 1u) : p;
-        const unsigned b = lanes_sum<P>(count_below(u, tv) | count_below(u, tn) << 16);
-        const unsigned c0 = b & 0xffffu, c1 = b >> 16;
-        bound(tv, c0);
-        bound(tn, c1);
-        const bool hit = (c0 <= k) & (c1 > k);
-        x = hit ? twin_key : x;
-        y = hit ? twin_key : y;
-        have_x = hit;
-        have_y |= hit & (c1 > k + 1u);
-        after = twin_key;
-        behind = hit;
-        p = hit ? tn : p;
+      bool few = false;                                  // columns of few values, which the slope does not find
+      if (__ballot(twin) != 0) {
+        // A lane's median and its successor are pivots: the values of rank k and k + 1 end here if they are that value.
+        bool own = twin;                                 // lanes whose median is tried
+        float aim_at = p;
+#pragma unroll 1
+        for (int tries = 0;; ++tries) {
+          const float apart = own ? __builtin_fabsf(w[0] - aim_at) : __builtin_inff(), least = lanes_fmin<P>(apart);
+          const unsigned key = ~lanes_min<P>((own & (apart == least)) ? ~sel_key(w[0] + 0.f) : UINT_MAX);   // 0: none
+          const float tv = key != 0u ? sel_float(key) : p, tn = key != 0u ? sel_float(key + 1u) : p;
+          const unsigned b = lanes_sum<P>(count_below(u, tv) | count_below(u, tn) << 16);
+          const unsigned c0 = b & 0xffffu, c1 = b >> 16;
+          bound(tv, c0);
+          bound(tn, c1);
+          const bool got_x = (key != 0u) & !have_x & (c0 <= k) & (c1 > k), got_y = (key != 0u) & !have_y & (c0 <= k + 1u) & (c1 > k + 1u);
+          x = got_x ? key : x;
+          y = got_y ? key : y;
+          have_x |= got_x;
+          have_y |= got_y;
+          const bool left = !(have_x & have_y);
+          if (tries == 0) {
+            behind = got_x;
+            after = key;
+            if (__ballot(left) == 0) break;
+            // Few values: lanes agree on one with some copies, in (nearly) all columns, or in half of them and not on account of a
+            // single value with many.
+            const unsigned copies = (c1 - c0) * (c1 - c0);
+            const int agreed = __popcll(__ballot(key != 0u)), some = __popcll(__ballot(kSome * copies >= (unsigned)m)),
+                      many = __popcll(__ballot(copies >= kMany * (unsigned)m));
+            few = 2 * some >= agreed && (agreed >= (P == 8 ? 48 : 64) || (agreed >= 32 && 2 * many < agreed));
+            if (!few) {
+              p = got_x ? tn : p;
+              break;
+            }
+            if (many < 32) {
+              // the bracket finds one of many values sooner; its other end is the outermost of the lanes' medians
+              const float side = c1 <= k ? -lanes_fmin<P>(-w[0]) : lanes_fmin<P>(w[0]);
+              bound(side, lanes_sum<P>(count_below(u, side)));
+              break;
+            }
+          }
+          // the next one: for y the lowest above x, for x the one nearest to where the slope puts it
+          aim_at = have_x ? sel_float(x) : c1 <= k ? tv + (float)(k - c1) * slope : tv - (float)(c0 - k) * slope;
+          own = left & (have_x ? w[0] > aim_at : (w[0] >= flo) & (w[0] < fhi));
+          if (__ballot(own) == 0 || tries == kTries) break;
+        }
       }
-      // half the lanes agreeing on a value: columns of few values, which the slope does not find
-      if ((__ballot(!(have_x & have_y)) != 0) & (__popcll(twins) < 32)) {
+      if ((__ballot(!(have_x & have_y)) != 0) & !few) {
         unsigned c = lanes_sum<P>(count_below(u, p));
         bound(p, c);
         // a second pivot, at rank k as far as the scale tells, and one a few ranks below it

@@ -194,6 +194,26 @@ def test_median_by_selection_at_the_edges_of_its_tiles(B, m, d):
     assert np.array_equal(med[ok], ref[ok])
 
 
+@pytest.mark.parametrize("m", [129, 130, 200, 300, 321, 512, 700, 1024])
+def test_median_by_selection_of_few_values(B, m):
+    """m > 128, columns of few to some hundred values, the same kind for all columns of a wave: the lanes' medians agree in all, most
+    or few columns, on values with many copies or some; the middle inside a block of equal values and at its edges."""
+    kinds = [0.25, 0.5, 1.0, 2.0, 4.0, 8.0, 16.0, 32.0, 64.0]
+    d = 64 * len(kinds)
+    g = torch.Generator().manual_seed(8500 + m)
+    G = torch.randn((m, d), generator=g)
+    for i, q in enumerate(kinds):
+        cols = slice(64 * i, 64 * i + 64)
+        G[:, cols] = torch.round(G[:, cols] * q) / q
+        G[:, 64 * i + 32: 64 * i + 64] *= 0.1 + torch.rand(32, generator=g)    # a scale of its own, as quantised gradients have
+    G[m // 3, 5::37] = float("nan")
+    G[: m // 2 + 1, 64 * 3 + 3] = 0.5                                          # a block that ends at the middle, and next to it
+    G[: (m + 1) // 2, 64 * 4 + 4] = -3.0
+    G[: m // 2, 64 * 5 + 5] = 100.0
+    med = B.zeno_median(G.cuda()).cpu().numpy()
+    assert np.array_equal(med, O.median(G.numpy()).astype(np.float32), equal_nan=True)
+
+
 @pytest.mark.parametrize("m,d", [(130, 524_388), (320, 262_500), (1024, 66_000)])
 def test_median_by_selection_over_many_tiles(B, m, d):
     """m > 128, more tiles than one generation of workgroups takes: every column near a multiple of 32 Ki columns and a random
