@@ -203,6 +203,7 @@ __device__ inline void lds_copy4(const float* p, long long step, unsigned lds_of
 // The lane permutations read a register two instructions after it was written at the earliest; the compiler keeps that distance
 // to its own instructions, but does not look into assembly for the write.
 __device__ inline void settle(unsigned& v) { asm("s_nop 1" : "+v"(v)); }
+__device__ inline void settle(unsigned& v, float& w) { asm("s_nop 1" : "+v"(v), "+v"(w)); }
 
 // Number of values below p, two instructions per value, as floats or as keys.  The comparison results go through four scalar
 // register pairs: left to itself the compiler sends all of them through vcc and has to wait two cycles between a comparison and
@@ -251,7 +252,7 @@ __device__ inline unsigned count_and_collect(const unsigned (&u)[NK], float p, f
       asm("v_min_f32_e32 %0, %0, %1" : "+v"(m1) : "v"(t[q]));
     }
   }
-  settle(c);
+  settle(c, m1);
   first[0] = m1, first[1] = m2, first[2] = m3, first[3] = m4;
   return c;
 }
