@@ -197,48 +197,51 @@ __device__ void pack_fragment(const ConvArgs& a, int s, int job) {
 }
 
 // The pass at x through a narrow fully connected layer, next to the candidates' last convolution, which it does not depend on
-// (a launch of the layer kernel behind it took 13 us, most of it latency; here the step is 11 us shorter).  One sample per
-// workgroup: a thread sums its quads of columns in float32, lanes by xor-shuffle tree and waves in order in float64.
-__device__ void fc_sample(const ConvArgs& a, int r, float* red) {
+// (a launch of the layer kernel behind it took 13 us, most of it latency; the step of 32-32-64-64 channels is 11 us shorter).  Eight
+// outputs of one sample per workgroup: a thread sums its quads of columns in float32, lanes by xor-shuffle tree and waves in order in
+// float64.  Against the launch of its own on 220 random models (64 to 9 M columns, 1 to 32 outputs, 1 to 128 samples): the step 1.13
+// times as fast, two of them slower, with more than a million columns (0.96 and 0.98; four others of that size 1.03-1.14).  With all
+// outputs of a sample in one workgroup, which read up to 32 rows of the weights one after the other, 41 were slower, by up to 42 %
+// (launch of its own -> one workgroup -> now, 32 outputs: 5000 columns 57 -> 65 -> 53 us, 123008 columns 322 -> 508 -> 290).
+constexpr int kFcOutputs = 8;
+inline __host__ __device__ int fc_groups(int N) { return (N + kFcOutputs - 1) / kFcOutputs; }
+__device__ void fc_sample(const ConvArgs& a, int r, int n0, float* red) {
   const float* __restrict__ W = a.x + a.fc_w_off;
   const float* __restrict__ h = a.fc_h0 + tiled_index<false>(r, 0, a.fc_Kp);
   const int T = blockDim.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int quads = a.fc_K >> 2;
-  for (int n0 = 0; n0 < a.fc_N; n0 += 8) {
-    f32x4 sum[8];
+  f32x4 sum[kFcOutputs];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < kFcOutputs; ++i) sum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll 2
-    for (int q = threadIdx.x; q < quads; q += T) {
-      const f32x4 hv = *reinterpret_cast<const f32x4*>(h + operand_column(4 * q));
+  for (int q = threadIdx.x; q < quads; q += T) {
+    const f32x4 hv = *reinterpret_cast<const f32x4*>(h + operand_column(4 * q));
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const f32x4 w = *reinterpret_cast<const f32x4_a4*>(W + (long long)(n0 + i < a.fc_N ? n0 + i : n0) * a.fc_K + 4 * q);
+    for (int i = 0; i < kFcOutputs; ++i) {
+      const f32x4 w = *reinterpret_cast<const f32x4_a4*>(W + (long long)(n0 + i < a.fc_N ? n0 + i : n0) * a.fc_K + 4 * q);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(hv[e], w[e], sum[i][e]);
-      }
+      for (int e = 0; e < 4; ++e) sum[i][e] = __builtin_fmaf(hv[e], w[e], sum[i][e]);
     }
-    const int k = 4 * quads + (int)threadIdx.x;      // up to three columns behind the quads
-    const bool rest = k < a.fc_K;
-    const float hr = rest ? h[operand_column(k)] : 0.f;
-    double* sums = reinterpret_cast<double*>(red);
-    __syncthreads();
+  }
+  const int k = 4 * quads + (int)threadIdx.x;        // up to three columns behind the quads
+  const bool rest = k < a.fc_K;
+  const float hr = rest ? h[operand_column(k)] : 0.f;
+  double* sums = reinterpret_cast<double*>(red);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int n = n0 + i < a.fc_N ? n0 + i : n0;
-      double t = ((double)sum[i][0] + sum[i][1]) + ((double)sum[i][2] + sum[i][3]);
-      if (rest) t += (double)hr * (double)W[(long long)n * a.fc_K + k];
+  for (int i = 0; i < kFcOutputs; ++i) {
+    const int n = n0 + i < a.fc_N ? n0 + i : n0;
+    double t = ((double)sum[i][0] + sum[i][1]) + ((double)sum[i][2] + sum[i][3]);
+    if (rest) t += (double)hr * (double)W[(long long)n * a.fc_K + k];
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
-      if (lane == 0) sums[wave * 8 + i] = t;
-    }
-    __syncthreads();
-    if (threadIdx.x < 8 && n0 + (int)threadIdx.x < a.fc_N) {
-      const int n = n0 + (int)threadIdx.x;
-      double t = a.fc_b_off >= 0 ? (double)a.x[a.fc_b_off + n] : 0.0;
-      for (int w = 0; w < T / 64; ++w) t += sums[w * 8 + threadIdx.x];
-      a.fc_z0[(long long)r * a.fc_N + n] = (float)t;
-    }
+    for (int off = 32; off > 0; off >>= 1) t += __shfl_xor(t, off, 64);
+    if (lane == 0) sums[wave * kFcOutputs + i] = t;
+  }
+  __syncthreads();
+  if (threadIdx.x < kFcOutputs && n0 + (int)threadIdx.x < a.fc_N) {
+    const int n = n0 + (int)threadIdx.x;
+    double t = a.fc_b_off >= 0 ? (double)a.x[a.fc_b_off + n] : 0.0;
+    for (int w = 0; w < T / 64; ++w) t += sums[w * kFcOutputs + threadIdx.x];
+    a.fc_z0[(long long)r * a.fc_N + n] = (float)t;
   }
 }
 // The layer's weights in matrix-operand order, columns beyond K zeros (rows beyond N only reach results that are discarded).
@@ -980,7 +983,8 @@ __device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, i
 }
 
 // Blocks: [tiles of the pass at x] [tiles x candidates, candidate fastest] [squared norms: pieces x candidates] [one that
-// clears the counters] [kernel fragments], or [samples of the fully connected layer] [its weights].  Returns whether the block is one of the small jobs, which it then has done.
+// clears the counters] [kernel fragments], or [samples of the fully connected layer x groups of its outputs] [its weights].  Returns
+// whether the block is one of the small jobs, which it then has done.
 __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& is_base, int& s, int& tile) {
   int b = blockIdx.x;
   is_base = b < a.base_blocks;
@@ -988,8 +992,9 @@ __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& i
   if (!is_base && b >= a.cand_blocks) {
     b -= a.cand_blocks;
     if (a.fc_N > 0) {                              // (a launch has these or the following)
-      if (b < a.n_r) fc_sample(a, b, reinterpret_cast<float*>(lds));
-      else fc_weights(a, b - a.n_r);
+      const int groups = fc_groups(a.fc_N);
+      if (b < a.n_r * groups) fc_sample(a, b / groups, b % groups * kFcOutputs, reinterpret_cast<float*>(lds));
+      else fc_weights(a, b - a.n_r * groups);
     } else if (b < a.aux_pieces * a.aux_m) {
       sumsq_piece(a, b / a.aux_pieces, b % a.aux_pieces, reinterpret_cast<double*>(lds));
     } else if (b == a.aux_pieces * a.aux_m) {
@@ -1093,7 +1098,7 @@ hipError_t plan_tiles(ConvArgs& a, int np_most, int wc, F job_lds, long long* ld
   const int waves = wc > 0 && np_most == 128 ? 4 : 8;
   *total = blocks[0] + blocks[1] + (long long)a.aux_pieces * a.aux_m + (a.aux_zero16 > 0 ? 1 : 0) +
            ((long long)a.pack_jobs * (a.pack_x + 1) + waves - 1) / waves;
-  if (a.fc_N > 0) *total += a.n_r + ((long long)a.fc_N * (a.fc_Kp / 4) + 64 * waves * kFcPieces - 1) / (64 * waves * kFcPieces);
+  if (a.fc_N > 0) *total += a.n_r * fc_groups(a.fc_N) + ((long long)a.fc_N * (a.fc_Kp / 4) + 64 * waves * kFcPieces - 1) / (64 * waves * kFcPieces);
   if (*total > kConvMostBlocks || *lds > kConvLdsMost) return hipErrorInvalidValue;
   a.base_blocks = (int)blocks[0];
   a.cand_blocks = (int)blocks[1];
