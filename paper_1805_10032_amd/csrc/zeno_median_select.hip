@@ -409,16 +409,20 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
           have_x |= got_x;
           have_y |= got_y;
           const bool left = !(have_x & have_y);
+          if (__ballot(left) == 0) break;
           if (tries == 0) {
             behind = got_x;
             after = key;
-            if (__ballot(left) == 0) break;
             // Few values: lanes agree on one with some copies, in (nearly) all columns, or in half of them and not on account of a
             // single value with many.
-            const unsigned copies = (c1 - c0) * (c1 - c0);
-            const int agreed = __popcll(__ballot(key != 0u)), some = __popcll(__ballot(kSome * copies >= (unsigned)m)),
-                      many = __popcll(__ballot(copies >= kMany * (unsigned)m));
-            few = 2 * some >= agreed && (agreed >= (P == 8 ? 48 : 64) || (agreed >= 32 && 2 * many < agreed));
+            const int agreed = __popcll(__ballot(key != 0u));
+            int many = 0;
+            if (agreed >= 32) {
+              const unsigned copies = (c1 - c0) * (c1 - c0);
+              const int some = __popcll(__ballot(kSome * copies >= (unsigned)m));
+              many = __popcll(__ballot(copies >= kMany * (unsigned)m));
+              few = 2 * some >= agreed && (agreed >= (P == 8 ? 48 : 64) || 2 * many < agreed);
+            }
             if (!few) {
               p = got_x ? tn : p;
               break;
