@@ -579,10 +579,10 @@ CnnPlan make_cnn_plan(const zeno_model* mdl, int m, int n_r, bool fragments) {
   return p;
 }
 
-// The plan for a workspace of `bytes`: with fragments where these fit and need at most kFragmentBytes more than the plan without
-// (split maps are half as large again; several GiB more could be memory that a caller's candidates need).  A model that fits the
-// static scratch array without them only does without them in every workspace, so that both entry points sum in the same order.
-// A workspace that is too small for the plan without is too small for either.
+// The plan for a workspace of `bytes`: with fragments where these are expected to be faster, fit and need at most kFragmentBytes
+// more than the plan without (split maps are half as large again; several GiB more could be memory that a caller's candidates need).
+// A model that fits the static scratch array without them only does without them in every workspace, so that both entry points sum in
+// the same order.  A workspace that is too small for the plan without is too small for either.
 constexpr size_t kFragmentBytes = size_t(4) << 30;
 CnnPlan pick_cnn_plan(const zeno_model* mdl, int m, int n_r, size_t bytes) {
   const CnnPlan plain = make_cnn_plan(mdl, m, n_r, false);
@@ -590,7 +590,10 @@ CnnPlan pick_cnn_plan(const zeno_model* mdl, int m, int n_r, size_t bytes) {
   if (f.total == 0) return plain;
   f.total = std::max(f.total, plain.total);
   const size_t fixed = ZENO_STATIC_SCRATCH_BYTES;
-  const bool take = f.total <= plain.total + kFragmentBytes && (f.total <= fixed || plain.total > fixed);
+  ConvLayer layers[ZENO_MAX_CONV];
+  for (int l = 0; l < mdl->cnn.n_conv; ++l) layers[l] = conv_layer(mdl, l);
+  const bool take = conv_fragments_cost(layers, mdl->cnn.n_conv, n_r, m) < 0.0 && f.total <= plain.total + kFragmentBytes &&
+                    (f.total <= fixed || plain.total > fixed);
   return take && f.total <= bytes ? f : plain;
 }
 

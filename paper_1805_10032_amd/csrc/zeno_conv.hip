@@ -73,6 +73,8 @@
 // The last convolution writes its outputs straight into the matrix-operand
 // order of the fully connected layer (rows = samples, columns = (y, x, c)), which the
 // streaming layer kernel then consumes.
+#include <cmath>
+
 #include "zeno_index.h"
 #include "zeno_layer_impl.h"
 #include "zeno_split.h"
@@ -950,8 +952,10 @@ __device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, i
   const unsigned char* __restrict__ frags = a.pack + (long long)s * a.pack_stride + J.pack_off + (long long)ct * STEPS * kConvFragBytes + lane * 16;
 #pragma unroll 1
   for (int i = tid; i < T.pixels; i += THREADS) {
+    const unsigned off = T.pixel_offset(a, J, (unsigned)i);
     f32x4 v[2];
-    load_pixel<false>(J.H0_in, T.pixel_offset(a, J, (unsigned)i), 0, L.Cin, v[0], v[1]);
+    if (L.Cin == 8) load_pixel<true>(J.H0_in, off, 0, 8, v[0], v[1]);   // (one by one: 2 us longer)
+    else load_pixel<false>(J.H0_in, off, 0, L.Cin, v[0], v[1]);
     store_split(lds + (unsigned)i * 16u, plane, v[0], v[1]);
   }
   f32x16 lead, rest;
@@ -1157,6 +1161,13 @@ hipError_t launch_deep_as(int groups, bool full, const ConvArgs& a, hipStream_t 
 bool few_channels(const ConvLayer& L) { return (L.Cin <= 2 && L.Cout <= 16) || (L.Cin <= 4 && L.Cout <= 8); }
 bool gathered(const ConvLayer& L) { return !full_groups(L) && L.Cin > 8; }
 
+// Tiles of 128 positions where they give every compute unit two workgroups or more.
+bool wide_tiles(const ConvLayer& L, int n_r, int sources) {
+  const long long rows = (long long)n_r * L.Hout * L.Wout;
+  const int ctiles = (L.Cout + 31) / 32, wc = ctiles == 1 ? 1 : 2;
+  return (rows + 127) / 128 * ((ctiles + wc - 1) / wc) * sources >= 512;
+}
+
 hipError_t launch_packed(ConvArgs a, hipStream_t stream) {
   static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_packed_kernel),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsTwo);
@@ -1219,9 +1230,8 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
     if (L.Cin > 8 && need[2] <= kConvLdsTwo) return 2;
     return need[1] <= kConvLdsMost ? 1 : 0;
   };
-  // tiles of 128 positions where they give every compute unit two workgroups or more
   const int wc = ctiles == 1 ? 1 : 2;
-  const bool wide = (rows + 127) / 128 * ((ctiles + wc - 1) / wc) * sources >= 512;
+  const bool wide = wide_tiles(L, a.n_r, sources);
   // Channels that are no multiple of eight: the gathering kernel, but for wide tiles of one group of them (before those give every
   // compute unit two workgroups, gathered / staged with the pass at x through the next layer: 1 -> 33 on 32x32, stride 2, m = 39,
   // n_r = 4: 26 / 43 us; 3 -> 64 on 8x8, stride 2, m = 10, n_r = 2: 16 / 24; from there on 3 -> 32 on 32x32, m = 20: n_r = 4 25 / 23,
@@ -1259,6 +1269,36 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
 bool conv_takes_fragments(const ConvLayer& L, int n_r, int index) {
   if (index == 0) return L.Cin <= 8 && !few_channels(L) && sizes_fit(L, n_r, 256) && map_bytes(L, 256, 1) <= kConvLdsTwo;
   return L.Cin > 8 && full_groups(L) && sizes_fit(L, n_r, 64) && split_unit_bytes(L) / 24 * 25 <= kConvLdsTwo;
+}
+
+// Fragments cost their launch 0.32 us per MB.  Where the kernels below take few large tiles (128 positions), the copies for 64
+// positions cost more than they save, unless many input channels share them: per million positions x channel tiles 77 + 30 (one
+// channel tile) - 40 us per sixteen channels with stride 1, 175 + 120 (the last group of eight alone) - 80 with stride 2; 15 us are
+// saved where the pass at x had a launch of its own.  Few tiles gain: 1.6 us per sixteen channels and round of two workgroups per compute
+// unit (0.2 where a position has so many pixels of its own that a stage holds one unit), and 60 per round after the first.  Fitted to
+// 1539 random models of one to five convolutions (5 to 230 pixels wide, 16 to 256 channels, 1 to 128 samples, 1 to 80 candidates), with
+// fragments always / where this is negative: 1.14 times as fast as without / 1.14; slower than without by more than 3 % 87 / 28 of
+// them, the slowest 0.72 / 0.89.
+double conv_fragments_cost(const ConvLayer* layers, int n, int n_r, int m) {
+  double us = 0.0, mb = 0.0;
+  for (int l = 0; l < n; ++l) {
+    const ConvLayer& L = layers[l];
+    const double rows = (double)n_r * L.Hout * L.Wout, ctiles = (L.Cout + 31) / 32, units = (L.Cin + 15) / 16;
+    const double millions = 1e-6 * m * rows * ctiles;
+    mb += 1e-6 * (m + 1.0) * ctiles * conv_steps(L.Cin) * (l > 0 ? 2 : 1) * kConvFragBytes;
+    const bool wide = wide_tiles(L, n_r, m);
+    if (l == 0) {
+      us -= 25.0 * millions + (!wide && L.Cin < 8 ? 1.0 : 0.0);   // (gathered without)
+    } else if (wide) {
+      us += millions * (L.stride == 1 ? 77.0 + (ctiles == 1 ? 30.0 : 0.0) - 40.0 * units
+                                      : 175.0 + (L.Cin % 16 != 0 ? 120.0 : 0.0) - 80.0 * units);
+      if (l + 1 < n) us -= 15.0;
+    } else {
+      const double tiles = m * std::ceil(rows / 64.0) * ctiles, rounds = tiles > 512.0 ? tiles / 512.0 : 1.0;
+      us -= 60.0 * (rounds - 1.0) + rounds * units * (split_unit_bytes(L) <= 6 * 6144 ? 1.6 : 0.2);
+    }
+  }
+  return us + 0.32 * mb;
 }
 
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream) {

@@ -273,6 +273,8 @@ constexpr int kConvFcMost = 32;   // widest layer that launch_conv takes as a sm
 // input maps of all but the first are then split maps: three bf16 pieces per value, [sixteen channels][piece][eight
 // channels][position][8], one more position of zeros behind the last, channels up to a multiple of 16 (zeros).
 bool conv_takes_fragments(const ConvLayer& L, int n_r, int index);
+// Estimate by how many microseconds a call with m candidates is longer that way (negative: shorter).
+double conv_fragments_cost(const ConvLayer* layers, int n, int n_r, int m);
 inline size_t split_map_bytes(int positions, int C) { return (size_t)3 * ((C + 15) / 16 * 2) * (positions + 1) * 16; }
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t stream);
 

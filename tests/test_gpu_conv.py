@@ -158,6 +158,15 @@ def test_cnn_fragments_and_split_maps(B, case):
     assert np.all(score_error(out[2], s_ref, scale) <= SCORE_TOL["fp32"])
 
 
+@pytest.mark.parametrize("h,conv_c,conv_stride,m,n_r", [
+    (10, [64, 64], [2, 2], 2, 3), (10, [64, 64], [2, 2], 30, 1),       # few tiles: taken, and not, the kernels outweigh their use
+    (20, [64, 64], [1, 1], 12, 20), (20, [16, 24], [1, 1], 16, 20),    # large tiles: many channels, few
+])
+def test_cnn_on_both_sides_of_the_line_for_fragments(B, h, conv_c, conv_stride, m, n_r):
+    desc = dict(in_h=h, in_w=h, in_c=3, conv_c=conv_c, conv_stride=conv_stride, fc_out=10, has_bias=True)
+    _check(B, WL.make_cnn_workload("cnn_line", 100 + h, desc, m, 1, n_r, 0.1, 1e-3, seed=m, n_flip=1, worker_batch=4))
+
+
 @pytest.mark.parametrize("out", [8, 9, 32, 33])
 @pytest.mark.parametrize("hw,conv_c", [(5, [7]), (8, [16, 24])])
 def test_cnn_widths_of_the_fully_connected_layer(B, hw, conv_c, out):
