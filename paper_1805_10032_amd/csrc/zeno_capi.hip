@@ -728,6 +728,7 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     ProfScope ps(ZENO_KERNEL_CONV_BASE, 0, conv_flops(0), stream);
     ZENO_TRY(launch_conv(a, stream));
   }
+  const bool fc_rides = conv_fc_rides(N, p.Kfc, n_r);
   for (int l = 0; l < C; ++l) {
     ConvArgs a = conv;
     a.n_cand = m;
@@ -737,7 +738,7 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
       a.has_base = 1;
       a.bj = conv_job(l + 1, false);
       flops += conv_flops(l + 1);
-    } else if (N <= kConvFcMost) {
+    } else if (fc_rides) {
       // the operand of the fully connected layer's pass at x has been complete for a launch
       a.fc_N = N;
       a.fc_K = p.Kfc;
@@ -751,7 +752,7 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     ProfScope ps(ZENO_KERNEL_CONV_CAND, l, flops, stream);
     ZENO_TRY(launch_conv(a, stream));
   }
-  if (N > kConvFcMost) {
+  if (!fc_rides) {
     LayerArgs b = common;
     b.has_base = 1;
     b.bj = j;

@@ -202,7 +202,7 @@ __device__ void pack_fragment(const ConvArgs& a, int s, int job) {
 // (a launch of the layer kernel behind it took 13 us, most of it latency; the step of 32-32-64-64 channels is 11 us shorter).  Eight
 // outputs of one sample per workgroup: a thread sums its quads of columns in float32, lanes by xor-shuffle tree and waves in order in
 // float64.  Against the launch of its own on 220 random models (64 to 9 M columns, 1 to 32 outputs, 1 to 128 samples): the step 1.13
-// times as fast, two of them slower, with more than a million columns (0.96 and 0.98; four others of that size 1.03-1.14).  With all
+// times as fast, two of them slower, with more than a million columns and few samples (conv_fc_rides).  With all
 // outputs of a sample in one workgroup, which read up to 32 rows of the weights one after the other, 41 were slower, by up to 42 %
 // (launch of its own -> one workgroup -> now, 32 outputs: 5000 columns 57 -> 65 -> 53 us, 123008 columns 322 -> 508 -> 290).
 constexpr int kFcOutputs = 8;

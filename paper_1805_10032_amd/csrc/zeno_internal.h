@@ -268,7 +268,11 @@ struct ConvArgs {
   unsigned magic_cand;
 };
 hipError_t launch_conv(const ConvArgs& a, hipStream_t stream);
-constexpr int kConvFcMost = 32;   // widest layer that launch_conv takes as a small job
+// Whether launch_conv takes the pass at x through a fully connected layer of N outputs and K columns as a small job.  With few samples
+// and more than eight outputs a million columns keep its few workgroups busy for longer than a launch of its own (step with that / with
+// the small job on random models beyond 2^20 columns: up to 8 samples, more than 8 outputs 0.98 on 19, the lowest 0.90; up to 8 outputs
+// 1.08 on 15; more samples 1.03 on 10.  2^19 to 2^20 columns, up to 8 samples, more than 8 outputs: 1.08 on 12).
+inline bool conv_fc_rides(int N, int K, int n_r) { return N <= 32 && (N <= 8 || K <= (1 << 20) || n_r > 8); }
 // Whether convolution `index` of a model may take its kernels as fragments (a model does if all of its convolutions do).  The
 // input maps of all but the first are then split maps: three bf16 pieces per value, [sixteen channels][piece][eight
 // channels][position][8], one more position of zeros behind the last, channels up to a multiple of 16 (zeros).

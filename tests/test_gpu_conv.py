@@ -176,6 +176,14 @@ def test_cnn_widths_of_the_fully_connected_layer(B, hw, conv_c, out):
     _check(B, WL.make_cnn_workload(f"cnn_fc{out}", 120 + out, desc, 4, 1, 6, 0.1, 1e-3, n_flip=1))
 
 
+@pytest.mark.parametrize("out", [8, 9])
+def test_cnn_fully_connected_layer_with_a_million_columns(B, out):
+    """1050625 columns of one sample: up to eight outputs beside the convolution, more in a launch of their own."""
+    desc = dict(in_h=1025, in_w=1025, in_c=1, conv_c=[1], conv_stride=[1], fc_out=out, has_bias=True)
+    w = WL.make_cnn_workload(f"cnn_columns{out}", 140 + out, desc, 2, 1, 1, 0.1, 1e-3, worker_batch=1)
+    _check(B, w)
+
+
 EDGES = [
     # (in_h, in_w, in_c, channels, strides), m, n_r
     ((9, 7, 8, [32, 33], [1, 2]), 3, 3),         # eight channels: steps of two taps; one channel beyond a tile
