@@ -372,6 +372,8 @@ __device__ inline ConvOut conv_out_request(const ConvArgs& a, const ConvJob& J, 
   }
   return o;
 }
+// SPLIT: the output may be a split map.
+template <bool SPLIT>
 __device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool cand, int s, const ConvOut& o, const f32x4& sum,
                                       unsigned r, unsigned rows, unsigned fo) {
   const unsigned C = (unsigned)J.L.Cout, row = r * C;
@@ -382,7 +384,7 @@ __device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool 
     res[i] = conv_result(a, cand, val[i], o.z0[i]);
   }
   float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
-  if (J.split_out) {
+  if (SPLIT && J.split_out) {
     if (r < rows && fo < C && !cand) *reinterpret_cast<f32x4*>(J.Z0 + (row + fo)) = val;
     store_split_out(out, C, res, r, rows, fo);
     return;
@@ -518,7 +520,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
     for (int q = 0; q < 4; ++q) {
       const unsigned fo = (unsigned)(ft * 32 + 8 * q + 4 * h);
       const f32x4 sum = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-      conv_out_store(a, J, cand, s, conv_out_request(a, J, cand, P, (unsigned)r, (unsigned)rows, fo), sum, (unsigned)r, (unsigned)rows, fo);
+      conv_out_store<true>(a, J, cand, s, conv_out_request(a, J, cand, P, (unsigned)r, (unsigned)rows, fo), sum, (unsigned)r, (unsigned)rows, fo);
     }
     return;
   }
@@ -551,7 +553,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
 // Many tiles: four waves, 32 PB WP positions x 32 WC channels.  One (map, channel chunk) unit at a time: its map values and
 // its kernel values are requested while the unit before is multiplied, split once and staged for all four waves.
 // CG: groups of eight channels per unit.
-template <int CG, bool FULL, int PB, int WP, int WC>
+template <int CG, bool FULL, int PB, int WP, int WC, bool SPLIT>
 __device__ __forceinline__ void conv_wide(const ConvArgs& a, const ConvJob& J, bool cand, int s, int tile, unsigned char* lds) {
   static_assert(WP * WC == 4, "four waves");
   constexpr int THREADS = 256, NP = 32 * PB * WP;
@@ -682,14 +684,14 @@ __device__ __forceinline__ void conv_wide(const ConvArgs& a, const ConvJob& J, b
       f32x4 sum;
 #pragma unroll
       for (int i = 0; i < 4; ++i) sum[i] = join_split(lead[pb][4 * q + i], rest[pb][4 * q + i]);
-      conv_out_store(a, J, cand, s, o[q], sum, pos_r[pb], T.rows, fo + 8u * q);
+      conv_out_store<SPLIT>(a, J, cand, s, o[q], sum, pos_r[pb], T.rows, fo + 8u * q);
     }
   }
 }
 
 // Few tiles: 64 positions x 32 channels, eight waves that share out the matrix steps.  Up to stage_units units are staged at
 // once; every wave requests the kernel values of all its steps of them before anything else.
-template <int CG, bool FULL>
+template <int CG, bool FULL, bool SPLIT>
 __device__ __forceinline__ void conv_deep(const ConvArgs& a, const ConvJob& J, bool cand, int s, int tile, unsigned char* lds) {
   constexpr int KW = 8, THREADS = 64 * KW, PB = 2, NP = 32 * PB;
   constexpr int STEPS = CG == 2 ? 9 : 5;
@@ -812,7 +814,7 @@ __device__ __forceinline__ void conv_deep(const ConvArgs& a, const ConvJob& J, b
   for (int w = 0; w < KW; ++w) part[w] = red[((w * PB + opb) * 4 + oq) * 64 + lane];
 #pragma unroll
   for (int w = 1; w < KW; ++w) part[0] += part[w];
-  conv_out_store(a, J, cand, s, o, part[0], r_out, T.rows, fo);
+  conv_out_store<SPLIT>(a, J, cand, s, o, part[0], r_out, T.rows, fo);
 }
 
 // The waves' accumulators of 64 positions x 32 channels, added in wave order; wave kw then finishes quarter kw % 4 of block kw / 4.
@@ -935,7 +937,7 @@ __device__ __forceinline__ void conv_packed(const ConvArgs& a, const ConvJob& J,
   const ConvOut o = conv_out_request(a, J, cand, P, r_out, T.rows, fo);
   __syncthreads();                                                 // the staged units are no longer needed
   const f32x4 sum = sum_waves<KW, PB>(lead, rest, lds, kw, lane);
-  conv_out_store(a, J, cand, s, o, sum, r_out, T.rows, fo);
+  conv_out_store<true>(a, J, cand, s, o, sum, r_out, T.rows, fo);
 }
 
 // The candidates' first convolution, at most eight input channels, kernel fragments from memory: eight waves with 32 positions x
@@ -982,20 +984,22 @@ __device__ __forceinline__ void conv_flat(const ConvArgs& a, const ConvJob& J, i
     f32x4 sum;
 #pragma unroll
     for (int i = 0; i < 4; ++i) sum[i] = join_split(lead[4 * q + i], rest[4 * q + i]);
-    conv_out_store(a, J, true, s, o[q], sum, r, T.rows, fo + 8u * q);
+    conv_out_store<true>(a, J, true, s, o[q], sum, r, T.rows, fo + 8u * q);
   }
 }
 
 // Blocks: [tiles of the pass at x] [tiles x candidates, candidate fastest] [squared norms: pieces x candidates] [one that
 // clears the counters] [kernel fragments], or [samples of the fully connected layer x groups of its outputs] [its weights].  Returns
-// whether the block is one of the small jobs, which it then has done.
+// whether the block is one of the small jobs, which it then has done.  EXTRA: the launch may have fragments to write, a fully connected
+// layer or split maps; code for these costs other launches instruction fetches (wide tiles 62 -> 69 us, few tiles 9.8 -> 10.4).
+template <bool EXTRA>
 __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& is_base, int& s, int& tile) {
   int b = blockIdx.x;
   is_base = b < a.base_blocks;
   if (!is_base) b -= a.base_blocks;
   if (!is_base && b >= a.cand_blocks) {
     b -= a.cand_blocks;
-    if (a.fc_N > 0) {                              // (a launch has these or the following)
+    if (EXTRA && a.fc_N > 0) {                     // (a launch has these or the following)
       const int groups = fc_groups(a.fc_N);
       if (b < a.n_r * groups) fc_sample(a, b / groups, b % groups * kFcOutputs, reinterpret_cast<float*>(lds));
       else fc_weights(a, b - a.n_r * groups);
@@ -1004,7 +1008,7 @@ __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& i
     } else if (b == a.aux_pieces * a.aux_m) {
       const uint4 z = {0u, 0u, 0u, 0u};
       for (int i = threadIdx.x; i < a.aux_zero16; i += blockDim.x) reinterpret_cast<uint4*>(a.aux_zero)[i] = z;
-    } else {
+    } else if (EXTRA) {
       const int waves = blockDim.x >> 6, job = (b - a.aux_pieces * a.aux_m - 1) * waves + (threadIdx.x >> 6);
       if (job < a.pack_jobs * (a.pack_x + 1)) pack_fragment(a, job / a.pack_jobs, job % a.pack_jobs);
     }
@@ -1016,29 +1020,31 @@ __device__ inline bool conv_block(const ConvArgs& a, unsigned char* lds, bool& i
   return false;
 }
 
-template <int CG, bool FULL, int PB, int WP, int WC>
+template <int CG, bool FULL, int PB, int WP, int WC, bool EXTRA>
 __global__ __launch_bounds__(256, 2) void conv_wide_kernel(const ConvArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
   bool is_base;
   int s, tile;
-  if (conv_block(a, conv_lds, is_base, s, tile)) return;
-  conv_wide<CG, FULL, PB, WP, WC>(a, is_base ? a.bj : a.cj, !is_base, s, tile, conv_lds);
+  if (conv_block<EXTRA>(a, conv_lds, is_base, s, tile)) return;
+  const ConvJob& J = is_base ? a.bj : a.cj;
+  conv_wide<CG, FULL, PB, WP, WC, EXTRA>(a, J, !is_base, s, tile, conv_lds);
 }
 
-template <int CG, bool FULL>
+template <int CG, bool FULL, bool EXTRA>
 __global__ __launch_bounds__(512, 2) void conv_deep_kernel(const ConvArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
   bool is_base;
   int s, tile;
-  if (conv_block(a, conv_lds, is_base, s, tile)) return;
-  conv_deep<CG, FULL>(a, is_base ? a.bj : a.cj, !is_base, s, tile, conv_lds);
+  if (conv_block<EXTRA>(a, conv_lds, is_base, s, tile)) return;
+  const ConvJob& J = is_base ? a.bj : a.cj;
+  conv_deep<CG, FULL, EXTRA>(a, J, !is_base, s, tile, conv_lds);
 }
 
 __global__ __launch_bounds__(512, 4) void conv_packed_kernel(const ConvArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char conv_lds[];
   bool is_base;
   int s, tile;
-  if (conv_block(a, conv_lds, is_base, s, tile)) return;
+  if (conv_block<true>(a, conv_lds, is_base, s, tile)) return;
   const ConvJob J = is_base ? a.bj : a.cj;
   if (J.flat) conv_flat(a, J, s, tile, conv_lds);
   else conv_packed(a, J, !is_base, s, tile, conv_lds);
@@ -1111,22 +1117,27 @@ hipError_t plan_tiles(ConvArgs& a, int np_most, int wc, F job_lds, long long* ld
   return hipSuccess;
 }
 
-template <int CG, bool FULL, int PB, int WP, int WC>
+// Whether a launch needs the kernels with everything in them.
+bool has_extra(const ConvArgs& a) { return a.fc_N > 0 || a.pack_jobs > 0 || (a.has_base && a.bj.split_out) || (a.n_cand > 0 && a.cj.split_out); }
+
+template <int CG, bool FULL, int PB, int WP, int WC, bool EXTRA>
 hipError_t launch_wide(ConvArgs a, hipStream_t stream) {
+  if (!EXTRA && has_extra(a)) return hipErrorInvalidValue;         // (not the instantiation for this launch)
   constexpr int NP = 32 * PB * WP;
-  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wide_kernel<CG, FULL, PB, WP, WC>),
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_wide_kernel<CG, FULL, PB, WP, WC, EXTRA>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsMost);
   if (attr_err != hipSuccess) return attr_err;
   long long lds = 512, total = 0;                                  // (the small jobs' partial sums)
   const hipError_t e = plan_tiles(a, NP, WC, [](ConvJob& j, int) { return wide_bytes(j.L, NP, WC, CG); }, &lds, &total);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_wide_kernel<CG, FULL, PB, WP, WC>), dim3((unsigned)total), dim3(256), (size_t)lds, stream, a);
+  hipLaunchKernelGGL((conv_wide_kernel<CG, FULL, PB, WP, WC, EXTRA>), dim3((unsigned)total), dim3(256), (size_t)lds, stream, a);
   return hipGetLastError();
 }
 
-template <int CG, bool FULL>
+template <int CG, bool FULL, bool EXTRA>
 hipError_t launch_deep(ConvArgs a, hipStream_t stream) {
-  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_deep_kernel<CG, FULL>),
+  if (!EXTRA && has_extra(a)) return hipErrorInvalidValue;
+  static const hipError_t attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&conv_deep_kernel<CG, FULL, EXTRA>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)kConvLdsMost);
   if (attr_err != hipSuccess) return attr_err;
   long long lds = 8 * 8192, total = 0;                             // at least the accumulators of eight waves
@@ -1139,19 +1150,27 @@ hipError_t launch_deep(ConvArgs a, hipStream_t stream) {
     return j.stage_units * unit;
   }, &lds, &total);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_deep_kernel<CG, FULL>), dim3((unsigned)total), dim3(512), (size_t)lds, stream, a);
+  hipLaunchKernelGGL((conv_deep_kernel<CG, FULL, EXTRA>), dim3((unsigned)total), dim3(512), (size_t)lds, stream, a);
   return hipGetLastError();
 }
 
 // (channels that are no multiple of eight are staged up to one group of them only)
+template <int PB, int WP, int WC, bool EXTRA>
+hipError_t launch_wide_groups(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
+  if (groups == 2) return launch_wide<2, true, PB, WP, WC, EXTRA>(a, stream);
+  return full ? launch_wide<1, true, PB, WP, WC, EXTRA>(a, stream) : launch_wide<1, false, PB, WP, WC, EXTRA>(a, stream);
+}
+template <bool EXTRA>
+hipError_t launch_deep_groups(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
+  if (groups == 2) return launch_deep<2, true, EXTRA>(a, stream);
+  return full ? launch_deep<1, true, EXTRA>(a, stream) : launch_deep<1, false, EXTRA>(a, stream);
+}
 template <int PB, int WP, int WC>
 hipError_t launch_wide_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
-  if (groups == 2) return launch_wide<2, true, PB, WP, WC>(a, stream);
-  return full ? launch_wide<1, true, PB, WP, WC>(a, stream) : launch_wide<1, false, PB, WP, WC>(a, stream);
+  return has_extra(a) ? launch_wide_groups<PB, WP, WC, true>(groups, full, a, stream) : launch_wide_groups<PB, WP, WC, false>(groups, full, a, stream);
 }
 hipError_t launch_deep_as(int groups, bool full, const ConvArgs& a, hipStream_t stream) {
-  if (groups == 2) return launch_deep<2, true>(a, stream);
-  return full ? launch_deep<1, true>(a, stream) : launch_deep<1, false>(a, stream);
+  return has_extra(a) ? launch_deep_groups<true>(groups, full, a, stream) : launch_deep_groups<false>(groups, full, a, stream);
 }
 
 // More than eight channels that are no multiple of eight: the gathering kernel.  The staged tiles would read every channel by
@@ -1263,7 +1282,7 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   if (e != hipSuccess || (a.aux_m <= 0 && a.aux_zero16 <= 0 && a.pack_jobs <= 0 && a.fc_N <= 0)) return e;
   r = a;                                           // the small jobs alone
   r.has_base = r.n_cand = 0;
-  return launch_wide<1, true, 1, 4, 1>(r, stream);
+  return launch_wide_as<1, 4, 1>(1, true, r, stream);
 }
 
 bool conv_takes_fragments(const ConvLayer& L, int n_r, int index) {
