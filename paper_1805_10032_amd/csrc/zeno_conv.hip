@@ -1290,14 +1290,14 @@ bool conv_takes_fragments(const ConvLayer& L, int n_r, int index) {
   return L.Cin > 8 && full_groups(L) && sizes_fit(L, n_r, 64) && split_unit_bytes(L) / 24 * 25 <= kConvLdsTwo;
 }
 
-// Fragments cost their launch 0.32 us per MB.  Where the kernels below take few large tiles (128 positions), the copies for 64
+// Fragments cost their launch 0.32 us per MB.  Where the kernels without them take large tiles (128 positions), the copies for 64
 // positions cost more than they save, unless many input channels share them: per million positions x channel tiles 77 + 30 (one
-// channel tile) - 40 us per sixteen channels with stride 1, 175 + 120 (the last group of eight alone) - 80 with stride 2; 15 us are
-// saved where the pass at x had a launch of its own.  Few tiles gain: 1.6 us per sixteen channels and round of two workgroups per compute
-// unit (0.2 where a position has so many pixels of its own that a stage holds one unit), and 60 per round after the first.  Fitted to
-// 1539 random models of one to five convolutions (5 to 230 pixels wide, 16 to 256 channels, 1 to 128 samples, 1 to 80 candidates), with
-// fragments always / where this is negative: 1.14 times as fast as without / 1.14; slower than without by more than 3 % 87 / 28 of
-// them, the slowest 0.72 / 0.89.
+// channel tile) + 30 (the last group of eight alone) - 40 us per sixteen channels with stride 1, 175 + 120 (the same) - 80 with
+// stride 2; 15 us are saved where the pass at x had a launch of its own.  Few tiles gain: 1.6 us per sixteen channels and round of two
+// workgroups per compute unit (0.2 where a position has so many pixels of its own that a stage holds one unit), and 60 per round
+// after the first.  Fitted to 1539 random models of one to five convolutions (5 to 230 pixels wide, 16 to 256 channels, 1 to 128
+// samples, 1 to 80 candidates), with fragments always / where this is negative: 1.14 times as fast as without in either case; slower
+// than without by more than 3 % 87 / 26 of them, the slowest 0.72 / 0.89.
 double conv_fragments_cost(const ConvLayer* layers, int n, int n_r, int m) {
   double us = 0.0, mb = 0.0;
   for (int l = 0; l < n; ++l) {
@@ -1309,8 +1309,9 @@ double conv_fragments_cost(const ConvLayer* layers, int n, int n_r, int m) {
     if (l == 0) {
       us -= 25.0 * millions + (!wide && L.Cin < 8 ? 1.0 : 0.0);   // (gathered without)
     } else if (wide) {
-      us += millions * (L.stride == 1 ? 77.0 + (ctiles == 1 ? 30.0 : 0.0) - 40.0 * units
-                                      : 175.0 + (L.Cin % 16 != 0 ? 120.0 : 0.0) - 80.0 * units);
+      const bool half = L.Cin % 16 != 0;
+      us += millions * (L.stride == 1 ? 77.0 + (ctiles == 1 ? 30.0 : 0.0) + (half ? 30.0 : 0.0) - 40.0 * units
+                                      : 175.0 + (half ? 120.0 : 0.0) - 80.0 * units);
       if (l + 1 < n) us -= 15.0;
     } else {
       const double tiles = m * std::ceil(rows / 64.0) * ctiles, rounds = tiles > 512.0 ? tiles / 512.0 : 1.0;
