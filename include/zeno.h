@@ -62,7 +62,7 @@ typedef enum {
   ZENO_OK = 0,
   ZENO_ERR_INVALID_ARG = 1, /* NULL/misaligned pointer, m<1, m>1024, b<0, b>=m, n_r<1, ldg<d, bad gamma/rho/dims */
   ZENO_ERR_UNSUPPORTED = 2, /* a size beyond what the kernels cover (see each call) */
-  ZENO_ERR_WORKSPACE = 3,   /* workspace NULL, misaligned (256 B) or smaller than the query says */
+  ZENO_ERR_WORKSPACE = 3,   /* workspace NULL, misaligned (256 B) or too small (see zeno_score, zeno_krum) */
   ZENO_ERR_DEVICE = 4,      /* a HIP launch failed */
   ZENO_ERR_HOST_MEMORY = 5  /* the host-side model object could not be allocated */
 } zeno_status_t;
@@ -140,9 +140,7 @@ int64_t zeno_model_num_params(const zeno_model_t* model);
 
 /* Bytes of DEVICE scratch that zeno_score needs for m candidates and a batch of
  * n_r samples (activations of the m+1 forward passes, partial norms).  Returns
- * 0 for invalid arguments.  A convolutional model whose convolutions have at most eight (the first) and
- * multiples of eight above that (all others) input channels also runs, more slowly, with less: without room for
- * reordered kernels and maps; its scores then agree up to the order of float32 sums. */
+ * 0 for invalid arguments. */
 size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t n_r);
 
 /* Definition 2 for every row of G:
@@ -158,7 +156,11 @@ size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t 
  *   gamma   learning rate, finite, >= 0;  rho  finite, >= 0 (rho = 0 is the
  *           appendix's choice for mu >= 0)
  *   scores  DEVICE [m] fp32 out
- *   workspace DEVICE, 256-byte aligned, >= zeno_score_workspace_bytes(model, m, n_r)
+ *   workspace DEVICE, 256-byte aligned, workspace_bytes >= zeno_score_workspace_bytes(model, m, n_r).  A smaller one gives
+ *             ZENO_ERR_WORKSPACE, with one exception: for some convolutional models the query includes room for reordered
+ *             copies of the kernels and maps, and a workspace that holds everything but these (no call returns that size) is
+ *             accepted and scored by slower kernels, whose scores agree up to the order of float32 sums.  Workspaces of the
+ *             queried size and larger ones give the same scores bit for bit.
  * Batches of more than 128 samples are processed in passes of 128, each pass
  * reading G again. */
 zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float* G, int64_t ldg, int32_t m,
@@ -210,7 +212,7 @@ zeno_status_t zeno_mean(const float* G, int64_t ldg, int32_t m, int64_t d, float
 
 /* Marginal median (Definition 4): out[j] = median_i G[i][j]; for even m the
  * midpoint of the two middle values (formed in float64, rounded once).  NaN entries
- * sort above +inf.  Up to m = 128 the values of a column are sorted in registers; for
+ * sort above +inf, -0 below +0.  Up to m = 128 the values of a column are sorted in registers; for
  * 128 < m <= 1024 the median is found by narrowing a bracket around its rank, whose speed
  * depends on the values (the result does not). */
 zeno_status_t zeno_median(const float* G, int64_t ldg, int32_t m, int64_t d, float* out, void* stream);
@@ -270,9 +272,11 @@ typedef enum {
   ZENO_KERNEL_AVERAGE_UPDATE = 8, /* selection + average + x_next = x - gamma * average */
   ZENO_KERNEL_KRUM = 9,           /* Gram matrix + selection + copy of the chosen row */
   ZENO_KERNEL_CONV_BASE = 10,     /* first convolution of the pass at x, with the squared norms of the candidates' convolution
-                                     kernels and the clearing of the arrival counters; one or two launches */
-  ZENO_KERNEL_CONV_CAND = 11,     /* one convolution of the m candidate passes and the pass at x through the next one; one or
-                                     two launches */
+                                     kernels, their reordered copies and the clearing of the arrival counters; one or two
+                                     launches */
+  ZENO_KERNEL_CONV_CAND = 11,     /* one convolution of the m candidate passes and the pass at x through the next one, in the last
+                                     one mostly through a fully connected layer of at most 32 outputs (which then has no
+                                     LAYER_BASE record); one or two launches */
   ZENO_KERNEL_AUX = 12            /* fills of padded operands */
 } zeno_kernel_t;
 
