@@ -13,9 +13,9 @@
 // convolution).  Nothing is unfolded in memory: a patch element (position, tap, channel) is
 // gathered from the NHWC map when a lane needs it as a matrix operand.
 //
-// conv_packed_kernel (models whose first convolution has up to eight input channels and all others a multiple of eight above).  The
-// products run on the bf16 matrix cores at float32 accuracy: both operands are split into three bf16 pieces each and the six
-// leading piece products accumulated (zeno_split.h).  Six v_mfma_f32_32x32x16_bf16 cover 16 channels of a tap in 192 cycles
+// conv_packed_kernel (models whose first convolution has up to eight input channels and all others a multiple of eight above, where
+// conv_fragments_cost expects a gain).  The products run on the bf16 matrix cores at float32 accuracy: both operands are split into
+// three bf16 pieces each and the six leading piece products accumulated (zeno_split.h).  Six v_mfma_f32_32x32x16_bf16 cover 16 channels of a tap in 192 cycles
 // where v_mfma_f32_32x32x2_f32 needs 512.  K is walked in units of (map of x or of the candidate) x (sixteen input channels), nine
 // steps (taps) each.
 //  * Every value is split once.  The first launch writes the kernels, U and W - gamma U, as fragments in the lanes' order (ConvPack),
@@ -31,10 +31,9 @@
 // copies are requested, 1.9 and 2.4 waiting for the copies of its two stages, 1.2 in the products of each, 2 in the sums and results.
 // Measured (MI355X, 32 x 32 x 3 images, convolutions 32-32-64-64 with strides 1-2-1-2, m = 20) against the kernels below:
 // n_r = 32, candidates' convolutions 66 + 10 / 99 + 10 / 109 + 13 / 115 us with the pass at x on its own -> 64 / 79 / 109 / 65, fragments 6 us,
-// the step 455 -> 343 us (334 with fc_sample); n_r = 4: 35 / 33 / 23 us for the last three -> 18 / 20 / 17, the step 159 -> 118 us (106).  Over 40 random models of
-// this kind 1.08 times as fast, single convolutions on 8 x 8 images as fast as before.  Models with other convolutions among them
-// would alternate between both kinds of maps, in two launches for every one: 0.81-0.95 on 14 of 18, so they keep to the
-// kernels below.  Splitting the maps in the workgroup that stages them (four times as many vector instructions): 106 us where the copies
+// the step 455 -> 343 us (331 with fc_sample); n_r = 4: 35 / 33 / 23 us for the last three -> 18 / 20 / 17, the step 159 -> 118 us
+// (104).  Other models: conv_fragments_cost.  Models with other convolutions among them would alternate between both kinds of maps,
+// in two launches for every one: 0.81-0.95 on 14 of 18, so they keep to the kernels below.  Splitting the maps in the workgroup that stages them (four times as many vector instructions): 106 us where the copies
 // take 79; persistent workgroups that request the next candidate's copies ahead of their sums: 95.
 //
 // conv_wide_kernel, conv_deep_kernel (other models, the pass at x through the first convolution, and calls whose workspace holds no
@@ -1258,7 +1257,8 @@ hipError_t launch_conv(const ConvArgs& a, hipStream_t stream) {
   // Neither where input and output channels are so few that a wide tile's products are mostly padding (time as wide tiles / gathered,
   // whole steps: up to 2 -> 16 or 4 -> 8 channels 1.04 on 21 random models, 19 of them slower as wide tiles, by up to 20 %; the
   // others 0.89 on 135).  The pass at x alone is staged up to 512 tiles of 64 positions x 32 channels, the small jobs of its launch
-  // need as long (staged / gathered: 0.97 below 256 tiles, 1.01 on 38 up to 512, 1.02 on 32 beyond, 22 of them slower).
+  // need as long (staged / gathered: 0.97 below 256 tiles, 1.01 on 38 up to 512, 1.02 on 32 beyond, 22 of them slower; measured
+  // without fragments among the small jobs).
   const bool gather = gathered(L) || (!full && (a.n_cand > 0 ? !wide || few_channels(L) : (rows + 63) / 64 * ctiles >= 512));
   if (a.n_cand > 0 && a.has_base && !gather && (wide || gathered(a.bj.L) || (full && !full_groups(a.bj.L)))) {
     // The pass at x on its own: next to wide tiles its few workgroups, each with all of K to walk, would be the last ones to end

@@ -176,6 +176,13 @@ def test_cnn_widths_of_the_fully_connected_layer(B, hw, conv_c, out):
     _check(B, WL.make_cnn_workload(f"cnn_fc{out}", 120 + out, desc, 4, 1, 6, 0.1, 1e-3, n_flip=1))
 
 
+@pytest.mark.parametrize("hw,conv_c", [(6, [16, 16]), (5, [9, 12])])
+def test_cnn_with_as_many_candidates_as_the_calls_take(B, hw, conv_c):
+    """1023 candidates, staged and gathered: every score."""
+    desc = dict(in_h=hw, in_w=hw, in_c=3, conv_c=conv_c, conv_stride=[1, 2], fc_out=4, has_bias=True)
+    _check(B, WL.make_cnn_workload("cnn_many", 150, desc, 1023, 300, 3, 0.1, 1e-3, n_flip=100, worker_batch=1))
+
+
 @pytest.mark.parametrize("out", [8, 9])
 def test_cnn_fully_connected_layer_with_a_million_columns(B, out):
     """1050625 columns of one sample: up to eight outputs beside the convolution, more in a launch of their own."""
