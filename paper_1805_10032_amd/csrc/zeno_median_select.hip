@@ -44,9 +44,11 @@
 // faulty 602 -> 510 us (3.7 TB/s), m = 129, d = 3.0 M 560 -> 468, m = 512, d = 0.8 M 548 -> 434, m = 1024, d = 0.4 M 629 -> 525; normally
 // distributed columns 18-28 % shorter; a fifth of the rows NaN 576 -> 465 for m = 300; 40 % zeros 588 -> 372.  Columns of few values,
 // normally distributed and rounded to a half, a quarter, an eighth, a sixteenth of their deviation (before -> lists alone -> now): m = 300
-// 535 -> 568 -> 396, 538 -> 770 -> 517, 540 -> 707 -> 535, 547 -> 560 -> 543; m = 129 448 -> 621 -> 364, 450 -> 667 -> 467, 457 ->
-// 506 -> 475, 463 -> 431 -> 454; m = 1024 486 -> 500 -> 375, 529 -> 829 -> 458, 529 -> 863 -> 607, 533 -> 788 -> 594: with one
-// workgroup per compute unit its slowest wave decides.
+// 535 -> 568 -> 395, 538 -> 770 -> 530, 540 -> 707 -> 544, 547 -> 560 -> 550; m = 129 448 -> 621 -> 381, 450 -> 667 -> 492, 457 ->
+// 506 -> 494, 463 -> 431 -> 458; m = 1024 486 -> 500 -> 370, 529 -> 829 -> 475, 529 -> 863 -> 617, 533 -> 788 -> 598: with one
+// workgroup per compute unit its slowest wave decides.  A third to a half of the rows faulty, half of these equal and off the
+// middle (lanes agree on them all the same): m = 436, d = 0.86 M 536 -> 560 -> 571, m = 236, d = 1.3 M 430 -> 388 -> 395, m = 130,
+// d = 3 M 583 -> 603 -> 615, m = 700, d = 0.4 M 434 -> 460 -> 472.
 #include <limits.h>
 #include <stdint.h>
 
@@ -86,6 +88,7 @@ constexpr int kAim = 5;                                 // ranks by which the co
 // m = 300, 15 copies 535 / 590, 30 copies 523 / 496; m = 1024, 50 copies 600 / 642, 100 copies 593 / 459; one try less costs 2-6 %).
 constexpr int kTries = 3;
 constexpr unsigned kMany = 3, kSome = 10;
+constexpr unsigned kNear = 7;                            // how far off the middle that value may be: a seventh of the rows
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor3 = 0x1B, kMirror8 = 0x141, kMirror16 = 0x140;  // lane permutations inside 4, 4, 8, 16 lanes
 // Reductions over the P lanes of a column; every lane receives the result.
 template <int P>
@@ -300,7 +303,7 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
   const float* mine = tile + part * COLS + (col ^ flip(part));
   const unsigned lds0 = (unsigned)(uintptr_t)(__attribute__((address_space(3))) void*)tile;
   const int n_copies = (m + ROWS - 1) / ROWS;
-  const unsigned k = (unsigned)(m - 1) / 2;
+  const unsigned k = (unsigned)(m - 1) / 2, reach = (unsigned)m / kNear;
   const float rank_scale = __builtin_amdgcn_rsqf((float)(P * m)) * (1.f / (0.55f * P));   // mean deviation of the lanes' medians -> one rank
 
   // tiles of this workgroup: the XCD (blockIdx % 8) owns a contiguous range; `step` workgroups at a time take kRun tiles each in turn
@@ -389,8 +392,9 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
       const bool twin = (wb == dpp<kXor1>(wb)) | (wb == dpp<kXor2>(wb)) | (wb == dpp<kMirror8>(wb)) | (P == 16 && wb == dpp<kMirror16>(wb));
       unsigned after = 0u;                               // the key whose successor the pivot is, where no wanted key is below it
       bool behind = false;                               // whether the pivot is such a one
-      bool few = false;                                  // columns of few values, which the slope does not find
-      if (__ballot(twin) != 0) {
+      bool few = false;                                  // columns of few values, which the slope does not find: no lists
+      const unsigned long long twins = __ballot(twin);
+      if (twins != 0) {
         // A lane's median and its successor are pivots: the values of rank k and k + 1 end here if they are that value.
         bool own = twin;                                 // lanes whose median is tried
         float aim_at = p;
@@ -403,7 +407,8 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
           const unsigned c0 = b & 0xffffu, c1 = b >> 16;
           bound(tv, c0);
           bound(tn, c1);
-          const bool got_x = (key != 0u) & !have_x & (c0 <= k) & (c1 > k), got_y = (key != 0u) & !have_y & (c0 <= k + 1u) & (c1 > k + 1u);
+          // (no key: c0 and c1 are the same; a value above x: c0 is above k)
+          const bool got_x = (c0 <= k) & (c1 > k), got_y = (c0 <= k + 1u) & (c1 > k + 1u);
           x = got_x ? key : x;
           y = got_y ? key : y;
           have_x |= got_x;
@@ -413,22 +418,25 @@ __global__ __launch_bounds__(64 * WAVES) void median_select_kernel(const float* 
           if (tries == 0) {
             behind = got_x;
             after = key;
-            // Few values: lanes agree on one with some copies, in (nearly) all columns, or in half of them and not on account of a
-            // single value with many.
-            const int agreed = __popcll(__ballot(key != 0u));
+            // Few values: lanes agree on one with some copies, not far from the middle, in (nearly) all columns, or in half of them and
+            // not on account of a single value with many.
+            const bool here = (c1 > c0) & (c0 <= k + reach) & (c1 > k - reach);
+            const int agreed = __popcll(__ballot(here));
             int many = 0;
             if (agreed >= 32) {
               const unsigned copies = (c1 - c0) * (c1 - c0);
-              const int some = __popcll(__ballot(kSome * copies >= (unsigned)m));
-              many = __popcll(__ballot(copies >= kMany * (unsigned)m));
+              const int some = __popcll(__ballot(here & (kSome * copies >= (unsigned)m)));
+              many = __popcll(__ballot(here & (copies >= kMany * (unsigned)m)));
               few = 2 * some >= agreed && (agreed >= (P == 8 ? 48 : 64) || 2 * many < agreed);
             }
+            const bool try_others = few & (many >= 32);
+            few |= __popcll(twins) >= 32;                  // (half the lanes agreeing on a value far from the middle: the bracket, too)
             if (!few) {
               p = got_x ? tn : p;
               break;
             }
-            if (many < 32) {
-              // the bracket finds one of many values sooner; its other end is the outermost of the lanes' medians
+            if (!try_others) {
+              // the bracket finds it sooner; its other end is the outermost of the lanes' medians
               const float side = c1 <= k ? -lanes_fmin<P>(-w[0]) : lanes_fmin<P>(w[0]);
               bound(side, lanes_sum<P>(count_below(u, side)));
               break;
