@@ -73,6 +73,8 @@ struct LayerArgs {
   int has_base;         // 1: the launch also runs the pass at x through bj
   int base_blocks;      // leading block indices reserved for the pass at x (multiple of 8)
   int n_r;              // valid samples (rows) in this pass
+  int row_groups;       // wide workgroups with split float32 operands: groups of 32 MB rows, a workgroup each (filled in by the launcher)
+  int float_products;   // wide workgroups with float32 matrix instructions (filled in by the launcher)
   LayerJob cj, bj;
   const void* D_cand;   // tiled scaled activation differences of candidate 0 (delta launches only)
   long long A_stride;   // bytes between consecutive candidates in D_cand

@@ -46,10 +46,17 @@ static int compute_units() {
   return n_cu;
 }
 
+static int row_groups(bool bf16, int MB, int NW);
+
 static int wgs_per_cu(bool bf16, bool delta, int MB, int NW, int k_waves = 1) {
+  MB /= row_groups(bf16, MB, NW);
   return bf16 ? (delta ? wgs_per_cu_bf16_delta(MB, NW, k_waves) : wgs_per_cu_bf16_first(MB, NW, k_waves))
               : (delta ? wgs_per_cu_f32_delta(MB, NW, k_waves) : wgs_per_cu_f32_first(MB, NW, k_waves));
 }
+
+// Wide workgroups with split float32 operands hold two accumulators per 32-row block: four row blocks run as two groups of two, a
+// workgroup each (G is read twice, the second time mostly from the L2 of the XCD both run on).
+static int row_groups(bool bf16, int MB, int NW) { return !bf16 && MB == 4 && NW > 1 ? 2 : 1; }
 
 static int ks_waves(bool bf16, bool delta, int MB) {
   return bf16 ? (delta ? ks_waves_for<true, true>(MB) : ks_waves_for<true, false>(MB))
@@ -65,11 +72,12 @@ static int ks_waves(bool bf16, bool delta, int MB) {
 // eight waves, which copy the activations once per 256 features instead of once per 128, win).
 static int nw_for(const LayerArgs& a, bool bf16, bool delta, int MB) {
   if (a.wide_nw > 0) return a.wide_nw;   // planned (layer_wide_plan, layer_tail_slices)
-  const int nw = launch_nw_for(a);
+  const int groups = row_groups(bf16, MB, 8);
+  const int nw = launch_nw_for(a, groups);
   if (nw != 8 || a.n_cand <= 0) return nw;
   if (wgs_per_cu(bf16, delta, MB, 4) < 2) return 8;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
-  const long long wgs = (long long)job_tiles(a.cj, 256) * a.n_cand;
+  const long long wgs = (long long)job_tiles(a.cj, 256) * a.n_cand * groups;
   const long long rounds = (wgs + slots - 1) / slots;
   return 10 * wgs >= 9 * rounds * slots ? 8 : 4;
 }
@@ -164,7 +172,7 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
   if (a.tail_slices >= 2 && NW == a.wide_nw) {
     const long long tiles = (a.has_base ? job_tiles(a.bj, 32 * NW) : 0) + (long long)job_tiles(a.cj, 32 * NW) * a.tail_cand;
     e.slice_bytes = tiles * a.tail_slices * NW * MB * 16 * 64 * (long long)sizeof(float);
-    e.slice_counters = (int)tiles;
+    e.slice_counters = (int)tiles * row_groups(bf16, MB, NW);
     e.norm_slots = a.tail_p_off - a.p_off + job_tiles(a.cj, 32 * NW) * a.tail_slices;   // both ranges, counted from p_off
   }
   return e;
@@ -172,6 +180,7 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
 
 // Does the workgroup of NW waves (8 or 4) of this kind double-buffer its activation chunks (slices need it)?
 static bool wide_double_buffered(bool bf16, bool delta, int MB, int NW) {
+  if (!bf16) return !delta || MB < 4;   // split operands always are; see row_groups for the four row blocks
   auto pick = [&](auto mb, auto nw) {
     constexpr int M = decltype(mb)::value, W = decltype(nw)::value;
     return bf16 ? (delta ? Lds<true, true, M, W>::DBUF : Lds<true, false, M, W>::DBUF)
@@ -205,9 +214,9 @@ static long long wide_tiles(const LayerArgs& a) {
 // Most K slices a launch of four-wave workgroups may be cut into: every slice keeps two chunks of every job, and the hand-over
 // buffers hold all tiles.  0: the launch never takes such workgroups by layer_wide_plan.  No device is asked.
 int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
-  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a, row_groups(bf16, MB, 8)) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
   const long long tiles = wide_tiles(a);
-  if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles > kMaxSliceGroups) return 1;
+  if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles * row_groups(bf16, MB, 4) > kMaxSliceGroups) return 1;
   const int chunks = a.cj.Kp >> 6, min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
   const long long by_bytes = (long long)(budget / wide_slice_bytes(MB)) / tiles;
   const long long most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
@@ -280,7 +289,7 @@ static bool on_shifted_grid(const LayerArgs& a, bool bf16, bool delta, int MB) {
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
   const int most = layer_wide_most(a, bf16, delta, MB, budget);
   if (most == 0) return 0;
-  const bool whole_tiles = launch_nw_for(a) == 4;
+  const bool whole_tiles = launch_nw_for(a, row_groups(bf16, MB, 8)) == 4;
   const long long tiles = wide_tiles(a);
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
   const double hand_over = bf16 && !delta ? 6.0 : 4.0;
@@ -308,17 +317,18 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 // Not where the workgroup is single-buffered.
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main_out) {
   *n_main_out = a.n_cand;
-  if (a.n_cand <= 0 || launch_nw_for(a) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
+  if (a.n_cand <= 0 || launch_nw_for(a, row_groups(bf16, MB, 8)) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
   if (!wide_double_buffered(bf16, delta, MB, 8)) return 0;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
-  const int tiles8 = job_tiles(a.cj, 256);
+  const int groups = row_groups(bf16, MB, 8);
+  const int tiles8 = job_tiles(a.cj, 256) * groups;
   const long long full = (long long)tiles8 * a.n_cand / slots * slots;
   const int n_main = (int)(full / tiles8), rest = a.n_cand - n_main;
   // (candidates that fill their rounds exactly leave the pass at x to a launch of its own: as a sliced tail of 16
   // tiles x 8 slices behind workload 5's 4096-wide layers it took 60 us, twice what the launch of one-wave tiles
   // with K split over waves and workgroups takes; with four row blocks the hand-over alone is seven round trips)
   if (n_main <= 0 || rest <= 0 || full % tiles8 != 0) return 0;
-  const long long tail_tiles = (long long)rest * tiles8 + (a.has_base ? job_tiles(a.bj, 256) : 0);
+  const long long tail_tiles = (long long)rest * tiles8 + (a.has_base ? job_tiles(a.bj, 256) * groups : 0);
   int min_chunks = a.cj.Kp >> 6;
   if (a.has_base && (a.bj.Kp >> 6) < min_chunks) min_chunks = a.bj.Kp >> 6;
   long long S = slots / tail_tiles;
@@ -347,8 +357,9 @@ bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB) {
   const int NW = nw_for(a, bf16, delta, MB);
   const int per_cu = wgs_per_cu(bf16, delta, MB, NW);
   const long long slots = (long long)n_cu * per_cu;
-  const long long cand = (long long)job_tiles(a.cj, 32 * NW) * a.n_cand;
-  const long long base = job_tiles(a.bj, 32 * NW);
+  const int groups = row_groups(bf16, MB, NW);
+  const long long cand = (long long)job_tiles(a.cj, 32 * NW) * a.n_cand * groups;
+  const long long base = job_tiles(a.bj, 32 * NW) * groups;
   const long long rounds_without = (cand + slots - 1) / slots, rounds_with = (cand + base + slots - 1) / slots;
   return rounds_with == rounds_without || rounds_without >= 8;
 }
@@ -372,10 +383,19 @@ hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, i
 hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipStream_t stream, LaunchShape* shape) {
   const int NW = nw_for(a, bf16, delta, MB);
   LayerArgs b = a;
+  b.row_groups = row_groups(bf16, MB, NW);
+  // Four-wave workgroups with at most one per compute unit, one row block and one product: a wave has its SIMD to itself, and the
+  // split of its operand takes as long as the float32 matrix instructions do, without a second wave to hide behind
+  // (20 candidates, n_r = 32: 3072 -> 512 in 243 workgroups 37.0 us with float32 products, 37.6-38.0 with split operands).
+  if (!bf16 && !delta && MB == 1 && NW == 4 && a.n_cand > 0) {
+    const long long slices = a.tail_slices >= 2 && a.tail_cand == a.n_cand ? a.tail_slices : 1;
+    b.float_products = wide_tiles(a) * slices <= compute_units();
+  }
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, true);
   b.k_waves = kp.k_waves;
   b.k_slices = kp.k_slices;
   b.slice_group0 = (a.has_base && a.n_cand > 0) ? job_tiles(a.bj, 32) : 0;
+  MB /= b.row_groups;
   if (bf16) {
     return delta ? launch_layer_bf16_delta(b, MB, NW, stream, shape) : launch_layer_bf16_first(b, MB, NW, stream, shape);
   }

@@ -37,14 +37,26 @@
 #define ZENO_LAYER_IMPL_H_
 
 #include <type_traits>
+#include <utility>
 
 #include "zeno_internal.h"
+#include "zeno_split.h"
 
 namespace zeno {
 
 namespace {
 
 typedef __attribute__((address_space(3))) void* lptr_t;
+
+// f(integral_constant 0), ..., f(integral_constant N - 1): indices that are constants whatever the unroller decides.
+template <class F, int... I>
+__device__ __attribute__((always_inline)) inline void static_for_impl(F& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __attribute__((always_inline)) inline void static_for(F f) {
+  static_for_impl(f, std::make_integer_sequence<int, N>{});
+}
 
 constexpr int kSrcChunk = 16;  // most sources per scheduling unit (one feature tile each)
 
@@ -375,13 +387,18 @@ __device__ inline void lds_dma16(const unsigned char* src, unsigned char* dst) {
 // LDS layout of a workgroup: [activation chunk buffers (one or two)] [one staging
 // tile per wave].  (Nothing else: with 4 row blocks, bf16 operands, the second product and
 // four waves the layout is exactly 80 KB, and two such workgroups share a compute unit.)
-template <bool BF16, bool DELTA, int MB, int NW, int RING = 0>
+//
+// SPLIT (float32 operands in wide workgroups): the activation buffers hold the three bf16 pieces of the operands, half as large
+// again as the floats, of a step of SUB_K = 64 / MB columns at a time; always two of them.
+template <bool BF16, bool DELTA, int MB, int NW, int RING = 0, bool F32 = false>
 struct Lds {
   using T = Tr<BF16>;
-  static constexpr int A_BYTES = MB * T::CH_BYTES;            // one operand, one chunk
+  static constexpr bool SPLIT = !BF16 && NW > 1 && !F32;
+  static constexpr int STEPS = SPLIT ? MB : 1;                // activation steps of a 64-wide K chunk
+  static constexpr int A_BYTES = SPLIT ? MB * 32 * 64 * 6 / STEPS : MB * T::CH_BYTES;   // one operand, one step
   static constexpr int AD_BYTES = A_BYTES * (DELTA ? 2 : 1);  // H (and D), one chunk
   static constexpr int STAGE_BYTES = 32 * 64 * T::ESIZE * (RING ? 2 : 1);   // RING: two tiles' worth of columns
-  static constexpr bool DBUF = 2 * AD_BYTES + NW * STAGE_BYTES <= 128 * 1024;
+  static constexpr bool DBUF = SPLIT || 2 * AD_BYTES + NW * STAGE_BYTES <= 128 * 1024;
   static constexpr int STAGE_OFF = AD_BYTES * (DBUF ? 2 : 1);
   static constexpr int TOTAL = STAGE_OFF + NW * STAGE_BYTES;
 };
@@ -410,11 +427,12 @@ struct Lds {
 // several times as many workgroups, each a fraction as long.  With all candidates in the tail (four-wave workgroups, chosen by
 // layer_wide_plan) the whole launch is sliced, and its blocks follow the same schedule as whole tiles do.  The slices of a tile hand their partial accumulators
 // over through memory as the K slices of one-wave tiles do (last workgroup to arrive adds them in slice order).
-template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS, int RING = 0, bool TAIL = false>
-__global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) {
+// F32: float32 matrix instructions in a wide workgroup (launch_layer says where they are the faster ones).
+template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS, int RING = 0, bool TAIL = false, bool F32 = false>
+__global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void layer_kernel(const LayerArgs a) {
   static_assert(KS == 1 || NW == 1, "K is only split in one-tile workgroups");
   using T = Tr<BF16>;
-  using LD = Lds<BF16, DELTA, MB, NW, RING>;
+  using LD = Lds<BF16, DELTA, MB, NW, RING, F32>;
   static_assert(!TAIL || (NW >= 4 && KS == 1 && LD::DBUF), "sliced tiles exist for double-buffered wide workgroups");
   static_assert(!RING || (BF16 && KS == 1 && NW > 1 && LD::DBUF), "the shifted grid exists for wide bf16 workgroups with double buffers");
   static_assert(KS == 1 || LD::DBUF, "the single-buffer loop has workgroup barriers, which waves with different K ranges cannot share");
@@ -427,6 +445,8 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   constexpr int BLOCK_KB = T::CH_BYTES / 1024;
   constexpr int STAGE_BYTES = LD::STAGE_BYTES;
   constexpr bool DBUF = LD::DBUF;
+  constexpr bool SPLIT = LD::SPLIT;
+  static_assert(!SPLIT || (MB <= 2 && !RING && KS == 1), "four row blocks of split operands run as two groups of two");
   constexpr int COPIES = (AD_KB + NW - 1) / NW;        // async copies issued per wave per chunk
   constexpr int WREGS = BF16 ? 4 : 8;
 
@@ -448,13 +468,16 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   // a candidate (its activations) is reused inside the workgroup through LDS.
   // TAIL: the block indices from a.main_blocks on are the sliced tiles, numbered [tiles of the pass at x]
   // [tail candidates x tiles], a.tail_slices consecutive blocks per tile; the pass at x has no leading blocks then.
+  // Row groups (SPLIT): the samples run in a.row_groups groups of 32 MB rows, each a workgroup of its own per tile; the groups of a
+  // source count as sources of their own and follow each other, so that they share the source's rows through their XCD's L2.
+  const int groups = SPLIT ? a.row_groups : 1;
   bool is_base = (int)blockIdx.x < a.base_blocks;
   int tail_tile = -1;   // >= 0: this workgroup runs one K slice of that tile of the tail
   int tail_base_tiles = 0;
   if constexpr (TAIL) {
     if ((int)blockIdx.x >= a.main_blocks) {
       tail_tile = ((int)blockIdx.x - a.main_blocks) / a.tail_slices;
-      tail_base_tiles = a.has_base ? (cover_rows(a.bj.N, a.bj.last) + BN - 1) / BN : 0;
+      tail_base_tiles = a.has_base ? (cover_rows(a.bj.N, a.bj.last) + BN - 1) / BN * groups : 0;
       is_base = tail_tile < tail_base_tiles;
     }
   }
@@ -462,7 +485,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   const int N = J.N, K = J.K, last = J.last, Np = J.Np;
   const int n_chunks = J.Kp >> 6;
   const int n_tiles = (cover_rows(N, last) + BN - 1) / BN;
-  int nt, s = 0;
+  int nt, s = 0, group = 0;
   // K slice of this workgroup: a launch of one-wave tiles whose tiles do not fill the chip well splits K
   // over k_slices workgroups per tile (on top of, or instead of, the split over the KS waves of a workgroup)
   int ks = 0;
@@ -471,43 +494,53 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   if (TAIL && tail_tile >= 0) {
     ks = ((int)blockIdx.x - a.main_blocks) % n_slices;
     if (is_base) {
-      nt = tail_tile;
+      nt = tail_tile / groups;
+      group = tail_tile % groups;
     } else if (n_main == 0) {
       // every tile is sliced: (tile, slice) pairs take the place of the tiles in the schedule below
       const int bid = (int)blockIdx.x - a.main_blocks - tail_base_tiles * n_slices;
       const int cc = a.src_chunk;
-      const int n_cchunks = (a.n_cand + cc - 1) / cc;
+      const int n_cchunks = (a.n_cand * groups + cc - 1) / cc;
       const int xcd = bid & 7, slot = bid >> 3;
       const int unit = (slot / cc) * 8 + xcd;
       if (unit >= n_tiles * n_slices * n_cchunks) return;
       nt = unit / n_cchunks / n_slices;
       ks = unit / n_cchunks % n_slices;
       s = (unit % n_cchunks) * cc + slot % cc;
-      if (s >= a.n_cand) return;
+      if (s >= a.n_cand * groups) return;
       tail_tile = tail_base_tiles + s * n_tiles + nt;   // its number among the tiles that hand over
+      group = s % groups;
+      s /= groups;
     } else {
       const int g = tail_tile - tail_base_tiles;
       nt = g % n_tiles;
-      s = n_main + g / n_tiles;
-      if (s >= a.n_cand) return;
+      s = n_main * groups + g / n_tiles;
+      if (s >= a.n_cand * groups) return;
+      group = s % groups;
+      s /= groups;
     }
   } else if (is_base) {
     nt = blockIdx.x / n_slices;
     ks = blockIdx.x % n_slices;
+    group = nt % groups;
+    nt /= groups;
     if (nt >= n_tiles) return;
   } else {
     int bid = blockIdx.x - a.base_blocks;
     ks = bid % n_slices;
     bid /= n_slices;
     const int cc = a.src_chunk;
-    const int n_cchunks = (n_main + cc - 1) / cc;
+    const int n_cchunks = (n_main * groups + cc - 1) / cc;
     const int xcd = bid & 7, slot = bid >> 3;
     const int unit = (slot / cc) * 8 + xcd;
     if (unit >= n_tiles * n_cchunks) return;
     nt = unit / n_cchunks;
     s = (unit % n_cchunks) * cc + slot % cc;
-    if (s >= n_main) return;
+    if (s >= n_main * groups) return;
+    group = s % groups;
+    s /= groups;
   }
+  const int mb0 = MB * group;   // first 32-row block of this workgroup's samples
   const float* __restrict__ P = is_base ? a.x : a.G + (long long)s * a.ldg;
   const int row0 = nt * BN + wave * 32;
   const float* __restrict__ Urow0 = P + J.w_off + (long long)row0 * K;  // wave-uniform
@@ -526,7 +559,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   const bool has_delta = DELTA && !is_base;
   const unsigned char* Dg = has_delta ? reinterpret_cast<const unsigned char*>(a.D_cand) + (long long)s * a.A_stride : Ag;
 
-  const bool pack = is_base && J.Wt != nullptr;
+  const bool pack = is_base && J.Wt != nullptr && group == 0;
   unsigned char* Wt_wave = reinterpret_cast<unsigned char*>(J.Wt) +
                            ((long long)(row0 >> 5) * n_chunks * WREGS * 64 + lane) * 16;
   // The main loop exists in six versions chosen per wave: full tile / full K with some
@@ -546,8 +579,16 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
 #pragma unroll
     for (int j = 0; j < 16; ++j) acc[mb][j] = 0.f;
 
-  const bool do_norm = (a.norm_partials != nullptr) && !is_base;
+  const bool do_norm = (a.norm_partials != nullptr) && !is_base && group == 0;
   double nrm = 0.0;
+  // SPLIT: the products below the leading ones (acc); joined behind the loop (join_split)
+  f32x16 rest[SPLIT ? MB : 1];
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int j = 0; j < 16; ++j) rest[mb][j] = 0.f;
+  }
 
   f32x4 u0[8], u1[8];
   f32x4 w0[WREGS], w1[WREGS];
@@ -751,9 +792,269 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     if (SECOND && (STEADY || c + 2 < c_end)) load_W(w, c + 2);
   };
 
+  // ---- SPLIT.  Activations: a step of 64 / STEPS columns holds (operand, row block, k-step of 16) units of 2 KB of floats in operand
+  // order, two 8-wide blocks of a lane's row each; the waves deal them out, load them to registers one step ahead, split them
+  // once for the whole workgroup and write the three pieces, 16 bytes a lane each, to the step's buffer.
+  // Weights: the tile is staged as floats and read back as two 8-wide blocks per k-step of 16 (the order of k inside a step is free, as
+  // long as both operands have the same); U and W - gamma U are split in registers.
+  // A wave issues in order, and a matrix instruction behind another waits for it: the vector instructions of the operand after
+  // next, of the activations and of the next tile's staging stand between the matrix instructions, a pair of floats (11) at a time,
+  // fenced, since the compiler would put all products of an operand behind its split and the two waves of a SIMD then find
+  // each other's pipe idle (2048 -> 2048, 64 candidates, n_r = 32: matrix cores busy for 32 % of the launch that way).
+  constexpr int STEPS = LD::STEPS, STEP_T = 4 / STEPS;    // activation steps of a chunk, k-steps of 16 of a step
+  constexpr int UNITS_1 = MB * STEP_T;                     // units of one operand
+  constexpr int HELD = SPLIT ? (UNITS_1 * (DELTA ? 2 : 1) + NW - 1) / NW : 1;
+  // Weight tiles in flight behind the staged one: two where the registers hold them.
+  constexpr int AHEAD = MB == 1 && !DELTA ? 2 : 1;
+  f32x4 act[HELD][2];
+  f32x4 raw[2][2];     // the two 8-wide blocks of the k-step in hand and of the one after it
+  SplitWords oper;     // the operand whose products come next
+  auto fence = [] __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+  auto load_act = [&](auto second_c, int step, int i) __attribute__((always_inline)) {
+    constexpr int UNITS = UNITS_1 * (decltype(second_c)::value ? 2 : 1);
+    int q = wave + i * NW;
+    if (UNITS % NW != 0) q = q < UNITS ? q : q % UNITS;   // a wave without a unit loads another's, so that no load is conditional
+    const int op = q / UNITS_1, mb = q % UNITS_1 / STEP_T, t = q % STEP_T;
+    const unsigned char* src = (op ? Dg : Ag) + (long long)(mb0 + mb) * n_chunks * T::CH_BYTES + (long long)step * (T::CH_BYTES / STEPS) +
+                               t * 2048 + lane * 16;
+    act[i][0] = *reinterpret_cast<const f32x4*>(src);
+    act[i][1] = *reinterpret_cast<const f32x4*>(src + 1024);
+  };
+  auto store_act = [&](auto second_c, const SplitWords& p, int buf, int i) __attribute__((always_inline)) {
+    constexpr int UNITS = UNITS_1 * (decltype(second_c)::value ? 2 : 1);
+    const int q = wave + i * NW;
+    if (UNITS % NW == 0 || q < UNITS) {
+      unsigned char* dst = lds + buf * AD_BYTES + q * 3072 + lane * 16;
+      *reinterpret_cast<u32x4*>(dst) = p.h;
+      *reinterpret_cast<u32x4*>(dst + 1024) = p.m;
+      *reinterpret_cast<u32x4*>(dst + 2048) = p.l;
+    }
+  };
+  auto read_raw = [&](f32x4 (&r)[2], int t) __attribute__((always_inline)) {
+    const int n = lane & 31, h = lane >> 5;
+    r[0] = *reinterpret_cast<const f32x4*>(stU + n * 256 + ((((4 * t + h) ^ n) & 15) << 4));
+    r[1] = *reinterpret_cast<const f32x4*>(stU + n * 256 + ((((4 * t + 2 + h) ^ n) & 15) << 4));
+  };
+  // One row group (four rows) of a tile: rows beyond the matrix discarded, its share of the norm, staged.
+  auto take_row = [&](auto full_c, auto base_c, f32x4 (&u)[8], float& q, int i) __attribute__((always_inline)) {
+    constexpr int MODE = decltype(full_c)::value;
+    const int r = 4 * i + (lane >> 4), kq = lane & 15;
+    f32x4 v = u[i];
+    if (MODE != 1) {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      v = row0 + r < N ? v : zero;
+    }
+    // A NaN needs its payload in the upper half (split_pair); a candidate's NaN reaches its score through its squared norm anyway.
+    if (decltype(base_c)::value) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = v[e] != v[e] ? __builtin_nanf("") : v[e];
+    } else {
+      q += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+    }
+    *reinterpret_cast<f32x4*>(stU + r * 256 + (((kq ^ r) & 15) << 4)) = v;
+  };
+  // Chunk c: `oper` and raw[0] hold its first operand, u its successor's tile.
+  auto chunk_split = [&](auto full_c, auto base_c, auto steady_c, auto odd, f32x4 (&u)[8], int c) __attribute__((always_inline)) {
+    const bool ODD = odd;   // c's parity, a constant in the steady loop
+    constexpr int MODE = decltype(full_c)::value;
+    constexpr bool BASE = decltype(base_c)::value;
+    constexpr bool STEADY = decltype(steady_c)::value;
+    constexpr bool SECOND = DELTA && !BASE;
+    using Second = std::integral_constant<bool, SECOND>;
+    constexpr int OPS = SECOND ? 2 : 1;
+    constexpr int SLOTS = 4 * OPS, STEP_SLOTS = SLOTS / STEPS;   // a slot: the products of one operand and k-step
+    constexpr int HELD_NOW = (UNITS_1 * OPS + NW - 1) / NW;
+    constexpr int PAIRS = (4 * HELD_NOW + STEP_SLOTS - 1) / STEP_SLOTS;   // pairs of the activations split in a slot
+    constexpr int PRODUCTS = 6 * MB;
+    const bool next_tile = STEADY || c + 1 < c_end;
+    Split8 as[MB];
+    SplitWords words;
+    float q = 0.f;
+    if constexpr (!SECOND) read_raw(raw[1], 1);
+    static_for<SLOTS>([&](auto slot_c) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_c)::value;
+      constexpr int t = slot / OPS, op = slot % OPS, sub = slot / STEP_SLOTS, in_step = slot % STEP_SLOTS;
+      const int buf = STEPS == 1 ? (ODD ? 1 : 0) : sub & 1;
+      const int step = c * STEPS + sub;
+      const bool split_next = STEADY || step + 1 < c_end * STEPS, load_next = STEADY || step + 2 < c_end * STEPS;
+      auto read_act = [&](int mb, int of_slot) __attribute__((always_inline)) {
+        const int ot = of_slot / OPS % STEP_T, oo = of_slot % OPS;
+        const unsigned char* at = lds + buf * AD_BYTES + (oo * UNITS_1 + mb * STEP_T + ot) * 3072 + lane * 16;
+        Split8 p;
+        p.h = *reinterpret_cast<const bf16x8*>(at);
+        p.m = *reinterpret_cast<const bf16x8*>(at + 1024);
+        p.l = *reinterpret_cast<const bf16x8*>(at + 2048);
+        return p;
+      };
+      if (in_step == 0) {
+        __syncthreads();   // the pieces of this step are written; everyone is done with the other buffer
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) as[mb] = read_act(mb, slot);
+      }
+      constexpr bool more_in_step = in_step + 1 < STEP_SLOTS;
+      Split8 as_next[MB];
+      if (MB == 1 && more_in_step) as_next[0] = read_act(0, slot + 1);
+      // blocks of the k-step that an operand of the next slot but one belongs to
+      f32x4 ahead[2];
+      constexpr bool wraps = t == 3 && op == OPS - 1;   // the next operand is the next chunk's first
+      constexpr bool read_ahead = SECOND ? op == 0 && t < 3 : t < 2;
+      if (read_ahead) read_raw(ahead, SECOND ? t + 1 : t + 2);
+      if (wraps && next_tile) read_raw(ahead, 0);
+      const Split8 cur = {__builtin_bit_cast(bf16x8, oper.h), __builtin_bit_cast(bf16x8, oper.m), __builtin_bit_cast(bf16x8, oper.l)};
+      SplitWords next;
+      auto next_pair = [&](auto pair_c) __attribute__((always_inline)) {
+        constexpr int I = decltype(pair_c)::value;
+        const f32x4& src = SECOND && op == 0 ? raw[0][I / 2] : wraps ? ahead[I / 2] : raw[1][I / 2];
+        float x = src[2 * I % 4], y = src[2 * I % 4 + 1];
+        if (SECOND && op == 0) {
+          x = __builtin_fmaf(neg_gamma, x, w0[2 * t + I / 2][2 * I % 4]);
+          y = __builtin_fmaf(neg_gamma, y, w0[2 * t + I / 2][2 * I % 4 + 1]);
+        }
+        next.template pair<I>(x, y);
+      };
+      auto act_pair = [&](auto j_c) __attribute__((always_inline)) {   // number of the pair in the step
+        constexpr int i = decltype(j_c)::value / 4, e = decltype(j_c)::value % 4;
+        if constexpr (i < HELD_NOW) {
+          if (!split_next) return;
+          words.template pair<e>(act[i][e / 2][2 * e % 4], act[i][e / 2][2 * e % 4 + 1]);
+          if constexpr (e == 3) {
+            store_act(Second{}, words, buf ^ 1, i);
+            if (load_next) load_act(Second{}, step + 2, i);
+          }
+        }
+      };
+      fence();
+      static_for<PRODUCTS>([&](auto k_c) __attribute__((always_inline)) {
+        constexpr int k = decltype(k_c)::value, mb = k / 6, kind = k % 6;   // smallest products first
+        const bf16x8 a = kind == 0 ? cur.l : kind == 2 || kind == 3 ? cur.m : cur.h;
+        const bf16x8 b = kind == 1 ? as[mb].l : kind == 2 || kind == 4 ? as[mb].m : as[mb].h;
+        if constexpr (kind < 5) rest[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, rest[mb], 0, 0, 0);
+        else acc[mb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[mb], 0, 0, 0);
+        if (MB > 1 && more_in_step && k % 6 == 5) as_next[mb] = read_act(mb, slot + 1);
+        // the vector work of this position: four pairs of the next operand, the step's activations, the next tile's rows
+        constexpr int pk = MB == 1 ? (wraps ? k - 2 : k) : k / 2 - 1;
+        if constexpr ((MB == 1 || k % 2 == 0) && pk >= 0 && pk < 4) {
+          if (!wraps || next_tile) next_pair(std::integral_constant<int, pk>{});
+        }
+        constexpr int ap = MB == 1 ? (wraps ? k : k - 4) : k % 2 ? k / 2 : -1;
+        if constexpr (ap >= 0 && ap < PAIRS) act_pair(std::integral_constant<int, in_step * PAIRS + ap>{});
+        if (slot == SLOTS - 2 && next_tile) {
+          if (MB == 1 ? k < 4 : k < 8) {
+            take_row(full_c, base_c, u, q, MB == 1 ? 2 * k : k);
+            if (MB == 1) take_row(full_c, base_c, u, q, 2 * k + 1);
+          }
+          if (k == PRODUCTS - 1) {
+            if (do_norm) nrm += (double)q;
+            if (STEADY || c + 1 + AHEAD < c_end)
+              load_tile<MODE, NT>(u, Urow0 + ((c + 1 + AHEAD) << 6), lane_off, row0, (c + 1 + AHEAD) << 6, N, K, lane);
+          }
+        }
+        fence();
+      });
+      if (SECOND && op == 0 && next_tile) {   // W - gamma U is split: the same blocks of the next chunk's W
+        w0[2 * t] = *reinterpret_cast<const f32x4*>(Wt_wave + ((long long)(c + 1) * WREGS + 2 * t) * 1024);
+        w0[2 * t + 1] = *reinterpret_cast<const f32x4*>(Wt_wave + ((long long)(c + 1) * WREGS + 2 * t + 1) * 1024);
+      }
+      if (BASE && pack) {
+        *reinterpret_cast<f32x4*>(Wt_wave + ((long long)c * WREGS + 2 * t) * 1024) = raw[0][0];
+        *reinterpret_cast<f32x4*>(Wt_wave + ((long long)c * WREGS + 2 * t + 1) * 1024) = raw[0][1];
+      }
+      oper = next;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        if (SECOND) {
+          if (op == 0) raw[1][i] = ahead[i];
+          else raw[0][i] = wraps ? ahead[i] : raw[1][i];
+        } else {
+          raw[0][i] = wraps ? ahead[i] : raw[1][i];
+          raw[1][i] = ahead[i];
+        }
+      }
+      if (more_in_step) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) as[mb] = as_next[mb];
+      }
+    });
+  };
+
   auto run = [&](auto full_c, auto base_c) __attribute__((always_inline)) {
     constexpr int MODE = decltype(full_c)::value;
     constexpr bool SECOND = DELTA && !decltype(base_c)::value;
+    using SteadyMode = std::integral_constant<int, MODE == 0 ? 2 : MODE>;
+    if constexpr (SPLIT) {
+      using Second = std::integral_constant<bool, SECOND>;
+      if (J.b_off >= 0 && lane < 32 && row0 + lane < N) bias_lane = P[J.b_off + row0 + lane];
+      int c = c_begin;
+      const float* Ufirst = Urow0 + (c_begin << 6);
+      const int c_full = MODE == 0 ? (c_end < (K >> 6) ? c_end : K >> 6) : c_end;
+      const bool steady = c_full - c_begin >= 3 + AHEAD;
+      constexpr int HELD_NOW = (UNITS_1 * (SECOND ? 2 : 1) + NW - 1) / NW;
+      // tile `ahead` chunks on
+      auto tile = [&](f32x4 (&u)[8], int ahead) __attribute__((always_inline)) {
+        if (steady) load_tile<SteadyMode::value, NT>(u, Ufirst + 64 * ahead, lane_off, row0, (c_begin + ahead) << 6, N, K, lane);
+        else if (c_begin + ahead < c_end) load_tile<MODE, NT>(u, Ufirst + 64 * ahead, lane_off, row0, (c_begin + ahead) << 6, N, K, lane);
+      };
+      // in the order in which the loop requests them: the compiler's wait counts in the loop are those of the worse of its two entries
+      const int first = c_begin * STEPS;
+#pragma unroll
+      for (int i = 0; i < HELD_NOW; ++i) load_act(Second{}, first, i);
+      fence();
+      tile(u0, 0);
+      fence();
+#pragma unroll
+      for (int i = 0; i < HELD_NOW; ++i) {
+        SplitWords p;
+        p.template pair<0>(act[i][0][0], act[i][0][1]);
+        p.template pair<1>(act[i][0][2], act[i][0][3]);
+        p.template pair<2>(act[i][1][0], act[i][1][1]);
+        p.template pair<3>(act[i][1][2], act[i][1][3]);
+        store_act(Second{}, p, 0, i);
+      }
+      fence();
+      if (AHEAD > 1) tile(u1, 1);
+      fence();
+      if (first + 1 < c_end * STEPS) {
+#pragma unroll
+        for (int i = 0; i < HELD_NOW; ++i) load_act(Second{}, first + 1, i);
+      }
+      fence();
+      if (SECOND) load_W(w0, c);
+      fence();
+      float q = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        if (steady) take_row(SteadyMode{}, base_c, u0, q, i);
+        else take_row(full_c, base_c, u0, q, i);
+      }
+      if (do_norm) nrm += (double)q;
+      fence();
+      tile(u0, AHEAD);
+      fence();
+      read_raw(raw[0], 0);
+      oper.template pair<0>(raw[0][0][0], raw[0][0][1]);
+      oper.template pair<1>(raw[0][0][2], raw[0][0][3]);
+      oper.template pair<2>(raw[0][1][0], raw[0][1][1]);
+      oper.template pair<3>(raw[0][1][2], raw[0][1][3]);
+      if (steady) {
+        for (; c + 2 + AHEAD < c_full; c += 2) {
+          chunk_split(SteadyMode{}, base_c, std::true_type{}, std::false_type{}, AHEAD > 1 ? u1 : u0, c);
+          chunk_split(SteadyMode{}, base_c, std::true_type{}, std::true_type{}, u0, c + 1);
+        }
+      }
+      if constexpr (AHEAD > 1) {
+        for (; c < c_end; c += 2) {
+          chunk_split(full_c, base_c, std::false_type{}, std::false_type{}, u1, c);
+          if (c + 1 < c_end) chunk_split(full_c, base_c, std::false_type{}, std::true_type{}, u0, c + 1);
+        }
+      } else {
+        for (; c < c_end; ++c) chunk_split(full_c, base_c, std::false_type{}, (c & 1) != 0, u0, c);
+      }
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[mb][j] = join_split(acc[mb][j], rest[mb][j]);
+      return;
+    }
     // The wave's 32 bias values are requested first of all (lane i < 32 keeps feature row0 + i's),
     // so that the epilogue does not start with a round trip to memory.
     if (J.b_off >= 0 && lane < 32 && row0 + lane < N) bias_lane = P[J.b_off + row0 + lane];
@@ -790,7 +1091,6 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     // steady loop of MODE 2, whose loads cross chunks, in wide workgroups (the waves of one-wave tiles split K and have few
     // chunks each, where the longer code only costs: 784 -> 10, 20 candidates: 16 -> 17 us) (33 candidates, 1001 -> 777, bf16, n_r = 128: 51 -> 43 us;
     // 3000 -> 1000, fp32, n_r = 32: 149 -> 121 us; 1500 -> 700, bf16, n_r = 32: 54 -> 42 us).
-    using SteadyMode = std::integral_constant<int, MODE == 0 ? 2 : MODE>;
     const int c_full = MODE == 0 ? (c_end < (K >> 6) ? c_end : K >> 6) : c_end;
     if ((MODE != 0 || NW > 1) && DBUF && c_full - c_begin >= 4) {
       // steady state: pairs of chunks whose loads (two chunks ahead) all exist
@@ -822,14 +1122,13 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
   };
   using M0 = std::integral_constant<int, 0>;
   using M1 = std::integral_constant<int, 1>;
-  using M2 = std::integral_constant<int, 2>;
   if (is_base) {
     if (all_full && full_rows) run(M1{}, std::true_type{});
-    else if (all_full || RING) run(M2{}, std::true_type{});   // the shifted grid is only launched for K a multiple of 64
+    else if (!SPLIT && (all_full || RING)) run(std::integral_constant<int, SPLIT ? 0 : 2>{}, std::true_type{});   // the shifted grid is only launched for K a multiple of 64
     else run(M0{}, std::true_type{});
   } else {
     if (all_full && full_rows) run(M1{}, std::false_type{});
-    else if (all_full || RING) run(M2{}, std::false_type{});
+    else if (!SPLIT && (all_full || RING)) run(std::integral_constant<int, SPLIT ? 0 : 2>{}, std::false_type{});
     else run(M0{}, std::false_type{});
   }
 
@@ -1007,7 +1306,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     if (hidden_cand) {
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        const int r = 32 * mb + n;
+        const int r = 32 * (mb0 + mb) + n;
         const int rc = r < a.n_r ? r : a.n_r - 1;
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -1016,7 +1315,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      const int r = 32 * mb + n;
+      const int r = 32 * (mb0 + mb) + n;
       const bool row_ok = r < a.n_r;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -1057,7 +1356,7 @@ __global__ __launch_bounds__(64 * NW * KS) void layer_kernel(const LayerArgs a) 
     // ragged tile: per-element guards
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) {
-      const int r = 32 * mb + n;
+      const int r = 32 * (mb0 + mb) + n;
       const bool row_ok = r < a.n_r;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -1133,7 +1432,8 @@ __global__ void pack_features_kernel(const float* __restrict__ features, int n_r
     zero[i] = 0.0;
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
     const int r = (int)(i / Kp), k = (int)(i % Kp);
-    const float v = (r < n_r && k < K) ? features[(long long)r * K + k] : 0.f;
+    float v = (r < n_r && k < K) ? features[(long long)r * K + k] : 0.f;
+    if (!BF16 && v != v) v = __builtin_nanf("");   // split_pair needs a NaN's payload in its upper half
     store_tiled<BF16>(tiled, r, k, Kp, v);
   }
 }
@@ -1157,7 +1457,7 @@ inline int source_chunk(int tiles, int n_src) {
 
 int job_tiles(const LayerJob& j, int BN) { return (cover_rows(j.N, j.last) + BN - 1) / BN; }
 
-template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS = 1, int RING = 0, bool TAIL = false>
+template <bool BF16, bool DELTA, int MB, int NW, bool NT, int KS = 1, int RING = 0, bool TAIL = false, bool F32 = false>
 hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   constexpr int BN = 32 * NW;
   if (shape != nullptr) {
@@ -1167,33 +1467,39 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
     shape->streaming = RING ? 1 + RING : NT ? 1 : 0;
     shape->row_blocks = MB;
   }
-  constexpr int lds_bytes = Lds<BF16, DELTA, MB, NW, RING>::TOTAL * KS;
+  using LD = Lds<BF16, DELTA, MB, NW, RING, F32>;
+  constexpr int lds_bytes = LD::TOTAL * KS;
   // once per process and instantiation (initialisation of a local static is thread-safe)
   static const hipError_t attr_err =
-      lds_bytes > 48 * 1024 ? hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_kernel<BF16, DELTA, MB, NW, NT, KS, RING, TAIL>),
+      lds_bytes > 48 * 1024 ? hipFuncSetAttribute(reinterpret_cast<const void*>(&layer_kernel<BF16, DELTA, MB, NW, NT, KS, RING, TAIL, F32>),
                                                   hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes)
                             : hipSuccess;
   if (attr_err != hipSuccess) return attr_err;
   // K slices (one-wave tiles only) come with the caller's plan; they need the partial and counter buffers
   if (NW != 1 || a.k_slices < 1) a.k_slices = 1;
   if (a.k_slices > 1 && (a.slice_partials == nullptr || a.slice_counters == nullptr)) return hipErrorInvalidValue;
+  constexpr bool SPLIT = LD::SPLIT;
+  const int groups = SPLIT ? a.row_groups : 1;
+  if (groups < 1 || (!SPLIT && a.row_groups > 1)) return hipErrorInvalidValue;
+  if (shape != nullptr) shape->row_blocks = MB * groups;
   if (!TAIL) a.tail_cand = a.tail_slices = 0;
   if (TAIL && (a.tail_cand < 0 || a.tail_cand > a.n_cand || (a.tail_cand == 0 && !a.has_base) || a.tail_slices < 2 ||
                a.slice_partials == nullptr || a.slice_counters == nullptr))
     return hipErrorInvalidValue;
   // TAIL: the pass at x has no leading blocks, its tiles are sliced like the tail candidates'
-  a.base_blocks = (a.has_base && !TAIL) ? (job_tiles(a.bj, BN) * a.k_slices + 7) / 8 * 8 : 0;
+  a.base_blocks = (a.has_base && !TAIL) ? (job_tiles(a.bj, BN) * groups * a.k_slices + 7) / 8 * 8 : 0;
   const int n_main = a.n_cand - a.tail_cand;
   int cand_blocks = 0;
   if (n_main > 0) {
-    const int cc = a.src_chunk = source_chunk(job_tiles(a.cj, BN), n_main);
+    const int cc = source_chunk(job_tiles(a.cj, BN), n_main);
     const int units = job_tiles(a.cj, BN) * ((n_main + cc - 1) / cc);
-    cand_blocks = ((units + 7) / 8) * 8 * cc * a.k_slices;
+    a.src_chunk = cc * groups;
+    cand_blocks = ((units + 7) / 8) * 8 * cc * groups * a.k_slices;
   }
   a.main_blocks = a.base_blocks + cand_blocks;
   int tail_blocks = 0;
   if (TAIL) {
-    const long long tiles = (a.has_base ? job_tiles(a.bj, BN) : 0) + (long long)job_tiles(a.cj, BN) * a.tail_cand;
+    const long long tiles = ((a.has_base ? job_tiles(a.bj, BN) : 0) + (long long)job_tiles(a.cj, BN) * a.tail_cand) * groups;
     // every slice keeps at least two chunks of every job; the hand-over buffers hold all sliced tiles
     if ((a.cj.Kp >> 6) < 2 * a.tail_slices || (a.has_base && (a.bj.Kp >> 6) < 2 * a.tail_slices) || tiles > kMaxSliceGroups ||
         (n_main > 0 && tiles * a.tail_slices > kMaxTailWorkgroups))
@@ -1201,12 +1507,13 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
     if (n_main > 0) {
       tail_blocks = (int)tiles * a.tail_slices;
     } else {
-      const int cc = a.src_chunk = source_chunk(job_tiles(a.cj, BN) * a.tail_slices, a.n_cand);
+      const int cc = source_chunk(job_tiles(a.cj, BN) * a.tail_slices, a.n_cand);
       const int units = job_tiles(a.cj, BN) * a.tail_slices * ((a.n_cand + cc - 1) / cc);
-      tail_blocks = (a.has_base ? job_tiles(a.bj, BN) * a.tail_slices : 0) + (units + 7) / 8 * 8 * cc;
+      a.src_chunk = cc * groups;
+      tail_blocks = (a.has_base ? job_tiles(a.bj, BN) * groups * a.tail_slices : 0) + (units + 7) / 8 * 8 * cc * groups;
     }
   }
-  hipLaunchKernelGGL((layer_kernel<BF16, DELTA, MB, NW, NT, KS, RING, TAIL>), dim3(a.main_blocks + tail_blocks),
+  hipLaunchKernelGGL((layer_kernel<BF16, DELTA, MB, NW, NT, KS, RING, TAIL, F32>), dim3(a.main_blocks + tail_blocks),
                      dim3(64 * NW * KS), lds_bytes, stream, a);
   return hipGetLastError();
 }
@@ -1237,8 +1544,10 @@ constexpr int split_k_waves() {
 // k_waves > 1: the one-wave-tile instantiation whose workgroups split K over that many waves
 template <bool BF16, bool DELTA, int MB>
 int wgs_per_cu_nw(int NW, int k_waves) {
-  if (NW == 8) return wgs_per_cu_inst<BF16, DELTA, MB, 8, 1>();
-  if (NW == 4) return wgs_per_cu_inst<BF16, DELTA, MB, 4, 1>();
+  if constexpr (BF16 || MB < 4) {
+    if (NW == 8) return wgs_per_cu_inst<BF16, DELTA, MB, 8, 1>();
+    if (NW == 4) return wgs_per_cu_inst<BF16, DELTA, MB, 4, 1>();
+  }
   constexpr int KS = split_k_waves<BF16, DELTA, MB>();
   if constexpr (KS > 1) {
     if (k_waves == KS) return wgs_per_cu_inst<BF16, DELTA, MB, 1, KS>();
@@ -1304,6 +1613,15 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
     const bool cand_ok = a.n_cand == 0 || (a.cj.Kp >> 6) >= 2 * a.k_slices;
     if (!(base_ok && cand_ok)) return hipErrorInvalidValue;
   }
+  if constexpr (!BF16 && !DELTA && MB == 1 && NW == 4) {
+    if (a.float_products) {
+      const bool lines = launch_lines_aligned(a);
+      if (a.tail_slices >= 2) return lines ? launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true, true>(a, stream, shape)
+                                           : launch_inst<BF16, DELTA, MB, NW, false, 1, 0, true, true>(a, stream, shape);
+      return lines ? launch_inst<BF16, DELTA, MB, NW, true, 1, 0, false, true>(a, stream, shape)
+                   : launch_inst<BF16, DELTA, MB, NW, false, 1, 0, false, true>(a, stream, shape);
+    }
+  }
   if constexpr (NW == 4 && Lds<BF16, DELTA, MB, NW>::DBUF) {
     if (a.tail_slices >= 2) {
       if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true>(a, stream, shape);
@@ -1333,8 +1651,11 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
 
 template <bool BF16, bool DELTA, int MB>
 hipError_t launch_nw(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape) {
-  if (NW == 8) return launch_nt<BF16, DELTA, MB, 8>(a, stream, shape);
-  if (NW == 4) return launch_nt<BF16, DELTA, MB, 4>(a, stream, shape);
+  if constexpr (BF16 || MB < 4) {   // float32 operands: see row_groups
+    if (NW == 8) return launch_nt<BF16, DELTA, MB, 8>(a, stream, shape);
+    if (NW == 4) return launch_nt<BF16, DELTA, MB, 4>(a, stream, shape);
+  }
+  if (NW != 1) return hipErrorInvalidValue;
   return launch_nt<BF16, DELTA, MB, 1>(a, stream, shape);
 }
 
@@ -1349,9 +1670,9 @@ int pick_nw(int rows, int n_src) {
 }
 
 // Waves per workgroup of a launch, from the job that dominates it.
-int launch_nw_for(const LayerArgs& a) {
-  if (a.n_cand > 0) return pick_nw(cover_rows(a.cj.N, a.cj.last), a.n_cand);
-  return pick_nw(cover_rows(a.bj.N, a.bj.last), 1);
+int launch_nw_for(const LayerArgs& a, int groups) {
+  if (a.n_cand > 0) return pick_nw(cover_rows(a.cj.N, a.cj.last), a.n_cand * groups);
+  return pick_nw(cover_rows(a.bj.N, a.bj.last), groups);
 }
 
 }  // namespace

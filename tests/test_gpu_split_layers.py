@@ -1,0 +1,74 @@
+"""Wide workgroups with split float32 operands (three bf16 pieces), one and two row blocks, and two groups of two row blocks:
+every score against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_10032_amd import workloads as WL
+from tests._util import SCORE_TOL, npy, oracle_terms, rows_to_gpu, score_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_1805_10032_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _run(B, w, row_align, G=None):
+    dev = torch.device("cuda", 0)
+    mdl = B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd)
+    G = rows_to_gpu(B, w.G if G is None else G, row_align, dev)
+    B.profile_enable(True)
+    try:
+        s = B.zeno_score(mdl, w.x.to(dev), G, w.features.to(dev), w.gamma, w.rho, labels=w.labels.to(dev))
+        torch.cuda.synchronize()
+        recs = [r for r in B.profile_collect(detail=True) if r["kernel"] == "layer_cand"]
+    finally:
+        B.profile_enable(False)
+    return npy(s), recs
+
+
+def _workload(name, dims, m, n_r, fwd="fp32", bias=True):
+    return WL.make_mlp_workload(name, 300 + n_r, dims, m, m // 3, n_r, 0.05, 1e-3, fwd, seed=m, has_bias=bias, n_flip=m // 6,
+                                n_noise=m // 6, noise_std=2.0, worker_batch=16)
+
+
+@pytest.mark.parametrize("n_r", [1, 32, 33, 64, 65, 97, 128])
+@pytest.mark.parametrize("dims,m,row_align,bias", [
+    ([512, 1024, 512, 10], 64, 32, True),     # four and eight waves, line-aligned rows
+    ([200, 1030, 500, 10], 57, 1, True),      # ragged K, tiles beyond the matrix, packed rows
+    ([130, 520, 260], 100, 4, False),         # three chunks: no steady loop
+])
+def test_split_operands(B, dims, m, row_align, bias, n_r):
+    """Both sides of every number of row blocks: 33 samples are two blocks, 65 two groups of two."""
+    w = _workload("split", dims, m, n_r, bias=bias)
+    s, recs = _run(B, w, row_align)
+    wide = [r for r in recs if r["waves"] >= 4]
+    assert len(wide) >= 2 and all(r["row_blocks"] == (1 if n_r <= 32 else 2 if n_r <= 64 else 4) for r in wide), recs
+    err = score_error(s, *oracle_terms(w))
+    assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
+
+
+def test_values_that_are_not_finite(B):
+    """Infinities, NaNs of any payload and the largest floats in a few candidates: their scores are not finite, and nobody else's
+    changes.  A NaN with its payload in the lower half must not become infinity on the way."""
+    w = _workload("special", [512, 1024, 512, 10], 64, 32)
+    clean, _ = _run(B, w, 32)
+    G = w.G.clone()
+    col = 3 * 512 + 7   # inside the first layer's weights
+    second = 1024 * 512 + 1024 + 5 * 1024 + 11
+    bits = torch.tensor([0x7f800001, -8388607], dtype=torch.int32).view(torch.float32)   # NaNs, payload in the lower half
+    G[0, col], G[1, col], G[2, col], G[3, col] = float("inf"), float("-inf"), float("nan"), 3.402e38
+    G[4].view(-1)[col:col + 1] = bits[:1]
+    G[5].view(-1)[second:second + 1] = bits[1:]
+    G[6, second], G[7, second] = float("inf"), -3.402e38
+    s, recs = _run(B, w, 32, G)
+    assert all(r["waves"] >= 4 for r in recs[:2]), recs
+    assert not np.isfinite(s[[0, 1, 2, 4, 5, 6]]).any(), s[:8]
+    assert np.isnan(s[[2, 4, 5]]).all(), s[:8]
+    assert (np.isnan(s[[3, 7]]) | (s[[3, 7]] < -1e30)).all(), s[:8]
+    assert np.array_equal(s[8:], clean[8:])
+
