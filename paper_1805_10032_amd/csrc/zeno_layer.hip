@@ -107,7 +107,7 @@ KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bo
   const int min_chunks = base_chunks < cand_chunks ? base_chunks : cand_chunks;
   const long long groups = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
   const int ks_max = ks_waves(bf16, delta, MB);
-  const bool wide_ok = ks_max > 1 && min_chunks >= 2 * ks_max;
+  const bool wide_ok = ks_max > 1 && (a.n_cand > 0 ? cand_chunks : base_chunks) >= ks_max;
   const bool can_slice = a.slice_partials != nullptr && a.slice_counters != nullptr && groups <= kMaxSliceGroups;
   // most workgroups per tile that the buffers and the two-chunk rule allow
   auto max_slices = [&](int kw) {
@@ -242,8 +242,10 @@ int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 //  * Layers without the second product in bf16, which wait for memory either way, only for four row blocks, or two beyond 1.25
 //    rounds (the others: 1.10, 8 of 49).
 static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int MB, int slices, double cost) {
-  const KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
+  KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
   const int chunks = a.cj.Kp >> 6, base_chunks = a.has_base ? a.bj.Kp >> 6 : 0;
+  // the lines below were measured with K split over waves where every job of the launch gives each wave two chunks
+  if (chunks < 2 * one.k_waves || (a.has_base && base_chunks < 2 * one.k_waves)) one.k_waves = 1;
   if (one.k_waves > 1 && base_chunks > 2 * chunks) return false;
   const long long base_tiles = a.has_base ? job_tiles(a.bj, 32) : 0, cand_tiles = (long long)job_tiles(a.cj, 32) * a.n_cand;
   const long long workgroups = (base_tiles + cand_tiles) * one.k_slices;

@@ -1594,15 +1594,14 @@ int launch_ring_kind(const LayerArgs& a) {
 
 template <bool BF16, bool DELTA, int MB, int NW>
 hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape) {
-  // One-tile workgroups whose plan splits K over the waves of a workgroup (every K of the launch gives each
-  // wave at least two chunks: the planner's condition, checked again because a wave without chunks would
-  // start a copy beyond the operand)
+  // One-tile workgroups whose plan splits K over the waves of a workgroup.  A wave may be without chunks (a short K of the
+  // pass at x); the chunk whose copy it starts all the same lies inside the operand as long as its slice has one.
   constexpr int KS = split_k_waves<BF16, DELTA, MB>();
   if constexpr (NW == 1 && KS > 1) {
     if (a.k_waves == KS) {
       const int slices = a.k_slices > 1 ? a.k_slices : 1;
-      const bool base_ok = !a.has_base || (a.bj.Kp >> 6) >= 2 * KS * slices;
-      const bool cand_ok = a.n_cand == 0 || (a.cj.Kp >> 6) >= 2 * KS * slices;
+      const bool base_ok = !a.has_base || (a.bj.Kp >> 6) >= slices;
+      const bool cand_ok = a.n_cand == 0 || (a.cj.Kp >> 6) >= slices;
       if (!((a.has_base || a.n_cand > 0) && base_ok && cand_ok)) return hipErrorInvalidValue;
       if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true, KS>(a, stream, shape);
       return launch_inst<BF16, DELTA, MB, NW, false, KS>(a, stream, shape);

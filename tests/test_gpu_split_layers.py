@@ -1,5 +1,5 @@
-"""Wide workgroups with split float32 operands (three bf16 pieces), one and two row blocks, and two groups of two row blocks:
-every score against the oracle."""
+"""Wide workgroups with split float32 operands (three bf16 pieces), one and two row blocks, two groups of two row blocks, and the
+one-wave tiles whose K is split over waves next to a pass at x of few chunks: every score against the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -72,3 +72,17 @@ def test_values_that_are_not_finite(B):
     assert (np.isnan(s[[3, 7]]) | (s[[3, 7]] < -1e30)).all(), s[:8]
     assert np.array_equal(s[8:], clean[8:])
 
+
+@pytest.mark.parametrize("dims,m,n_r,fwd,row_align", [
+    ([784, 256, 128, 10], 20, 32, "fp32", 1),    # the pass at x has four and two chunks next to 13 and four
+    ([512, 30, 200], 20, 20, "fp32", 32),        # ... one chunk: three of four waves have none
+    ([1000, 100, 40, 7], 24, 40, "bf16", 1),
+    ([300, 64, 64, 2], 9, 100, "bf16", 4),       # two waves a tile, one chunk each
+    ([256, 100, 64, 10], 40, 70, "fp32", 1),
+])
+def test_k_split_next_to_a_short_pass_at_x(B, dims, m, n_r, fwd, row_align):
+    w = _workload("shortk", dims, m, n_r, fwd)
+    s, recs = _run(B, w, row_align)
+    assert any(r["waves"] == 1 and r["k_split"] > 1 and r["merged"] for r in recs), recs
+    err = score_error(s, *oracle_terms(w))
+    assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
