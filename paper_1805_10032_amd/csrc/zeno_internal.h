@@ -73,7 +73,8 @@ struct LayerArgs {
   int has_base;         // 1: the launch also runs the pass at x through bj
   int base_blocks;      // leading block indices reserved for the pass at x (multiple of 8)
   int n_r;              // valid samples (rows) in this pass
-  int row_groups;       // wide workgroups with split float32 operands: groups of 32 MB rows, a workgroup each (filled in by the launcher)
+  int passes;           // groups of 128 samples that the launch runs side by side (0 or 1: one group, of at most 128)
+  int row_groups;       // groups of 32 MB rows, a workgroup each (filled in by the launcher: passes, twice that for split operands)
   int float_products;   // wide workgroups with float32 matrix instructions (filled in by the launcher)
   LayerJob cj, bj;
   const void* D_cand;   // tiled scaled activation differences of candidate 0 (delta launches only)
@@ -109,10 +110,12 @@ struct LayerArgs {
   int src_chunk;        // sources per scheduling unit, filled in by the launcher
 };
 
+inline int launch_passes(const LayerArgs& a) { return a.passes > 1 ? a.passes : 1; }
+
 // Launchers.  Each returns the hipError_t of its launches.
 // also clears the n_counters workgroup-arrival counters of the pass (may be 0)
 // ... and n_zero doubles at `zero` (the candidates' partial-norm slots; may be 0)
-hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int MB, bool bf16,
+hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int n_pad, bool bf16,
                                 void* tiled, unsigned int* counters, int n_counters, double* zero, long long n_zero,
                                 hipStream_t stream);
 // Limits of a launch whose K is split over workgroups: bytes of partial accumulators (tiles x slices x row
@@ -163,6 +166,7 @@ struct LayerExtents {
   long long slice_bytes;       // partial accumulators of a launch with K split over workgroups
   int slice_counters;          // arrival counters it uses
 };
+bool layer_passes_merge(const int* dims, int L, int m, bool bf16);   // may groups of 128 samples share their launches?
 LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device);
 hipError_t launch_loss(const float* Z0, const float* dZ, const int32_t* labels, const float* targets,
                        int loss, int m, int n_r_total, int chunk_begin, int chunk_rows, int C,

@@ -138,12 +138,20 @@ KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bo
   return plan;
 }
 
+// Does any candidate launch of these layers take eight-wave workgroups?  Those run one group of 128 samples at a time.  Host
+// arithmetic only: the workspace's size depends on it.
+bool layer_passes_merge(const int* dims, int L, int m, bool bf16) {
+  for (int l = 0; l < L; ++l)
+    if (pick_nw(cover_rows(dims[l + 1], l + 1 == L), m * row_groups(bf16, 4, 8)) == 8) return false;
+  return true;
+}
+
 // What a launch of workgroup width NW writes, from the kernel's own index formulas: the
 // host checks these against the workspace slots before anything is enqueued.
 LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device) {
   LayerExtents e;
   std::memset(&e, 0, sizeof(e));
-  const int esize = bf16 ? 2 : 4, wregs = bf16 ? 4 : 8, n_pad = 32 * MB;
+  const int esize = bf16 ? 2 : 4, wregs = bf16 ? 4 : 8, passes = launch_passes(a), n_pad = 32 * MB * passes;
   auto tiled_bytes = [&](int Np) {
     const long long last = bf16 ? tiled_index<true>(n_pad - 1, Np - 1, Np) : tiled_index<false>(n_pad - 1, Np - 1, Np);
     return (last + 1) * esize;
@@ -165,14 +173,14 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, device);
   if (kp.k_slices > 1) {
     const long long groups = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
-    e.slice_bytes = groups * kp.k_slices * MB * 16 * 64 * (long long)sizeof(float);
-    e.slice_counters = (int)groups;
+    e.slice_bytes = groups * passes * kp.k_slices * MB * 16 * 64 * (long long)sizeof(float);
+    e.slice_counters = (int)groups * passes;
     if (a.n_cand > 0) e.norm_slots *= kp.k_slices;
   }
   if (a.tail_slices >= 2 && NW == a.wide_nw) {
     const long long tiles = (a.has_base ? job_tiles(a.bj, 32 * NW) : 0) + (long long)job_tiles(a.cj, 32 * NW) * a.tail_cand;
-    e.slice_bytes = tiles * a.tail_slices * NW * MB * 16 * 64 * (long long)sizeof(float);
-    e.slice_counters = (int)tiles * row_groups(bf16, MB, NW);
+    e.slice_bytes = tiles * passes * a.tail_slices * NW * MB * 16 * 64 * (long long)sizeof(float);
+    e.slice_counters = (int)tiles * passes * row_groups(bf16, MB, NW);
     e.norm_slots = a.tail_p_off - a.p_off + job_tiles(a.cj, 32 * NW) * a.tail_slices;   // both ranges, counted from p_off
   }
   return e;
@@ -366,10 +374,9 @@ bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB) {
   return rounds_with == rounds_without || rounds_without >= 8;
 }
 
-hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int MB, bool bf16, void* tiled,
+hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int n_pad, bool bf16, void* tiled,
                                 unsigned int* counters, int n_counters, double* zero, long long n_zero,
                                 hipStream_t stream) {
-  const int n_pad = 32 * MB;
   const long long total = (long long)n_pad * Kp;
   const int grid = (int)((total + 255) / 256 > 4096 ? 4096 : (total + 255) / 256);
   if (bf16) {
@@ -385,7 +392,8 @@ hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, i
 hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipStream_t stream, LaunchShape* shape) {
   const int NW = nw_for(a, bf16, delta, MB);
   LayerArgs b = a;
-  b.row_groups = row_groups(bf16, MB, NW);
+  const int groups = row_groups(bf16, MB, NW);
+  b.row_groups = groups * launch_passes(a);
   // Four-wave workgroups with at most one per compute unit, one row block and one product: a wave has its SIMD to itself, and the
   // split of its operand takes as long as the float32 matrix instructions do, without a second wave to hide behind
   // (20 candidates, n_r = 32: 3072 -> 512 in 243 workgroups 37.0 us with float32 products, 37.6-38.0 with split operands).
@@ -396,8 +404,8 @@ hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipSt
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, true);
   b.k_waves = kp.k_waves;
   b.k_slices = kp.k_slices;
-  b.slice_group0 = (a.has_base && a.n_cand > 0) ? job_tiles(a.bj, 32) : 0;
-  MB /= b.row_groups;
+  b.slice_group0 = (a.has_base && a.n_cand > 0) ? job_tiles(a.bj, 32) * launch_passes(a) : 0;
+  MB /= groups;
   if (bf16) {
     return delta ? launch_layer_bf16_delta(b, MB, NW, stream, shape) : launch_layer_bf16_first(b, MB, NW, stream, shape);
   }

@@ -446,6 +446,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   constexpr int STAGE_BYTES = LD::STAGE_BYTES;
   constexpr bool DBUF = LD::DBUF;
   constexpr bool SPLIT = LD::SPLIT;
+  constexpr bool GROUPED = SPLIT || NW <= 4;
   static_assert(!SPLIT || (MB <= 2 && !RING && KS == 1), "four row blocks of split operands run as two groups of two");
   constexpr int COPIES = (AD_KB + NW - 1) / NW;        // async copies issued per wave per chunk
   constexpr int WREGS = BF16 ? 4 : 8;
@@ -468,9 +469,9 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   // a candidate (its activations) is reused inside the workgroup through LDS.
   // TAIL: the block indices from a.main_blocks on are the sliced tiles, numbered [tiles of the pass at x]
   // [tail candidates x tiles], a.tail_slices consecutive blocks per tile; the pass at x has no leading blocks then.
-  // Row groups (SPLIT): the samples run in a.row_groups groups of 32 MB rows, each a workgroup of its own per tile; the groups of a
+  // Row groups: the samples run in a.row_groups groups of 32 MB rows, each a workgroup of its own per tile; the groups of a
   // source count as sources of their own and follow each other, so that they share the source's rows through their XCD's L2.
-  const int groups = SPLIT ? a.row_groups : 1;
+  const int groups = GROUPED ? a.row_groups : 1;
   bool is_base = (int)blockIdx.x < a.base_blocks;
   int tail_tile = -1;   // >= 0: this workgroup runs one K slice of that tile of the tail
   int tail_base_tiles = 0;
@@ -541,6 +542,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     s /= groups;
   }
   const int mb0 = MB * group;   // first 32-row block of this workgroup's samples
+  if (GROUPED && 32 * mb0 >= a.n_r) return;   // a last group without samples (uniform; nobody reads its rows, nobody waits for it)
   const float* __restrict__ P = is_base ? a.x : a.G + (long long)s * a.ldg;
   const int row0 = nt * BN + wave * 32;
   const float* __restrict__ Urow0 = P + J.w_off + (long long)row0 * K;  // wave-uniform
@@ -604,7 +606,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
       if (AD_KB % NW == 0 || q < AD_KB) {
         const int op = q / A_KB, piece = q % A_KB;
         const int mb = piece / BLOCK_KB, within = piece % BLOCK_KB;
-        const unsigned char* src = (op ? Dg : Ag) + ((long long)mb * n_chunks + c) * T::CH_BYTES + within * 1024 + lane * 16;
+        const unsigned char* src = (op ? Dg : Ag) + ((long long)(mb0 + mb) * n_chunks + c) * T::CH_BYTES + within * 1024 + lane * 16;
         unsigned char* dst = lds + buf * AD_BYTES + q * 1024;
         lds_dma16(src, dst);
       }
@@ -1181,7 +1183,8 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     constexpr int WAVE_FLOATS = MB * 16 * 64;
     const long long slice_stride = (long long)NW * WAVE_FLOATS;
     // the tile this workgroup shares (TAIL: the sliced tiles are numbered as their blocks are)
-    const long long grp = TAIL ? tail_tile : is_base ? nt : a.slice_group0 + (long long)s * n_tiles + nt;
+    const long long grp = TAIL ? tail_tile : is_base ? nt * groups + group
+                                           : a.slice_group0 + ((long long)s * groups + group) * n_tiles + nt;
     float* part = a.slice_partials + grp * n_slices * slice_stride + wave * WAVE_FLOATS;   // this wave's features
     float* mine = part + ks * slice_stride;
 #pragma unroll
@@ -1478,10 +1481,10 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   // K slices (one-wave tiles only) come with the caller's plan; they need the partial and counter buffers
   if (NW != 1 || a.k_slices < 1) a.k_slices = 1;
   if (a.k_slices > 1 && (a.slice_partials == nullptr || a.slice_counters == nullptr)) return hipErrorInvalidValue;
-  constexpr bool SPLIT = LD::SPLIT;
-  const int groups = SPLIT ? a.row_groups : 1;
-  if (groups < 1 || (!SPLIT && a.row_groups > 1)) return hipErrorInvalidValue;
-  if (shape != nullptr) shape->row_blocks = MB * groups;
+  constexpr bool GROUPED = LD::SPLIT || NW <= 4;
+  const int groups = GROUPED ? a.row_groups : 1;
+  if (groups < 1 || (!GROUPED && a.row_groups > 1)) return hipErrorInvalidValue;
+  if (shape != nullptr) shape->row_blocks = MB * groups / launch_passes(a);
   if (!TAIL) a.tail_cand = a.tail_slices = 0;
   if (TAIL && (a.tail_cand < 0 || a.tail_cand > a.n_cand || (a.tail_cand == 0 && !a.has_base) || a.tail_slices < 2 ||
                a.slice_partials == nullptr || a.slice_counters == nullptr))
@@ -1501,7 +1504,7 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   if (TAIL) {
     const long long tiles = ((a.has_base ? job_tiles(a.bj, BN) : 0) + (long long)job_tiles(a.cj, BN) * a.tail_cand) * groups;
     // every slice keeps at least two chunks of every job; the hand-over buffers hold all sliced tiles
-    if ((a.cj.Kp >> 6) < 2 * a.tail_slices || (a.has_base && (a.bj.Kp >> 6) < 2 * a.tail_slices) || tiles > kMaxSliceGroups ||
+    if ((a.cj.Kp >> 6) < 2 * a.tail_slices || (a.has_base && (a.bj.Kp >> 6) < 2 * a.tail_slices) || tiles > (long long)kMaxSliceGroups * launch_passes(a) ||
         (n_main > 0 && tiles * a.tail_slices > kMaxTailWorkgroups))
       return hipErrorInvalidValue;
     if (n_main > 0) {
