@@ -145,7 +145,7 @@ constexpr size_t kSharedPassBytes = size_t(1) << 30;   // most that sharing may 
 Plan pick_plan(const zeno_model* mdl, int m, int n_r, size_t bytes) {
   const Plan plain = make_plan(mdl, m, n_r);
   const int passes = (n_r + kMaxPassRows - 1) / kMaxPassRows;
-  if (passes < 2 || passes > kMaxSharedPasses || !layer_passes_merge(mdl->desc.dims, plain.L, m, plain.esize == 2)) return plain;
+  if (passes < 2 || passes > kMaxSharedPasses || !layer_passes_merge(mdl->desc.dims, plain.L, m)) return plain;
   Plan shared = make_plan(mdl, m, n_r, passes, &plain);
   shared.total = std::max(shared.total, plain.total);
   return shared.total <= plain.total + kSharedPassBytes && shared.total <= bytes ? shared : plain;

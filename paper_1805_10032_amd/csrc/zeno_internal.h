@@ -166,7 +166,7 @@ struct LayerExtents {
   long long slice_bytes;       // partial accumulators of a launch with K split over workgroups
   int slice_counters;          // arrival counters it uses
 };
-bool layer_passes_merge(const int* dims, int L, int m, bool bf16);   // may groups of 128 samples share their launches?
+bool layer_passes_merge(const int* dims, int L, int m);   // may groups of 128 samples share their launches?
 LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device);
 hipError_t launch_loss(const float* Z0, const float* dZ, const int32_t* labels, const float* targets,
                        int loss, int m, int n_r_total, int chunk_begin, int chunk_rows, int C,

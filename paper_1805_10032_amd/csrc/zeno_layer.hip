@@ -1,6 +1,6 @@
 // Dispatcher of the streaming layer kernel: launch shapes, the choice between merged
 // and separate launches of the pass at x, and the packing of the batch.  The kernel
-// itself lives in zeno_layer_impl.h and is compiled in twelve objects (the four files
+// itself lives in zeno_layer_impl.h and is compiled in ten objects (the four files
 // zeno_layer_{bf16,f32}_{first,delta}.hip, each once per number of row blocks).
 #include <cstring>
 
@@ -8,28 +8,29 @@
 
 namespace zeno {
 
-// the entry points of the twelve kernel objects: (operand type, second product) x row blocks
-#define ZENO_DECLARE_LAYER(NAME)                                                                                  \
-  hipError_t launch_layer_##NAME##_mb1(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape);       \
-  hipError_t launch_layer_##NAME##_mb2(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape);       \
-  hipError_t launch_layer_##NAME##_mb4(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape);       \
-  int wgs_per_cu_##NAME##_mb1(int NW, int k_waves);                                                               \
-  int wgs_per_cu_##NAME##_mb2(int NW, int k_waves);                                                               \
-  int wgs_per_cu_##NAME##_mb4(int NW, int k_waves);                                                               \
+// the entry points of the ten kernel objects: (operand type, second product) x row blocks (four of them in bf16 only)
+#define ZENO_DECLARE_LAYER_MB(NAME, MB)                                                                              \
+  hipError_t launch_layer_##NAME##_mb##MB(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape);       \
+  int wgs_per_cu_##NAME##_mb##MB(int NW, int k_waves);
+#define ZENO_DECLARE_LAYER(NAME, MOST)                                                                              \
+  ZENO_DECLARE_LAYER_MB(NAME, 1)                                                                                    \
+  ZENO_DECLARE_LAYER_MB(NAME, 2)                                                                                    \
+  ZENO_DECLARE_LAYER_MB(NAME, MOST)                                                                                 \
   static hipError_t launch_layer_##NAME(const LayerArgs& a, int MB, int NW, hipStream_t stream, LaunchShape* shape) { \
     return MB == 1 ? launch_layer_##NAME##_mb1(a, NW, stream, shape)                                              \
          : MB == 2 ? launch_layer_##NAME##_mb2(a, NW, stream, shape)                                              \
-                   : launch_layer_##NAME##_mb4(a, NW, stream, shape);                                             \
+                   : launch_layer_##NAME##_mb##MOST(a, NW, stream, shape);                                          \
   }                                                                                                               \
   static int wgs_per_cu_##NAME(int MB, int NW, int k_waves) {                                                     \
     return MB == 1 ? wgs_per_cu_##NAME##_mb1(NW, k_waves) : MB == 2 ? wgs_per_cu_##NAME##_mb2(NW, k_waves)        \
-                                                                     : wgs_per_cu_##NAME##_mb4(NW, k_waves);      \
+                                                                     : wgs_per_cu_##NAME##_mb##MOST(NW, k_waves);   \
   }
-ZENO_DECLARE_LAYER(bf16_delta)
-ZENO_DECLARE_LAYER(bf16_first)
-ZENO_DECLARE_LAYER(f32_delta)
-ZENO_DECLARE_LAYER(f32_first)
+ZENO_DECLARE_LAYER(bf16_delta, 4)
+ZENO_DECLARE_LAYER(bf16_first, 4)
+ZENO_DECLARE_LAYER(f32_delta, 2)
+ZENO_DECLARE_LAYER(f32_first, 2)
 #undef ZENO_DECLARE_LAYER
+#undef ZENO_DECLARE_LAYER_MB
 
 template <bool BF16, bool DELTA>
 static int ks_waves_for(int MB) {
@@ -46,17 +47,17 @@ static int compute_units() {
   return n_cu;
 }
 
-static int row_groups(bool bf16, int MB, int NW);
+// Float32 operands: four row blocks run as two groups of two, a workgroup each (G is read twice, the second time mostly from the L2 of
+// the XCD both run on).  Split operands have two accumulators per block, and with four blocks neither the LDS nor the registers held
+// the buffers that keep loads in flight.  As one group, on float32 matrix instructions (us): 2048 -> 2048, 20 candidates, 573 (now 317);
+// one-wave tiles with the second product, whose K no two waves could share, 777 -> 333, 33 candidates, 155.
+static int row_groups(bool bf16, int MB) { return !bf16 && MB == 4 ? 2 : 1; }
 
 static int wgs_per_cu(bool bf16, bool delta, int MB, int NW, int k_waves = 1) {
-  MB /= row_groups(bf16, MB, NW);
+  MB /= row_groups(bf16, MB);
   return bf16 ? (delta ? wgs_per_cu_bf16_delta(MB, NW, k_waves) : wgs_per_cu_bf16_first(MB, NW, k_waves))
               : (delta ? wgs_per_cu_f32_delta(MB, NW, k_waves) : wgs_per_cu_f32_first(MB, NW, k_waves));
 }
-
-// Wide workgroups with split float32 operands hold two accumulators per 32-row block: four row blocks run as two groups of two, a
-// workgroup each (G is read twice, the second time mostly from the L2 of the XCD both run on).
-static int row_groups(bool bf16, int MB, int NW) { return !bf16 && MB == 4 && NW > 1 ? 2 : 1; }
 
 static int ks_waves(bool bf16, bool delta, int MB) {
   return bf16 ? (delta ? ks_waves_for<true, true>(MB) : ks_waves_for<true, false>(MB))
@@ -72,8 +73,8 @@ static int ks_waves(bool bf16, bool delta, int MB) {
 // eight waves, which copy the activations once per 256 features instead of once per 128, win).
 static int nw_for(const LayerArgs& a, bool bf16, bool delta, int MB) {
   if (a.wide_nw > 0) return a.wide_nw;   // planned (layer_wide_plan, layer_tail_slices)
-  const int groups = row_groups(bf16, MB, 8);
-  const int nw = launch_nw_for(a, groups);
+  const int groups = row_groups(bf16, MB);
+  const int nw = launch_nw_for(a);
   if (nw != 8 || a.n_cand <= 0) return nw;
   if (wgs_per_cu(bf16, delta, MB, 4) < 2) return 8;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
@@ -100,20 +101,25 @@ int layer_nw(const LayerArgs& a, bool bf16, bool delta, int MB) { return nw_for(
 //    features take four-wave workgroups instead (layer_wide_plan).  Score and update, without / with it: fp32, n_r = 32,
 //    2048 -> 64, m = 140 and 185: 81.1 / 77.1, 92.3 / 88.2 us; 3072 -> 50, m = 150: 102.5 / 99.3; 4096 -> 64, m = 130:
 //    102.0 / 98.4; with n_r = 64 103.3 / 98.0, 115.2 / 131.6 (the one shape that loses), 133.3 / 129.3, 140.4 / 136.1.
+static long long one_wave_tiles(const LayerArgs& a) {
+  return (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
+}
+
 KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device) {
   KPlan plan = {1, 1};
   if (NW != 1 || (!a.has_base && a.n_cand <= 0)) return plan;
   const int base_chunks = a.has_base ? a.bj.Kp >> 6 : 1 << 30, cand_chunks = a.n_cand > 0 ? a.cj.Kp >> 6 : 1 << 30;
   const int min_chunks = base_chunks < cand_chunks ? base_chunks : cand_chunks;
-  const long long groups = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
-  const int ks_max = ks_waves(bf16, delta, MB);
+  const int row_blocks = MB / row_groups(bf16, MB);
+  const long long groups = row_groups(bf16, MB) * one_wave_tiles(a);
+  const int ks_max = ks_waves(bf16, delta, row_blocks);
   const bool wide_ok = ks_max > 1 && (a.n_cand > 0 ? cand_chunks : base_chunks) >= ks_max;
   const bool can_slice = a.slice_partials != nullptr && a.slice_counters != nullptr && groups <= kMaxSliceGroups;
   // most workgroups per tile that the buffers and the two-chunk rule allow
   auto max_slices = [&](int kw) {
     if (!can_slice) return 1;
     long long s = min_chunks / (2 * kw);
-    const long long by_bytes = (long long)(kSlicePartialBytes / ((size_t)MB * 16 * 64 * sizeof(float))) / groups;
+    const long long by_bytes = (long long)(kSlicePartialBytes / ((size_t)row_blocks * 16 * 64 * sizeof(float))) / groups;
     if (s > by_bytes) s = by_bytes;
     if (s > 8) s = 8;
     return s < 1 ? 1 : (int)s;
@@ -140,9 +146,9 @@ KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bo
 
 // Does any candidate launch of these layers take eight-wave workgroups?  Those run one group of 128 samples at a time.  Host
 // arithmetic only: the workspace's size depends on it.
-bool layer_passes_merge(const int* dims, int L, int m, bool bf16) {
+bool layer_passes_merge(const int* dims, int L, int m) {
   for (int l = 0; l < L; ++l)
-    if (pick_nw(cover_rows(dims[l + 1], l + 1 == L), m * row_groups(bf16, 4, 8)) == 8) return false;
+    if (pick_nw(cover_rows(dims[l + 1], l + 1 == L), m) == 8) return false;
   return true;
 }
 
@@ -172,15 +178,14 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
   // K split over workgroups as well (one-wave tiles)
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, device);
   if (kp.k_slices > 1) {
-    const long long groups = (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
-    e.slice_bytes = groups * passes * kp.k_slices * MB * 16 * 64 * (long long)sizeof(float);
-    e.slice_counters = (int)groups * passes;
+    e.slice_bytes = one_wave_tiles(a) * passes * kp.k_slices * MB * 16 * 64 * (long long)sizeof(float);
+    e.slice_counters = (int)one_wave_tiles(a) * passes * row_groups(bf16, MB);
     if (a.n_cand > 0) e.norm_slots *= kp.k_slices;
   }
   if (a.tail_slices >= 2 && NW == a.wide_nw) {
     const long long tiles = (a.has_base ? job_tiles(a.bj, 32 * NW) : 0) + (long long)job_tiles(a.cj, 32 * NW) * a.tail_cand;
     e.slice_bytes = tiles * passes * a.tail_slices * NW * MB * 16 * 64 * (long long)sizeof(float);
-    e.slice_counters = (int)tiles * passes * row_groups(bf16, MB, NW);
+    e.slice_counters = (int)tiles * passes * row_groups(bf16, MB);
     e.norm_slots = a.tail_p_off - a.p_off + job_tiles(a.cj, 32 * NW) * a.tail_slices;   // both ranges, counted from p_off
   }
   return e;
@@ -188,7 +193,7 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
 
 // Does the workgroup of NW waves (8 or 4) of this kind double-buffer its activation chunks (slices need it)?
 static bool wide_double_buffered(bool bf16, bool delta, int MB, int NW) {
-  if (!bf16) return !delta || MB < 4;   // split operands always are; see row_groups for the four row blocks
+  if (!bf16) return true;   // split operands always are
   auto pick = [&](auto mb, auto nw) {
     constexpr int M = decltype(mb)::value, W = decltype(nw)::value;
     return bf16 ? (delta ? Lds<true, true, M, W>::DBUF : Lds<true, false, M, W>::DBUF)
@@ -222,9 +227,9 @@ static long long wide_tiles(const LayerArgs& a) {
 // Most K slices a launch of four-wave workgroups may be cut into: every slice keeps two chunks of every job, and the hand-over
 // buffers hold all tiles.  0: the launch never takes such workgroups by layer_wide_plan.  No device is asked.
 int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
-  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a, row_groups(bf16, MB, 8)) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
   const long long tiles = wide_tiles(a);
-  if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles * row_groups(bf16, MB, 4) > kMaxSliceGroups) return 1;
+  if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles * row_groups(bf16, MB) > kMaxSliceGroups) return 1;
   const int chunks = a.cj.Kp >> 6, min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
   const long long by_bytes = (long long)(budget / wide_slice_bytes(MB)) / tiles;
   const long long most = min_chunks / 2 < 8 ? min_chunks / 2 : 8;
@@ -250,12 +255,17 @@ int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 //  * Layers without the second product in bf16, which wait for memory either way, only for four row blocks, or two beyond 1.25
 //    rounds (the others: 1.10, 8 of 49).
 static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int MB, int slices, double cost) {
-  KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
   const int chunks = a.cj.Kp >> 6, base_chunks = a.has_base ? a.bj.Kp >> 6 : 0;
+  const long long base_tiles = a.has_base ? job_tiles(a.bj, 32) : 0, cand_tiles = (long long)job_tiles(a.cj, 32) * a.n_cand;
+  if (!bf16 && MB == 4) {
+    // two groups of two row blocks (row_groups): with the second product always; without it by the lines below as they were for four
+    // blocks, whose tile two waves shared
+    return delta || (base_chunks <= 2 * chunks && (chunks >= 16 || base_tiles + cand_tiles > compute_units()));
+  }
+  KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
   // the lines below were measured with K split over waves where every job of the launch gives each wave two chunks
   if (chunks < 2 * one.k_waves || (a.has_base && base_chunks < 2 * one.k_waves)) one.k_waves = 1;
   if (one.k_waves > 1 && base_chunks > 2 * chunks) return false;
-  const long long base_tiles = a.has_base ? job_tiles(a.bj, 32) : 0, cand_tiles = (long long)job_tiles(a.cj, 32) * a.n_cand;
   const long long workgroups = (base_tiles + cand_tiles) * one.k_slices;
   const long long round = (long long)compute_units() * one_wave_residents(bf16, delta, MB, one.k_waves);
   if (bf16 && !delta && MB < 4) return MB == 2 && one.k_waves > 1 && 4 * workgroups > 5 * round;
@@ -299,7 +309,7 @@ static bool on_shifted_grid(const LayerArgs& a, bool bf16, bool delta, int MB) {
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
   const int most = layer_wide_most(a, bf16, delta, MB, budget);
   if (most == 0) return 0;
-  const bool whole_tiles = launch_nw_for(a, row_groups(bf16, MB, 8)) == 4;
+  const bool whole_tiles = launch_nw_for(a) == 4;
   const long long tiles = wide_tiles(a);
   const int n_cu = compute_units(), chunks = a.cj.Kp >> 6;
   const double hand_over = bf16 && !delta ? 6.0 : 4.0;
@@ -327,10 +337,10 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 // Not where the workgroup is single-buffered.
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main_out) {
   *n_main_out = a.n_cand;
-  if (a.n_cand <= 0 || launch_nw_for(a, row_groups(bf16, MB, 8)) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
-  if (!wide_double_buffered(bf16, delta, MB, 8)) return 0;
+  if (a.n_cand <= 0 || launch_nw_for(a) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
+  if (!wide_double_buffered(bf16, delta, MB, 8) || (!bf16 && delta && MB == 4)) return 0;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
-  const int groups = row_groups(bf16, MB, 8);
+  const int groups = row_groups(bf16, MB);
   const int tiles8 = job_tiles(a.cj, 256) * groups;
   const long long full = (long long)tiles8 * a.n_cand / slots * slots;
   const int n_main = (int)(full / tiles8), rest = a.n_cand - n_main;
@@ -367,7 +377,7 @@ bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB) {
   const int NW = nw_for(a, bf16, delta, MB);
   const int per_cu = wgs_per_cu(bf16, delta, MB, NW);
   const long long slots = (long long)n_cu * per_cu;
-  const int groups = row_groups(bf16, MB, NW);
+  const int groups = row_groups(bf16, MB);
   const long long cand = (long long)job_tiles(a.cj, 32 * NW) * a.n_cand * groups;
   const long long base = job_tiles(a.bj, 32 * NW) * groups;
   const long long rounds_without = (cand + slots - 1) / slots, rounds_with = (cand + base + slots - 1) / slots;
@@ -392,7 +402,7 @@ hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, i
 hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipStream_t stream, LaunchShape* shape) {
   const int NW = nw_for(a, bf16, delta, MB);
   LayerArgs b = a;
-  const int groups = row_groups(bf16, MB, NW);
+  const int groups = row_groups(bf16, MB);
   b.row_groups = groups * launch_passes(a);
   // Four-wave workgroups with at most one per compute unit, one row block and one product: a wave has its SIMD to itself, and the
   // split of its operand takes as long as the float32 matrix instructions do, without a second wave to hide behind
@@ -404,7 +414,7 @@ hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipSt
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, true);
   b.k_waves = kp.k_waves;
   b.k_slices = kp.k_slices;
-  b.slice_group0 = (a.has_base && a.n_cand > 0) ? job_tiles(a.bj, 32) * launch_passes(a) : 0;
+  b.slice_group0 = (a.has_base && a.n_cand > 0) ? job_tiles(a.bj, 32) * b.row_groups : 0;
   MB /= groups;
   if (bf16) {
     return delta ? launch_layer_bf16_delta(b, MB, NW, stream, shape) : launch_layer_bf16_first(b, MB, NW, stream, shape);

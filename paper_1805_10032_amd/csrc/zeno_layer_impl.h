@@ -1547,10 +1547,8 @@ constexpr int split_k_waves() {
 // k_waves > 1: the one-wave-tile instantiation whose workgroups split K over that many waves
 template <bool BF16, bool DELTA, int MB>
 int wgs_per_cu_nw(int NW, int k_waves) {
-  if constexpr (BF16 || MB < 4) {
-    if (NW == 8) return wgs_per_cu_inst<BF16, DELTA, MB, 8, 1>();
-    if (NW == 4) return wgs_per_cu_inst<BF16, DELTA, MB, 4, 1>();
-  }
+  if (NW == 8) return wgs_per_cu_inst<BF16, DELTA, MB, 8, 1>();
+  if (NW == 4) return wgs_per_cu_inst<BF16, DELTA, MB, 4, 1>();
   constexpr int KS = split_k_waves<BF16, DELTA, MB>();
   if constexpr (KS > 1) {
     if (k_waves == KS) return wgs_per_cu_inst<BF16, DELTA, MB, 1, KS>();
@@ -1653,11 +1651,9 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
 
 template <bool BF16, bool DELTA, int MB>
 hipError_t launch_nw(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape) {
-  if constexpr (BF16 || MB < 4) {   // float32 operands: see row_groups
-    if (NW == 8) return launch_nt<BF16, DELTA, MB, 8>(a, stream, shape);
-    if (NW == 4) return launch_nt<BF16, DELTA, MB, 4>(a, stream, shape);
-  }
-  if (NW != 1) return hipErrorInvalidValue;
+  static_assert(BF16 || MB < 4, "four row blocks of float32 operands run as two groups of two");
+  if (NW == 8) return launch_nt<BF16, DELTA, MB, 8>(a, stream, shape);
+  if (NW == 4) return launch_nt<BF16, DELTA, MB, 4>(a, stream, shape);
   return launch_nt<BF16, DELTA, MB, 1>(a, stream, shape);
 }
 
@@ -1672,19 +1668,18 @@ int pick_nw(int rows, int n_src) {
 }
 
 // Waves per workgroup of a launch, from the job that dominates it.
-int launch_nw_for(const LayerArgs& a, int groups) {
-  if (a.n_cand > 0) return pick_nw(cover_rows(a.cj.N, a.cj.last), a.n_cand * groups);
-  return pick_nw(cover_rows(a.bj.N, a.bj.last), groups);
+int launch_nw_for(const LayerArgs& a) {
+  if (a.n_cand > 0) return pick_nw(cover_rows(a.cj.N, a.cj.last), a.n_cand);
+  return pick_nw(cover_rows(a.bj.N, a.bj.last), 1);
 }
 
 }  // namespace
 
 }  // namespace zeno
 
-// The kernel is compiled in twelve objects so that the instantiations build in parallel: four source files, one per
-// (operand type, second product) pair, each compiled once per number of row blocks (-DZENO_LAYER_MB=1, 2, 4; without
-// the definition a file holds all three).  Each object defines the two entry points of its (pair, row blocks) that the
-// dispatcher in zeno_layer.hip calls.
+// The kernel is compiled in ten objects so that the instantiations build in parallel: four source files, one per
+// (operand type, second product) pair, each compiled once per number of row blocks (-DZENO_LAYER_MB=1, 2, and 4 in bf16).  Each object
+// defines the two entry points of its (pair, row blocks) that the dispatcher in zeno_layer.hip calls.
 #define ZENO_LAYER_INSTANCE_MB_(NAME, BF16, DELTA, MB)                                                       \
   namespace zeno {                                                                                           \
   hipError_t launch_layer_##NAME##_mb##MB(const LayerArgs& a, int NW, hipStream_t stream, LaunchShape* shape) { \
@@ -1693,13 +1688,6 @@ int launch_nw_for(const LayerArgs& a, int groups) {
   int wgs_per_cu_##NAME##_mb##MB(int NW, int k_waves) { return wgs_per_cu_nw<BF16, DELTA, MB>(NW, k_waves); }   \
   }
 #define ZENO_LAYER_INSTANCE_MB(NAME, BF16, DELTA, MB) ZENO_LAYER_INSTANCE_MB_(NAME, BF16, DELTA, MB)
-#ifdef ZENO_LAYER_MB
 #define ZENO_LAYER_INSTANCE(NAME, BF16, DELTA) ZENO_LAYER_INSTANCE_MB(NAME, BF16, DELTA, ZENO_LAYER_MB)
-#else
-#define ZENO_LAYER_INSTANCE(NAME, BF16, DELTA) \
-  ZENO_LAYER_INSTANCE_MB(NAME, BF16, DELTA, 1) \
-  ZENO_LAYER_INSTANCE_MB(NAME, BF16, DELTA, 2) \
-  ZENO_LAYER_INSTANCE_MB(NAME, BF16, DELTA, 4)
-#endif
 
 #endif  // ZENO_LAYER_IMPL_H_
