@@ -22,7 +22,7 @@ OBJ_DIR = os.path.join(HERE, "_build")
 LAYER_UNITS = ["zeno_layer_bf16_delta.hip", "zeno_layer_bf16_first.hip", "zeno_layer_f32_delta.hip", "zeno_layer_f32_first.hip"]
 SOURCES = ([(u, f"_mb{mb}", [f"-DZENO_LAYER_MB={mb}"]) for mb in (4, 2, 1) for u in LAYER_UNITS if mb < 4 or "bf16" in u] +
            [(s, "", []) for s in ("zeno_median.hip", "zeno_krum.hip", "zeno_capi.hip", "zeno_layer.hip", "zeno_loss.hip",
-                                  "zeno_aggregate.hip", "zeno_median_select.hip", "zeno_conv.hip", "zeno_small.hip")])
+                                  "zeno_aggregate.hip", "zeno_median_select.hip", "zeno_conv.hip", "zeno_small.hip", "zeno_first.hip")])
 
 # Packed-fp32 instruction selection is switched off for all device code.
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -48,7 +48,7 @@ def _fresh(obj, src, stamp):
             return False
         t = os.path.getmtime(obj)
         deps = [os.path.join(CSRC, src), os.path.join(CSRC, "zeno_internal.h"), os.path.join(ROOT, "include", "zeno.h")]
-        if src.startswith("zeno_layer") or src in ("zeno_krum.hip", "zeno_conv.hip", "zeno_small.hip"):
+        if src.startswith("zeno_layer") or src in ("zeno_krum.hip", "zeno_conv.hip", "zeno_small.hip", "zeno_first.hip"):
             deps.append(os.path.join(CSRC, "zeno_layer_impl.h"))
             deps.append(os.path.join(CSRC, "zeno_split.h"))
         if src == "zeno_conv.hip":

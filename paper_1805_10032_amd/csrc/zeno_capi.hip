@@ -471,14 +471,32 @@ zeno_status_t score_enqueue(const zeno_model* model, const Plan& p, const float*
     // nothing is enqueued for a pass unless every launch of it stays inside its slots
     for (const Launch& l : seq)
       if (!launch_fits(p, l, layer_nw(l.a, bf16, l.delta, p.MB), true)) return ZENO_ERR_WORKSPACE;
-    {
+    const float* features = batch->features + (size_t)begin * D.dims[0];
+    unsigned int* counters = reinterpret_cast<unsigned int*>(ws + p.off_slice_cnt);
+    double* zero = begin == 0 ? norm_partials : nullptr;
+    const long long n_zero = begin == 0 ? (long long)m * P : 0;
+    const bool with_first = L > 1 && first_layer_fits(D.dims[0], n_r);   // the sequence's first launch, the pass at x through layer 0, comes with it
+    if (with_first) {
+      FirstArgs f;
+      std::memset(&f, 0, sizeof(f));
+      f.x = x;
+      f.features = features;
+      f.n_r = rows;
+      f.job = seq[0].a.bj;
+      f.tiled = ws + p.off_feat;
+      f.counters = counters;
+      f.n_counters = p.n_counters;
+      f.zero = zero;
+      f.n_zero = n_zero;
+      ProfScope ps(ZENO_KERNEL_LAYER_BASE, 0, seq[0].bytes + 4.0 * rows * D.dims[0], stream);
+      ZENO_TRY(launch_first_layer(f, bf16, stream));
+    } else {
       ProfScope ps(ZENO_KERNEL_PACK, 0, 4.0 * rows * D.dims[0], stream);
-      ZENO_TRY(launch_pack_features(batch->features + (size_t)begin * D.dims[0], rows, D.dims[0], pad64(D.dims[0]),
-                                    p.n_pad, bf16, ws + p.off_feat,
-                                    reinterpret_cast<unsigned int*>(ws + p.off_slice_cnt), p.n_counters,
-                                    begin == 0 ? norm_partials : nullptr, begin == 0 ? (long long)m * P : 0, stream));
+      ZENO_TRY(launch_pack_features(features, rows, D.dims[0], pad64(D.dims[0]), p.n_pad, bf16, ws + p.off_feat, counters, p.n_counters,
+                                    zero, n_zero, stream));
     }
-    for (const Launch& l : seq) {
+    for (size_t i = with_first ? 1 : 0; i < seq.size(); ++i) {
+      const Launch& l = seq[i];
       ProfScope ps(l.kernel, l.layer, l.bytes, stream);
       LaunchShape shape;
       ZENO_TRY(launch_layer(l.a, bf16, l.delta, p.MB, stream, &shape));

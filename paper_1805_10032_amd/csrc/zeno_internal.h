@@ -118,6 +118,20 @@ inline int launch_passes(const LayerArgs& a) { return a.passes > 1 ? a.passes : 
 hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int n_pad, bool bf16,
                                 void* tiled, unsigned int* counters, int n_counters, double* zero, long long n_zero,
                                 hipStream_t stream);
+// ---- the packing of the batch and the pass at x through layer 0 in one launch (zeno_first.hip)
+struct FirstArgs {
+  const float* x;
+  const float* features;   // [n_r x job.K]
+  int n_r;
+  LayerJob job;            // layer 0 (a hidden layer); Z0 and H_base are written
+  void* tiled;             // the batch in operand order, written
+  unsigned int* counters;  // cleared, with n_zero doubles at zero, as launch_pack_features does
+  int n_counters;
+  double* zero;
+  long long n_zero;
+};
+bool first_layer_fits(int K, int n_r);
+hipError_t launch_first_layer(const FirstArgs& a, bool bf16, hipStream_t stream);
 // Limits of a launch whose K is split over workgroups: bytes of partial accumulators (tiles x slices x row
 // blocks x 4 KB) and tiles (= arrival counters).  One buffer of each serves all launches of a pass, which run
 // one after the other and leave the counters at zero.

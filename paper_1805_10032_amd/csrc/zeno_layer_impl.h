@@ -487,6 +487,12 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   const int n_chunks = J.Kp >> 6;
   const int n_tiles = (cover_rows(N, last) + BN - 1) / BN;
   int nt, s = 0, group = 0;
+  auto by_group = [&](int& v) __attribute__((always_inline)) {   // (two divisions, which a launch of one group does not wait for)
+    if (groups > 1) {
+      group = v % groups;
+      v /= groups;
+    }
+  };
   // K slice of this workgroup: a launch of one-wave tiles whose tiles do not fill the chip well splits K
   // over k_slices workgroups per tile (on top of, or instead of, the split over the KS waves of a workgroup)
   int ks = 0;
@@ -495,8 +501,8 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   if (TAIL && tail_tile >= 0) {
     ks = ((int)blockIdx.x - a.main_blocks) % n_slices;
     if (is_base) {
-      nt = tail_tile / groups;
-      group = tail_tile % groups;
+      nt = tail_tile;
+      by_group(nt);
     } else if (n_main == 0) {
       // every tile is sliced: (tile, slice) pairs take the place of the tiles in the schedule below
       const int bid = (int)blockIdx.x - a.main_blocks - tail_base_tiles * n_slices;
@@ -510,21 +516,18 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
       s = (unit % n_cchunks) * cc + slot % cc;
       if (s >= a.n_cand * groups) return;
       tail_tile = tail_base_tiles + s * n_tiles + nt;   // its number among the tiles that hand over
-      group = s % groups;
-      s /= groups;
+      by_group(s);
     } else {
       const int g = tail_tile - tail_base_tiles;
       nt = g % n_tiles;
       s = n_main * groups + g / n_tiles;
       if (s >= a.n_cand * groups) return;
-      group = s % groups;
-      s /= groups;
+      by_group(s);
     }
   } else if (is_base) {
     nt = blockIdx.x / n_slices;
     ks = blockIdx.x % n_slices;
-    group = nt % groups;
-    nt /= groups;
+    by_group(nt);
     if (nt >= n_tiles) return;
   } else {
     int bid = blockIdx.x - a.base_blocks;
@@ -538,8 +541,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     nt = unit / n_cchunks;
     s = (unit % n_cchunks) * cc + slot % cc;
     if (s >= n_main * groups) return;
-    group = s % groups;
-    s /= groups;
+    by_group(s);
   }
   const int mb0 = MB * group;   // first 32-row block of this workgroup's samples
   if (GROUPED && 32 * mb0 >= a.n_r) return;   // a last group without samples (uniform; nobody reads its rows, nobody waits for it)

@@ -1,0 +1,41 @@
+"""Models of several layers with at most 1024 inputs, at most 32 samples: the packing of the batch and the pass at x through layer 0
+share the first launch.  Edges of its chunks, waves and rows, and the first sizes beyond it; every score against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1805_10032_amd import workloads as WL
+from tests._util import SCORE_TOL, npy, oracle_terms, rows_to_gpu, score_error
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_r,m", [(1, 5), (31, 6), (32, 7), (33, 5)])
+@pytest.mark.parametrize("dims", [[1, 130, 20], [3, 200, 17], [63, 131, 20], [64, 129, 140, 5], [65, 33, 300], [449, 300, 20], [1000, 31, 40],
+                                  [1024, 520, 10], [1025, 140, 20]])
+@pytest.mark.parametrize("fwd", ["fp32", "bf16"])
+def test_first_launch(dims, n_r, m, fwd):
+    from paper_1805_10032_amd import binding as B
+    B.load_library()
+    w = WL.make_mlp_workload("first", 500 + n_r, dims, m, 1, n_r, 0.05, 1e-3, fwd, seed=dims[0], n_flip=1, n_noise=1, noise_std=2.0,
+                             worker_batch=16)
+    dev = torch.device("cuda", 0)
+    mdl = B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd)
+    args = (mdl, w.x.to(dev), rows_to_gpu(B, w.G, 1, dev), w.features.to(dev), w.gamma, w.rho)
+    labels = w.labels.to(dev)
+    ws = torch.full((mdl.workspace_bytes(m, n_r),), 0xff, dtype=torch.uint8, device=dev)   # NaNs: every slot is written before it is read
+    B.profile_enable(True)
+    try:
+        s = B.zeno_score(*args, labels=labels, workspace=ws)
+        torch.cuda.synchronize()
+        kernels = [r["kernel"] for r in B.profile_collect(detail=True)]
+    finally:
+        B.profile_enable(False)
+    assert kernels[0] == ("layer_base" if dims[0] <= 1024 and n_r <= 32 else "pack"), kernels
+    s_ref, scale = oracle_terms(w)
+    err = score_error(npy(s), s_ref, scale)
+    tol = SCORE_TOL[fwd]
+    if n_r == 1:
+        tol *= 10   # one sample: the change of the loss may cancel four digits of dz (the same rows miss by as much with separate launches)
+    assert np.all(err <= tol), (float(err.max()), int(err.argmax()))
+    assert torch.equal(s, B.zeno_score(*args, labels=labels, workspace=ws))
