@@ -77,15 +77,16 @@ __device__ inline float sgd_step(float x, double gamma, double avg) {
 
 // UPDATE: also (or only, out == nullptr) write x_next = x - gamma * average; x_next may
 // be x itself (every column is read and written by one thread).
-// V: float4 columns of a thread (kVec, or one where the columns are few).
+// V: float4 columns of a thread (kVec, or one where the columns are few).  width: float4 columns of a block, at most V a thread
+// (one column a thread: always all of them).
 template <bool ALL, bool UPDATE, int V>
 __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* __restrict__ G,
                                                                   const float* __restrict__ scores, int m,
-                                                                  long long d, long long ldg, int b, int n_blocks,
+                                                                  long long d, long long ldg, int b, int n_blocks, int width,
                                                                   float* __restrict__ out,
                                                                   int32_t* __restrict__ selected, float gamma,
                                                                   const float* x, float* x_next) {
-  constexpr int BLOCK = kThreads * V;
+  const int BLOCK = V == 1 ? kThreads : width;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
   // [selected row list][burst buffer]; the selection's scratch (keys, flags) lies
   // in the burst buffer, which is not used before the selection is over
@@ -109,18 +110,19 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
   for (long long g = blk_begin; g < blk_end; g += n_blocks) {
     const int nb = (int)(blk_end - g < n_blocks ? blk_end - g : n_blocks);
     for (int i = 0; i < nb; ++i) {
-      const long long c0 = (g + i) * BLOCK + threadIdx.x;
+      const long long c0 = (g + i) * BLOCK;
+      const int here = (int)(n_vec - c0 < BLOCK ? n_vec - c0 : BLOCK);
       double acc[V][4];
 #pragma unroll
       for (int v = 0; v < V; ++v)
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[v][e] = 0.0;
-      // columns beyond the end re-read the last full column (in bounds) and are not written
+      // columns beyond the block or the end re-read the last one (in bounds) and are not written
       long long col[V];
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        const long long c = c0 + v * kThreads;
-        col[v] = (c < n_vec ? c : n_vec - 1) * 4;
+        const int c = v * kThreads + (int)threadIdx.x;
+        col[v] = (c0 + (c < here ? c : here - 1)) * 4;
       }
       f32x4 xv[V];
       if (UPDATE) {
@@ -177,7 +179,9 @@ __global__ __launch_bounds__(kThreads) void masked_average_kernel(const float* _
           r[e] = (float)avg;
           if (UPDATE) xn[e] = sgd_step(xv[v][e], (double)gamma, avg);
         }
-        const int slot = i * BLOCK + v * kThreads + threadIdx.x;
+        const int c = v * kThreads + (int)threadIdx.x;
+        if (V > 1 && c >= BLOCK) continue;
+        const int slot = i * BLOCK + c;
         if (!UPDATE || out != nullptr) burst[slot] = r;
         if (UPDATE) burst[xoff + slot] = xn;
       }
@@ -221,7 +225,7 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   // 9.9 -> 7.5 / 11.6 -> 7.1, d = 500000 10.9 -> 8.8 / 11.1 -> 8.1, d = 1000001 13.9 -> 13.7 / 15.1 -> 15.6; beyond that slower (m = 20,
   // d = 4000000 41.9 -> 46.4 / 53.1 -> 57.0).  Eight and sixteen rows in flight gain at d = 7850 only (18.0 and 17.8) and lose above.
   const bool few = n_vec < 163840;
-  const int block_vec = few ? kThreads : kBlockVec;
+  int block_vec = few ? kThreads : kBlockVec;
   // burst length: as long as LDS allows while at least ~512 workgroups' worth of groups remain
   long long nb = few ? 1 : n_vec / ((long long)kBlockVec * 512);
   const int n_blocks = (int)(nb < 1 ? 1 : (nb > max_blocks ? max_blocks : nb));
@@ -236,8 +240,19 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   }();
   int per_cu = (int)((160 * 1024) / (lds + 512));
   per_cu = per_cu < 1 ? 1 : (per_cu > 8 ? 8 : per_cu);
-  const long long blocks_total = (n_vec + block_vec - 1) / block_vec;
+  long long blocks_total = (n_vec + block_vec - 1) / block_vec;
   const long long resident = (long long)n_cu * per_cu;
+  // One block a workgroup and more blocks than compute units: as many workgroups on each compute unit, of narrower blocks (whole
+  // units of 64), instead of two on some and one on the others.  Us per update / Mean, full blocks -> narrower: m = 20, d = 1200000
+  // 16.8 -> 14.6 / 20.7 -> 18.1, d = 1578506 17.7 -> 17.0 / 27.0 -> 25.7, d = 2400000 24.7 -> 23.5 / 35.0 -> 33.7, d = 4000000 no
+  // change; m = 100, d = 1200000 61.6 -> 52.5 / 87.3 -> 74.4, d = 1578506 68.9 -> 66.0 / 104.3 -> 96.2.  Not below one block per compute unit (m = 64, d = 1000001 30.5 -> 32.2
+  // / 42.0 -> 43.7), and not where a workgroup has several blocks: m = 20, d = 14.7 M took 8 us longer with 15 blocks of equal
+  // width than with 14, or 15 in a few workgroups.
+  if (!few && n_blocks == 1 && blocks_total > n_cu && blocks_total <= resident) {
+    const long long even = (blocks_total + n_cu - 1) / n_cu * n_cu;
+    block_vec = (int)((n_vec + 64 * even - 1) / (64 * even) * 64);
+    blocks_total = (n_vec + block_vec - 1) / block_vec;
+  }
   const int grid = (int)(blocks_total < 1 ? 1 : (blocks_total > resident ? resident : blocks_total));
   // once per process (initialisation of a local static is thread-safe)
   static const hipError_t attr_err = [] {
@@ -258,10 +273,10 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
 #define ZENO_LAUNCH_AVG(ALLV, UPD)                                                                                  \
   if (few)                                                                                                          \
     hipLaunchKernelGGL((masked_average_kernel<ALLV, UPD, 1>), dim3(grid), dim3(kThreads), lds, stream, G, scores,    \
-                       m, d, ldg, bb, n_blocks, out, selected, gamma, x, x_next);                                   \
+                       m, d, ldg, bb, n_blocks, block_vec, out, selected, gamma, x, x_next);                        \
   else                                                                                                              \
     hipLaunchKernelGGL((masked_average_kernel<ALLV, UPD, kVec>), dim3(grid), dim3(kThreads), lds, stream, G, scores, \
-                       m, d, ldg, bb, n_blocks, out, selected, gamma, x, x_next)
+                       m, d, ldg, bb, n_blocks, block_vec, out, selected, gamma, x, x_next)
   if (all && !update) { ZENO_LAUNCH_AVG(true, false); }
   else if (all) { ZENO_LAUNCH_AVG(true, true); }
   else if (!update) { ZENO_LAUNCH_AVG(false, false); }
