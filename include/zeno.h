@@ -73,7 +73,9 @@ typedef enum {
 } zeno_loss_t;
 
 typedef enum {
-  ZENO_FWD_FP32 = 0, /* forward-pass products in fp32 (fp32 matrix cores), fp32 accumulate */
+  ZENO_FWD_FP32 = 0, /* forward-pass products at float32 accuracy, fp32 accumulate: fp32 matrix cores, or for wide layers the
+                        bf16 ones, every operand split into three bf16 pieces (six piece products; products of operands
+                        below about 1e-33 keep fewer than 24 bits) */
   ZENO_FWD_BF16 = 1  /* matrix operands rounded to bf16, fp32 accumulate */
 } zeno_fwd_dtype_t;
 
@@ -157,12 +159,14 @@ size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t 
  *           appendix's choice for mu >= 0)
  *   scores  DEVICE [m] fp32 out
  *   workspace DEVICE, 256-byte aligned, workspace_bytes >= zeno_score_workspace_bytes(model, m, n_r).  A smaller one gives
- *             ZENO_ERR_WORKSPACE, with one exception: for some convolutional models the query includes room for reordered
+ *             ZENO_ERR_WORKSPACE, with two exceptions.  For some convolutional models the query includes room for reordered
  *             copies of the kernels and maps, and a workspace that holds everything but these (no call returns that size) is
  *             accepted and scored by slower kernels, whose scores agree up to the order of float32 sums.  Workspaces of the
- *             queried size and larger ones give the same scores bit for bit.
- * Batches of more than 128 samples are processed in passes of 128, each pass
- * reading G again. */
+ *             queried size and larger ones give the same scores bit for bit.  For batches of 129 to 512 samples the query may
+ *             include room for all groups of 128 samples at once; a workspace that holds one group is accepted, with the
+ *             same scores bit for bit.
+ * Batches of more than 128 samples are processed in groups of 128: up to four side by side in the same launches where the
+ * layers are small and the workspace has room, otherwise one after the other, each pass reading G again. */
 zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float* G, int64_t ldg, int32_t m,
                          const zeno_batch_t* batch, float gamma, float rho, float* scores,
                          void* workspace, size_t workspace_bytes, void* stream);
@@ -172,7 +176,7 @@ zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float*
  * arguments, kernels and results as zeno_score, bit for bit, but the scratch is a static device
  * array inside the library (ZENO_STATIC_SCRATCH_BYTES per GPU, held until the process ends), so
  * the call allocates nothing, frees nothing and takes no workspace.
- *   UNSUPPORTED if zeno_score_workspace_bytes(model, m, n_r) exceeds ZENO_STATIC_SCRATCH_BYTES
+ *   UNSUPPORTED if the smallest workspace that zeno_score accepts exceeds ZENO_STATIC_SCRATCH_BYTES
  *     (32 MiB covers e.g. a 3072->512->10 model with m = 20, or the paper's m = 20, n_r = 4 on
  *     far larger models; it does not cover hundreds of candidates on 2048-wide layers);
  *   DEVICE if the array's address cannot be obtained on the current device.

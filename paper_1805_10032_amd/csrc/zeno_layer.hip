@@ -85,6 +85,10 @@ static int nw_for(const LayerArgs& a, bool bf16, bool delta, int MB) {
 
 int layer_nw(const LayerArgs& a, bool bf16, bool delta, int MB) { return nw_for(a, bf16, delta, MB); }
 
+static long long one_wave_tiles(const LayerArgs& a) {
+  return (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
+}
+
 // K split of a launch of one-wave tiles.  Such a launch has few feature tiles (the pass at x: N/32; a narrow
 // layer: one or a few per candidate), so a tile's K is divided among the k_waves waves of its workgroup (which
 // add their accumulators through LDS) and among k_slices workgroups (which add theirs through memory, the
@@ -101,10 +105,6 @@ int layer_nw(const LayerArgs& a, bool bf16, bool delta, int MB) { return nw_for(
 //    features take four-wave workgroups instead (layer_wide_plan).  Score and update, without / with it: fp32, n_r = 32,
 //    2048 -> 64, m = 140 and 185: 81.1 / 77.1, 92.3 / 88.2 us; 3072 -> 50, m = 150: 102.5 / 99.3; 4096 -> 64, m = 130:
 //    102.0 / 98.4; with n_r = 64 103.3 / 98.0, 115.2 / 131.6 (the one shape that loses), 133.3 / 129.3, 140.4 / 136.1.
-static long long one_wave_tiles(const LayerArgs& a) {
-  return (a.has_base ? job_tiles(a.bj, 32) : 0) + (long long)(a.n_cand > 0 ? job_tiles(a.cj, 32) : 0) * a.n_cand;
-}
-
 KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bool device) {
   KPlan plan = {1, 1};
   if (NW != 1 || (!a.has_base && a.n_cand <= 0)) return plan;
