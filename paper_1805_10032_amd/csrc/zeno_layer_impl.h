@@ -1223,41 +1223,37 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     // The other workgroups' partials are read with system-scope loads (they bypass the caches on the way,
     // as the stores did, so no cache has to be written back or invalidated).  A round trip to memory is
     // long while other workgroups stream at full rate, so the loads of several slices (up to 64 registers'
-    // worth) are issued together and completed by one wait; the wait statements name the loaded registers
-    // as operands so that no use of them can be scheduled ahead of it.  The sum is taken in slice order
+    // worth) are issued together.  They are loads that the compiler knows (a buffer resource for the tile's partials, cache
+    // policy in the last argument): it waits for each before it uses, copies or reuses the registers.  The sum is taken in slice order
     // whoever adds it; this workgroup's own slice comes from its registers (bit-identical to what it stored).
     // slices per round trip: 4, 2 or 1; sliced tails with one or two row blocks have the registers for 8 or 4
     constexpr int BATCH = (TAIL && MB < 4 ? 8 : 4) / MB;
+    constexpr int SYSTEM_SCOPE = 1 | 16;   // sc0 and sc1
+    asm volatile("" ::: "memory");         // no load moves up past the arrival
+    const auto partials = __builtin_amdgcn_make_buffer_rsrc(part, 0, (int)((n_slices - 1) * slice_stride + WAVE_FLOATS) * 4, 0x00020000);
     f32x16 total[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
       for (int j = 0; j < 16; ++j) total[mb][j] = 0.f;
     for (int q0 = 0; q0 < n_slices; q0 += BATCH) {
-      f32x4 t[BATCH][MB][4];
+      u32x4 t[BATCH][MB][4];
 #pragma unroll
       for (int i = 0; i < BATCH; ++i) {
         const int q = q0 + i;
         if (q < n_slices && q != ks) {   // uniform over the wave
-          const float* other = part + q * slice_stride;
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              asm volatile("global_load_dwordx4 %0, %1, off sc0 sc1" : "=v"(t[i][mb][r]) : "v"(other + ((mb * 4 + r) * 64 + lane) * 4) : "memory");
+              t[i][mb][r] = __builtin_amdgcn_raw_buffer_load_b128(partials, ((mb * 4 + r) * 64 + lane) * 16, q * (int)(slice_stride * 4), SYSTEM_SCOPE);
         } else {
 #pragma unroll
           for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) t[i][mb][r] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int r = 0; r < 4; ++r) t[i][mb][r] = u32x4{0u, 0u, 0u, 0u};
         }
       }
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-      for (int i = 0; i < BATCH; ++i)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-          asm volatile("" : "+v"(t[i][mb][0]), "+v"(t[i][mb][1]), "+v"(t[i][mb][2]), "+v"(t[i][mb][3])::"memory");
 #pragma unroll
       for (int i = 0; i < BATCH; ++i) {
         const int q = q0 + i;
@@ -1273,7 +1269,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
 #pragma unroll
             for (int r = 0; r < 4; ++r)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) total[mb][4 * r + e] += t[i][mb][r][e];
+              for (int e = 0; e < 4; ++e) total[mb][4 * r + e] += __builtin_bit_cast(f32x4, t[i][mb][r])[e];
         }
       }
     }

@@ -149,3 +149,14 @@ def test_sliced_launches_stay_inside_their_slots(B, fwd, n_r):
         mdl = B.ZenoModel(dims, False, "softmax_ce", fwd)
         for m in (1, 3, 63, 64, 255, 1024):
             assert mdl.plan_check(m, n_r) == 0, (dims, m)
+
+
+def test_no_asm_load_leaves_its_wait_to_another_statement():
+    """The compiler takes the outputs of an inline-asm statement as written at its end: a load there that is not waited for in the
+    same statement leaves registers that may be copied, spilled or reused while it is in flight."""
+    csrc = os.path.join(ROOT, "paper_1805_10032_amd", "csrc")
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        for stmt in re.findall(r"\basm\b[^;]*?\((.*?)\)\s*;", text, re.S):
+            if re.search(r"\b(global|buffer|flat|scratch|ds|s)_(load|read)", stmt):
+                assert "waitcnt" in stmt, (name, stmt)
