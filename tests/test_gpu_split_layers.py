@@ -73,6 +73,110 @@ def test_values_that_are_not_finite(B):
     assert np.array_equal(s[8:], clean[8:])
 
 
+NAN_BITS = {1.0: 0x7f800001, -1.0: -8388607}   # NaNs that are infinity, of either sign, without their lower half
+
+
+def _nan(sign):
+    return torch.tensor([NAN_BITS[sign]], dtype=torch.int32).view(torch.float32)
+
+
+def _all_scores_nan(B, w, place, sign):
+    """place(w, v) puts v where the test wants the NaN.  An infinity of the same sign there must leave every score finite (so
+    that a NaN taken for one would be seen), the NaN itself no score at all."""
+    place(w, torch.tensor([sign * float("inf")]))
+    with np.errstate(invalid="ignore"):
+        assert np.isfinite(oracle_terms(w)[0]).all()
+    place(w, _nan(sign))
+    s, recs = _run(B, w, 32)
+    assert any(r["waves"] >= 4 for r in recs), recs
+    assert np.isnan(s).all(), s
+
+
+@pytest.mark.parametrize("dims,n_r", [([512, 1024, 512, 10], 32), ([512, 1024, 512, 10], 40), ([512, 1024, 512, 10], 100),
+                                      ([1088, 1024, 512, 10], 9)])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_a_nan_in_the_batch(B, dims, n_r, sign):
+    """One feature of one sample, packed by the first launch (up to 1024 inputs and 32 samples) or by a launch of its own.  As an
+    infinity it would push the sample's hidden features to minus infinity, at x and at the candidates, and from there to zero."""
+    w = _workload("nanbatch", dims, 64, n_r)
+    col, K, N = 70, dims[0], dims[1]
+    w.x[:N * K].view(N, K)[:, col] = -0.01 * sign
+    w.G[:, :N * K].view(-1, N, K)[:, :, col] = 0.01 * sign
+
+    def place(w, v):
+        w.features[min(3, n_r - 1), col:col + 1] = v
+    _all_scores_nan(B, w, place, sign)
+
+
+@pytest.mark.parametrize("n_r", [32, 48, 100])
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+def test_a_nan_in_x_of_a_wide_output_layer(B, n_r, sign):
+    """The pass at x rides in the candidates' launch, on split operands.  As an infinity it would take one class's logit to minus
+    infinity for every sample, and no sample has that label."""
+    w = _workload("nanx1", [512, 1024], 64, n_r)
+    col, cls = 70, 33
+    w.features[:, col] = -sign * w.features[:, col].abs().clamp_min(0.1)
+    w.G[:, cls * 512 + col] = 0.0
+    w.labels[w.labels == cls] = cls + 1
+
+    def place(w, v):
+        w.x[cls * 512 + col:cls * 512 + col + 1] = v
+    _all_scores_nan(B, w, place, sign)
+
+
+@pytest.mark.parametrize("n_r", [32, 48, 100])
+def test_a_nan_in_x_of_a_wide_hidden_layer(B, n_r):
+    """A weight of the second hidden layer: the pass at x writes it in operand order, where every candidate's second product reads it.
+    As minus infinity it would take one hidden feature, whose input is positive for all samples, to zero."""
+    dims = [512, 1024, 512, 10]
+    w = _workload("nanx2", dims, 64, n_r)
+    unit, row, b0, w1 = 5, 11, 512 * 1024, 512 * 1024 + 1024
+    w.x[b0 + unit], w.G[:, b0 + unit] = 100.0, -1.0                       # positive at x, larger at every candidate
+    w.G[:, unit * 512:(unit + 1) * 512] = 0.0
+    at = w1 + row * 1024 + unit
+    w.G[:, at] = 0.0
+
+    def place(w, v):
+        w.x[at:at + 1] = v
+    _all_scores_nan(B, w, place, -1.0)
+
+
+@pytest.mark.parametrize("n_r", [32, 48, 100])
+@pytest.mark.parametrize("row_align", [1, 32])
+def test_operands_near_the_end_of_the_range(B, n_r, row_align):
+    """Finite operands from 3.396e38 on, which a leading piece rounded to nearest takes to infinity, in the batch, in x's first
+    layer and in x's second layer, next to factors of 1e-31 and less: every score is finite and right.  (A candidate's own values of
+    that size make its squared norm infinite.)"""
+    dims = [512, 1024, 512, 10]
+    w = _workload("top", dims, 64, n_r)
+    top, gen = 3.4e38, torch.Generator().manual_seed(n_r)
+
+    def noise(*shape, std):
+        return torch.randn(shape, generator=gen) * std
+    K, N, b0, w1 = 512, 1024, 512 * 1024, 512 * 1024 + 1024
+    b1 = w1 + 512 * 1024
+    x0, G0 = w.x[:N * K].view(N, K), w.G[:, :N * K].view(64, N, K)
+    x1, G1 = w.x[w1:b1].view(512, N), w.G[:, w1:b1].view(64, 512, N)
+    x2, G2 = w.x[b1 + 512:b1 + 512 + 5120].view(10, 512), w.G[:, b1 + 512:b1 + 512 + 5120].view(64, 10, 512)
+    w.features[:, 70] = top * torch.where(torch.rand(n_r, generator=gen) < 0.5, 1.0, -1.0)     # in the batch: z about 3e7
+    x0[:, 70], G0[:, :, 70] = noise(N, std=1e-31), noise(64, N, std=1e-32)
+    x0[:, 71], w.features[:, 71], G0[:, :, 71] = top, noise(n_r, std=1e-31), 0.0               # in x
+    x1 *= 1e-7
+    G1 *= 1e-7
+    unit = 5                                                                                   # in x's second layer
+    x0[unit], G0[:, unit], w.x[b0 + unit], w.G[:, b0 + unit] = 0.0, 0.0, 1e-31, noise(64, std=1e-32)
+    x1[11, unit], G1[:, 11, unit] = -top, 0.0
+    x1[12, unit], G1[:, 12, unit] = top, 0.0
+    x2[:, 12] *= 1e-7
+    G2[:, :, 12] *= 1e-7
+    s, recs = _run(B, w, row_align)
+    assert all(r["waves"] >= 4 for r in recs[:2]), recs
+    s_ref, scale = oracle_terms(w)
+    assert np.isfinite(s_ref).all()
+    err = score_error(s, s_ref, scale)
+    assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
+
+
 @pytest.mark.parametrize("dims,m,n_r,fwd,row_align", [
     ([784, 256, 128, 10], 20, 32, "fp32", 1),    # the pass at x has four and two chunks next to 13 and four
     ([512, 30, 200], 20, 20, "fp32", 32),        # ... one chunk: three of four waves have none
