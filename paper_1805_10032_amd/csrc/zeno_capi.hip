@@ -664,6 +664,7 @@ zeno_status_t cnn_score_enqueue(const zeno_model* mdl, const CnnPlan& p, const f
     j.pack_off = p.pack[l].off;
     j.pack_sets = p.pack[l].sets;
     j.tiled_out = l + 1 == C;
+    j.out_scale = !j.tiled_out ? 1.f : cand ? kScaleD : kScaleH;
     j.Kp_fc = p.Kp;
     if (fragments && l > 0) j.H0_in = reinterpret_cast<const float*>(ws + p.off_hs[l]);
     j.split_out = fragments && l + 1 < C;

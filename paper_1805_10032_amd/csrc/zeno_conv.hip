@@ -241,11 +241,11 @@ __device__ void fc_sample(const ConvArgs& a, int r, int n0, float* red) {
   if (threadIdx.x < kFcOutputs && n0 + (int)threadIdx.x < a.fc_N) {
     const int n = n0 + (int)threadIdx.x;
     double t = a.fc_b_off >= 0 ? (double)a.x[a.fc_b_off + n] : 0.0;
-    for (int w = 0; w < T / 64; ++w) t += sums[w * kFcOutputs + threadIdx.x];
+    for (int w = 0; w < T / 64; ++w) t += (double)(1.f / kScaleH) * sums[w * kFcOutputs + threadIdx.x];
     a.fc_z0[(long long)r * a.fc_N + n] = (float)t;
   }
 }
-// The layer's weights in matrix-operand order, columns beyond K zeros (rows beyond N only reach results that are discarded).
+// The layer's weights in matrix-operand order (times kScaleW), columns beyond K zeros (rows beyond N only reach results that are discarded).
 constexpr int kFcPieces = 4;   // 16-byte pieces a thread copies
 __device__ void fc_weights(const ConvArgs& a, int block) {
   const long long pieces = (long long)a.fc_N * (a.fc_Kp >> 2);
@@ -255,7 +255,7 @@ __device__ void fc_weights(const ConvArgs& a, int block) {
     if (at >= pieces) return;
     const int n = (int)(at / (a.fc_Kp >> 2)), k = 4 * (int)(at % (a.fc_Kp >> 2));
     const f32x4 v = load4_masked(a.x + a.fc_w_off + (long long)n * a.fc_K, k, a.fc_K, k < a.fc_K);
-    *reinterpret_cast<f32x4*>(a.fc_wt + tiled_index<false>(n, k, a.fc_Kp)) = v;
+    *reinterpret_cast<f32x4*>(a.fc_wt + tiled_index<false>(n, k, a.fc_Kp)) = v * kScaleW;
   }
 }
 
@@ -380,7 +380,7 @@ __device__ inline void conv_out_store(const ConvArgs& a, const ConvJob& J, bool 
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     val[i] = sum[i] + o.bias[i];
-    res[i] = conv_result(a, cand, val[i], o.z0[i]);
+    res[i] = conv_result(a, cand, val[i], o.z0[i]) * J.out_scale;
   }
   float* __restrict__ out = cand ? J.out + (long long)s * J.out_stride : J.out;
   if (SPLIT && J.split_out) {
@@ -541,6 +541,7 @@ __global__ __launch_bounds__(64 * TW) void conv_layer_kernel(const ConvArgs a) {
       const float dd = (z0 > 0.f) ? ((dz < -z0) ? -z0 : dz) : hr;
       res = dd * a.neg_inv_gamma;
     }
+    res *= J.out_scale;
     if (J.tiled_out) {
       out[tiled_index<false>(smp, pos * L.Cout + fo, J.Kp_fc)] = res;
     } else {

@@ -61,9 +61,8 @@ __global__ __launch_bounds__(64 * WAVES) void first_layer_kernel(const FirstArgs
     for (int i = 0; i < 8; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float v = n < a.n_r ? f[i][e] : 0.f;
-        if (!BF16) v = v != v ? __builtin_nanf("") : v;   // split_pair needs a NaN's payload in its upper half
-        f[i][e] = v;
+        const float v = n < a.n_r ? f[i][e] : 0.f;
+        f[i][e] = BF16 ? v : v * kScaleH;
       }
     const bool copy = c % n_tiles == nt;    // this workgroup writes the chunk's operand-order copy
 #pragma unroll
@@ -111,8 +110,9 @@ __global__ __launch_bounds__(64 * WAVES) void first_layer_kernel(const FirstArgs
     f32x4 val, hv;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      val[i] = acc[4 * q + i] + __shfl(bias_lane, 8 * q + 4 * h + i, 64);
-      hv[i] = (n < a.n_r && f0 + i < N) ? relu_nan(val[i]) : 0.f;
+      const float bias = __shfl(bias_lane, 8 * q + 4 * h + i, 64);
+      val[i] = BF16 ? acc[4 * q + i] + bias : __builtin_fmaf(acc[4 * q + i], 1.f / kScaleH, bias);
+      hv[i] = (n < a.n_r && f0 + i < N) ? relu_nan(val[i]) * (BF16 ? 1.f : kScaleH) : 0.f;
     }
     if (n < a.n_r) store4_masked(J.Z0 + (long long)n * N, f0, N, val);
     if (f0 < J.Np) store_tiled4<BF16>(J.H_base, n, f0, J.Np, hv);

@@ -83,7 +83,7 @@ struct LayerArgs {
   void* Dl_cand;        // tiled scaled output differences of candidate 0 (hidden layers)
   long long H_stride;   // bytes between consecutive candidates in Dl_cand
   float gamma;
-  float neg_inv_gamma;  // -1/gamma, or 0 when gamma == 0
+  float neg_inv_gamma;  // -1/gamma, or 0 when gamma == 0 (D is that times the difference, float32: times kScaleD)
   double* norm_partials;  // [m x P] partial sums of squares, or NULL in passes after the first
   // K split of a launch of one-wave tiles (the launcher fills these in from layer_k_plan): k_waves waves of a
   // workgroup share a feature tile and split K (1, or the widest split the LDS layout allows), and K is also
@@ -109,6 +109,14 @@ struct LayerArgs {
   int main_blocks;      // filled in by the launcher
   int src_chunk;        // sources per scheduling unit, filled in by the launcher
 };
+
+// Float32 operands of a linear layer that stand in operand order are stored scaled by powers of two: the activations of the pass at x,
+// the candidates' D and the copy of W.  The split of an operand into bf16 pieces rounds the leading one to nearest, to infinity from
+// 0x1.ffp127 (3.396e38) on: scaled, no finite operand gets there, and sums have two binary digits of room at the end of the range.  Both
+// products of a candidate, (H0 / 4) U and (D / 2) ((W - gamma U) / 2), come out at a quarter; the epilogue's addition of the bias takes
+// the factor back.  (Without scaling: a test of every operand, one instruction in ten of the split, or a leading piece cut toward
+// zero, which makes the dropped piece products four times as large.)
+constexpr float kScaleH = 0.25f, kScaleD = 0.5f, kScaleW = 0.5f;
 
 inline int launch_passes(const LayerArgs& a) { return a.passes > 1 ? a.passes : 1; }
 
@@ -237,6 +245,7 @@ struct ConvJob {
   float* out;             // pass at x: relu map; candidates: candidate 0's scaled change of the output map
   long long out_stride;   // floats between candidates (candidates' pass)
   int split_out;          // 1: out is a split map (below)
+  float out_scale;        // what results are multiplied by: kScaleH or kScaleD with tiled_out, else 1
   int tiled_out;          // 1: out is the operand of the fully connected layer: rows = samples, k = (position, channel),
   int Kp_fc;              //    in matrix-operand order of padded width Kp_fc
   long long pack_off;     // byte offset of the layer's kernel fragments inside a source's

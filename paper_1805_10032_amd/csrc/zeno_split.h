@@ -80,24 +80,20 @@ __device__ inline Split8 split8(const f32x4& v0, const f32x4& v1) {
 }
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-// The same with the upper half of the float as its leading piece (toward zero, one permutation for two floats): nothing is
-// rounded to infinity, so no test for values at the end of the range is needed.  x - h has at most 16 significant bits and m, rounded to
-// nearest, leaves at most eight, so x = h + m + l still holds exactly above 1e-33.  m is up to twice as large as with a rounded
-// leading piece, l is as small and of either sign, so the dropped products m l average out as before.  NaNs need their payload in the
-// upper half.
+// The same pieces of two floats, without the test for values that the leading piece would round to infinity: the caller's operands
+// stay below 0x1.ffp127 (kScaleH in zeno_internal.h).
 // The remainders are masks, shifts and subtractions, eleven instructions for two floats, not the bf16 dot products of split3 (seven):
 // a dot product waits for the matrix cores (measured next to a wave that keeps them busy: 38 cycles each, the others 7).
 __device__ inline void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  auto bits = [](float v) { return __builtin_bit_cast(unsigned, v); };
   auto real = [](unsigned v) { return __builtin_bit_cast(float, v); };
   auto pack = [](float x, float y) {
     const f32x2 t = {x, y};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(t, bf16x2));
   };
-  h = __builtin_amdgcn_perm(bits(b), bits(a), 0x07060302u);
-  const float ra = a - real(bits(a) & 0xffff0000u), rb = b - real(bits(b) & 0xffff0000u);
+  h = pack(a, b);
+  const float ra = a - real(h << 16), rb = b - real(h & 0xffff0000u);
   m = pack(ra, rb);
   l = pack(ra - real(m << 16), rb - real(m & 0xffff0000u));
 }
@@ -118,7 +114,7 @@ struct SplitWords {
 // one; what is dropped is about 2^-24 of |a||b| per product, one float32 rounding.  The leading products have an
 // accumulator of their own: an operand that is not finite has no useful remainder (inf - inf), and the
 // leading products alone say what the float32 product would have been (join_split).  A sum of leading products may overflow
-// where the float32 sum ends within 1 % of its largest value.
+// where the float32 sum ends within 1 % of its largest value (not in linear layers, whose operands are stored scaled).
 __device__ inline void mfma_split(const Split8& a, const Split8& b, f32x16& lead, f32x16& rest) {
   rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, rest, 0, 0, 0);
   rest = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, rest, 0, 0, 0);

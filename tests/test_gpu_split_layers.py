@@ -52,6 +52,39 @@ def test_split_operands(B, dims, m, row_align, bias, n_r):
     assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
 
 
+@pytest.mark.parametrize("n_r", [32, 48, 100])
+@pytest.mark.parametrize("row_align", [1, 32])
+def test_a_product_keeps_24_bits(B, n_r, row_align):
+    """Sums of one product, so that nothing averages out: one weight of the first layer moves one hidden unit, and one weight of x
+    carries it through the second.  In units of 2^-24: at most 1 for what the six piece products leave out and 1 for the rounding
+    of the sum, at each of the two layers, and 1 for the score; everything else is exact.  Factors close to 1 + 2^-7 from below have a
+    middle piece of 2^-16 and hardly a last one, so that nothing is left out (leading pieces cut toward zero would leave most behind
+    there, 2.8 to 4.7 units in all)."""
+    K, N, N2 = 512, 1024, 512
+    w = _workload("bits", [K, N, N2, 10], 64, n_r)
+    w.dims, w.loss, w.has_bias, w.gamma, w.rho = [K, N, N2, 1], "squared", True, 2.0 ** -4, 0.0
+    w.labels, w.targets = None, torch.full((n_r,), -1024.0)
+    b0, w1 = N * K, N * K + N
+    b1 = w1 + N2 * N
+    w2 = b1 + N2
+    d = w2 + N2 + 1
+    unit, row, col = 37, 11, 70
+    w.x, w.G = torch.zeros(d), torch.zeros((64, d))
+    near = 1 + 2.0 ** -7 - 2.0 ** -15 + 2.0 ** -16 - torch.arange(1, 65, dtype=torch.float64) * 2.0 ** -23
+    gen = torch.Generator().manual_seed(3)
+    u = torch.where(torch.arange(64) < 40, near, 1 + torch.rand(64, generator=gen, dtype=torch.float64)).float()
+    w.features = torch.zeros((n_r, K))
+    w.features[:, col] = near[9]
+    w.G[:, unit * K + col] = -u
+    w.x[b0 + unit], w.x[w1 + row * N + unit], w.x[w2 + row] = 1.0, near[21], 1.0
+    dev = torch.device("cuda", 0)
+    mdl = B.ZenoModel(w.dims, w.has_bias, w.loss, w.fwd)
+    s = npy(B.zeno_score(mdl, w.x.to(dev), rows_to_gpu(B, w.G, row_align, dev), w.features.to(dev), w.gamma, w.rho, targets=w.targets.to(dev)))
+    ref = oracle_terms(w)[0]
+    err = np.abs(s - ref) / np.abs(ref) * 2.0 ** 24
+    assert err[:40].max() <= 3.1 and err[40:].max() <= 5.1, (float(err[:40].max()), float(err[40:].max()))
+
+
 def test_values_that_are_not_finite(B):
     """Infinities, NaNs of any payload and the largest floats in a few candidates: their scores are not finite, and nobody else's
     changes.  A NaN with its payload in the lower half must not become infinity on the way."""
@@ -175,6 +208,27 @@ def test_operands_near_the_end_of_the_range(B, n_r, row_align):
     assert np.isfinite(s_ref).all()
     err = score_error(s, s_ref, scale)
     assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
+
+
+@pytest.mark.parametrize("n_r", [32, 48, 100])
+def test_the_largest_floats_next_to_zeros(B, n_r):
+    """A candidate's weights of 3.402e38 whose inputs are zero for all samples: the squared norm is infinite, the products are zeros and
+    not infinity times zero.  Infinities in their place are."""
+    dims, rows = [512, 1024, 512, 10], 1024
+    w = _workload("topzero", dims, 64, n_r)
+    cols = torch.tensor([5, 300])   # in the first tile, and in one that the steady loop takes
+    w.features[:, cols] = 0.0
+    unit, b0, w1 = 21, 512 * 1024, 512 * 1024 + 1024
+    w.x[unit * 512:(unit + 1) * 512], w.x[b0 + unit] = 0.0, 0.0          # a hidden unit that is zero everywhere
+    w.G[:, unit * 512:(unit + 1) * 512], w.G[:, b0 + unit] = 0.0, 0.0
+    G0, G1 = w.G[:, :b0].view(64, rows, 512), w.G[:, w1:w1 + 512 * 1024].view(64, 512, 1024)
+    G0[0][7, cols], G0[1][1023, cols], G1[2][100, unit] = 3.402e38, -3.402e38, 3.402e38
+    G0[3][7, cols] = float("inf")
+    s, recs = _run(B, w, 32)
+    assert all(r["waves"] >= 4 for r in recs[:2]), recs
+    assert np.all(s[:3] == -np.inf) and np.isnan(s[3]), s[:4]
+    s_ref, scale = oracle_terms(w)
+    assert np.all(score_error(s, s_ref, scale)[4:] <= SCORE_TOL["fp32"])
 
 
 @pytest.mark.parametrize("dims,m,n_r,fwd,row_align", [
