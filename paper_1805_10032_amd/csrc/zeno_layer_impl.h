@@ -403,6 +403,13 @@ struct Lds {
   static constexpr int TOTAL = STAGE_OFF + NW * STAGE_BYTES;
 };
 
+// Instantiations that run several groups of 32 MB rows side by side: only batches of more than 64 samples in float32, which run as
+// groups of two row blocks, or of more than 128 have any.  The others do not ask for a group.
+template <bool BF16, int MB, int NW>
+constexpr bool row_groups_run() {
+  return BF16 ? MB == 4 && NW <= 4 : MB == 2;
+}
+
 // KS > 1 (launches of one-wave tiles, NW == 1): the KS waves of a workgroup own the SAME
 // 32 features and split the K range between them, each with a private copy of the LDS
 // layout and no barrier inside the loop; the partial accumulators (and the partial
@@ -446,7 +453,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   constexpr int STAGE_BYTES = LD::STAGE_BYTES;
   constexpr bool DBUF = LD::DBUF;
   constexpr bool SPLIT = LD::SPLIT;
-  constexpr bool GROUPED = SPLIT || NW <= 4;
+  constexpr bool GROUPED = row_groups_run<BF16, MB, NW>();
   static_assert(!SPLIT || (MB <= 2 && !RING && KS == 1), "four row blocks of split operands run as two groups of two");
   constexpr int COPIES = (AD_KB + NW - 1) / NW;        // async copies issued per wave per chunk
   constexpr int WREGS = BF16 ? 4 : 8;
@@ -1498,7 +1505,7 @@ hipError_t launch_inst(LayerArgs a, hipStream_t stream, LaunchShape* shape) {
   // K slices (one-wave tiles only) come with the caller's plan; they need the partial and counter buffers
   if (NW != 1 || a.k_slices < 1) a.k_slices = 1;
   if (a.k_slices > 1 && (a.slice_partials == nullptr || a.slice_counters == nullptr)) return hipErrorInvalidValue;
-  constexpr bool GROUPED = LD::SPLIT || NW <= 4;
+  constexpr bool GROUPED = row_groups_run<BF16, MB, NW>();
   const int groups = GROUPED ? a.row_groups : 1;
   if (groups < 1 || (!GROUPED && a.row_groups > 1)) return hipErrorInvalidValue;
   if (shape != nullptr) shape->row_blocks = MB * groups / launch_passes(a);
