@@ -33,8 +33,8 @@ ZENO_DECLARE_LAYER(f32_first, 2)
 #undef ZENO_DECLARE_LAYER_MB
 
 template <bool BF16, bool DELTA>
-static int ks_waves_for(int MB) {
-  return MB == 1 ? split_k_waves<BF16, DELTA, 1>() : MB == 2 ? split_k_waves<BF16, DELTA, 2>() : split_k_waves<BF16, DELTA, 4>();
+static int ks_waves_for(int MB) {   // (float32: a workgroup has at most two row blocks)
+  return MB == 1 ? split_k_waves<BF16, DELTA, 1>() : MB == 2 ? split_k_waves<BF16, DELTA, 2>() : split_k_waves<BF16, DELTA, BF16 ? 4 : 2>();
 }
 
 static int compute_units() {
@@ -92,9 +92,10 @@ static long long one_wave_tiles(const LayerArgs& a) {
 // K split of a launch of one-wave tiles.  Such a launch has few feature tiles (the pass at x: N/32; a narrow
 // layer: one or a few per candidate), so a tile's K is divided among the k_waves waves of its workgroup (which
 // add their accumulators through LDS) and among k_slices workgroups (which add theirs through memory, the
-// last one to arrive finishing the tile).  Every wave keeps at least two chunks.
-//  * The waves of a workgroup split K as widely as the LDS layout allows (four or two private copies).
-//  * Workgroups per tile: as many as bring the launch to about one workgroup per compute unit, at most 8.
+// last one to arrive finishing the tile).
+//  * The waves of a workgroup split K as widely as the LDS layout allows (four or two private copies), wherever each gets a chunk of
+//    the candidates' K (a pass at x with fewer chunks leaves some of them without any).
+//  * Workgroups per tile: as many as bring the launch to about one workgroup per compute unit, at most 8; every wave keeps two chunks.
 //    Measured: on an otherwise idle chip every doubling helps down to two chunks per wave (a ten-class
 //    layer behind 4096 inputs, 20 candidates: 8 slices 35 us, 4 slices 42 us), while a launch that already
 //    has a workgroup per compute unit only gets slower (its workgroups queue, and the round trips of the
@@ -191,27 +192,12 @@ LayerExtents layer_extents(const LayerArgs& a, bool bf16, bool delta, int MB, in
   return e;
 }
 
-// Does the workgroup of NW waves (8 or 4) of this kind double-buffer its activation chunks (slices need it)?
-static bool wide_double_buffered(bool bf16, bool delta, int MB, int NW) {
-  if (!bf16) return true;   // split operands always are
-  auto pick = [&](auto mb, auto nw) {
-    constexpr int M = decltype(mb)::value, W = decltype(nw)::value;
-    return bf16 ? (delta ? Lds<true, true, M, W>::DBUF : Lds<true, false, M, W>::DBUF)
-                : (delta ? Lds<false, true, M, W>::DBUF : Lds<false, false, M, W>::DBUF);
-  };
-  auto pick_nw = [&](auto mb) {
-    return NW == 8 ? pick(mb, std::integral_constant<int, 8>{}) : pick(mb, std::integral_constant<int, 4>{});
-  };
-  return MB == 1 ? pick_nw(std::integral_constant<int, 1>{}) : MB == 2 ? pick_nw(std::integral_constant<int, 2>{})
-                                                                        : pick_nw(std::integral_constant<int, 4>{});
-}
-
 // One-wave workgroups (k_waves of them sharing a tile) that fit on a compute unit by their LDS.
 static int one_wave_residents(bool bf16, bool delta, int MB, int k_waves) {
   auto pick = [&](auto mb) {
     constexpr int M = decltype(mb)::value;
     return bf16 ? (delta ? Lds<true, true, M, 1>::TOTAL : Lds<true, false, M, 1>::TOTAL)
-                : (delta ? Lds<false, true, M, 1>::TOTAL : Lds<false, false, M, 1>::TOTAL);
+                : (delta ? Lds<false, true, M < 4 ? M : 2, 1>::TOTAL : Lds<false, false, M < 4 ? M : 2, 1>::TOTAL);
   };
   const int lds = MB == 1 ? pick(std::integral_constant<int, 1>{}) : MB == 2 ? pick(std::integral_constant<int, 2>{})
                                                                               : pick(std::integral_constant<int, 4>{});
@@ -227,7 +213,7 @@ static long long wide_tiles(const LayerArgs& a) {
 // Most K slices a launch of four-wave workgroups may be cut into: every slice keeps two chunks of every job, and the hand-over
 // buffers hold all tiles.  0: the launch never takes such workgroups by layer_wide_plan.  No device is asked.
 int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
-  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8 || !wide_double_buffered(bf16, delta, MB, 4)) return 0;
+  if (a.n_cand <= 0 || a.cj.N <= 64 || launch_nw_for(a) == 8) return 0;
   const long long tiles = wide_tiles(a);
   if (a.slice_partials == nullptr || a.slice_counters == nullptr || tiles * row_groups(bf16, MB) > kMaxSliceGroups) return 1;
   const int chunks = a.cj.Kp >> 6, min_chunks = a.has_base && (a.bj.Kp >> 6) < chunks ? a.bj.Kp >> 6 : chunks;
@@ -277,15 +263,7 @@ static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int
 }
 
 // Does a launch of four-wave workgroups stream its rows on the shifted column grid, which its slices do not have?
-static bool on_shifted_grid(const LayerArgs& a, bool bf16, bool delta, int MB) {
-  auto has_grid = [&](auto mb) {
-    constexpr int M = decltype(mb)::value;
-    return delta ? Lds<true, true, M, 4, 1>::DBUF : Lds<true, false, M, 4, 1>::DBUF;
-  };
-  if (!bf16 || launch_lines_aligned(a) || launch_ring_kind(a) == 0) return false;
-  return MB == 1 ? has_grid(std::integral_constant<int, 1>{}) : MB == 2 ? has_grid(std::integral_constant<int, 2>{})
-                                                                         : has_grid(std::integral_constant<int, 4>{});
-}
+static bool on_shifted_grid(const LayerArgs& a, bool bf16) { return bf16 && !launch_lines_aligned(a) && launch_ring_kind(a) != 0; }
 
 // Candidate launches with too few 256-feature tiles for eight-wave workgroups.
 // Fewer 128-feature tiles than compute units (one-wave tiles otherwise): four-wave workgroups, all tiles (and those of
@@ -315,7 +293,7 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
   const double hand_over = bf16 && !delta ? 6.0 : 4.0;
   if (whole_tiles) {
     const bool last_round_empty = (long long)job_tiles(a.cj, 128) * a.n_cand > n_cu && 3 * tiles <= 4 * n_cu;
-    return last_round_empty && chunks >= 28 && most >= 3 && (delta || !bf16) && !on_shifted_grid(a, bf16, delta, MB) ? 3 : 0;
+    return last_round_empty && chunks >= 28 && most >= 3 && (delta || !bf16) && !on_shifted_grid(a, bf16) ? 3 : 0;
   }
   int best = 1;
   double best_cost = 0.0;
@@ -334,11 +312,10 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 // into K slices, as many as bring their workgroups to about one round: the round then lasts a fraction of a whole
 // tile's time, and the slices start as soon as slots free up behind the whole tiles.  Workload 4's 2048-wide layers
 // (100 candidates x 8 tiles = 3.125 rounds of 256): candidates 96..99 and the pass at x are 40 tiles, cut six ways.
-// Not where the workgroup is single-buffered.
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main_out) {
   *n_main_out = a.n_cand;
   if (a.n_cand <= 0 || launch_nw_for(a) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
-  if (!wide_double_buffered(bf16, delta, MB, 8) || (!bf16 && delta && MB == 4)) return 0;
+  if (!bf16 && delta && MB == 4) return 0;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
   const int groups = row_groups(bf16, MB);
   const int tiles8 = job_tiles(a.cj, 256) * groups;

@@ -384,12 +384,12 @@ __device__ inline void lds_dma16(const unsigned char* src, unsigned char* dst) {
                : "memory");
 }
 
-// LDS layout of a workgroup: [activation chunk buffers (one or two)] [one staging
+// LDS layout of a workgroup: [two activation chunk buffers] [one staging
 // tile per wave].  (Nothing else: with 4 row blocks, bf16 operands, the second product and
 // four waves the layout is exactly 80 KB, and two such workgroups share a compute unit.)
 //
 // SPLIT (float32 operands in wide workgroups): the activation buffers hold the three bf16 pieces of the operands, half as large
-// again as the floats, of a step of SUB_K = 64 / MB columns at a time; always two of them.
+// again as the floats, of a step of 64 / MB columns at a time.
 template <bool BF16, bool DELTA, int MB, int NW, int RING = 0, bool F32 = false>
 struct Lds {
   using T = Tr<BF16>;
@@ -398,8 +398,7 @@ struct Lds {
   static constexpr int A_BYTES = SPLIT ? MB * 32 * 64 * 6 / STEPS : MB * T::CH_BYTES;   // one operand, one step
   static constexpr int AD_BYTES = A_BYTES * (DELTA ? 2 : 1);  // H (and D), one chunk
   static constexpr int STAGE_BYTES = 32 * 64 * T::ESIZE * (RING ? 2 : 1);   // RING: two tiles' worth of columns
-  static constexpr bool DBUF = SPLIT || 2 * AD_BYTES + NW * STAGE_BYTES <= 128 * 1024;
-  static constexpr int STAGE_OFF = AD_BYTES * (DBUF ? 2 : 1);
+  static constexpr int STAGE_OFF = 2 * AD_BYTES;
   static constexpr int TOTAL = STAGE_OFF + NW * STAGE_BYTES;
 };
 
@@ -440,9 +439,9 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   static_assert(KS == 1 || NW == 1, "K is only split in one-tile workgroups");
   using T = Tr<BF16>;
   using LD = Lds<BF16, DELTA, MB, NW, RING, F32>;
-  static_assert(!TAIL || (NW >= 4 && KS == 1 && LD::DBUF), "sliced tiles exist for double-buffered wide workgroups");
-  static_assert(!RING || (BF16 && KS == 1 && NW > 1 && LD::DBUF), "the shifted grid exists for wide bf16 workgroups with double buffers");
-  static_assert(KS == 1 || LD::DBUF, "the single-buffer loop has workgroup barriers, which waves with different K ranges cannot share");
+  static_assert(LD::TOTAL * KS <= 160 * 1024, "the LDS of a compute unit");
+  static_assert(!TAIL || NW >= 4, "sliced tiles exist for wide workgroups");
+  static_assert(!RING || (BF16 && NW > 1), "the shifted grid exists for wide bf16 workgroups");
   extern __shared__ __attribute__((aligned(16))) unsigned char lds_all[];
   constexpr int BN = 32 * NW;
   constexpr int A_BYTES = LD::A_BYTES;
@@ -451,7 +450,6 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   constexpr int A_KB = A_BYTES / 1024;
   constexpr int BLOCK_KB = T::CH_BYTES / 1024;
   constexpr int STAGE_BYTES = LD::STAGE_BYTES;
-  constexpr bool DBUF = LD::DBUF;
   constexpr bool SPLIT = LD::SPLIT;
   constexpr bool GROUPED = row_groups_run<BF16, MB, NW>();
   static_assert(!SPLIT || (MB <= 2 && !RING && KS == 1), "four row blocks of split operands run as two groups of two");
@@ -707,40 +705,33 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     constexpr bool SECOND = DELTA && !BASE;           // second product D W^T present
     // wide workgroups start at an even chunk, so the parity of c, and with it every LDS address of the chunk,
     // is a compile-time constant; waves that split K may start anywhere
-    const int buf = DBUF ? (NW > 1 ? (ODD ? 1 : 0) : (c & 1)) : 0;
+    const int buf = NW > 1 ? (ODD ? 1 : 0) : (c & 1);
     // RING: u holds tile c + 1 of the shifted grid, staged one chunk ahead of the products
     take_tile(full_c, std::integral_constant<bool, !ODD>{}, u, !(RING && TAIL) || c + 1 < c_end || c_end == n_chunks);
-    if (DBUF) {
-      // copies(c) were issued before U(c+1) [8 loads] and W(c+1) [WREGS loads]; the
-      // last chunk has no such loads behind its copies and waits for everything
-      // (the stores of the pass at x, which writes W in operand order, share the counter;
-      // they can only make this wait longer, never let it pass early)
-      // (shifted grid: the tile requested behind copies(c) is tile c + 2, which is not requested at all where it
-      // would lie wholly behind rows that start on a line; then the copies are the newest but WREGS loads)
-      if (FULL && (STEADY || (c + 1 < c_end && (!RING || c + 2 < n_chunks || sigma > 0)))) {
-        wait_vmcnt<8 + (SECOND ? WREGS : 0)>();
-      } else {
-        wait_vmcnt<0>();
-      }
-      if (KS == 1) {
-        __syncthreads();  // copies of every wave have landed; everyone is done with buffer buf^1
-      } else {
-        asm volatile("" ::: "memory");  // private buffers: only the compiler must not move LDS reads above the wait
-      }
-      // Issue priorities of a wave inside a chunk: highest while it requests the next copies and weight
-      // tiles (memory requests leave as early as possible), raised during the matrix products, lowest
-      // while it converts and stages a tile.  Of the two waves that share a SIMD the one that is behind
-      // (still in its products while the other already stages the next tile) is served first, and it is
-      // the one every other wave of the workgroup will wait for at the next barrier.
-      __builtin_amdgcn_s_setprio(3);
-      if (STEADY || c + 1 < c_end) copy_AD(c + 1, buf ^ 1);
-      __builtin_amdgcn_sched_barrier(0);  // the wait above counts on the copies being issued before the next loads
+    // copies(c) were issued before U(c+1) [8 loads] and W(c+1) [WREGS loads]; the
+    // last chunk has no such loads behind its copies and waits for everything
+    // (the stores of the pass at x, which writes W in operand order, share the counter;
+    // they can only make this wait longer, never let it pass early)
+    // (shifted grid: the tile requested behind copies(c) is tile c + 2, which is not requested at all where it
+    // would lie wholly behind rows that start on a line; then the copies are the newest but WREGS loads)
+    if (FULL && (STEADY || (c + 1 < c_end && (!RING || c + 2 < n_chunks || sigma > 0)))) {
+      wait_vmcnt<8 + (SECOND ? WREGS : 0)>();
     } else {
-      __syncthreads();  // single buffer: everyone is done with the previous chunk
-      copy_AD(c, 0);
       wait_vmcnt<0>();
-      __syncthreads();
     }
+    if (KS == 1) {
+      __syncthreads();  // copies of every wave have landed; everyone is done with buffer buf^1
+    } else {
+      asm volatile("" ::: "memory");  // private buffers: only the compiler must not move LDS reads above the wait
+    }
+    // Issue priorities of a wave inside a chunk: highest while it requests the next copies and weight
+    // tiles (memory requests leave as early as possible), raised during the matrix products, lowest
+    // while it converts and stages a tile.  Of the two waves that share a SIMD the one that is behind
+    // (still in its products while the other already stages the next tile) is served first, and it is
+    // the one every other wave of the workgroup will wait for at the next barrier.
+    __builtin_amdgcn_s_setprio(3);
+    if (STEADY || c + 1 < c_end) copy_AD(c + 1, buf ^ 1);
+    __builtin_amdgcn_sched_barrier(0);  // the wait above counts on the copies being issued before the next loads
     if constexpr (RING) {
       if (STEADY) load_tile<MODE, NT>(u, Uring + ((c + 3) << 6), lane_off, row0, (c + 3) << 6, N, K, lane);
       else if (c + 3 <= c_end) load_ring(full_c, u, c + 3);
@@ -1087,7 +1078,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     // so that the epilogue does not start with a round trip to memory.
     if (J.b_off >= 0 && lane < 32 && row0 + lane < N) bias_lane = P[J.b_off + row0 + lane];
     __builtin_amdgcn_sched_barrier(0);
-    if (DBUF) copy_AD(c_begin, NW > 1 ? 0 : c_begin & 1);
+    copy_AD(c_begin, NW > 1 ? 0 : c_begin & 1);
     __builtin_amdgcn_sched_barrier(0);
     int c = c_begin;
     const float* Ufirst = Urow0 + (c_begin << 6);
@@ -1120,7 +1111,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     // chunks each, where the longer code only costs: 784 -> 10, 20 candidates: 16 -> 17 us) (33 candidates, 1001 -> 777, bf16, n_r = 128: 51 -> 43 us;
     // 3000 -> 1000, fp32, n_r = 32: 149 -> 121 us; 1500 -> 700, bf16, n_r = 32: 54 -> 42 us).
     const int c_full = MODE == 0 ? (c_end < (K >> 6) ? c_end : K >> 6) : c_end;
-    if ((MODE != 0 || NW > 1) && DBUF && c_full - c_begin >= 4) {
+    if ((MODE != 0 || NW > 1) && c_full - c_begin >= 4) {
       // steady state: pairs of chunks whose loads (two chunks ahead) all exist
       load_tile<SteadyMode::value, NT>(u0, Ufirst, lane_off, row0, c_begin << 6, N, K, lane);
       load_tile<SteadyMode::value, NT>(u1, Ufirst + 64, lane_off, row0, (c_begin + 1) << 6, N, K, lane);
@@ -1560,12 +1551,12 @@ int wgs_per_cu_inst() {
 }
 
 // Waves that share one feature tile and split K: four, or two where four private LDS layouts do not
-// fit into the 160 KB of a compute unit (0: the layout is single-buffered or too large even twice).
+// fit into the 160 KB of a compute unit.
 template <bool BF16, bool DELTA, int MB>
 constexpr int split_k_waves() {
   using L = Lds<BF16, DELTA, MB, 1>;
-  if (!L::DBUF) return 0;
-  return L::TOTAL * 4 <= 160 * 1024 ? 4 : L::TOTAL * 2 <= 160 * 1024 ? 2 : 0;
+  static_assert(L::TOTAL * 2 <= 160 * 1024, "two waves always fit");
+  return L::TOTAL * 4 <= 160 * 1024 ? 4 : 2;
 }
 
 // k_waves > 1: the one-wave-tile instantiation whose workgroups split K over that many waves
@@ -1574,9 +1565,7 @@ int wgs_per_cu_nw(int NW, int k_waves) {
   if (NW == 8) return wgs_per_cu_inst<BF16, DELTA, MB, 8, 1>();
   if (NW == 4) return wgs_per_cu_inst<BF16, DELTA, MB, 4, 1>();
   constexpr int KS = split_k_waves<BF16, DELTA, MB>();
-  if constexpr (KS > 1) {
-    if (k_waves == KS) return wgs_per_cu_inst<BF16, DELTA, MB, 1, KS>();
-  }
+  if (k_waves == KS) return wgs_per_cu_inst<BF16, DELTA, MB, 1, KS>();
   return wgs_per_cu_inst<BF16, DELTA, MB, 1, 1>();
 }
 
@@ -1622,7 +1611,7 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
   // One-tile workgroups whose plan splits K over the waves of a workgroup.  A wave may be without chunks (a short K of the
   // pass at x); the chunk whose copy it starts all the same lies inside the operand as long as its slice has one.
   constexpr int KS = split_k_waves<BF16, DELTA, MB>();
-  if constexpr (NW == 1 && KS > 1) {
+  if constexpr (NW == 1) {
     if (a.k_waves == KS) {
       const int slices = a.k_slices > 1 ? a.k_slices : 1;
       const bool base_ok = !a.has_base || (a.bj.Kp >> 6) >= slices;
@@ -1646,16 +1635,16 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
                    : launch_inst<BF16, DELTA, MB, NW, false, 1, 0, false, true>(a, stream, shape);
     }
   }
-  if constexpr (NW == 4 && Lds<BF16, DELTA, MB, NW>::DBUF) {
+  if constexpr (NW == 4) {
     if (a.tail_slices >= 2) {
       if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true>(a, stream, shape);
       return launch_inst<BF16, DELTA, MB, NW, false, 1, 0, true>(a, stream, shape);
     }
   }
-  if constexpr (NW == 8 && Lds<BF16, DELTA, MB, NW>::DBUF) {
+  if constexpr (NW == 8) {
     if (a.tail_slices >= 2) {
       if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true>(a, stream, shape);
-      if constexpr (BF16 && Lds<BF16, DELTA, MB, NW, 1>::DBUF) {
+      if constexpr (BF16) {
         const int ring = launch_ring_kind(a);
         if (ring == 1) return launch_inst<BF16, DELTA, MB, NW, true, 1, 1, true>(a, stream, shape);
         if (ring == 2) return launch_inst<BF16, DELTA, MB, NW, true, 1, 2, true>(a, stream, shape);
@@ -1665,7 +1654,7 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
   }
   if (a.tail_slices >= 2) return hipErrorInvalidValue;   // planned for a launch shape that has no sliced tail
   if (launch_lines_aligned(a)) return launch_inst<BF16, DELTA, MB, NW, true>(a, stream, shape);
-  if constexpr (BF16 && NW > 1 && Lds<BF16, DELTA, MB, NW, 1>::DBUF) {
+  if constexpr (BF16 && NW > 1) {
     const int ring = launch_ring_kind(a);
     if (ring == 1) return launch_inst<BF16, DELTA, MB, NW, true, 1, 1>(a, stream, shape);
     if (ring == 2) return launch_inst<BF16, DELTA, MB, NW, true, 1, 2>(a, stream, shape);
