@@ -381,12 +381,14 @@ hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipSt
   LayerArgs b = a;
   const int groups = row_groups(bf16, MB);
   b.row_groups = groups * launch_passes(a);
-  // Four-wave workgroups with at most one per compute unit, one row block and one product: a wave has its SIMD to itself, and the
-  // split of its operand takes as long as the float32 matrix instructions do, without a second wave to hide behind
-  // (20 candidates, n_r = 32: 3072 -> 512 in 243 workgroups 37.0 us with float32 products, 37.6-38.0 with split operands).
-  if (!bf16 && !delta && MB == 1 && NW == 4 && a.n_cand > 0) {
-    const long long slices = a.tail_slices >= 2 && a.tail_cand == a.n_cand ? a.tail_slices : 1;
-    b.float_products = wide_tiles(a) * slices <= compute_units();
+  // Packed rows, one row block, one product and four-wave workgroups for at least four fifths of the compute units but at most one each
+  // keep the float32 matrix instructions: a wave has its SIMD to itself, without a second one whose products hide the split of its
+  // operand.  Score and update of models of one and two layers over buffers in turn, split / float32 products: there 1.00 (30 of them,
+  // 0.97 to 1.03; 3072 -> 512 -> 10, 20 candidates 88.7 / 86.9 us), with fewer workgroups 0.99 (20), with line-aligned rows, whose
+  // loads arrive sooner, 0.98 (30).
+  if (!bf16 && !delta && MB == 1 && NW == 4 && a.n_cand > 0 && !launch_lines_aligned(a)) {
+    const long long wgs = wide_tiles(a) * (a.tail_slices >= 2 && a.tail_cand == a.n_cand ? a.tail_slices : 1);
+    b.float_products = wgs <= compute_units() && 5 * wgs >= 4LL * compute_units();
   }
   const KPlan kp = layer_k_plan(a, bf16, delta, MB, NW, true);
   b.k_waves = kp.k_waves;

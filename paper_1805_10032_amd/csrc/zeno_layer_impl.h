@@ -1628,11 +1628,8 @@ hipError_t launch_nt(const LayerArgs& a, hipStream_t stream, LaunchShape* shape)
   }
   if constexpr (!BF16 && !DELTA && MB == 1 && NW == 4) {
     if (a.float_products) {
-      const bool lines = launch_lines_aligned(a);
-      if (a.tail_slices >= 2) return lines ? launch_inst<BF16, DELTA, MB, NW, true, 1, 0, true, true>(a, stream, shape)
-                                           : launch_inst<BF16, DELTA, MB, NW, false, 1, 0, true, true>(a, stream, shape);
-      return lines ? launch_inst<BF16, DELTA, MB, NW, true, 1, 0, false, true>(a, stream, shape)
-                   : launch_inst<BF16, DELTA, MB, NW, false, 1, 0, false, true>(a, stream, shape);
+      if (a.tail_slices >= 2) return launch_inst<BF16, DELTA, MB, NW, false, 1, 0, true, true>(a, stream, shape);
+      return launch_inst<BF16, DELTA, MB, NW, false, 1, 0, false, true>(a, stream, shape);
     }
   }
   if constexpr (NW == 4) {

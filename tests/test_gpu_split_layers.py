@@ -210,6 +210,22 @@ def test_operands_near_the_end_of_the_range(B, n_r, row_align):
     assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
 
 
+@pytest.mark.parametrize("row_align", [1, 32])
+@pytest.mark.parametrize("dims,m,slices", [
+    ([512, 1000], 24, 1), ([512, 1000], 25, 1), ([512, 1000], 31, 1),   # 200, 208 and 256 workgroups
+    ([500, 1000], 32, 1),                                               # 264; ragged K
+    ([768, 1201], 7, 3), ([1114, 1278], 8, 2),                          # slices: 240 and 180
+])
+def test_both_kinds_of_products(B, dims, m, slices, row_align):
+    """Both sides of the line between float32 matrix instructions and split operands: packed rows take the former in launches of 205 to
+    256 workgroups."""
+    w = _workload("kinds", dims, m, 9)
+    s, (rec,) = _run(B, w, row_align)
+    assert (rec["waves"], rec["k_slices"]) == (4, slices), rec
+    err = score_error(s, *oracle_terms(w))
+    assert np.all(err <= SCORE_TOL["fp32"]), (float(err.max()), int(err.argmax()))
+
+
 @pytest.mark.parametrize("n_r", [32, 48, 100])
 def test_the_largest_floats_next_to_zeros(B, n_r):
     """A candidate's weights of 3.402e38 whose inputs are zero for all samples: the squared norm is infinite, the products are zeros and
