@@ -243,12 +243,12 @@ hipError_t launch_masked_average(const float* G, long long ldg, const float* sco
   long long blocks_total = (n_vec + block_vec - 1) / block_vec;
   const long long resident = (long long)n_cu * per_cu;
   // One block a workgroup and more blocks than compute units: about as many workgroups on each compute unit, of narrower blocks
-  // (units of 64 columns; units of 16 come closer, Mean 25.7 -> 24.3 at d = 1578506, but score and update of 3072 -> 512 -> 10 took 85.6
-  // instead of 85.0), instead of two on some and one on the others.  Us per update / Mean, full blocks -> narrower: m = 20, d = 1200000
-  // 16.8 -> 14.6 / 20.7 -> 18.1, d = 1578506 17.7 -> 17.0 / 27.0 -> 25.7, d = 2400000 24.7 -> 23.5 / 35.0 -> 33.7, d = 4000000 no
-  // change; m = 100, d = 1200000 61.6 -> 52.5 / 87.3 -> 74.4, d = 1578506 68.9 -> 66.0 / 104.3 -> 96.2.  Not below one block per compute unit (m = 64, d = 1000001 30.5 -> 32.2
-  // / 42.0 -> 43.7), and not where a workgroup has several blocks: m = 20, d = 14.7 M took 8 us longer with 15 blocks of equal
-  // width than with 14, or 15 in a few workgroups.
+  // (units of 64 columns; units of 16 come closer and change nothing: 28 sizes, update 0.996 and Mean 1.006 times as fast), instead of
+  // two on some and one on the others.  Us per update / Mean, full blocks -> narrower: m = 20, d = 1200000 16.8 -> 14.6 / 20.7 -> 18.1,
+  // d = 1578506 17.7 -> 17.0 / 27.0 -> 25.7, d = 2400000 24.7 -> 23.5 / 35.0 -> 33.7, d = 4000000 no change; m = 100, d = 1200000
+  // 61.6 -> 52.5 / 87.3 -> 74.4, d = 1578506 68.9 -> 66.0 / 104.3 -> 96.2.  Not below one block per compute unit (m = 64, d = 1000001
+  // 30.5 -> 32.2 / 42.0 -> 43.7), and not where a workgroup has several blocks: m = 20, d = 14.7 M took 8 us longer with 15 blocks of
+  // equal width than with 14, or 15 in a few workgroups.
   if (!few && n_blocks == 1 && blocks_total > n_cu && blocks_total <= resident) {
     const long long even = (blocks_total + n_cu - 1) / n_cu * n_cu;
     block_vec = (int)((n_vec + 64 * even - 1) / (64 * even) * 64);

@@ -228,7 +228,10 @@ int layer_wide_most(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 // LDS for it that a compute unit runs one to four such workgroups; but it hands nothing over through memory, and as long as
 // its workgroups are resident all at once it is the faster of the two.  Measured on 3692 random launches (K 64 to 4096, 66 to
 // 2048 features, 3 to 100 candidates; time as one-wave tiles / as four-wave workgroups, geometric mean, and how many of the latter
-// are more than 3 % slower; by the rule as a whole 1.43, 27 of 832):
+// are more than 3 % slower; by the rule as a whole 1.43, 27 of 832).  The float32 ones among them ran wide workgroups on float32
+// matrix instructions.  With split operands, score and update of 350 models of one to three layers over buffers in turn, the launch
+// the one way and the other: what the rule takes to four waves 1.22 (6 of 101 slower), what it leaves to one 0.94 (four waves
+// more than 3 % faster on 67 of 249):
 //  * K split over waves, all resident at once: 0.93, 999 of 1473; more than one round of them: 1.44, 33 of 642.
 //    Two waves are few for a compute unit: where no more fit and the tile is not cut into K slices either, more than half a round is
 //    enough from 16 chunks on (1.41, 5 of 70).
@@ -244,8 +247,8 @@ static bool one_wave_tiles_slower(const LayerArgs& a, bool bf16, bool delta, int
   const int chunks = a.cj.Kp >> 6, base_chunks = a.has_base ? a.bj.Kp >> 6 : 0;
   const long long base_tiles = a.has_base ? job_tiles(a.bj, 32) : 0, cand_tiles = (long long)job_tiles(a.cj, 32) * a.n_cand;
   if (!bf16 && MB == 4) {
-    // two groups of two row blocks (row_groups): with the second product always; without it by the lines below as they were for four
-    // blocks, whose tile two waves shared
+    // Two groups of two row blocks (row_groups): with the second product always (1.41, 2 of 24); without it from 16 chunks on or where
+    // the one-wave tiles of one group outnumber the compute units (1.24, none of 17; the others 0.97, 14 of 44 more than 3 % faster).
     return delta || (base_chunks <= 2 * chunks && (chunks >= 16 || base_tiles + cand_tiles > compute_units()));
   }
   KPlan one = layer_k_plan(a, bf16, delta, MB, 1, true);
@@ -271,18 +274,17 @@ static bool on_shifted_grid(const LayerArgs& a, bool bf16) { return bf16 && !lau
 //     rounds x (chunks of a slice + hand-over if sliced),   rounds = workgroups per compute unit, rounded up,
 // in chunk times, the hand-over of the partial accumulators being 4 of them, 6 in bf16 without the second product, whose chunks
 // are the shortest (113 launches with four row blocks: 1.35 and 1.37 times as fast as one-wave tiles with 4 and 6).
-// Measured (us; slices 1 / 2 / 3 / 4, before): fp32, n_r = 32, m = 20: 3072 -> 512 (81 tiles) 77 / 50 / 40 / 48, 48.
-// bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88; 777 -> 333 with the second product (100 tiles)
-// 41 / 37 / 49 / 49, 57.
+// Measured (us; slices 1 / 2 / 3 / 4, before): bf16, n_r = 128, m = 33: 1001 -> 777 (234 tiles) 41 / 63 / 72 / 80, 88; 777 -> 333
+// with the second product (100 tiles) 41 / 37 / 49 / 49, 57.  fp32, n_r = 32, m = 20: 3072 -> 512 (81 tiles) 35 in three slices.
+// With split operands, score and update of 60 models each whose launch it changes: 6 chunk times instead of 4 take 1.15 times as long, 2
+// 0.95 times.
 // More of them (whole four-wave tiles otherwise): three slices where the candidates fill more than one round of compute units and
 // all tiles at most 4/3, which the slices make four full rounds of a third, for K from 28 chunks on.  Random launches, whole /
-// sliced: 1.14 (5 of 128 more than 3 % slower); from 12 chunks on 1.08 (42 of 242); up to 3/2 rounds in two
-// slices 0.95 (28 of 43); in bf16 without the second product, which waits for memory either way, 1.02 (20 of 64); on the
-// shifted grid, which slices do not have, 0.93 (5 of 10).  fp32, n_r = 32, m = 20: 3072 -> 2048 (336 tiles) 141 whole, 125 in
-// three slices; 2048 -> 2048 with the second product 162, 143.
+// sliced: in bf16 without the second product, which waits for memory either way, 1.02 (20 of 64 more than 3 % slower); on the
+// shifted grid, which slices do not have, 0.93 (5 of 10).  Split operands, score and update: with one product 1.07 (none of 14; from 12
+// chunks on 0.99, 2 of 11), with the second 1.12 (none of 31; from 12 chunks on 1.04, 2 of 21); beyond 4/3 rounds 1.03 (none of 10).
 // Layers of at most 64 features keep the one-wave tiles (half a workgroup or more would be idle), and so do launches that
-// are faster on them (one_wave_tiles_slower) or make no half round of workgroups this way (896 -> 100, 7 candidates: 7
-// tiles; fp32 with the second product and four row blocks, which is single-buffered and has no slices: 24 -> 100 us).
+// are faster on them (one_wave_tiles_slower) or make no half round of workgroups this way.
 // Returns the slices (1: none) or 0 where the launch keeps its shape; budget: bytes for the partial accumulators.
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget) {
   const int most = layer_wide_most(a, bf16, delta, MB, budget);
@@ -315,6 +317,8 @@ int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t bu
 int layer_tail_slices(const LayerArgs& a, bool bf16, bool delta, int MB, int* n_main_out) {
   *n_main_out = a.n_cand;
   if (a.n_cand <= 0 || launch_nw_for(a) != 8 || a.slice_partials == nullptr || a.slice_counters == nullptr) return 0;
+  // Float32 layers with the second product and four row blocks keep whole tiles of four waves: eight-wave workgroups with the tail
+  // are faster for a long K only (score and update of 20 models, whole / tail: 32 chunks 1.05 to 1.11, 16 1.03 to 1.06, 8 0.94 to 1.02).
   if (!bf16 && delta && MB == 4) return 0;
   const long long slots = (long long)compute_units() * wgs_per_cu(bf16, delta, MB, 8);
   const int groups = row_groups(bf16, MB);
