@@ -163,8 +163,8 @@ size_t zeno_score_workspace_bytes(const zeno_model_t* model, int32_t m, int32_t 
  *             copies of the kernels and maps, and a workspace that holds everything but these (no call returns that size) is
  *             accepted and scored by slower kernels, whose scores agree up to the order of float32 sums.  Workspaces of the
  *             queried size and larger ones give the same scores bit for bit.  For batches of 129 to 512 samples the query may
- *             include room for all groups of 128 samples at once; a workspace that holds one group is accepted, with the
- *             same scores bit for bit.
+ *             include room for all groups of 128 samples at once, up to 1 GiB more than for one; a workspace that holds one
+ *             group (no call returns that size) is accepted, with the same scores bit for bit.
  * Batches of more than 128 samples are processed in groups of 128: up to four side by side in the same launches where the
  * layers are small and the workspace has room, otherwise one after the other, each pass reading G again. */
 zeno_status_t zeno_score(const zeno_model_t* model, const float* x, const float* G, int64_t ldg, int32_t m,
@@ -265,7 +265,8 @@ zeno_status_t zeno_score_plan_check(const zeno_model_t* model, int32_t m, int32_
  * of the same process beyond a mutex around the record list. */
 typedef enum {
   ZENO_KERNEL_PACK = 0,       /* batch features into matrix-operand order */
-  ZENO_KERNEL_LAYER_BASE = 1, /* one layer of the pass at x */
+  ZENO_KERNEL_LAYER_BASE = 1, /* one layer of the pass at x; the first one of a model of several layers with at most 1024 inputs, for
+                                 at most 32 samples, also does what PACK does elsewhere (and adds the batch to its bytes) */
   ZENO_KERNEL_LAYER_CAND = 2, /* one layer of the m candidate passes (streams G); the whole score of a small model, which is
                                  one launch (its record has layer 0 and no launch shape: waves = 0) */
   ZENO_KERNEL_LOSS = 3,       /* per-sample loss differences; up to 16 classes and 64 samples also what COMBINE does */
@@ -291,12 +292,14 @@ typedef struct {
   double algorithmic_bytes;
   /* layer kernels only (else 0): the launch shape that ran */
   int32_t waves;      /* waves per workgroup that own different 32-feature tiles: 1, 4 or 8 */
-  int32_t k_split;    /* waves that share one feature tile and split the input width: 1, 2 or 4 */
+  int32_t k_split;    /* waves that share one feature tile and split the input width: 1, 2 or 4 (4, 8 or 16 in the LAYER_BASE
+                         launch that also packs the batch) */
   int32_t streaming;  /* 1: rows read with non-temporal loads (line-aligned layout), 0: plain loads,
                          2: non-temporal loads on a column grid shifted to the lines of each candidate's rows
                             (16-byte aligned dense rows, bf16 forward), 3: the same for rows that are only 8-byte
                             aligned (d mod 4 = 2) */
-  int32_t row_blocks; /* 32-sample accumulator blocks per wave: 1, 2 or 4 */
+  int32_t row_blocks; /* 32-sample accumulator blocks that a feature tile has for a group of 128 samples: 1, 2 or 4.  A wave holds
+                         all of them, except that 4 in a float32 launch are two workgroups with two each */
   int32_t merged;     /* 1: the launch carries the candidates' layer AND the pass at x through another layer */
   int32_t second;     /* 1: candidates with the second matrix product (layers after the first) */
   int32_t k_slices;   /* workgroups that share one feature tile and split the input width: 1..8 (launches of one-wave

@@ -489,7 +489,9 @@ zeno_status_t score_enqueue(const zeno_model* model, const Plan& p, const float*
       f.zero = zero;
       f.n_zero = n_zero;
       ProfScope ps(ZENO_KERNEL_LAYER_BASE, 0, seq[0].bytes + 4.0 * rows * D.dims[0], stream);
-      ZENO_TRY(launch_first_layer(f, bf16, stream));
+      LaunchShape shape;
+      ZENO_TRY(launch_first_layer(f, bf16, stream, &shape));
+      ps.set_shape(shape, false, false, 0, 0);
     } else {
       ProfScope ps(ZENO_KERNEL_PACK, 0, 4.0 * rows * D.dims[0], stream);
       ZENO_TRY(launch_pack_features(features, rows, D.dims[0], pad64(D.dims[0]), p.n_pad, bf16, ws + p.off_feat, counters, p.n_counters,

@@ -120,7 +120,8 @@ __global__ __launch_bounds__(64 * WAVES) void first_layer_kernel(const FirstArgs
 }
 
 template <bool BF16, int WAVES>
-hipError_t launch_first_inst(const FirstArgs& a, hipStream_t stream) {
+hipError_t launch_first_inst(const FirstArgs& a, hipStream_t stream, LaunchShape* shape) {
+  *shape = {1, WAVES, 1, 0, 1};
   constexpr int staging = WAVES * 32 * 64 * Tr<BF16>::ESIZE, reduction = WAVES / 2 * 16 * 64 * 4;
   constexpr int lds_bytes = staging > reduction ? staging : reduction;
   static const hipError_t attr_err =
@@ -133,20 +134,20 @@ hipError_t launch_first_inst(const FirstArgs& a, hipStream_t stream) {
   return hipGetLastError();
 }
 template <bool BF16>
-hipError_t launch_first(const FirstArgs& a, hipStream_t stream) {
+hipError_t launch_first(const FirstArgs& a, hipStream_t stream, LaunchShape* shape) {
   const int chunks = a.job.Kp >> 6;
-  if (chunks <= 4) return launch_first_inst<BF16, 4>(a, stream);
-  if (chunks <= 8) return launch_first_inst<BF16, 8>(a, stream);
-  return launch_first_inst<BF16, 16>(a, stream);
+  if (chunks <= 4) return launch_first_inst<BF16, 4>(a, stream, shape);
+  if (chunks <= 8) return launch_first_inst<BF16, 8>(a, stream, shape);
+  return launch_first_inst<BF16, 16>(a, stream, shape);
 }
 
 }  // namespace
 
 bool first_layer_fits(int K, int n_r) { return K <= 64 * kFirstChunks && n_r <= kFirstRows; }
 
-hipError_t launch_first_layer(const FirstArgs& a, bool bf16, hipStream_t stream) {
+hipError_t launch_first_layer(const FirstArgs& a, bool bf16, hipStream_t stream, LaunchShape* shape) {
   if (!first_layer_fits(a.job.K, a.n_r) || a.job.last) return hipErrorInvalidValue;
-  return bf16 ? launch_first<true>(a, stream) : launch_first<false>(a, stream);
+  return bf16 ? launch_first<true>(a, stream, shape) : launch_first<false>(a, stream, shape);
 }
 
 }  // namespace zeno

@@ -126,20 +126,6 @@ inline int launch_passes(const LayerArgs& a) { return a.passes > 1 ? a.passes : 
 hipError_t launch_pack_features(const float* features, int n_r, int K, int Kp, int n_pad, bool bf16,
                                 void* tiled, unsigned int* counters, int n_counters, double* zero, long long n_zero,
                                 hipStream_t stream);
-// ---- the packing of the batch and the pass at x through layer 0 in one launch (zeno_first.hip)
-struct FirstArgs {
-  const float* x;
-  const float* features;   // [n_r x job.K]
-  int n_r;
-  LayerJob job;            // layer 0 (a hidden layer); Z0 and H_base are written
-  void* tiled;             // the batch in operand order, written
-  unsigned int* counters;  // cleared, with n_zero doubles at zero, as launch_pack_features does
-  int n_counters;
-  double* zero;
-  long long n_zero;
-};
-bool first_layer_fits(int K, int n_r);
-hipError_t launch_first_layer(const FirstArgs& a, bool bf16, hipStream_t stream);
 // Limits of a launch whose K is split over workgroups: bytes of partial accumulators (tiles x slices x row
 // blocks x 4 KB) and tiles (= arrival counters).  One buffer of each serves all launches of a pass, which run
 // one after the other and leave the counters at zero.
@@ -161,13 +147,27 @@ KPlan layer_k_plan(const LayerArgs& a, bool bf16, bool delta, int MB, int NW, bo
 // Which instantiation of the layer kernel a launch took (reported in the per-launch timing records).
 struct LaunchShape {
   int waves;       // waves per workgroup that own different feature tiles (1, 4 or 8)
-  int k_split;     // waves that share one feature tile and split K (1, 2 or 4)
+  int k_split;     // waves that share one feature tile and split K (1, 2 or 4; 4, 8 or 16 in launch_first_layer)
   int k_slices;    // workgroups that share one feature tile and split K (1 to 8)
   int streaming;   // 1: rows read with non-temporal loads (line-aligned layout), 2: the same on the shifted column grid
-  int row_blocks;  // 32-sample accumulator blocks per wave (1, 2 or 4)
+  int row_blocks;  // 32-sample accumulator blocks of a group of 128 samples (1, 2 or 4), whatever number of workgroups shares them
 };
 hipError_t launch_layer(const LayerArgs& a, bool bf16, bool delta, int MB, hipStream_t stream,
                         LaunchShape* shape = nullptr);
+// ---- the packing of the batch and the pass at x through layer 0 in one launch (zeno_first.hip)
+struct FirstArgs {
+  const float* x;
+  const float* features;   // [n_r x job.K]
+  int n_r;
+  LayerJob job;            // layer 0 (a hidden layer); Z0 and H_base are written
+  void* tiled;             // the batch in operand order, written
+  unsigned int* counters;  // cleared, with n_zero doubles at zero, as launch_pack_features does
+  int n_counters;
+  double* zero;
+  long long n_zero;
+};
+bool first_layer_fits(int K, int n_r);
+hipError_t launch_first_layer(const FirstArgs& a, bool bf16, hipStream_t stream, LaunchShape* shape);
 bool layer_merge_pays(const LayerArgs& a, bool bf16, bool delta, int MB);  // run a.bj inside the candidates' launch?
 // K slices of all tiles of a launch of four-wave workgroups (1: whole tiles), 0: the launch keeps its shape
 int layer_wide_plan(const LayerArgs& a, bool bf16, bool delta, int MB, size_t budget);

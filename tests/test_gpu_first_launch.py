@@ -48,10 +48,15 @@ def test_first_launch(dims, n_r, m, fwd):
     try:
         s = B.zeno_score(*args, labels=labels, workspace=ws)
         torch.cuda.synchronize()
-        kernels = [r["kernel"] for r in B.profile_collect(detail=True)]
+        first = B.profile_collect(detail=True)[0]
     finally:
         B.profile_enable(False)
-    assert kernels[0] == ("layer_base" if dims[0] <= 1024 and n_r <= 32 else "pack"), kernels
+    if dims[0] <= 1024 and n_r <= 32:
+        chunks = (dims[0] + 63) // 64
+        assert first["kernel"] == "layer_base" and first["row_blocks"] == first["waves"] == 1, first
+        assert first["k_split"] == (4 if chunks <= 4 else 8 if chunks <= 8 else 16), first
+    else:
+        assert first["kernel"] == "pack", first
     s_ref, scale = oracle_terms(w)
     err = score_error(npy(s), s_ref, np.maximum(scale, _conditioned(w)) if n_r == 1 else scale)
     assert np.all(err <= SCORE_TOL[fwd]), (float(err.max()), int(err.argmax()))
