@@ -804,7 +804,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
   // A wave issues in order, and a matrix instruction behind another waits for it: the vector instructions of the operand after
   // next, of the activations and of the next tile's staging stand between the matrix instructions, a pair of floats (11) at a time,
   // fenced, since the compiler would put all products of an operand behind its split and the two waves of a SIMD then find
-  // each other's pipe idle (2048 -> 2048, 64 candidates, n_r = 32: matrix cores busy for 32 % of the launch that way).
+  // each other's pipe idle.
   constexpr int STEPS = LD::STEPS, STEP_T = 4 / STEPS;    // activation steps of a chunk, k-steps of 16 of a step
   constexpr int UNITS_1 = MB * STEP_T;                     // units of one operand
   constexpr int HELD = SPLIT ? (UNITS_1 * (DELTA ? 2 : 1) + NW - 1) / NW : 1;

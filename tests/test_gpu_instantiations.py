@@ -197,7 +197,7 @@ TAIL_DIMS = {10: [1024, 2048, 2048, 10], 12: [1024, 2048, 2048, 12]}
     ("bf16", 160, 32, 10),     # two passes over G (128 + 32 samples): the second finds the arrival counters at zero
     # dense bf16 rows: the sliced tail on the shifted column grid, 8-byte (d mod 4 = 2) and 16-byte aligned rows
     ("bf16", 32, 1, 10), ("bf16", 64, 1, 10), ("bf16", 128, 1, 10), ("bf16", 32, 1, 12), ("bf16", 64, 1, 12), ("bf16", 128, 1, 12),
-    # fp32 with four row blocks: the layer with the second product is single-buffered and keeps its whole tiles
+    # fp32 with four row blocks: the layer with the second product keeps its whole tiles (the tail pays for a long K only)
     ("fp32", 128, 32, 10)])
 def test_last_round_of_a_launch_in_k_slices(B, fwd, n_r, row_align, classes):
     """36 candidates on 2048-wide layers are 288 eight-wave workgroups: one full round of 256 and a round that
@@ -266,7 +266,7 @@ def test_zz_which_instantiations_ran(B):
                 if not any(s[0] == "bf16" and s[1] == second and s[2] in (4, 8) and s[4] == kind and s[5] == mb for s in SEEN):
                     missing.append(("bf16", second, "4|8 waves", "shifted grid", kind, mb))
     # sliced tails: every kind of row access, with and without the second product, every number of row blocks that
-    # has the instantiation (fp32 with the second product and four row blocks is single-buffered: no tail)
+    # has the instantiation (fp32 with the second product and four row blocks takes no tail)
     for fwd, kinds in (("bf16", (0, 1, 2, 3)), ("fp32", (0, 1))):
         for second in (0, 1):
             for kind in kinds:
