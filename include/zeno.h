@@ -75,7 +75,9 @@ typedef enum {
 typedef enum {
   ZENO_FWD_FP32 = 0, /* forward-pass products at float32 accuracy, fp32 accumulate: fp32 matrix cores, or for wide layers the
                         bf16 ones, every operand split into three bf16 pieces (six piece products, which leave out at most 2^-24
-                        of a product; products of operands below about 6e-33 keep fewer than 24 bits) */
+                        of a product; products of operands below about 6e-33 keep fewer than 24 bits).  A candidate with
+                        values from 1.8e19 on has an infinite squared norm: its score is minus infinity or a NaN, which
+                        rank alike */
   ZENO_FWD_BF16 = 1  /* matrix operands rounded to bf16, fp32 accumulate */
 } zeno_fwd_dtype_t;
 

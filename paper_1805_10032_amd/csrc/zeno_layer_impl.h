@@ -778,7 +778,16 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
                                                             __builtin_bit_cast(bf16x8, fr[g][mb]), acc[mb], 0, 0, 0);
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[e], fr[g][mb][e], acc[mb], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) {
+            acc[mb] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[e], fr[g][mb][e], acc[mb], 0, 0, 0);
+            // (the multiplications stand in the shadow of a matrix instruction: behind the products of the k-step they made the pass at
+            // x through 19 chunks next to 64 -> 1216 2 % longer, and out of line 5 %)
+            if (BASE && e == 0 && mb == 0 && op == 0 && pack) {
+              __builtin_amdgcn_sched_barrier(0);
+              *reinterpret_cast<f32x4*>(Wt_wave + ((long long)c * WREGS + t) * 1024) = bq[t] * kScaleW;
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -788,9 +797,7 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
         read_group(fr[g + 1], g + 1);
         if ((g + 1) % OPS == 0) bq[(g + 1) / OPS] = read_b((g + 1) / OPS);
       }
-      // (float32: out of the way of a pass at x that writes no copy, which fetches every instruction once: 3072 -> 512 12.5 -> 11.5 us)
-      if (BASE && op == 0 && (BF16 ? pack : __builtin_expect(pack, 0)))
-        *reinterpret_cast<f32x4*>(Wt_wave + ((long long)c * WREGS + t) * 1024) = BF16 ? bq[t] : bq[t] * kScaleW;
+      if (BF16 && BASE && pack && op == 0) *reinterpret_cast<f32x4*>(Wt_wave + ((long long)c * WREGS + t) * 1024) = bq[t];
     }
     __builtin_amdgcn_s_setprio(0);
     if (SECOND && (STEADY || c + 2 < c_end)) load_W(w, c + 2);
@@ -851,24 +858,6 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
     if (decltype(base_c)::value) v *= kScaleW;
     else q += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
     *reinterpret_cast<f32x4*>(stU + r * 256 + (((kq ^ r) & 15) << 4)) = v;
-  };
-  // A candidate's values are staged as they are (halving them on the way: 2 % longer on average, up to 18 %).  Where their squares
-  // overflow, its squared norm is infinite whatever the products are: the finite ones that split_pair would round to infinity (which
-  // times zero is a NaN) are taken down to the largest bf16 value.
-  // (Behind the request of the next tile: in front of it, score and update of 1024 -> 1024^3 -> 10, n_r = 40, took 233 instead of 205 us.)
-  auto below_infinity = [&](auto base_c, float q) __attribute__((always_inline)) {
-    if (decltype(base_c)::value || __builtin_expect(!__any(!(q < __builtin_inff())), 1)) return;
-    const float top = 0x1.fep127f;
-#pragma unroll 1
-    for (int i = 0; i < 8; ++i) {   // what this lane staged: the tile's registers need not live that long
-      const int r = 4 * i + (lane >> 4), kq = lane & 15;
-      f32x4* at = reinterpret_cast<f32x4*>(stU + r * 256 + (((kq ^ r) & 15) << 4));
-      f32x4 v = *at;
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (__builtin_fabsf(v[e]) > top && __builtin_fabsf(v[e]) < __builtin_inff()) v[e] = __builtin_copysignf(top, v[e]);
-      *at = v;
-    }
   };
   // Chunk c: `oper` and raw[0] hold its first operand, u its successor's tile.
   auto chunk_split = [&](auto full_c, auto base_c, auto steady_c, auto odd, f32x4 (&u)[8], int c) __attribute__((always_inline)) {
@@ -964,7 +953,6 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
             if (do_norm) nrm += (double)q;
             if (STEADY || c + 1 + AHEAD < c_end)
               load_tile<MODE, NT>(u, Urow0 + ((c + 1 + AHEAD) << 6), lane_off, row0, (c + 1 + AHEAD) << 6, N, K, lane);
-            below_infinity(base_c, q);
           }
         }
         fence();
@@ -1045,7 +1033,6 @@ __global__ __launch_bounds__(64 * NW * KS, !BF16 && NW > 1 && !F32 ? 2 : 1) void
         else take_row(full_c, base_c, u0, q, i);
       }
       if (do_norm) nrm += (double)q;
-      below_infinity(base_c, q);
       fence();
       tile(u0, AHEAD);
       fence();

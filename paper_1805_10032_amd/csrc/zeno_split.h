@@ -83,7 +83,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 // The same pieces of two floats, without the test for values that the leading piece would round to infinity: the caller's operands
 // stay below 0x1.ffp127 (kScaleH in zeno_internal.h).
 // The remainders are masks, shifts and subtractions, eleven instructions for two floats, not the bf16 dot products of split3 (seven):
-// a dot product waits for the matrix cores (measured next to a wave that keeps them busy: 38 cycles each, the others 7).
+// a dot product waits for the matrix cores (next to a wave that keeps them busy 328 cycles each, the others 11; alone 8 and 9).
 __device__ inline void split_pair(float a, float b, unsigned& h, unsigned& m, unsigned& l) {
   typedef float f32x2 __attribute__((ext_vector_type(2)));
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));

@@ -227,24 +227,27 @@ def test_both_kinds_of_products(B, dims, m, slices, row_align):
 
 
 @pytest.mark.parametrize("n_r", [32, 48, 100])
-def test_the_largest_floats_next_to_zeros(B, n_r):
-    """A candidate's weights of 3.402e38 whose inputs are zero for all samples: the squared norm is infinite, the products are zeros and
-    not infinity times zero.  Infinities in their place are."""
-    dims, rows = [512, 1024, 512, 10], 1024
+def test_candidates_with_the_largest_floats(B, n_r):
+    """Weights of 3.402e38, which the split rounds to infinity, whose inputs are zero or not: the squared norm is infinite, the candidate
+    ranks last, and nobody else's score changes.  Without them the same rows score as the oracle says, next to weights of 1e19 (the
+    largest whose squares do not overflow) whose inputs are zero."""
+    dims = [512, 1024, 512, 10]
     w = _workload("topzero", dims, 64, n_r)
     cols = torch.tensor([5, 300])   # in the first tile, and in one that the steady loop takes
     w.features[:, cols] = 0.0
-    unit, b0, w1 = 21, 512 * 1024, 512 * 1024 + 1024
-    w.x[unit * 512:(unit + 1) * 512], w.x[b0 + unit] = 0.0, 0.0          # a hidden unit that is zero everywhere
-    w.G[:, unit * 512:(unit + 1) * 512], w.G[:, b0 + unit] = 0.0, 0.0
-    G0, G1 = w.G[:, :b0].view(64, rows, 512), w.G[:, w1:w1 + 512 * 1024].view(64, 512, 1024)
-    G0[0][7, cols], G0[1][1023, cols], G1[2][100, unit] = 3.402e38, -3.402e38, 3.402e38
-    G0[3][7, cols] = float("inf")
-    s, recs = _run(B, w, 32)
+    b0, w1 = 512 * 1024, 512 * 1024 + 1024
+    G0, G1 = w.G[:, :b0].view(64, 1024, 512), w.G[:, w1:w1 + 512 * 1024].view(64, 512, 1024)
+    G0[4][7, cols] = 1e19
+    clean, recs = _run(B, w, 32)
     assert all(r["waves"] >= 4 for r in recs[:2]), recs
-    assert np.all(s[:3] == -np.inf) and np.isnan(s[3]), s[:4]
-    s_ref, scale = oracle_terms(w)
-    assert np.all(score_error(s, s_ref, scale)[4:] <= SCORE_TOL["fp32"])
+    assert np.all(score_error(clean, *oracle_terms(w)) <= SCORE_TOL["fp32"])
+    G0[0][7, cols], G0[1][1023, 17], G1[2][100, 21], G0[3][7, cols] = 3.402e38, -3.402e38, 3.402e38, float("inf")
+    s, _ = _run(B, w, 32)
+    assert np.all(np.isnan(s[:4]) | (s[:4] == -np.inf)), s[:4]
+    assert np.array_equal(s[4:], clean[4:])
+    G = w.G.to("cuda")
+    _, selected = B.zeno_aggregate(G, torch.from_numpy(s).to("cuda"), 4)
+    assert selected.tolist() == list(range(4, 64))
 
 
 @pytest.mark.parametrize("dims,m,n_r,fwd,row_align", [
